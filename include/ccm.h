@@ -92,16 +92,19 @@ typedef struct {
 /* Cross-map kernel as a persistent grid pulling work items from an atomic
    queue (default: one workgroup per work item, longest first). */
 #define CCM_FLAG_PERSISTENT 4u
-/* Distance indexing table (Section 3.2): before the cross map, build for
-   every library embedding that needs it a table whose row i lists the
-   first CCM_TABLE_WIDTH embedded points in ascending (d2, index) order
-   from point i, and find each query's E+1 neighbours by walking its row
-   until E+1 library members (not excluded) are seen.  Used for the
-   realizations whose expected walk is short (large libraries); the others,
-   and any wavefront whose walk runs off the end of its rows, scan by brute
-   force.  Neighbours, predictions and rho are bitwise identical to the
-   brute-force path.  Costs n_e * CCM_TABLE_WIDTH * 4 bytes of device memory
-   per table.  Honoured by the served form too (ccm_submit). */
+/* Distance indexing table (Section 3.2): row i of an embedding's table lists
+   its nearest embedded points (at most CCM_TABLE_WIDTH) in ascending
+   (d2, index) order from point i, and a query's E+1 neighbours in a library
+   are the first E+1 library members (not excluded) of its row.  The batched
+   calls build such rows whenever they expect them to be cheaper than
+   scanning the call's libraries; with this flag every realization whose
+   expected walk is short (large libraries) takes them, whatever the call's
+   size.  The others scan every library point, and a library that finds fewer
+   than E+1 members in a row is searched in full.  Neighbours, predictions
+   and rho are bitwise identical either way.  The rows cost n_e * width * 8
+   bytes of device memory per embedding, at most 2 GiB at once (n_e *
+   CCM_TABLE_WIDTH * 4 bytes per table in the served form and in
+   CCM_FLAG_PLAIN calls).  Honoured by the served form too (ccm_submit). */
 #define CCM_FLAG_TABLE 8u
 #define CCM_TABLE_WIDTH 1024
 /* Nested libraries (an option of this library, not of the paper): the
@@ -149,7 +152,8 @@ const char *ccm_last_error(const ccm_ctx *ctx);
  * fit, consecutive E merged while they fit, one E split over several waves
  * when it alone does not fit (at least one realization per wave).  The
  * results do not depend on the bound; other buffers of a call (series,
- * embeddings, visiting orders, per-tile moments) are not counted.  bytes = 0
+ * embeddings, visiting orders, per-tile moments, neighbour rows and the
+ * walks' output: at most 2.5 GiB) are not counted.  bytes = 0
  * restores the default, min(8 GiB, device memory / 8) and at least 1 GiB.
  * The bound applies to calls made after it is set.
  */
@@ -364,13 +368,17 @@ ccm_status ccm_neighbors(ccm_ctx *ctx, const double *lib_series,
    While enabled, batched calls issue their launches directly (no graph: the
    runtime cannot time events recorded by graph nodes). */
 typedef struct {
-  double kernel_ms;      /* summed duration of cross-map kernel launches */
-  int64_t launches;      /* cross-map kernel launches timed */
-  double pairs;          /* (query, candidate) distance evaluations */
+  double kernel_ms;      /* summed duration of cross-map launches (the scan of
+                            one E in one wave, with the neighbour rows and
+                            walks of that E) */
+  int64_t launches;      /* cross-map launches timed */
+  double pairs;          /* (query, candidate) pairs the cross map ranges over
+                            (neighbour rows evaluate a row's pairs once for
+                            every library of the call) */
   double flops;          /* 3E-1 binary32 flops per pair, summed */
   double predictions;    /* cross-map predictions made */
   double realizations;   /* rho values produced */
-  double table_realizations; /* of which walked a distance indexing table */
+  double table_realizations; /* of which walked a table for CCM_FLAG_TABLE */
   double waves;          /* waves of realizations run (ccm_set_wave_limit) */
 } ccm_profile;
 

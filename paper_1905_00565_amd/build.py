@@ -33,6 +33,8 @@ INST_E = tuple(range(1, 11))
 # loop-invariant hoisting (the unit's header says why).
 MULTI_SOURCE = "ccm_inst_multi.hip"
 MULTI_FLAGS = ("-mllvm", "-disable-machine-licm")
+# The neighbour-row kernels, also once per E.
+WALK_SOURCE = "ccm_inst_walk.hip"
 
 
 def hipcc() -> str:
@@ -62,6 +64,8 @@ def units(defines=()):
                     [f"-DCCM_INST_E={e}", *defines]))
         out.append((MULTI_SOURCE, os.path.join(BUILD, f"ccm_inst_multi_e{e}.o"),
                     [f"-DCCM_INST_E={e}", *MULTI_FLAGS, *defines]))
+        out.append((WALK_SOURCE, os.path.join(BUILD, f"ccm_inst_walk_e{e}.o"),
+                    [f"-DCCM_INST_E={e}", *defines]))
     return out
 
 

@@ -48,6 +48,19 @@ struct PlanBuffers {
   int32_t* shuffle = nullptr;
   int32_t* segs = nullptr;
   Realization* rz_fin = nullptr;
+  RowJob* row_jobs = nullptr;        // neighbour rows and their walks
+  MaskJob* mask_jobs = nullptr;
+  WalkLib* walk_libs = nullptr;
+  WalkGroup* walk_groups = nullptr;
+  Item* walk_items = nullptr;
+  Item* mom_items = nullptr;
+  int64_t* walk_out_off = nullptr;
+  uint64_t* rows = nullptr;
+  uint64_t* bits = nullptr;
+  uint64_t* masks = nullptr;
+  float* opts = nullptr;
+  float* boxes = nullptr;
+  double* walk_out = nullptr;
 };
 
 struct Exec {
@@ -59,6 +72,8 @@ struct Exec {
   DevBuf d_tt;       // causal matrix: targets time-major [N][target_stride(M)]
   DevBuf d_tables, d_table;   // distance indexing table jobs and rows
   DevBuf d_nested, d_scratch, d_segs, d_rz_fin;   // nested libraries
+  DevBuf d_row_jobs, d_mask_jobs, d_walk_libs, d_walk_groups, d_walk_items, d_mom_items,
+      d_walk_off, d_rows, d_bits, d_masks, d_opts, d_boxes, d_walk_out;   // neighbour rows
   std::vector<int64_t> plain_first;   // per realization: first plain item
   PlanBuffers buf;
   hipGraphExec_t graph = nullptr;

@@ -90,12 +90,15 @@ struct Spec {
   // Largest device bytes of drawn libraries and gathered library points held
   // at once; the realizations are run in waves that fit (0: one wave).
   uint64_t wave_limit = 0;
+  // Whether realizations may walk neighbour rows where that is cheaper than
+  // the scan (the batched calls; not the served and no-allocation forms).
+  bool walk = false;
 
   bool operator==(const Spec& o) const {
     return M == o.M && N == o.N && E == o.E && tau == o.tau && L == o.L && r == o.r &&
            seed == o.seed && excl == o.excl && query_set == o.query_set &&
            (flags & ~CCM_FLAG_NO_GRAPH) == (o.flags & ~CCM_FLAG_NO_GRAPH) &&
-           wave_limit == o.wave_limit;
+           wave_limit == o.wave_limit && walk == o.walk;
   }
 };
 
@@ -110,11 +113,31 @@ inline int64_t min_library(int32_t E, int32_t excl) {
   return (int64_t)E + 1 + w;
 }
 
-// One cross-map launch: the work items of one E within a wave.
+// One part of a launch's walks whose output is held at once: the walk items
+// ({group, block of queries}), then the moment items ({realization, tile}).
+struct WalkChunk {
+  int64_t item_first = 0, item_count = 0;   // into Plan::walk_items
+  int64_t mom_first = 0, mom_count = 0;     // into Plan::mom_items
+};
+
+// Embeddings whose neighbour rows are held at once, and the chunks that walk
+// them.
+struct WalkBatch {
+  int32_t emb_first = 0, emb_count = 0;     // into Plan::row_jobs
+  int32_t max_ne = 0, max_w = 0;
+  int32_t rows_per_block = 1;
+  int32_t chunk_first = 0, chunk_count = 0; // into Plan::walk_chunks
+};
+
+// One cross-map launch: the work of one E within a wave, the scanned items
+// and the walks.
 struct Launch {
   int32_t E;
   int32_t first;      // into Plan::items
   int32_t count;
+  int32_t mask_first = 0, mask_count = 0, mask_max_ne = 0;   // into Plan::mask_jobs
+  int32_t batch_first = 0, batch_count = 0;                  // into Plan::walk_batches
+  int32_t walk_per = 0;                                      // queries per walk item
 };
 
 // A wave: realizations whose drawn libraries and gathered points are live at
@@ -177,6 +200,27 @@ struct Plan {
   int te_max_ne[kMaxE + 1] = {0};     // largest table of E (launch grid)
   int e_table_ne[kMaxE + 1] = {0};    // largest n_e walked by E's items (launch LDS)
   int64_t table_rz = 0;               // realizations that walk a table
+  // neighbour rows (ccm_walk.h): the rows, groups of libraries and items of
+  // the realizations that walk them (walked[r]); the pools are reused by
+  // every wave (bitmaps), launch (masks), batch (rows, points, boxes) and
+  // chunk (output)
+  std::vector<char> want_table;       // CCM_FLAG_TABLE asks realization r to walk
+  std::vector<char> walked;
+  std::vector<RowJob> row_jobs;
+  std::vector<MaskJob> mask_jobs;
+  std::vector<WalkLib> walk_libs;
+  std::vector<WalkGroup> walk_groups;
+  std::vector<Item> walk_items, mom_items;
+  std::vector<int64_t> walk_out;      // per realization: its offset in the output
+  std::vector<WalkBatch> walk_batches;
+  std::vector<WalkChunk> walk_chunks;
+  int64_t n_rows = 0, n_opts = 0, n_box = 0, n_bits = 0, n_mask = 0, n_walk_out = 0;
+  uint64_t walk_bytes() const {
+    return (uint64_t)(n_rows + n_bits + n_mask + n_walk_out) * 8 + (uint64_t)(n_opts + n_box) * 4 +
+           row_jobs.size() * sizeof(RowJob) + mask_jobs.size() * sizeof(MaskJob) +
+           walk_libs.size() * sizeof(WalkLib) + walk_groups.size() * sizeof(WalkGroup) +
+           (walk_items.size() + mom_items.size()) * sizeof(Item) + walk_out.size() * 8;
+  }
   // nested libraries (CCM_FLAG_NESTED): rz holds chains, rz_fin one record
   // per rho (slot range of its segment, output index)
   std::vector<NestedJob> nested;

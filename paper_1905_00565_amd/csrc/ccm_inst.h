@@ -40,4 +40,26 @@ template <int E>
 hipError_t launch_table_build_e(const TableJob* jobs, int n_jobs, int max_n_e, const float* emb,
                                 int32_t* table, hipStream_t st);
 
+template <int E>
+hipError_t launch_order_points_e(const RowJob* jobs, int n_jobs, int max_ne, const float* emb,
+                                 const int32_t* qord, float* pts, float* box, hipStream_t st);
+
+template <int E>
+hipError_t launch_rows_e(const RowJob* jobs, int n_jobs, int max_ne, int max_w, int per_block,
+                         const float* pts, const float* box, const int32_t* qord,
+                         uint64_t* rows, hipStream_t st);
+
+template <int E>
+hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,
+                         const RowJob* embs, const Item* items, int n_items, int per,
+                         const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
+                         const float* emb, const double* tgt, double* out, int excl,
+                         int query_set, hipStream_t st);
+
+template <int E>
+hipError_t launch_walk_moments_e(const Realization* rzs, const int64_t* out_off,
+                                 const Item* items, int n_items, const double* out,
+                                 const int32_t* pj, const int32_t* qord, const double* tgt,
+                                 Moments* partial, int query_set, hipStream_t st);
+
 }  // namespace ccmk

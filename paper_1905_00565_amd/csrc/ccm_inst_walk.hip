@@ -1,0 +1,74 @@
+// ccm_inst_walk.hip -- the neighbour-row kernels of one embedding dimension
+// (ccm_walk.h), compiled once per E = 1..10 with -DCCM_INST_E=E.
+#include "ccm_walk.h"
+#include "ccm_inst.h"
+
+#ifndef CCM_INST_E
+#error "compile with -DCCM_INST_E=<embedding dimension>"
+#endif
+
+namespace ccmk {
+
+template <int E>
+hipError_t launch_order_points_e(const RowJob* jobs, int n_jobs, int max_ne, const float* emb,
+                                 const int32_t* qord, float* pts, float* box, hipStream_t st) {
+  const unsigned runs = (unsigned)((max_ne + 63) / 64);
+  k_order_points<E><<<dim3((runs + kWaves - 1) / kWaves, (unsigned)n_jobs), kBlock, 0, st>>>(
+      jobs, emb, qord, pts, box);
+  return hipGetLastError();
+}
+
+template <int E>
+hipError_t launch_rows_e(const RowJob* jobs, int n_jobs, int max_ne, int max_w, int per_block,
+                         const float* pts, const float* box, const int32_t* qord,
+                         uint64_t* rows, hipStream_t st) {
+  const dim3 grid((unsigned)((max_ne + per_block - 1) / per_block), (unsigned)n_jobs);
+  k_rows<E><<<grid, kBlock, row_lds_bytes(max_w), st>>>(jobs, per_block, pts, box, qord, rows);
+  return hipGetLastError();
+}
+
+template <int E>
+hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,
+                         const RowJob* embs, const Item* items, int n_items, int per,
+                         const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
+                         const float* emb, const double* tgt, double* out, int excl,
+                         int query_set, hipStream_t st) {
+  if (keys)
+    k_walk<E, true><<<(unsigned)n_items, kBlock, 0, st>>>(groups, libs, embs, items, per, masks,
+                                                          rows, qord, emb, tgt, out, excl,
+                                                          query_set);
+  else
+    k_walk<E, false><<<(unsigned)n_items, kBlock, 0, st>>>(groups, libs, embs, items, per, masks,
+                                                           rows, qord, emb, tgt, out, excl,
+                                                           query_set);
+  return hipGetLastError();
+}
+
+template <int E>
+hipError_t launch_walk_moments_e(const Realization* rzs, const int64_t* out_off,
+                                 const Item* items, int n_items, const double* out,
+                                 const int32_t* pj, const int32_t* qord, const double* tgt,
+                                 Moments* partial, int query_set, hipStream_t st) {
+  k_walk_moments<E, DefaultQ<E>::Q><<<(unsigned)n_items, kBlock, 0, st>>>(
+      rzs, out_off, items, n_items, out, pj, qord, tgt, partial, query_set);
+  return hipGetLastError();
+}
+
+template hipError_t launch_order_points_e<CCM_INST_E>(const RowJob*, int, int, const float*,
+                                                      const int32_t*, float*, float*,
+                                                      hipStream_t);
+template hipError_t launch_rows_e<CCM_INST_E>(const RowJob*, int, int, int, int, const float*,
+                                              const float*, const int32_t*, uint64_t*,
+                                              hipStream_t);
+template hipError_t launch_walk_e<CCM_INST_E>(int, const WalkGroup*, const WalkLib*,
+                                              const RowJob*, const Item*, int, int,
+                                              const uint64_t*, const uint64_t*, const int32_t*,
+                                              const float*, const double*, double*, int, int,
+                                              hipStream_t);
+template hipError_t launch_walk_moments_e<CCM_INST_E>(const Realization*, const int64_t*,
+                                                      const Item*, int, const double*,
+                                                      const int32_t*, const int32_t*,
+                                                      const double*, Moments*, int,
+                                                      hipStream_t);
+
+}  // namespace ccmk

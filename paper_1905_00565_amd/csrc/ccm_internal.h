@@ -79,7 +79,8 @@ struct SampleJob {
   int32_t E;
   int32_t tau;
   int32_t r_index;
-  int32_t pad;
+  int32_t no_list;   // 1: the indices are not written (only the bitmap)
+  int64_t bits;      // 1 + uint64 offset of the bitmap over 0..n_e-1 (0: none)
 };
 
 // One library gather: the library of one realization laid out in visiting
@@ -171,6 +172,49 @@ struct Dump {
   double* pred;   // [n_e]
 };
 
+// Neighbour rows of one embedding (ccm_walk.h): row p holds the first w
+// embedded points in ascending (d2, j) order from the point at visiting
+// position p, as keys (d2 bits << 32 | j); w is a multiple of 64, entries
+// past n_e are ~0.
+struct RowJob {
+  int64_t emb_off;   // floats: AoS embedding
+  int64_t qord_off;  // int32: its points in visiting order
+  int64_t pts_off;   // floats: its points in visiting order, [E][n_e]
+  int64_t box_off;   // floats: bounding boxes of runs of 64 of them, [runs][2][E]
+  int64_t out_off;   // uint64: rows [n_e][w]
+  int32_t n_e;
+  int32_t w;
+};
+
+// A library of a walk group, and where its predictions (or neighbour keys)
+// go in the walk's output.
+struct WalkLib {
+  int64_t bit_off;   // uint64: its bitmap over 0..n_e-1
+  int64_t out_off;   // doubles into the walk's output
+  int32_t l_eff;
+  int32_t rz;
+};
+
+// Up to 64 libraries of one embedding that walk its rows together.
+struct WalkGroup {
+  int64_t mask_off;  // uint64 [n_e]: bit l of word j set when library l holds j
+  int64_t lib_first; // into the walk's libraries
+  int64_t tgt_off;   // doubles: target at embedded point 0 (pairs only)
+  int32_t n_lib;
+  int32_t emb;       // into the row jobs
+  int32_t chunks;    // 64-entry chunks of a row these libraries may need
+  int32_t pad;
+};
+
+// Membership words of one group of libraries (shared by the groups of every
+// embedding that draws the same libraries).
+struct MaskJob {
+  int64_t mask_off;
+  int64_t lib_first;
+  int32_t n_lib;
+  int32_t n_e;
+};
+
 // Launchers (defined with the kernels).
 // Queries per lane of the cross-map kernel of E (a tile holds kBlock times
 // as many); the same for batched launches and the per-query hook.
@@ -188,7 +232,7 @@ hipError_t launch_order_keys(const OrderJob* jobs, int n_jobs, const float* s32,
                              uint32_t* keys, hipStream_t st);
 hipError_t launch_query_order(const EmbedJob* jobs, int n_jobs,
                               const int32_t* order, int32_t* qord, hipStream_t st);
-hipError_t launch_sample(const SampleJob* jobs, int64_t n_jobs, int32_t* out,
+hipError_t launch_sample(const SampleJob* jobs, int64_t n_jobs, int32_t* out, uint64_t* bits,
                          hipStream_t st);
 hipError_t launch_gather(const GatherJob* jobs, int64_t n_jobs, int64_t max_n_e,
                          const float* emb, const int32_t* lib, const int32_t* order,
@@ -270,6 +314,34 @@ hipError_t sort_series(void* temp, size_t& temp_bytes, const uint32_t* keys_in,
 hipError_t refine_orders_kd(const OrderJob* orders, int32_t n_sets, int levels,
                             int64_t n_series, const float* emb, int32_t* order, int32_t* alt,
                             uint32_t* keys, hipStream_t st);
+
+// Neighbour-row path.  Rows of jobs [0, n_jobs) (max_ne, max_w: the largest
+// of them), the points' visiting-order copies and boxes first; per_block
+// consecutive rows per workgroup.
+hipError_t launch_order_points(int E, const RowJob* jobs, int n_jobs, int max_ne,
+                               const float* emb, const int32_t* qord, float* pts, float* box,
+                               hipStream_t st);
+hipError_t launch_rows(int E, const RowJob* jobs, int n_jobs, int max_ne, int max_w,
+                       int per_block, const float* pts, const float* box, const int32_t* qord,
+                       uint64_t* rows, hipStream_t st);
+hipError_t launch_masks(const MaskJob* jobs, int n_jobs, int max_ne, const WalkLib* libs,
+                        const uint64_t* bits, uint64_t* masks, hipStream_t st);
+// The walk of `per` queries per item ({group, block of queries}): keys == 0
+// leaves predictions, else the E+1 neighbour keys per query ([t][n_e] per
+// library).  excl: candidates within it of the query in index are dropped
+// (-1: none).
+hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* libs,
+                       const RowJob* embs, const Item* items, int n_items, int per,
+                       const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
+                       const float* emb, const double* tgt, double* out, int excl,
+                       int query_set, hipStream_t st);
+// Moments of the items' tiles from the predictions at out + out_off[rz].
+hipError_t launch_walk_moments(int E, const Realization* rzs, const int64_t* out_off,
+                               const Item* items, int n_items, const double* out,
+                               const int32_t* pj, const int32_t* qord, const double* tgt,
+                               Moments* partial, int query_set, hipStream_t st);
+constexpr int kRowMaxW = 1024;              // longest neighbour row
+constexpr int kWalkLibs = 64;               // libraries per walk group
 
 // Largest embedding whose membership bitmask fits the gather kernel's LDS.
 int64_t gather_max_sorted_n_e();

@@ -20,6 +20,10 @@
 //   k_crossmap     fused distance / top-(E+1) / prediction / Pearson moments,
 //                  one workgroup per (realization, query tile) work item,
 //                  optionally persistent with an atomic work queue
+//   k_masks, k_order_points, k_rows, k_walk, k_walk_moments
+//                  the same result through sorted neighbour rows shared by
+//                  all libraries of an embedding (ccm_walk.h), for the
+//                  realizations where the planner finds that cheaper
 //   k_finalize     merge the per-tile moments of each realization -> rho
 //
 // Arithmetic that must agree bit for bit with the CPU oracle:
@@ -34,9 +38,9 @@
 // The order in which candidates are visited is free: selection uses the exact
 // (d2, j) key.  Queries are grouped and candidates visited roughly nearest
 // first (along a space-filling curve) only so that the running lists settle
-// early and the insertion path stays rare; every (query, candidate) pair is
-// still evaluated.
-#include "ccm_device.h"
+// early and the insertion path stays rare; the scan still evaluates every
+// (query, candidate) pair.
+#include "ccm_walk.h"
 #include "ccm_inst.h"
 #include "ccm_copy.h"
 
@@ -402,9 +406,14 @@ __device__ __forceinline__ uint64_t sm_mix(uint64_t z) {
 // needed) takes the rest.  Each u_j is below n_e < 2^31.
 constexpr uint64_t kGamma = 0x9e3779b97f4a7c15ull;
 
+// The candidates at or below n_e - 1 among the 64 from j0 on.
+__device__ __forceinline__ uint64_t tail_word(int64_t ne, int64_t j0) {
+  return ne - j0 >= 64 ? ~0ull : ~(~0ull << (ne - j0));
+}
+
 __global__ __launch_bounds__(256) void k_sample(const SampleJob* __restrict__ jobs,
-                                                int64_t n_jobs,
-                                                int32_t* __restrict__ out_pool) {
+                                                int64_t n_jobs, int32_t* __restrict__ out_pool,
+                                                uint64_t* __restrict__ bit_pool) {
   const int lane = threadIdx.x & 63;
   const int64_t id = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (id >= n_jobs) return;                       // the whole wavefront
@@ -417,9 +426,14 @@ __global__ __launch_bounds__(256) void k_sample(const SampleJob* __restrict__ jo
   st = sm_mix(st ^ (uint64_t)(int64_t)J.r_index);
   int32_t* __restrict__ out = out_pool + J.out_off;
   const int64_t ne = J.n_e, le = J.l_eff;
+  const bool list = J.no_list == 0;
+  uint64_t* __restrict__ bits = J.bits > 0 ? bit_pool + (J.bits - 1) : nullptr;
+  const int64_t nw = (ne + 63) / 64;
+  uint64_t word = 0;                              // word 64 * (j0 / 4096) + lane
   const uint64_t below_lane = lane == 0 ? 0ull : (~0ull >> (64 - lane));
   int64_t s = 0;                                  // taken so far
-  for (int64_t j0 = 0; s < le && j0 < ne; j0 += 64) {
+  int64_t j0 = 0;
+  for (; s < le && j0 < ne; j0 += 64) {
     const int64_t j = j0 + lane;
     const bool valid = j < ne;
     int64_t u = 0;
@@ -444,12 +458,65 @@ __global__ __launch_bounds__(256) void k_sample(const SampleJob* __restrict__ jo
       rest = j0 + l;
       take &= (1ull << l) - 1ull;
     }
-    if ((take >> lane) & 1ull) out[s + __popcll(take & below_lane)] = (int32_t)j;
+    if (list && ((take >> lane) & 1ull)) out[s + __popcll(take & below_lane)] = (int32_t)j;
     s += __popcll(take);
     if (rest >= 0) {
-      for (int64_t k = lane; k < le - s; k += 64) out[s + k] = (int32_t)(rest + k);
+      if (list)
+        for (int64_t k = lane; k < le - s; k += 64) out[s + k] = (int32_t)(rest + k);
       s = le;
+      // candidates rest .. n_e - 1, all of them: to the end of the bitmap
+      take |= (~0ull << (rest - j0)) & tail_word(ne, j0);
     }
+    if (bits) {
+      const int64_t x = j0 >> 6;
+      if (lane == (int)(x & 63)) word = take;
+      if ((x & 63) == 63) {
+        bits[x - 63 + lane] = word;
+        word = 0;
+      }
+      if (rest >= 0) {
+        // the words not yet stored of this 64, then the remaining ones
+        const int64_t y0 = (x & ~63ll) + ((x & 63) == 63 ? 64 : 0);
+        for (int64_t y = y0 + lane; y < nw; y += 64)
+          bits[y] = y <= x ? word : tail_word(ne, y * 64);
+        return;
+      }
+    }
+  }
+  if (bits) {
+    // every candidate is taken already: the pending words, then zeros
+    const int64_t x = j0 >> 6;                    // words formed
+    for (int64_t y = (x & ~63ll) + lane; y < nw; y += 64) bits[y] = y < x ? word : 0ull;
+  }
+}
+
+// Membership words of the libraries of walk groups: bit l of word j is set
+// when library l of the group holds embedded point j -- the transpose of the
+// libraries' bitmaps, 64 x 64 bits at a time, one library per lane.  Each
+// wavefront takes kMaskWords consecutive bitmap words (a cache line of each
+// library's).
+constexpr int kMaskWords = 8;
+
+__global__ __launch_bounds__(kBlock) void k_masks(const MaskJob* __restrict__ jobs,
+                                                  const WalkLib* __restrict__ libs,
+                                                  const uint64_t* __restrict__ bit_pool,
+                                                  uint64_t* __restrict__ mask_pool) {
+  const MaskJob J = jobs[blockIdx.y];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int x0 = ((int)blockIdx.x * kWaves + wave) * kMaskWords;
+  const int nw = (J.n_e + 63) / 64;
+  const bool mine = lane < J.n_lib;
+  const uint64_t* __restrict__ bits = bit_pool + libs[J.lib_first + (mine ? lane : 0)].bit_off;
+  const BitTranspose transpose(lane);
+  uint64_t v[kMaskWords];
+#pragma unroll
+  for (int u = 0; u < kMaskWords; ++u) v[u] = mine && x0 + u < nw ? bits[x0 + u] : 0ull;
+#pragma unroll
+  for (int u = 0; u < kMaskWords; ++u) {
+    const uint64_t m = transpose(v[u]);
+    const int j = (x0 + u) * 64 + lane;
+    if (j < J.n_e) mask_pool[J.mask_off + j] = m;
   }
 }
 
@@ -687,11 +754,11 @@ hipError_t refine_orders_kd(const OrderJob* orders, int32_t n_sets, int levels,
 }
 
 
-hipError_t launch_sample(const SampleJob* jobs, int64_t n_jobs, int32_t* out,
+hipError_t launch_sample(const SampleJob* jobs, int64_t n_jobs, int32_t* out, uint64_t* bits,
                          hipStream_t st) {
   if (n_jobs <= 0) return hipSuccess;
   const unsigned blocks = (unsigned)((n_jobs + 3) / 4);   // one wavefront per library
-  k_sample<<<blocks, 256, 0, st>>>(jobs, n_jobs, out);
+  k_sample<<<blocks, 256, 0, st>>>(jobs, n_jobs, out, bits);
   return hipGetLastError();
 }
 
@@ -711,6 +778,76 @@ hipError_t launch_gather(const GatherJob* jobs, int64_t n_jobs, int64_t max_n_e,
   k_gather<<<(unsigned)n_jobs, kBlock, (size_t)words * 4, st>>>(jobs, emb, lib, order,
                                                                  pts, pj, start);
   return hipGetLastError();
+}
+
+hipError_t launch_masks(const MaskJob* jobs, int n_jobs, int max_ne, const WalkLib* libs,
+                        const uint64_t* bits, uint64_t* masks, hipStream_t st) {
+  if (n_jobs <= 0 || max_ne <= 0) return hipSuccess;
+  constexpr int span = kWaves * kMaskWords * 64;
+  const dim3 grid((unsigned)((max_ne + span - 1) / span), (unsigned)n_jobs);
+  k_masks<<<grid, kBlock, 0, st>>>(jobs, libs, bits, masks);
+  return hipGetLastError();
+}
+
+#define CCM_BY_E(E, CALL)                                                             \
+  switch (E) {                                                                        \
+    case 1: return CALL(1);                                                           \
+    case 2: return CALL(2);                                                           \
+    case 3: return CALL(3);                                                           \
+    case 4: return CALL(4);                                                           \
+    case 5: return CALL(5);                                                           \
+    case 6: return CALL(6);                                                           \
+    case 7: return CALL(7);                                                           \
+    case 8: return CALL(8);                                                           \
+    case 9: return CALL(9);                                                           \
+    case 10: return CALL(10);                                                         \
+    default: return hipErrorInvalidValue;                                             \
+  }
+
+hipError_t launch_order_points(int E, const RowJob* jobs, int n_jobs, int max_ne,
+                               const float* emb, const int32_t* qord, float* pts, float* box,
+                               hipStream_t st) {
+  if (n_jobs <= 0 || max_ne <= 0) return hipSuccess;
+#define CCM_CALL(e) launch_order_points_e<e>(jobs, n_jobs, max_ne, emb, qord, pts, box, st)
+  CCM_BY_E(E, CCM_CALL)
+#undef CCM_CALL
+}
+
+hipError_t launch_rows(int E, const RowJob* jobs, int n_jobs, int max_ne, int max_w,
+                       int per_block, const float* pts, const float* box, const int32_t* qord,
+                       uint64_t* rows, hipStream_t st) {
+  if (n_jobs <= 0 || max_ne <= 0) return hipSuccess;
+  if (max_w < 64 || max_w > kRowMaxW || max_w % 64 != 0 || per_block < 1)
+    return hipErrorInvalidValue;
+#define CCM_CALL(e) \
+  launch_rows_e<e>(jobs, n_jobs, max_ne, max_w, per_block, pts, box, qord, rows, st)
+  CCM_BY_E(E, CCM_CALL)
+#undef CCM_CALL
+}
+
+hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* libs,
+                       const RowJob* embs, const Item* items, int n_items, int per,
+                       const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
+                       const float* emb, const double* tgt, double* out, int excl,
+                       int query_set, hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+#define CCM_CALL(e)                                                                        \
+  launch_walk_e<e>(keys, groups, libs, embs, items, n_items, per, masks, rows, qord, emb, \
+                   tgt, out, excl, query_set, st)
+  CCM_BY_E(E, CCM_CALL)
+#undef CCM_CALL
+}
+
+hipError_t launch_walk_moments(int E, const Realization* rzs, const int64_t* out_off,
+                               const Item* items, int n_items, const double* out,
+                               const int32_t* pj, const int32_t* qord, const double* tgt,
+                               Moments* partial, int query_set, hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+#define CCM_CALL(e)                                                                       \
+  launch_walk_moments_e<e>(rzs, out_off, items, n_items, out, pj, qord, tgt, partial,     \
+                           query_set, st)
+  CCM_BY_E(E, CCM_CALL)
+#undef CCM_CALL
 }
 
 hipError_t launch_zero_int(int* p, int n, hipStream_t st) {

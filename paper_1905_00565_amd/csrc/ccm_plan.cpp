@@ -1,5 +1,6 @@
 // ccm_plan.cpp -- validation of a call and layout of its realizations,
 // work items and device pools (the planner of libccm).
+#include <map>
 #include <numeric>
 #include <unordered_map>
 
@@ -264,11 +265,256 @@ static void split_waves(Plan& p) {
   if (nested) p.n_scratch = max_scr;
 }
 
-// Waves, then the work items of each wave grouped by E (one launch each),
-// the costliest first within a group: a scan costs n_query * l_eff pairs, a
+// Device bytes of neighbour rows held at once (a batch holds at least one
+// embedding's; a single embedding past the cap scans instead), and of walk
+// output held at once.  Larger pools measured no faster.
+constexpr int64_t kRowPoolBytes = 1ll << 30;
+constexpr int64_t kRowPoolCap = 2ll << 30;
+constexpr int64_t kWalkOutBytes = 256ll << 20;
+
+// Row entries that hold, all but about once in 10^7, the first E+1 acceptable
+// members of a library of le of ne points: a member turns up every ne / le
+// entries, and the spread of their number is at most a Poisson variable's;
+// `excl` entries may be excluded ones.  (At once in 10^5 the searches of the
+// libraries that ran short took longer than the rest of the walk at N = 10^5,
+// 5.0 against 1.1 ms.)
+static int64_t row_need(int E, double excl, int64_t ne, int64_t le) {
+  const double k = E + 1;
+  const double n = (k + 5.5 * std::sqrt(k) + 9.0) * (double)ne / (double)le + excl;
+  return n < 1e9 ? (int64_t)n + 1 : (int64_t)1e9;
+}
+
+// Costs in instruction slots of a wavefront, per query of an embedding: one
+// scanned library (64 queries share a wavefront), one walk of a group of
+// libraries, and building a row of w entries.
+static double scan_cost(int E, int64_t le) {
+  return ((2.0 * E + 4.0) * (double)le * 1.25 + 110.0 * (E + 1) + 120.0) / 64.0;
+}
+static double walk_cost(int E, int64_t chunks) {
+  return 150.0 + 150.0 * (double)chunks + 30.0 * (E + 1) + 90.0 * (E + 1);
+}
+static double row_cost(int E, int64_t ne, int64_t w) {
+  return (2.0 * E + 20.0) * (double)ne / 64.0 + 8.0 * (double)w + 1500.0;
+}
+// Slots below which the walk's extra launches cost more than it saves.
+constexpr double kWalkMinGain = 2.0e7;
+
+// The realizations of one launch (rzs: one E of one wave) that walk
+// neighbour rows: per embedding its largest libraries, in groups of 64, as
+// many groups as each save more than they cost, when all they save together
+// exceeds the cost of the rows.
+static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int64_t& bits) {
+  if (!p.spec.walk || rzs.empty()) return;
+  const int E = la.E;
+  const bool keys = p.spec.M > 0;
+  const double excl =
+      p.mode == kExclSelf ? 1.0 : (p.mode == kWindow ? 2.0 * p.window + 1.0 : 0.0);
+  std::map<int64_t, std::vector<int32_t>> by_emb;   // in embedding order
+  for (int32_t r : rzs) by_emb[p.rz[r].emb_off].push_back(r);
+
+  struct Pick {
+    std::vector<std::vector<int32_t>> groups;
+    std::vector<int32_t> chunks;
+    int64_t w = 0;
+  };
+  std::vector<Pick> picks;
+  double gain_all = 0;
+  bool forced_any = false;
+  for (auto& kv : by_emb) {
+    std::vector<int32_t>& v = kv.second;
+    std::stable_sort(v.begin(), v.end(), [&](int32_t a, int32_t b) {
+      const bool fa = p.want_table[a] != 0, fb = p.want_table[b] != 0;
+      if (fa != fb) return fa;
+      return p.rz[a].l_eff > p.rz[b].l_eff;
+    });
+    const int64_t ne = p.rz[v[0]].n_e;
+    const int64_t full = (ne + 63) / 64 * 64;
+    Pick pk;
+    double gain = 0;
+    bool forced = false;
+    for (size_t g0 = 0; g0 < v.size(); g0 += kWalkLibs) {
+      const size_t g1 = std::min(v.size(), g0 + kWalkLibs);
+      std::vector<int32_t> grp;
+      int64_t need = 64;
+      double scan = 0;
+      bool force = false;
+      for (size_t k = g0; k < g1; ++k) {
+        const Realization& R = p.rz[v[k]];
+        int64_t n = std::min(full, (row_need(E, excl, ne, R.l_eff) + 63) / 64 * 64);
+        const bool want = p.want_table[v[k]] != 0;
+        if (want) n = std::min<int64_t>(n, kRowMaxW);
+        if (n > kRowMaxW) continue;
+        force |= want;
+        need = std::max(need, n);
+        scan += scan_cost(E, R.l_eff) * (double)R.n_query / (double)ne;
+        grp.push_back(v[k]);
+      }
+      if (grp.empty()) continue;
+      const double save = scan - walk_cost(E, need / 64);
+      if (save <= 0 && !force) continue;
+      gain += save;
+      forced |= force;
+      pk.w = std::max(pk.w, need);
+      pk.groups.push_back(std::move(grp));
+      pk.chunks.push_back((int32_t)(need / 64));
+    }
+    const bool fits = ne * pk.w * 8 <= kRowPoolCap;
+    gain = (gain - row_cost(E, ne, pk.w)) * (double)ne;
+    if (pk.groups.empty() || !fits || (gain <= 0 && !forced)) continue;
+    gain_all += gain;
+    forced_any |= forced;
+    picks.push_back(std::move(pk));
+  }
+  if (picks.empty() || (gain_all < kWalkMinGain && !forced_any)) return;
+
+  // groups of different embeddings that draw the same libraries share masks
+  std::map<std::vector<int64_t>, int64_t> mask_of;
+  int64_t masks = 0, total_q = 0;
+  la.mask_first = (int32_t)p.mask_jobs.size();
+  const size_t group0 = p.walk_groups.size();
+  std::vector<size_t> emb_group;      // first group of each row job
+  const int32_t job0 = (int32_t)p.row_jobs.size();
+  for (Pick& pk : picks) {
+    const Realization& R0 = p.rz[pk.groups[0][0]];
+    RowJob rj{};
+    rj.emb_off = R0.emb_off;
+    rj.qord_off = R0.qord_off;
+    rj.n_e = R0.n_e;
+    rj.w = (int32_t)pk.w;
+    emb_group.push_back(p.walk_groups.size());
+    for (size_t g = 0; g < pk.groups.size(); ++g) {
+      const std::vector<int32_t>& grp = pk.groups[g];
+      WalkGroup wg{};
+      wg.lib_first = (int64_t)p.walk_libs.size();
+      wg.tgt_off = keys ? 0 : R0.tgt_off + (int64_t)(E - 1) * R0.tau;
+      wg.n_lib = (int32_t)grp.size();
+      wg.emb = (int32_t)p.row_jobs.size();
+      wg.chunks = pk.chunks[g];
+      std::vector<int64_t> sig;
+      for (int32_t r : grp) {
+        WalkLib wl{};
+        // the draw's bitmap, one per draw of the wave
+        SampleJob& sj = p.sample[p.rz_sample[r]];
+        if (sj.bits == 0) {
+          sj.bits = 1 + bits;
+          bits += (rj.n_e + 63) / 64;
+        }
+        wl.bit_off = sj.bits - 1;
+        wl.l_eff = p.rz[r].l_eff;
+        wl.rz = r;
+        p.walk_libs.push_back(wl);
+        p.walked[r] = 1;
+        if (p.want_table[r]) p.table_rz += keys ? p.spec.M - 1 : 1;
+        sig.push_back(wl.bit_off);
+      }
+      const auto it = mask_of.emplace(sig, masks);
+      wg.mask_off = it.first->second;
+      if (it.second) {
+        p.mask_jobs.push_back({masks, wg.lib_first, wg.n_lib, rj.n_e});
+        la.mask_max_ne = std::max(la.mask_max_ne, rj.n_e);
+        masks += rj.n_e;
+      }
+      p.walk_groups.push_back(wg);
+      total_q += rj.n_e;
+    }
+    p.row_jobs.push_back(rj);
+  }
+  emb_group.push_back(p.walk_groups.size());
+  la.mask_count = (int32_t)p.mask_jobs.size() - la.mask_first;
+  p.n_mask = std::max(p.n_mask, masks);
+  (void)group0;
+
+  // enough items to fill the chip, at most 64 queries each
+  la.walk_per = (int32_t)std::min<int64_t>(64, std::max<int64_t>(4, total_q / 8192 / 4 * 4));
+
+  la.batch_first = (int32_t)p.walk_batches.size();
+  const int32_t n_jobs = (int32_t)p.row_jobs.size() - job0;
+  const int64_t per_query = keys ? E + 1 : 1;
+  for (int32_t e0 = 0; e0 < n_jobs;) {
+    WalkBatch wb;
+    wb.emb_first = job0 + e0;
+    int64_t rows = 0, opts = 0, box = 0, n_row = 0;
+    int32_t e1 = e0;
+    for (; e1 < n_jobs; ++e1) {
+      RowJob& rj = p.row_jobs[job0 + e1];
+      const int64_t need = (int64_t)rj.n_e * rj.w;
+      if (e1 > e0 && (rows + need) * 8 > kRowPoolBytes) break;
+      if (e1 - e0 >= 65535) break;
+      rj.out_off = rows;
+      rj.pts_off = opts;
+      rj.box_off = box;
+      rows += need;
+      opts += (int64_t)rj.n_e * E;
+      box += (int64_t)((rj.n_e + 63) / 64) * 2 * E;
+      n_row += rj.n_e;
+      wb.max_ne = std::max(wb.max_ne, rj.n_e);
+      wb.max_w = std::max(wb.max_w, rj.w);
+    }
+    wb.emb_count = e1 - e0;
+    wb.rows_per_block = (int32_t)std::min<int64_t>(16, std::max<int64_t>(1, n_row / 4096));
+    p.n_rows = std::max(p.n_rows, rows);
+    p.n_opts = std::max(p.n_opts, opts);
+    p.n_box = std::max(p.n_box, box);
+    wb.chunk_first = (int32_t)p.walk_chunks.size();
+    // chunks: consecutive groups whose output fits; within a chunk the
+    // groups of one embedding take the same block of queries together, so
+    // they read its rows from cache
+    size_t g = emb_group[e0];
+    const size_t g_end = emb_group[e1];
+    while (g < g_end) {
+      WalkChunk ch;
+      ch.item_first = (int64_t)p.walk_items.size();
+      ch.mom_first = (int64_t)p.mom_items.size();
+      int64_t out = 0;
+      size_t h = g;
+      for (; h < g_end; ++h) {
+        const WalkGroup& wg = p.walk_groups[h];
+        const int64_t ne = p.row_jobs[wg.emb].n_e;
+        const int64_t need = (int64_t)wg.n_lib * ne * per_query;
+        if (h > g && (out + need) * 8 > kWalkOutBytes) break;
+        for (int l = 0; l < wg.n_lib; ++l) {
+          WalkLib& wl = p.walk_libs[wg.lib_first + l];
+          wl.out_off = out + (int64_t)l * ne * per_query;
+          p.walk_out[wl.rz] = wl.out_off;
+        }
+        out += need;
+      }
+      for (size_t a = g; a < h;) {
+        size_t b = a;
+        while (b < h && p.walk_groups[b].emb == p.walk_groups[a].emb) ++b;
+        const int32_t ne = p.row_jobs[p.walk_groups[a].emb].n_e;
+        const int32_t blocks = (ne + la.walk_per - 1) / la.walk_per;
+        for (int32_t q = 0; q < blocks; ++q)
+          for (size_t x = a; x < b; ++x) p.walk_items.push_back({(int32_t)x, q});
+        for (size_t x = a; x < b; ++x)
+          for (int l = 0; l < p.walk_groups[x].n_lib; ++l) {
+            const int32_t r = p.walk_libs[p.walk_groups[x].lib_first + l].rz;
+            for (int32_t t = 0; t < p.rz[r].n_tiles; ++t) p.mom_items.push_back({r, t});
+          }
+        a = b;
+      }
+      ch.item_count = (int64_t)p.walk_items.size() - ch.item_first;
+      ch.mom_count = (int64_t)p.mom_items.size() - ch.mom_first;
+      p.n_walk_out = std::max(p.n_walk_out, out);
+      p.walk_chunks.push_back(ch);
+      g = h;
+    }
+    wb.chunk_count = (int32_t)p.walk_chunks.size() - wb.chunk_first;
+    p.walk_batches.push_back(wb);
+    e0 = e1;
+  }
+  la.batch_count = (int32_t)p.walk_batches.size() - la.batch_first;
+}
+
+// Waves, then the work items of each wave grouped by E (one launch each):
+// the realizations that walk neighbour rows, and the scanned ones, the
+// costliest first within a group: a scan costs n_query * l_eff pairs, a
 // table walk about n_query * (E+1) n_e / l_eff row entries.
 static void order_items(Plan& p) {
   split_waves(p);
+  p.walked.assign(p.rz.size(), 0);
+  p.want_table.resize(p.rz.size(), 0);
+  if (p.spec.walk) p.walk_out.assign(p.rz.size(), 0);
   auto cost = [&](const Realization& R) {
     return R.table_off >= 0 ? (double)R.n_query * (R.E + 1) * R.n_e / R.l_eff / 8.0
                             : (double)R.n_query * R.l_eff;
@@ -281,15 +527,50 @@ static void order_items(Plan& p) {
       return cost(p.rz[a]) > cost(p.rz[b]);
     });
     p.waves[w].launch_first = (int32_t)p.launches.size();
-    for (int32_t idx : order) {
-      const Realization& R = p.rz[idx];
-      if (p.launches.size() == (size_t)p.waves[w].launch_first || p.launches.back().E != R.E)
-        p.launches.push_back({R.E, (int32_t)p.items.size(), 0});
-      for (int t = 0; t < R.n_tiles; ++t) p.items.push_back({idx, t});
-      p.launches.back().count += R.n_tiles;
-      if (p.items.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many work items");
+    int64_t bits = 0;                 // words of the wave's bitmaps
+    for (size_t a = 0; a < order.size();) {
+      size_t b = a;
+      while (b < order.size() && p.rz[order[b]].E == p.rz[order[a]].E) ++b;
+      Launch la{};
+      la.E = p.rz[order[a]].E;
+      la.first = (int32_t)p.items.size();
+      plan_walks(p, std::vector<int32_t>(order.begin() + a, order.begin() + b), la,
+                 bits);
+      for (; a < b; ++a) {
+        if (p.walked[order[a]]) continue;
+        const Realization& R = p.rz[order[a]];
+        for (int t = 0; t < R.n_tiles; ++t) p.items.push_back({order[a], t});
+        la.count += R.n_tiles;
+        if (p.items.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many work items");
+      }
+      p.launches.push_back(la);
     }
     p.waves[w].launch_count = (int32_t)p.launches.size() - p.waves[w].launch_first;
+    p.n_bits = std::max(p.n_bits, bits);
+  }
+  if (p.walk_groups.empty()) return;
+  // a walked realization needs neither its draw as a list nor a gathered
+  // library, but for library-point queries, whose order is the gathered one
+  if (p.spec.query_set == 0) {
+    for (size_t r = 0; r < p.rz.size(); ++r)
+      if (p.walked[r]) p.sample[p.rz_sample[r]].no_list = 1;
+    for (size_t r = 0; r < p.rz.size(); ++r)
+      if (!p.walked[r]) p.sample[p.rz_sample[r]].no_list = 0;
+    std::vector<char> skip(p.gather.size(), 0);
+    for (size_t r = 0; r < p.rz.size(); ++r)
+      if (p.walked[r]) skip[p.rz_gather[r]] = 1;
+    for (Wave& w : p.waves) {
+      std::vector<GatherJob> keep;
+      int64_t max_ne = 0;
+      for (int64_t g = w.gather_first; g < w.gather_first + w.gather_count; ++g)
+        if (!skip[g]) {
+          keep.push_back(p.gather[g]);
+          if (p.gather[g].sorted) max_ne = std::max(max_ne, p.gather[g].n_e);
+        }
+      std::copy(keep.begin(), keep.end(), p.gather.begin() + w.gather_first);
+      w.gather_count = (int64_t)keep.size();
+      w.max_sorted_n_e = max_ne;
+    }
   }
 }
 
@@ -481,7 +762,7 @@ static Plan make_plan_shared(const Spec& s) {
       for (int ie = 0; ie < nE; ++ie) p.L_eff[((size_t)ie * nT + it) * nL + il] = le;
       for (int ri = 0; ri < s.r; ++ri) {
         const int64_t lib_off = p.n_lib;
-        p.sample.push_back({s.seed, nc, le, lib_off, 0, tau, ri, 0});
+        p.sample.push_back({s.seed, nc, le, lib_off, 0, tau, ri, 0, 0});
         p.n_lib += le;
         for (int dir = 0; dir < 2; ++dir) {
           const int lib_s = dir == 0 ? 1 : 0;
@@ -615,7 +896,7 @@ Plan make_plan(const Spec& s) {
         p.L_eff[((size_t)ie * nT + it) * nL + il] = le;
         for (int ri = 0; ri < s.r; ++ri) {
           const int64_t lib_off = p.n_lib;
-          p.sample.push_back({s.seed, ne, le, lib_off, E, tau, ri, 0});
+          p.sample.push_back({s.seed, ne, le, lib_off, E, tau, ri, 0, 0});
           p.n_lib += le;
           for (int dir = 0; dir < 2; ++dir) {
             // dir 0: library Y (series 1) predicts X (series 0); dir 1: reverse
@@ -636,7 +917,9 @@ Plan make_plan(const Spec& s) {
             R.slot_base = p.n_slots;
             R.out_index = ((((int64_t)dir * nE + ie) * nT + it) * nL + il) * s.r + ri;
             R.table_off = -1;
-            if (use_table(p, E, ne, le)) {
+            const bool table = use_table(p, E, ne, le);
+            p.want_table.push_back(table && s.walk);
+            if (table && !s.walk) {
               R.table_off = table_for(p, R.emb_off, ne, E);
               R.table_w = (int32_t)std::min<int64_t>(kTableWidth, ne);
               p.e_table_ne[E] = std::max(p.e_table_ne[E], (int)ne);
@@ -687,7 +970,8 @@ Plan make_plan(const Spec& s) {
                    (size_t)p.n_ord * 16 + p.n_table * 4 + p.tables.size() * sizeof(TableJob) +
                    p.n_slots * sizeof(Moments) + p.n_out * 8 +
                    p.rz.size() * sizeof(Realization) + p.items.size() * sizeof(Item) +
-                   p.sample.size() * sizeof(SampleJob) + p.gather.size() * sizeof(GatherJob);
+                   p.sample.size() * sizeof(SampleJob) + p.gather.size() * sizeof(GatherJob) +
+                   p.walk_bytes();
   return p;
 }
 
@@ -747,7 +1031,7 @@ Plan make_plan_matrix(const Spec& s) {
     p.L_eff[il] = le;
     for (int ri = 0; ri < s.r; ++ri) {
       lib_off[(size_t)il * s.r + ri] = p.n_lib;
-      p.sample.push_back({s.seed, ne, le, p.n_lib, E, tau, ri, 0});
+      p.sample.push_back({s.seed, ne, le, p.n_lib, E, tau, ri, 0, 0});
       p.n_lib += le;
     }
   }
@@ -770,7 +1054,9 @@ Plan make_plan_matrix(const Spec& s) {
         R.slot_base = p.n_slots;
         R.out_index = (((int64_t)a * M) * nL + il) * s.r + ri;   // target 0 of row a
         R.table_off = -1;
-        if (use_table(p, E, ne, le)) {
+        const bool table = use_table(p, E, ne, le);
+        p.want_table.push_back(table && s.walk);
+        if (table && !s.walk) {
           R.table_off = table_for(p, R.emb_off, ne, E);
           R.table_w = (int32_t)std::min<int64_t>(kTableWidth, ne);
           p.e_table_ne[E] = std::max(p.e_table_ne[E], (int)ne);
@@ -816,7 +1102,8 @@ Plan make_plan_matrix(const Spec& s) {
                    N * target_stride(M) * 8 + p.n_table * 4 +
                    p.tables.size() * sizeof(TableJob) +
                    p.rz.size() * (sizeof(Realization) + 4) + p.items.size() * sizeof(Item) +
-                   p.sample.size() * sizeof(SampleJob) + p.gather.size() * sizeof(GatherJob);
+                   p.sample.size() * sizeof(SampleJob) + p.gather.size() * sizeof(GatherJob) +
+                   p.walk_bytes();
   return p;
 }
 

@@ -44,6 +44,13 @@ void drain_events(ccm_ctx* c) {
   c->ev_pending.clear();
 }
 
+// The batched forms walk neighbour rows; the plain baseline and the forms
+// with draws of their own scan.
+bool walks(const Spec& s) {
+  return s.M == 0 &&
+         !(s.flags & (CCM_FLAG_PLAIN | CCM_FLAG_NESTED | CCM_FLAG_SHARED_E));
+}
+
 // Device buffers and descriptors for a plan (reused when the shape repeats).
 Exec* prepare(ccm_ctx* c, const Spec& s) {
   if (c->exec && c->exec->plan.spec == s) return c->exec.get();
@@ -54,9 +61,16 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   }
   auto ex = std::make_unique<Exec>();
   ex->plan = s.M > 0 ? make_plan_matrix(s) : make_plan(s);
-  Plan& p = ex->plan;
   size_t free_b = 0, total_b = 0;
   HIPCHK(hipMemGetInfo(&free_b, &total_b));
+  if (ex->plan.device_bytes > free_b && !ex->plan.walk_groups.empty()) {
+    // the neighbour rows are what does not fit: scan instead
+    Spec scan = s;
+    scan.walk = false;
+    ex->plan = s.M > 0 ? make_plan_matrix(scan) : make_plan(scan);
+    ex->plan.spec.walk = s.walk;
+  }
+  Plan& p = ex->plan;
   if (p.device_bytes > free_b)
     fail(CCM_E_NOMEM, "plan needs " + std::to_string(p.device_bytes) + " device bytes, " +
                           std::to_string(free_b) + " free");
@@ -87,6 +101,21 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
     upload(ex->d_segs, p.segs);
   }
   if (!p.rz_fin.empty()) upload(ex->d_rz_fin, p.rz_fin);
+  if (!p.walk_groups.empty()) {
+    upload(ex->d_row_jobs, p.row_jobs);
+    upload(ex->d_mask_jobs, p.mask_jobs);
+    upload(ex->d_walk_libs, p.walk_libs);
+    upload(ex->d_walk_groups, p.walk_groups);
+    upload(ex->d_walk_items, p.walk_items);
+    upload(ex->d_mom_items, p.mom_items);
+    upload(ex->d_walk_off, p.walk_out);
+    ex->d_rows.ensure(p.n_rows * 8);
+    ex->d_bits.ensure(p.n_bits * 8);
+    ex->d_masks.ensure(p.n_mask * 8);
+    ex->d_opts.ensure(p.n_opts * 4);
+    ex->d_boxes.ensure(p.n_box * 4);
+    ex->d_walk_out.ensure(p.n_walk_out * 8);
+  }
   ex->d_s64.ensure(p.n64 * 8);
   ex->d_s32.ensure(p.n32 * 4);
   ex->d_iota.ensure(p.n_ord * 4);
@@ -143,6 +172,19 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   b.shuffle = ex->d_scratch.as<int32_t>();
   b.segs = ex->d_segs.as<int32_t>();
   b.rz_fin = ex->d_rz_fin.as<Realization>();
+  b.row_jobs = ex->d_row_jobs.as<RowJob>();
+  b.mask_jobs = ex->d_mask_jobs.as<MaskJob>();
+  b.walk_libs = ex->d_walk_libs.as<WalkLib>();
+  b.walk_groups = ex->d_walk_groups.as<WalkGroup>();
+  b.walk_items = ex->d_walk_items.as<Item>();
+  b.mom_items = ex->d_mom_items.as<Item>();
+  b.walk_out_off = ex->d_walk_off.as<int64_t>();
+  b.rows = ex->d_rows.as<uint64_t>();
+  b.bits = ex->d_bits.as<uint64_t>();
+  b.masks = ex->d_masks.as<uint64_t>();
+  b.opts = ex->d_opts.as<float>();
+  b.boxes = ex->d_boxes.as<float>();
+  b.walk_out = ex->d_walk_out.as<double>();
   c->exec = std::move(ex);
   return c->exec.get();
 }
@@ -153,16 +195,46 @@ int persistent_grid(ccm_ctx* c, int n_items) {
   return std::min(g, n_items);
 }
 
+// The walks of one launch: membership words, then per batch of embeddings
+// their neighbour rows, and per chunk the walk and the moments it leaves.
+void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStream_t st) {
+  if (L.batch_count == 0) return;
+  const int excl = p.mode == kKeepSelf ? -1 : p.window;
+  for (int m0 = 0; m0 < L.mask_count; m0 += 65535)
+    HIPCHK(launch_masks(b.mask_jobs + L.mask_first + m0, std::min(65535, L.mask_count - m0),
+                        L.mask_max_ne, b.walk_libs, b.bits, b.masks, st));
+  for (int bi = L.batch_first; bi < L.batch_first + L.batch_count; ++bi) {
+    const WalkBatch& wb = p.walk_batches[bi];
+    const RowJob* jobs = b.row_jobs + wb.emb_first;
+    HIPCHK(launch_order_points(L.E, jobs, wb.emb_count, wb.max_ne, b.emb, b.qord, b.opts,
+                               b.boxes, st));
+    HIPCHK(launch_rows(L.E, jobs, wb.emb_count, wb.max_ne, wb.max_w, wb.rows_per_block, b.opts,
+                       b.boxes, b.qord, b.rows, st));
+    for (int ci = wb.chunk_first; ci < wb.chunk_first + wb.chunk_count; ++ci) {
+      const WalkChunk& ch = p.walk_chunks[ci];
+      HIPCHK(launch_walk(L.E, 0, b.walk_groups, b.walk_libs, b.row_jobs,
+                         b.walk_items + ch.item_first, (int)ch.item_count, L.walk_per, b.masks,
+                         b.rows, b.qord, b.emb, b.s64, b.walk_out, excl,
+                         p.spec.query_set, st));
+      HIPCHK(launch_walk_moments(L.E, b.rz, b.walk_out_off, b.mom_items + ch.mom_first,
+                                 (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.s64,
+                                 static_cast<Moments*>(b.partial), p.spec.query_set, st));
+    }
+  }
+}
+
 // One cross-map launch over items [first, first + n) of b.items (or of
-// b.plain_items), E's kernel variant for the plan's form.
+// b.plain_items), E's kernel variant for the plan's form, after the walks of
+// `walks` (null: none).
 void launch_items(ccm_ctx* c, const Plan& p, const PlanBuffers& b, const Item* items, int n,
-                  int E, int grid, int* next, int table_ne, hipStream_t st,
+                  int E, int grid, int* next, int table_ne, const Launch* walks, hipStream_t st,
                   std::vector<EvPair>* evs) {
   EvPair ev;
   if (evs) {
     ev = take_events(c);
     HIPCHK(hipEventRecord(ev.a, st));
   }
+  if (walks) launch_walks(p, b, *walks, st);
   const Dump nodump{nullptr, nullptr, nullptr};
   if (p.shared_emax > 0)
     HIPCHK(launch_crossmap_shared(E, p.mode, grid, b.rz, items, n, next, b.emb, b.pts, b.pj,
@@ -222,20 +294,20 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
         HIPCHK(launch_sample_nested(b.nested + w.sample_first, w.sample_count, b.shuffle, b.lib,
                                     st));
       else
-        HIPCHK(launch_sample(b.sample + w.sample_first, w.sample_count, b.lib, st));
+        HIPCHK(launch_sample(b.sample + w.sample_first, w.sample_count, b.lib, b.bits, st));
       HIPCHK(launch_gather(b.gather + w.gather_first, w.gather_count, w.max_sorted_n_e, b.emb,
                            b.lib, b.order, b.pts, b.pj, b.start, st));
       for (int li = w.launch_first; li < w.launch_first + w.launch_count; ++li) {
         const Launch& L = p.launches[li];
         int grid = L.count;
         int* next = nullptr;
-        if (persistent) {
+        if (persistent && L.count > 0) {
           grid = persistent_grid(c, L.count);
           next = b.counter + li;
           HIPCHK(launch_zero_int(next, 1, st));
         }
         launch_items(c, p, b, b.items + L.first, L.count, L.E, grid, next, p.e_table_ne[L.E],
-                     st, evs);
+                     &L, st, evs);
       }
     } else {
       // the unbatched baseline: sampler, gather and cross-map launched per
@@ -246,14 +318,14 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
         const Realization& R = p.rz[r];
         const int64_t sj = p.rz_sample[r];
         if (!sampled[sj - w.sample_first]) {
-          HIPCHK(launch_sample(b.sample + sj, 1, b.lib, st));
+          HIPCHK(launch_sample(b.sample + sj, 1, b.lib, b.bits, st));
           sampled[sj - w.sample_first] = 1;
         }
         const GatherJob& G = p.gather[p.rz_gather[r]];
         HIPCHK(launch_gather(b.gather + p.rz_gather[r], 1, G.sorted ? G.n_e : 0, b.emb, b.lib,
                              b.order, b.pts, b.pj, b.start, st));
         launch_items(c, p, b, b.plain_items + plain_first[r], R.n_tiles, R.E, R.n_tiles,
-                     nullptr, R.table_off >= 0 ? R.n_e : 0, st, evs);
+                     nullptr, R.table_off >= 0 ? R.n_e : 0, nullptr, st, evs);
       }
     }
   }
@@ -431,6 +503,7 @@ ccm_status ccm_sweep(ccm_ctx* c, const double* X, const double* Y, int64_t N,
     if (!rho) fail(CCM_E_INVAL, "rho is NULL");
     Spec s = make_spec(N, E, nE, tau, ntau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
+    s.walk = walks(s);
     check_host_series(X, N, "X");
     check_host_series(Y, N, "Y");
     Exec* ex = prepare(c, s);
@@ -451,6 +524,7 @@ ccm_status ccm(ccm_ctx* c, const double* X, const double* Y, int64_t N, int32_t 
     if (!rho_xy || !rho_yx) fail(CCM_E_INVAL, "rho output is NULL");
     Spec s = make_spec(N, &E, 1, &tau, 1, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
+    s.walk = walks(s);
     check_host_series(X, N, "X");
     check_host_series(Y, N, "Y");
     Exec* ex = prepare(c, s);
@@ -475,6 +549,7 @@ ccm_status ccm_sweep_dev(ccm_ctx* c, const double* X, const double* Y, int64_t N
     if (!X || !Y || !rho) fail(CCM_E_INVAL, "NULL device pointer");
     Spec s = make_spec(N, E, nE, tau, ntau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
+    s.walk = walks(s);
     hipStream_t st = static_cast<hipStream_t>(stream);
     Exec* ex = prepare(c, s);
     HIPCHK(launch_copy_pair(X, Y, N, ex->d_s64.as<double>(), st));
@@ -491,6 +566,7 @@ ccm_status ccm_dev(ccm_ctx* c, const double* X, const double* Y, int64_t N, int3
     if (!X || !Y || !rho_xy || !rho_yx) fail(CCM_E_INVAL, "NULL device pointer");
     Spec s = make_spec(N, &E, 1, &tau, 1, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
+    s.walk = walks(s);
     hipStream_t st = static_cast<hipStream_t>(stream);
     Exec* ex = prepare(c, s);
     HIPCHK(launch_copy_pair(X, Y, N, ex->d_s64.as<double>(), st));
@@ -509,6 +585,7 @@ ccm_status ccm_matrix(ccm_ctx* c, const double* S, int32_t M, int64_t N, int32_t
     if (!rho) fail(CCM_E_INVAL, "rho is NULL");
     Spec s = make_matrix_spec(M, N, E, tau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
+    s.walk = walks(s);
     check_host_series(S, (int64_t)M * N, "S");
     Exec* ex = prepare(c, s);
     const int64_t n_out = ex->plan.n_out;
@@ -528,6 +605,7 @@ ccm_status ccm_matrix_dev(ccm_ctx* c, const double* S, int32_t M, int64_t N, int
     if (!S || !rho) fail(CCM_E_INVAL, "NULL device pointer");
     Spec s = make_matrix_spec(M, N, E, tau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
+    s.walk = walks(s);
     hipStream_t st = static_cast<hipStream_t>(stream);
     Exec* ex = prepare(c, s);
     HIPCHK(hipMemcpyAsync(ex->d_s64.p, S, (size_t)M * N * 8, hipMemcpyDeviceToDevice, st));
@@ -544,10 +622,10 @@ ccm_status ccm_library(ccm_ctx* c, int64_t N_e, int32_t E, int32_t tau, int64_t 
       fail(CCM_E_INVAL, "need 1 <= L_eff <= N_e < 2^31");
     if (E < 1 || E > kMaxE || tau < 1) fail(CCM_E_INVAL, "E in [1, 10] and tau >= 1");
     DevBuf job, out;
-    std::vector<SampleJob> j{{seed, N_e, L_eff, 0, E, tau, r_index, 0}};
+    std::vector<SampleJob> j{{seed, N_e, L_eff, 0, E, tau, r_index, 0, 0}};
     upload(job, j);
     out.ensure(L_eff * 4);
-    HIPCHK(launch_sample(job.as<SampleJob>(), 1, out.as<int32_t>(), c->stream));
+    HIPCHK(launch_sample(job.as<SampleJob>(), 1, out.as<int32_t>(), nullptr, c->stream));
     HIPCHK(hipMemcpyAsync(idx_out, out.p, L_eff * 4, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
   });

@@ -324,7 +324,7 @@ void start_job(ccm_server* s, Job& j) {
   HIPCHK(launch_query_order(at<EmbedJob>(s, R0 + L.d_embed), (int)p.embed.size(),
                             at<int32_t>(s, R0 + L.order), at<int32_t>(s, R0 + L.qord), st));
   HIPCHK(launch_sample(at<SampleJob>(s, R0 + L.d_sample), (int64_t)p.sample.size(),
-                       at<int32_t>(s, R0 + L.lib), st));
+                       at<int32_t>(s, R0 + L.lib), nullptr, st));
   HIPCHK(launch_gather(at<GatherJob>(s, R0 + L.d_gather), (int64_t)p.gather.size(),
                        p.max_sorted_n_e, at<float>(s, R0 + L.emb), at<int32_t>(s, R0 + L.lib),
                        at<int32_t>(s, R0 + L.order), at<float>(s, R0 + L.pts),

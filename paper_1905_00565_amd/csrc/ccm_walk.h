@@ -1,0 +1,636 @@
+// ccm_walk.h -- device templates of the neighbour-row path: the sorted
+// neighbour rows of an embedding, the walk of a row by 64 libraries at once,
+// and the moments of the predictions it leaves (one translation unit per
+// embedding dimension instantiates them, see ccm_inst_walk.hip).
+//
+// A query's neighbours in any library are the first E+1 members of that
+// library (not excluded) in the query's row: every embedded point in (d2, j)
+// order.  The rows do not depend on the library, so a call with many
+// libraries per embedding (L list times r) pays for the search once per
+// query instead of once per query and library; what is left per library is
+// a walk of about (E+1) n_e / l_eff row entries.  The rows hold the same
+// binary32 d2 as the scan and the order is the same total order, so the
+// neighbours, and with the same operations in the same order the
+// predictions, moments and rho, are the scan's bit for bit.
+#pragma once
+#include "ccm_device.h"
+
+namespace ccmk {
+
+// ---------------------------------------------------------------------------
+// neighbour rows
+// ---------------------------------------------------------------------------
+
+// The points of one embedding in visiting order, one array per coordinate
+// (float [E][n_e]), and the bounding box of every run of 64 of them (float
+// [E] lowest, then [E] highest, per run).  One wavefront per run.
+template <int E>
+__global__ __launch_bounds__(kBlock) void k_order_points(const RowJob* __restrict__ jobs,
+                                                         const float* __restrict__ emb_pool,
+                                                         const int32_t* __restrict__ qord_pool,
+                                                         float* __restrict__ pts_pool,
+                                                         float* __restrict__ box_pool) {
+  const RowJob J = jobs[blockIdx.y];
+  const int lane = threadIdx.x & 63;
+  const int b = blockIdx.x * kWaves + (threadIdx.x >> 6);
+  if (b * 64 >= J.n_e) return;
+  const int p = min(b * 64 + lane, J.n_e - 1);     // the tail repeats the last point
+  const int i = qord_pool[J.qord_off + p];
+  const float* __restrict__ v = emb_pool + J.emb_off + (int64_t)i * E;
+  float* __restrict__ o = pts_pool + J.pts_off;
+  float* __restrict__ box = box_pool + J.box_off + (int64_t)b * (2 * E);
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const float x = v[k];
+    o[(int64_t)k * J.n_e + p] = x;
+    float lo = x, hi = x;
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+      lo = fminf(lo, __shfl_xor(lo, s, 64));
+      hi = fmaxf(hi, __shfl_xor(hi, s, 64));
+    }
+    if (lane == 0) {
+      box[k] = lo;
+      box[E + k] = hi;
+    }
+  }
+}
+
+// LDS of the row kernel (dynamic): four candidate segments of seg keys, one
+// per wavefront; the same candidates grouped by bucket; bucket counters.
+constexpr int kRowBuckets = 1024;
+constexpr int row_segment(int w) { return w / 2 + 192; }
+inline size_t row_lds_bytes(int w) {
+  return (size_t)kWaves * row_segment(w) * 16 + kRowBuckets * 4;
+}
+
+// Distances of the lanes' points of run b to the query.
+template <int E>
+__device__ __forceinline__ float run_d2(const float* __restrict__ pts, int n_e, int c,
+                                        const float (&q)[E]) {
+  float d = q[0] - pts[c];
+  float acc = d * d;
+#pragma unroll
+  for (int k = 1; k < E; ++k) {
+    d = q[k] - pts[(int64_t)k * n_e + c];
+    acc = __builtin_fmaf(d, d, acc);
+  }
+  return acc;
+}
+
+// A lower bound of run b's distances: the same binary32 chain over the gap
+// between the query and the run's box.  Subtraction, product and fused
+// multiply-add round monotonically, so no point of the box has a smaller d2.
+template <int E>
+__device__ __forceinline__ float run_bound(const float* __restrict__ box, const float (&q)[E]) {
+  float acc = 0.f;
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const float g = fmaxf(fmaxf(box[k] - q[k], q[k] - box[E + k]), 0.f);
+    acc = k == 0 ? g * g : __builtin_fmaf(g, g, acc);
+  }
+  return acc;
+}
+
+__device__ __forceinline__ uint64_t row_key(float d2, int j) {
+  return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
+}
+__device__ __forceinline__ int row_bucket(uint64_t key, float scale) {
+  const float x = __uint_as_float((uint32_t)(key >> 32)) * scale;
+  return x < (float)(kRowBuckets - 1) ? (int)x : (x >= 0.f ? kRowBuckets - 1 : 0);
+}
+
+// Calls f(c, d2, valid) for the 64 points c of every run whose bound does
+// not exceed t, runs dealt to the workgroup's wavefronts in turn.
+template <int E, class F>
+__device__ __forceinline__ void visit_runs(const float* __restrict__ pts,
+                                           const float* __restrict__ boxes, int n_e,
+                                           const float (&q)[E], float t, F&& f) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = (n_e + 63) >> 6;
+  for (int g = 0; g < nb; g += kBlock) {
+    const int b = g + lane * kWaves + wave;
+    const bool near = b < nb && run_bound<E>(boxes + (int64_t)b * (2 * E), q) <= t;
+    uint64_t open = __builtin_amdgcn_ballot_w64(near);
+    while (open) {
+      const int l = __builtin_ctzll(open);
+      open &= open - 1ull;
+      const int c = (g + l * kWaves + wave) * 64 + lane;
+      const bool valid = c < n_e;
+      const float d2 = run_d2<E>(pts, n_e, valid ? c : n_e - 1, q);
+      f(c, d2, valid);
+    }
+  }
+}
+
+// Neighbour rows: row p of a job = the first w embedded points of its
+// embedding in ascending (d2, j) order from the point at visiting position
+// p, as keys (d2 bits, j); entries past n_e are ~0.
+//
+// One workgroup per run of consecutive positions.  The w-th distance changes
+// little from one position to the next, so each row starts from a threshold
+// just above the previous row's w-th distance: one pass over the runs of 64
+// points whose box reaches within it collects the candidates (bound by that
+// pass: 2E operations and one load per coordinate for each point visited),
+// and only a row whose threshold caught too few or too many repeats it with
+// another.  The candidates, about 1.2 w, are then ordered by bucket of d2
+// and by comparison within a bucket, a tenth of the work of a sorting
+// network at w = 1024.  A row whose w-th distance is shared by more points
+// than fit (repeated values) is selected by radix passes instead.
+template <int E>
+__global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs, int per_block,
+                                                 const float* __restrict__ pts_pool,
+                                                 const float* __restrict__ box_pool,
+                                                 const int32_t* __restrict__ qord_pool,
+                                                 uint64_t* __restrict__ row_pool) {
+  extern __shared__ uint64_t row_lds[];
+  __shared__ int s_n[kWaves], s_wave[kWaves];
+  __shared__ float s_t;
+  __shared__ uint32_t s_pick[2];
+  const RowJob J = jobs[blockIdx.y];
+  const int n = J.n_e;
+  const int p0 = (int)blockIdx.x * per_block;
+  if (p0 >= n) return;                            // the whole workgroup
+  const int w = min(J.w, n);
+  const int seg = row_segment(J.w);
+  uint64_t* __restrict__ cand = row_lds;
+  uint64_t* __restrict__ grouped = row_lds + kWaves * seg;
+  uint32_t* __restrict__ hist = reinterpret_cast<uint32_t*>(grouped + kWaves * seg);
+  const float* __restrict__ pts = pts_pool + J.pts_off;
+  const float* __restrict__ boxes = box_pool + J.box_off;
+  const int32_t* __restrict__ qord = qord_pool + J.qord_off;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  float slack = 1.25f;
+  float t_next = -1.f;
+
+  for (int p = p0; p < min(p0 + per_block, n); ++p) {
+    float q[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) q[k] = pts[(int64_t)k * n + p];
+    uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)p * J.w;
+    float t = t_next;
+    if (t < 0.f) {
+      // the first row: the farthest of the w points around it in visiting
+      // order bounds the w-th distance
+      const int a = max(0, min(p - w / 2, n - w));
+      float m = 0.f;
+      for (int c = a + tid; c < a + w; c += kBlock) m = fmaxf(m, run_d2<E>(pts, n, c, q));
+#pragma unroll
+      for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
+      if (lane == 0) s_n[wave] = __float_as_int(m);
+      __syncthreads();
+      t = 0.f;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) t = fmaxf(t, __int_as_float(s_n[v]));
+      __syncthreads();
+    }
+    // thresholds known to catch too few / too many
+    float t_few = -1.f, t_many = __builtin_inff();
+    int total = 0;
+    bool done = false;
+    for (int attempt = 0; attempt < 16 && !done; ++attempt) {
+      int mine = 0;
+      visit_runs<E>(pts, boxes, n, q, t, [&](int c, float d2, bool valid) {
+        const bool keep = valid && d2 <= t;
+        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
+        if (m) {
+          const int at = mine + __popcll(m & below);
+          if (keep && at < seg) cand[wave * seg + at] = row_key(d2, qord[c]);
+          mine += __popcll(m);
+        }
+      });
+      if (lane == 0) s_n[wave] = mine;
+      __syncthreads();
+      bool over = false;
+      total = 0;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {
+        over |= s_n[v] > seg;
+        total += s_n[v];
+      }
+      __syncthreads();
+      if (total < w) {
+        t_few = t;
+        slack = fminf(2.f, 1.f + (slack - 1.f) * 1.5f);
+        t = t_many < __builtin_inff() ? 0.5f * (t_few + t_many)
+                                      : fmaxf(t * (attempt < 3 ? 1.5f : 4.f), 1e-37f);
+        if (!(t > t_few && t < t_many)) break;
+      } else if (over) {
+        t_many = t;
+        t = t_few >= 0.f ? 0.5f * (t_few + t_many) : 0.6f * t;
+        if (!(t > t_few && t < t_many)) break;
+      } else {
+        done = true;
+      }
+    }
+    if (done) {
+      const float scale = t > 0.f ? (float)kRowBuckets / t : 0.f;
+      for (int b = tid; b < kRowBuckets; b += kBlock) hist[b] = 0u;
+      __syncthreads();
+      const int mine = s_n[wave];
+      for (int x = lane; x < mine; x += 64)
+        atomicAdd(&hist[row_bucket(cand[wave * seg + x], scale)], 1u);
+      __syncthreads();
+      // exclusive prefix over the buckets: four per thread
+      constexpr int per = kRowBuckets / kBlock;
+      uint32_t h[per], sum = 0;
+#pragma unroll
+      for (int u = 0; u < per; ++u) {
+        h[u] = hist[tid * per + u];
+        sum += h[u];
+      }
+      uint32_t inc = sum;
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) {
+        const uint32_t y = __shfl_up(inc, s, 64);
+        if (lane >= s) inc += y;
+      }
+      if (lane == 63) s_wave[wave] = (int)inc;
+      __syncthreads();
+      uint32_t at = inc - sum;
+      for (int v = 0; v < wave; ++v) at += (uint32_t)s_wave[v];
+#pragma unroll
+      for (int u = 0; u < per; ++u) {
+        hist[tid * per + u] = at;
+        at += h[u];
+      }
+      __syncthreads();
+      // grouped by bucket; afterwards hist[b] is the end of bucket b
+      for (int x = lane; x < mine; x += 64) {
+        const uint64_t key = cand[wave * seg + x];
+        grouped[atomicAdd(&hist[row_bucket(key, scale)], 1u)] = key;
+      }
+      __syncthreads();
+      for (int x = tid; x < total; x += kBlock) {
+        const uint64_t key = grouped[x];
+        const int b = row_bucket(key, scale);
+        const int lo = b ? (int)hist[b - 1] : 0, hi = (int)hist[b];
+        if (lo >= w) continue;
+        int r = lo;
+        for (int y = lo; y < hi; ++y) r += grouped[y] < key ? 1 : 0;
+        if (r < w) row[r] = key;
+        if (r == w - 1) s_t = __uint_as_float((uint32_t)(key >> 32));
+      }
+      __syncthreads();
+      if (total > w + w / 2) slack = 1.f + (slack - 1.f) * 0.7f;
+    } else {
+      // more points share the w-th distance than the segments hold: radix
+      // select of that distance (four 8-bit passes over the runs that can
+      // hold it), then the nearer points and the lowest-index ones at it
+      const float reach = t_many;
+      uint32_t prefix = 0u, mask = 0u, need = (uint32_t)w;
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        hist[tid] = 0u;
+        __syncthreads();
+        visit_runs<E>(pts, boxes, n, q, reach, [&](int, float d2, bool valid) {
+          const uint32_t u = __float_as_uint(d2);
+          if (valid && (u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 255u], 1u);
+        });
+        __syncthreads();
+        if (tid == 0) {
+          uint32_t cum = 0u, b = 0u;
+          for (; b < 255u && cum + hist[b] < need; ++b) cum += hist[b];
+          s_pick[0] = b;
+          s_pick[1] = need - cum;
+        }
+        __syncthreads();
+        prefix |= s_pick[0] << shift;
+        mask |= 255u << shift;
+        need = s_pick[1];
+        __syncthreads();
+      }
+      // rank of the last index taken at distance T: radix select on j
+      const uint32_t T = prefix;
+      uint32_t jpre = 0u, jmask = 0u, jneed = need;
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        hist[tid] = 0u;
+        __syncthreads();
+        visit_runs<E>(pts, boxes, n, q, reach, [&](int c, float d2, bool valid) {
+          if (valid && __float_as_uint(d2) == T) {
+            const uint32_t j = (uint32_t)qord[c];
+            if ((j & jmask) == jpre) atomicAdd(&hist[(j >> shift) & 255u], 1u);
+          }
+        });
+        __syncthreads();
+        if (tid == 0) {
+          uint32_t cum = 0u, b = 0u;
+          for (; b < 255u && cum + hist[b] < jneed; ++b) cum += hist[b];
+          s_pick[0] = b;
+          s_pick[1] = jneed - cum;
+        }
+        __syncthreads();
+        jpre |= s_pick[0] << shift;
+        jmask |= 255u << shift;
+        jneed = s_pick[1];
+        __syncthreads();
+      }
+      // exactly w keys are at most (T, jpre): collect and sort them
+      const uint64_t last = ((uint64_t)T << 32) | jpre;
+      if (tid == 0) s_wave[0] = 0;
+      __syncthreads();
+      visit_runs<E>(pts, boxes, n, q, reach, [&](int c, float d2, bool valid) {
+        const uint64_t key = row_key(d2, valid ? qord[c] : -1);
+        if (valid && key <= last) {
+          const int at = atomicAdd(&s_wave[0], 1);
+          if (at < w) grouped[at] = key;
+        }
+      });
+      int P = 1;
+      while (P < w) P <<= 1;
+      for (int x = w + tid; x < P; x += kBlock) grouped[x] = ~0ull;
+      __syncthreads();
+      for (int size = 2; size <= P; size <<= 1)
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+          for (int x = tid; x < P / 2; x += kBlock) {
+            const int lo = 2 * x - (x & (stride - 1));
+            const int hi = lo + stride;
+            const bool up = (lo & size) == 0;
+            const uint64_t a = grouped[lo], b = grouped[hi];
+            if ((a > b) == up) {
+              grouped[lo] = b;
+              grouped[hi] = a;
+            }
+          }
+          __syncthreads();
+        }
+      for (int x = tid; x < w; x += kBlock) row[x] = grouped[x];
+      if (tid == 0) s_t = __uint_as_float(T);
+      __syncthreads();
+    }
+    for (int x = w + tid; x < J.w; x += kBlock) row[x] = ~0ull;
+    t_next = s_t * slack;
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the walk: 64 libraries per wavefront
+// ---------------------------------------------------------------------------
+
+// Transpose of a 64 x 64 bit matrix, row l in lane l: afterwards bit e of
+// lane r is what bit r of lane e was.  Blocks of 32, 16, ..., 1 are
+// exchanged between lanes that far apart; 32 and 16 with the half- and
+// row-swap instructions, 8 and below within rows of 16 lanes (DPP).
+struct BitTranspose {
+  uint32_t sel16, sel8, rot4, m4, rot2, m2, rot1, m1;
+  __device__ __forceinline__ explicit BitTranspose(int lane) {
+    sel16 = (lane & 16) ? 0x07060302u : 0x05040100u;   // bytes of (odd row, even row)
+    sel8 = (lane & 8) ? 0x03070105u : 0x06020400u;     // bytes of (partner, own)
+    rot4 = (lane & 4) ? 4u : 28u;
+    m4 = (lane & 4) ? 0xf0f0f0f0u : 0x0f0f0f0fu;
+    rot2 = (lane & 2) ? 2u : 30u;
+    m2 = (lane & 2) ? 0xccccccccu : 0x33333333u;
+    rot1 = (lane & 1) ? 1u : 31u;
+    m1 = (lane & 1) ? 0xaaaaaaaau : 0x55555555u;
+  }
+  template <int CTRL>
+  __device__ __forceinline__ static uint32_t dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, true);
+  }
+  __device__ __forceinline__ uint32_t within(uint32_t x) const {
+    // rows of 16 lanes: even rows keep their low halves and take the odd
+    // row's low halves above them, odd rows the high halves likewise
+    const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = __builtin_amdgcn_perm(s[1], s[0], sel16);
+    // 8: row_ror:8 pairs lanes l and l ^ 8
+    x = __builtin_amdgcn_perm(dpp<0x128>(x), x, sel8);
+    // 4: mirror within 8, then within 4
+    uint32_t y = dpp<0x1b>(dpp<0x141>(x));
+    y = __builtin_amdgcn_alignbit(y, y, rot4);
+    x = (x & m4) | (y & ~m4);
+    y = dpp<0x4e>(x);                                  // quad_perm 2,3,0,1
+    y = __builtin_amdgcn_alignbit(y, y, rot2);
+    x = (x & m2) | (y & ~m2);
+    y = dpp<0xb1>(x);                                  // quad_perm 1,0,3,2
+    y = __builtin_amdgcn_alignbit(y, y, rot1);
+    return (x & m1) | (y & ~m1);
+  }
+  __device__ __forceinline__ uint64_t operator()(uint64_t m) const {
+    const auto s = __builtin_amdgcn_permlane32_swap((uint32_t)m, (uint32_t)(m >> 32), false,
+                                                    false);
+    return (uint64_t)within(s[0]) | ((uint64_t)within(s[1]) << 32);
+  }
+};
+
+// Quotient x / y of finite x >= 0, y > 0 with r = fl(1 / y): x r corrected
+// twice by its exact remainder, which gives the correctly rounded quotient
+// (Markstein, "Computation of elementary functions on the IBM RISC
+// System/6000 processor", 1990) as long as neither the quotient nor a
+// remainder underflows; smaller x take the division.
+__device__ __forceinline__ double quotient(double x, double y, double r) {
+  double q = x * r;
+  q = __builtin_fma(__builtin_fma(-q, y, x), r, q);
+  q = __builtin_fma(__builtin_fma(-q, y, x), r, q);
+  if (__builtin_expect(!(x > 0x1p-900), 0)) {
+    asm volatile("");                              // a branch, not a select
+    q = x / y;
+  }
+  return q;
+}
+
+// LDS of one wavefront of the walk: the chunk's values by entry, then the
+// accepted ones by rank and lane.
+template <int E, bool KEYS>
+struct WalkLds {
+  static constexpr int K = E + 1;
+  double chunk[KEYS ? 1 : 2][64];
+  double slot[KEYS ? 1 : 2][K][64];
+};
+
+// One item: the queries at visiting positions [tile * per, (tile + 1) * per)
+// of one embedding against the (at most 64) libraries of one group, lane l
+// of each wavefront holding library l.  Per query the row is read 64 entries
+// at a time; each lane reads one entry and its membership word (bit l:
+// library l holds the point; 0 for excluded points), and the transposed
+// words give every library its members among the 64 entries in row order.
+// Lanes take their lowest set bits until they hold E+1 neighbours; then the
+// prediction is formed with simplex_weights' operations (KEYS: the
+// neighbours' keys are written instead).  A library that finds fewer than
+// E+1 in the whole row (its rows were cut at w entries) is searched in full
+// by the wavefront (about one query in 10^7 by the planner's row length).
+//
+// Bound by the FP64 exponentials of the predictions (E+1 each), and below
+// that by instruction issue: a chunk costs about 31 instructions for the
+// transpose, and a member about 18 to take out.
+template <int E, bool KEYS>
+__global__ __launch_bounds__(kBlock) void k_walk(
+    const WalkGroup* __restrict__ groups, const WalkLib* __restrict__ libs,
+    const RowJob* __restrict__ embs, const Item* __restrict__ items, int per,
+    const uint64_t* __restrict__ mask_pool, const uint64_t* __restrict__ row_pool,
+    const int32_t* __restrict__ qord_pool, const float* __restrict__ emb_pool,
+    const double* __restrict__ tgt_pool, double* __restrict__ out, int excl, int query_set) {
+  constexpr int K = E + 1;
+  __shared__ WalkLds<E, KEYS> s_lds[kWaves];
+  const Item I = items[xcd_item(blockIdx.x, gridDim.x)];
+  const WalkGroup G = groups[I.rz];
+  const RowJob J = embs[G.emb];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  WalkLds<E, KEYS>& lds = s_lds[wave];
+  const uint64_t* __restrict__ masks = mask_pool + G.mask_off;
+  const int32_t* __restrict__ qord = qord_pool + J.qord_off;
+  const double* __restrict__ tgt = tgt_pool + G.tgt_off;
+  const bool mine = lane < G.n_lib;
+  const int64_t out_off = libs[G.lib_first + (mine ? lane : 0)].out_off;
+  const BitTranspose transpose(lane);
+  const int sub = (per + kWaves - 1) / kWaves;
+  const int pa = I.tile * per + wave * sub;
+  const int pb = min(min(pa + sub, I.tile * per + per), J.n_e);
+
+  for (int p = pa; p < pb; ++p) {
+    const int i = qord[p];
+    const uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)p * J.w;
+    bool active = mine;
+    if (query_set) active = active && ((masks[i] >> lane) & 1ull);
+    int cnt = active ? 0 : K;
+    for (int c = 0; c < G.chunks; ++c) {
+      if (!__builtin_amdgcn_ballot_w64(cnt < K)) break;
+      const uint64_t key = row[c * 64 + lane];
+      const int j = (int)(uint32_t)key;
+      uint64_t m = 0;
+      wave_sync();
+      if (j >= 0) {
+        const int gap = j > i ? j - i : i - j;
+        if (gap > excl) m = masks[j];
+        if (KEYS) {
+          lds.chunk[0][lane] = __longlong_as_double((long long)key);
+        } else {
+          lds.chunk[0][lane] = sqrt((double)__uint_as_float((uint32_t)(key >> 32)));
+          lds.chunk[KEYS ? 0 : 1][lane] = tgt[j];
+        }
+      }
+      uint64_t bits = transpose(m);
+      if (cnt >= K) bits = 0;
+      wave_sync();
+      while (__builtin_amdgcn_ballot_w64(bits != 0)) {
+        if (bits) {
+          const int e = __builtin_ctzll(bits);
+          bits &= bits - 1ull;
+          lds.slot[0][cnt][lane] = lds.chunk[0][e];
+          if (!KEYS) lds.slot[KEYS ? 0 : 1][cnt][lane] = lds.chunk[KEYS ? 0 : 1][e];
+          if (++cnt == K) bits = 0;
+        }
+      }
+    }
+    // libraries whose row ran short: the wavefront looks through the whole
+    // library, each lane keeping the K smallest keys of its share, and takes
+    // the K smallest of all of them one by one
+    uint64_t shortfall = __builtin_amdgcn_ballot_w64(cnt < K);
+    while (shortfall) {
+      const int l = __builtin_ctzll(shortfall);
+      shortfall &= shortfall - 1ull;
+      const float* __restrict__ emb = emb_pool + J.emb_off;
+      float q[E];
+#pragma unroll
+      for (int k = 0; k < E; ++k) q[k] = emb[(int64_t)i * E + k];
+      double best[K];
+#pragma unroll
+      for (int t = 0; t < K; ++t) best[t] = empty_key();
+      constexpr int kAhead = 8;                    // membership words in flight
+      for (int j0 = 0; j0 < J.n_e; j0 += 64 * kAhead) {
+        uint64_t m[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) m[u] = masks[min(j0 + u * 64 + lane, J.n_e - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const int j = j0 + u * 64 + lane;
+          const int gap = j > i ? j - i : i - j;
+          if (j < J.n_e && gap > excl && ((m[u] >> l) & 1ull))
+            insert_key<K>(best, make_key(sqdist<E>(q, emb + (int64_t)j * E), j));
+        }
+      }
+#pragma unroll 1
+      for (int t = 0; t < K; ++t) {
+        double lo = best[0];
+#pragma unroll
+        for (int s = 32; s > 0; s >>= 1) {
+          const double o = __hiloint2double(__shfl_xor(__double2hiint(lo), s, 64),
+                                            __shfl_xor(__double2loint(lo), s, 64));
+          lo = kmin(lo, o);
+        }
+        if (__double_as_longlong(best[0]) == __double_as_longlong(lo)) {
+#pragma unroll
+          for (int u = 0; u + 1 < K; ++u) best[u] = best[u + 1];
+          best[K - 1] = empty_key();
+        }
+        if (lane == l) {
+          if (KEYS) {
+            lds.slot[0][t][lane] = lo;
+          } else {
+            lds.slot[0][t][lane] = sqrt((double)key_d2(lo));
+            lds.slot[KEYS ? 0 : 1][t][lane] = tgt[key_j(lo)];
+          }
+        }
+      }
+    }
+    if (active) {
+      if constexpr (KEYS) {
+#pragma unroll
+        for (int t = 0; t < K; ++t) out[out_off + (int64_t)t * J.n_e + p] = lds.slot[0][t][lane];
+      } else {
+        // the operations of simplex_weights and of the weighted sum
+        double u[K];
+        const double d0 = lds.slot[0][0][lane];
+        if (d0 > 0.0) {
+          const double r = 1.0 / d0;
+#pragma unroll
+          for (int t = 0; t < K; ++t) u[t] = exp(-quotient(lds.slot[0][t][lane], d0, r));
+        } else {
+#pragma unroll
+          for (int t = 0; t < K; ++t) u[t] = lds.slot[0][t][lane] == 0.0 ? 1.0 : 0.0;
+        }
+        double su = 0.0;
+#pragma unroll
+        for (int t = 0; t < K; ++t) su += u[t];
+        const double rs = 1.0 / su;
+        double pred = 0.0;
+#pragma unroll
+        for (int t = 0; t < K; ++t)
+          pred += quotient(u[t], su, rs) * lds.slot[KEYS ? 0 : 1][t][lane];
+        out[out_off + (query_set ? i : p)] = pred;
+      }
+    }
+  }
+}
+
+// Moments of one query tile of a walked realization from its predictions:
+// the same queries per lane, operations and merge order as crossmap_item.
+template <int E, int Q>
+__global__ __launch_bounds__(kBlock) void k_walk_moments(
+    const Realization* __restrict__ rzs, const int64_t* __restrict__ out_off,
+    const Item* __restrict__ items, int n_items, const double* __restrict__ pred,
+    const int32_t* __restrict__ pj_pool, const int32_t* __restrict__ qord_pool,
+    const double* __restrict__ tgt_pool, Moments* __restrict__ partial, int query_set) {
+  __shared__ Moments red[kBlock];
+  const Item I = items[xcd_item(blockIdx.x, gridDim.x)];
+  const Realization R = rzs[I.rz];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const double* __restrict__ tgt = tgt_pool + R.tgt_off + (int64_t)(E - 1) * R.tau;
+  const int32_t* __restrict__ q = query_set ? pj_pool + R.pj_off : qord_pool + R.qord_off;
+  const double* __restrict__ pr = pred + out_off[I.rz];
+  Moments mo = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int m = 0; m < Q; ++m) {
+    const int qq = I.tile * (kBlock * Q) + wave * (64 * Q) + m * 64 + lane;
+    if (qq < R.n_query) {
+      const int i = q[qq];
+      mom_add(mo, tgt[i], pr[query_set ? i : qq]);
+    }
+  }
+  red[tid] = mo;
+  __syncthreads();
+#pragma unroll
+  for (int s = kBlock / 2; s > 0; s >>= 1) {
+    if (tid < s) red[tid] = mom_merge(red[tid], red[tid + s]);
+    __syncthreads();
+  }
+  if (tid == 0) partial[R.slot_base + I.tile] = red[0];
+}
+
+}  // namespace ccmk
