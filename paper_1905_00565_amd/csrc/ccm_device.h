@@ -825,6 +825,29 @@ __device__ __forceinline__ void multi_target_block(const ScanState<E, Q, MODE>& 
   __syncthreads();
 }
 
+// Per-target stage.  Row t of the time-major table holds every series'
+// value at time t.  Lane b of a wavefront owns target b0 + b and walks the
+// wavefront's queries (staged in LDS one query set at a time): each
+// neighbour's row is then read by one coalesced load for all 64 targets.
+// A target's sums are shifted by its first embedded value (time off).
+// With at most 64 targets there is one block, and each query set's running
+// list is dead once its weights are staged (fewer live registers).
+template <int E, int Q, int MODE>
+__device__ __forceinline__ void multi_targets(const ScanState<E, Q, MODE>& S,
+                                              const Realization& R, int tile,
+                                              const double* __restrict__ tt, int m_series,
+                                              int self, Sums* __restrict__ partial,
+                                              unsigned char* lds) {
+  const int mp = target_stride(m_series);
+  const double* __restrict__ T = tt + (int64_t)(E - 1) * R.tau * mp;
+  if (m_series <= 64) {
+    multi_target_block<E, Q, MODE>(S, R, tile, T, 0, m_series, self, mp, partial, lds);
+  } else {
+    for (int b0 = 0; b0 < m_series; b0 += 64)
+      multi_target_block<E, Q, MODE>(S, R, tile, T, b0, m_series, self, mp, partial, lds);
+  }
+}
+
 template <int E, int Q, int MODE, bool TBL>
 __device__ __forceinline__ void crossmap_multi_item(
     const Realization& R, int tile, const float* __restrict__ emb_pool,
@@ -833,33 +856,12 @@ __device__ __forceinline__ void crossmap_multi_item(
     const double* __restrict__ tt, int m_series, int self,
     Sums* __restrict__ partial, int query_set, int window, unsigned char* lds,
     const TableArgs& ta, uint32_t* tlds) {
-  constexpr int K = E + 1;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int mp = target_stride(m_series);
-  const int64_t off = (int64_t)(E - 1) * R.tau;
-
   if constexpr (TBL)
     if (R.table_off >= 0 && ta.words > 0) table_bitmask(R, pj_pool, tlds);
   ScanState<E, Q, MODE> S;
   scan_library<E, Q, MODE, TBL>(R, tile, emb_pool, pts_pool, pj_pool, qord_pool, start_pool,
                                 query_set, window, ta, tlds, S);
-
-  // Per-target stage.  Row t of the time-major table holds every series'
-  // value at time t.  Lane b of a wavefront owns target b0 + b and walks the
-  // wavefront's queries (staged in LDS one query set at a time): each
-  // neighbour's row is then read by one coalesced load for all 64 targets.
-  // A target's sums are shifted by its first embedded value (time off).
-  // With at most 64 targets there is one block, and each query set's running
-  // list is dead once its weights are staged (fewer live registers).
-  const double* __restrict__ T = tt + off * mp;
-  if (m_series <= 64) {
-    multi_target_block<E, Q, MODE>(S, R, tile, T, 0, m_series, self, mp, partial, lds);
-  } else {
-    for (int b0 = 0; b0 < m_series; b0 += 64)
-      multi_target_block<E, Q, MODE>(S, R, tile, T, b0, m_series, self, mp, partial, lds);
-  }
+  multi_targets<E, Q, MODE>(S, R, tile, tt, m_series, self, partial, lds);
 }
 
 // Build one row of a distance indexing table (one workgroup per row i): the

@@ -8,7 +8,7 @@
 // through the whole neighbour scan, and the scan spills its running lists
 // inside the insertion branches.  The cross-map kernels of ccm_inst.hip do
 // not gain from the flag and keep the default pipeline.
-#include "ccm_device.h"
+#include "ccm_walk.h"
 #include "ccm_inst.h"
 
 #ifndef CCM_INST_E
@@ -49,6 +49,23 @@ hipError_t launch_multi_e(int mode, int grid, const Realization* rzs, const int3
   return hipGetLastError();
 }
 
+template <int E>
+hipError_t launch_multi_keys_e(const Realization* rzs, const int32_t* self_of,
+                               const int64_t* key_off, const Item* items, int n_items,
+                               const double* keys, const int32_t* pj, const int32_t* qord,
+                               const double* tt, int m_series, void* partial, int query_set,
+                               hipStream_t st) {
+  k_multi_keys<E, DefaultQ<E>::Q><<<(unsigned)n_items, kBlock, 0, st>>>(
+      rzs, self_of, key_off, items, keys, pj, qord, tt, m_series, static_cast<Sums*>(partial),
+      query_set);
+  return hipGetLastError();
+}
+
+template hipError_t launch_multi_keys_e<CCM_INST_E>(const Realization*, const int32_t*,
+                                                    const int64_t*, const Item*, int,
+                                                    const double*, const int32_t*,
+                                                    const int32_t*, const double*, int, void*,
+                                                    int, hipStream_t);
 template hipError_t launch_multi_e<CCM_INST_E>(int, int, const Realization*, const int32_t*,
                                                const Item*, int, int*, const float*,
                                                const float*, const int32_t*, const int32_t*,

@@ -340,6 +340,13 @@ hipError_t launch_walk_moments(int E, const Realization* rzs, const int64_t* out
                                const Item* items, int n_items, const double* out,
                                const int32_t* pj, const int32_t* qord, const double* tgt,
                                Moments* partial, int query_set, hipStream_t st);
+// Causal matrix: the per-target stage of the items' tiles from the walk's keys
+// at keys + key_off[rz].
+hipError_t launch_multi_keys(int E, const Realization* rzs, const int32_t* self_of,
+                             const int64_t* key_off, const Item* items, int n_items,
+                             const double* keys, const int32_t* pj, const int32_t* qord,
+                             const double* tt, int m_series, void* partial, int query_set,
+                             hipStream_t st);
 constexpr int kRowMaxW = 1024;              // longest neighbour row
 constexpr int kWalkLibs = 64;               // libraries per walk group
 

@@ -850,6 +850,19 @@ hipError_t launch_walk_moments(int E, const Realization* rzs, const int64_t* out
 #undef CCM_CALL
 }
 
+hipError_t launch_multi_keys(int E, const Realization* rzs, const int32_t* self_of,
+                             const int64_t* key_off, const Item* items, int n_items,
+                             const double* keys, const int32_t* pj, const int32_t* qord,
+                             const double* tt, int m_series, void* partial, int query_set,
+                             hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+#define CCM_CALL(e)                                                                        \
+  launch_multi_keys_e<e>(rzs, self_of, key_off, items, n_items, keys, pj, qord, tt,        \
+                         m_series, partial, query_set, st)
+  CCM_BY_E(E, CCM_CALL)
+#undef CCM_CALL
+}
+
 hipError_t launch_zero_int(int* p, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   k_zero_int<<<(n + 255) / 256, 256, 0, st>>>(p, n);

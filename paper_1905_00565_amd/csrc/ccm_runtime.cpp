@@ -47,8 +47,7 @@ void drain_events(ccm_ctx* c) {
 // The batched forms walk neighbour rows; the plain baseline and the forms
 // with draws of their own scan.
 bool walks(const Spec& s) {
-  return s.M == 0 &&
-         !(s.flags & (CCM_FLAG_PLAIN | CCM_FLAG_NESTED | CCM_FLAG_SHARED_E));
+  return !(s.flags & (CCM_FLAG_PLAIN | CCM_FLAG_NESTED | CCM_FLAG_SHARED_E));
 }
 
 // Device buffers and descriptors for a plan (reused when the shape repeats).
@@ -212,13 +211,18 @@ void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStrea
                        b.boxes, b.qord, b.rows, st));
     for (int ci = wb.chunk_first; ci < wb.chunk_first + wb.chunk_count; ++ci) {
       const WalkChunk& ch = p.walk_chunks[ci];
-      HIPCHK(launch_walk(L.E, 0, b.walk_groups, b.walk_libs, b.row_jobs,
+      HIPCHK(launch_walk(L.E, p.spec.M > 0, b.walk_groups, b.walk_libs, b.row_jobs,
                          b.walk_items + ch.item_first, (int)ch.item_count, L.walk_per, b.masks,
                          b.rows, b.qord, b.emb, b.s64, b.walk_out, excl,
                          p.spec.query_set, st));
-      HIPCHK(launch_walk_moments(L.E, b.rz, b.walk_out_off, b.mom_items + ch.mom_first,
-                                 (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.s64,
-                                 static_cast<Moments*>(b.partial), p.spec.query_set, st));
+      if (p.spec.M > 0)
+        HIPCHK(launch_multi_keys(L.E, b.rz, b.self, b.walk_out_off, b.mom_items + ch.mom_first,
+                                 (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.tt, p.spec.M,
+                                 b.partial, p.spec.query_set, st));
+      else
+        HIPCHK(launch_walk_moments(L.E, b.rz, b.walk_out_off, b.mom_items + ch.mom_first,
+                                   (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.s64,
+                                   static_cast<Moments*>(b.partial), p.spec.query_set, st));
     }
   }
 }

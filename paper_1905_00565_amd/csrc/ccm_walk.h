@@ -570,7 +570,8 @@ __global__ __launch_bounds__(kBlock) void k_walk(
     if (active) {
       if constexpr (KEYS) {
 #pragma unroll
-        for (int t = 0; t < K; ++t) out[out_off + (int64_t)t * J.n_e + p] = lds.slot[0][t][lane];
+        for (int t = 0; t < K; ++t)
+          out[out_off + (int64_t)t * J.n_e + (query_set ? i : p)] = lds.slot[0][t][lane];
       } else {
         // the operations of simplex_weights and of the weighted sum
         double u[K];
@@ -631,6 +632,37 @@ __global__ __launch_bounds__(kBlock) void k_walk_moments(
     __syncthreads();
   }
   if (tid == 0) partial[R.slot_base + I.tile] = red[0];
+}
+
+// Causal matrix: one query tile of a walked realization, its neighbours read
+// from the walk's keys ([t][n_e] per library) instead of searched; then the
+// per-target stage of crossmap_multi_item.
+template <int E, int Q>
+__global__ __launch_bounds__(kBlock) void k_multi_keys(
+    const Realization* __restrict__ rzs, const int32_t* __restrict__ self_of,
+    const int64_t* __restrict__ key_off, const Item* __restrict__ items,
+    const double* __restrict__ keys, const int32_t* __restrict__ pj_pool,
+    const int32_t* __restrict__ qord_pool, const double* __restrict__ tt, int m_series,
+    Sums* __restrict__ partial, int query_set) {
+  __shared__ __align__(16) unsigned char lds[MultiLds<E>::kBytes];
+  const Item I = items[xcd_item(blockIdx.x, gridDim.x)];
+  const Realization R = rzs[I.rz];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int32_t* __restrict__ q = query_set ? pj_pool + R.pj_off : qord_pool + R.qord_off;
+  const double* __restrict__ k = keys + key_off[I.rz];
+  ScanState<E, Q, kKeepSelf> S;
+#pragma unroll
+  for (int m = 0; m < Q; ++m) {
+    const int qq = I.tile * (kBlock * Q) + wave * (64 * Q) + m * 64 + lane;
+    const bool valid = qq < R.n_query;
+    const int i = valid ? q[qq] : 0;
+    const int at = query_set ? i : (valid ? qq : 0);
+    S.qi[m] = valid ? i : -1;
+#pragma unroll
+    for (int t = 0; t < E + 1; ++t) S.key[m][t] = k[(int64_t)t * R.n_e + at];
+  }
+  multi_targets<E, Q, kKeepSelf>(S, R, I.tile, tt, m_series, self_of[I.rz], partial, lds);
 }
 
 }  // namespace ccmk

@@ -81,3 +81,21 @@ def test_rows_by_rule_equal_scan(ctx, excl, qs):
         a = ctx.ccm_sweep(*args, exclusion_radius=excl, query_set=qs)
         b = ctx.ccm_sweep(*args, exclusion_radius=excl, query_set=qs, flags=PLAIN)
         assert np.array_equal(a.view(np.uint64), b.view(np.uint64))
+
+
+@pytest.mark.parametrize("M,N,E,L,excl,qs", [
+    (3, 700, 2, [300, 699], 0, 0), (6, 1500, 4, [700, 1497], 0, 0),
+    (5, 1300, 3, [600, 1298], 4, 1), (66, 400, 1, [200, 400], -1, 0)])
+def test_rows_matrix_equal_scan(ctx, M, N, E, L, excl, qs):
+    """The causal matrix through neighbour rows: odd M, more than 64 targets,
+    windows, library-point queries."""
+    S, _ = synth.logistic_network(M, N, seed=5)
+    kw = dict(exclusion_radius=excl, query_set=qs)
+    ctx.profile_enable(True)
+    ctx.profile_read(reset=True)
+    a = ctx.ccm_matrix(S, E, 1, L, 5, 3, flags=TABLE, **kw)
+    walked = ctx.profile_read(reset=True)["table_realizations"]
+    ctx.profile_enable(False)
+    assert walked > 0
+    b = ctx.ccm_matrix(S, E, 1, L, 5, 3, flags=PLAIN, **kw)
+    assert np.array_equal(a.view(np.uint64), b.view(np.uint64))
