@@ -57,14 +57,14 @@ hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,
                          int query_set, hipStream_t st);
 
 template <int E>
-hipError_t launch_walk_moments_e(const Realization* rzs, const int64_t* out_off,
+hipError_t launch_walk_moments_e(const Realization* rzs, const WalkOut* where,
                                  const Item* items, int n_items, const double* out,
                                  const int32_t* pj, const int32_t* qord, const double* tgt,
                                  Moments* partial, int query_set, hipStream_t st);
 
 template <int E>
 hipError_t launch_multi_keys_e(const Realization* rzs, const int32_t* self_of,
-                               const int64_t* key_off, const Item* items, int n_items,
+                               const WalkOut* where, const Item* items, int n_items,
                                const double* keys, const int32_t* pj, const int32_t* qord,
                                const double* tt, int m_series, void* partial, int query_set,
                                hipStream_t st);

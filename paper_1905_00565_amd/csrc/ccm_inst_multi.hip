@@ -51,18 +51,18 @@ hipError_t launch_multi_e(int mode, int grid, const Realization* rzs, const int3
 
 template <int E>
 hipError_t launch_multi_keys_e(const Realization* rzs, const int32_t* self_of,
-                               const int64_t* key_off, const Item* items, int n_items,
+                               const WalkOut* where, const Item* items, int n_items,
                                const double* keys, const int32_t* pj, const int32_t* qord,
                                const double* tt, int m_series, void* partial, int query_set,
                                hipStream_t st) {
   k_multi_keys<E, DefaultQ<E>::Q><<<(unsigned)n_items, kBlock, 0, st>>>(
-      rzs, self_of, key_off, items, keys, pj, qord, tt, m_series, static_cast<Sums*>(partial),
+      rzs, self_of, where, items, keys, pj, qord, tt, m_series, static_cast<Sums*>(partial),
       query_set);
   return hipGetLastError();
 }
 
 template hipError_t launch_multi_keys_e<CCM_INST_E>(const Realization*, const int32_t*,
-                                                    const int64_t*, const Item*, int,
+                                                    const WalkOut*, const Item*, int,
                                                     const double*, const int32_t*,
                                                     const int32_t*, const double*, int, void*,
                                                     int, hipStream_t);

@@ -186,23 +186,33 @@ struct RowJob {
   int32_t w;
 };
 
-// A library of a walk group, and where its predictions (or neighbour keys)
-// go in the walk's output.
+// A library of a walk group.
 struct WalkLib {
   int64_t bit_off;   // uint64: its bitmap over 0..n_e-1
-  int64_t out_off;   // doubles into the walk's output
   int32_t l_eff;
   int32_t rz;
 };
 
-// Up to 64 libraries of one embedding that walk its rows together.
+// Up to 64 libraries of one embedding that walk its rows together.  The walk
+// leaves the prediction of query position p by library l at
+// out[out_off + p * n_lib + l] (keys: neighbour t's at
+// out[out_off + (p * (E+1) + t) * n_lib + l]), so that a wavefront's stores
+// fill whole cache lines.
 struct WalkGroup {
   int64_t mask_off;  // uint64 [n_e]: bit l of word j set when library l holds j
   int64_t lib_first; // into the walk's libraries
   int64_t tgt_off;   // doubles: target at embedded point 0 (pairs only)
+  int64_t out_off;   // doubles into the walk's output
   int32_t n_lib;
   int32_t emb;       // into the row jobs
   int32_t chunks;    // 64-entry chunks of a row these libraries may need
+  int32_t pad;
+};
+
+// Where a realization's walk output is: out[off + p * stride], or its keys'.
+struct WalkOut {
+  int64_t off;
+  int32_t stride;
   int32_t pad;
 };
 
@@ -327,23 +337,22 @@ hipError_t launch_rows(int E, const RowJob* jobs, int n_jobs, int max_ne, int ma
 hipError_t launch_masks(const MaskJob* jobs, int n_jobs, int max_ne, const WalkLib* libs,
                         const uint64_t* bits, uint64_t* masks, hipStream_t st);
 // The walk of `per` queries per item ({group, block of queries}): keys == 0
-// leaves predictions, else the E+1 neighbour keys per query ([t][n_e] per
-// library).  excl: candidates within it of the query in index are dropped
+// leaves predictions, else the E+1 neighbour keys per query.  excl: candidates within it of the query in index are dropped
 // (-1: none).
 hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* libs,
                        const RowJob* embs, const Item* items, int n_items, int per,
                        const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
                        const float* emb, const double* tgt, double* out, int excl,
                        int query_set, hipStream_t st);
-// Moments of the items' tiles from the predictions at out + out_off[rz].
-hipError_t launch_walk_moments(int E, const Realization* rzs, const int64_t* out_off,
+// Moments of the items' tiles from the predictions at where[rz].
+hipError_t launch_walk_moments(int E, const Realization* rzs, const WalkOut* where,
                                const Item* items, int n_items, const double* out,
                                const int32_t* pj, const int32_t* qord, const double* tgt,
                                Moments* partial, int query_set, hipStream_t st);
 // Causal matrix: the per-target stage of the items' tiles from the walk's keys
-// at keys + key_off[rz].
+// at where[rz].
 hipError_t launch_multi_keys(int E, const Realization* rzs, const int32_t* self_of,
-                             const int64_t* key_off, const Item* items, int n_items,
+                             const WalkOut* where, const Item* items, int n_items,
                              const double* keys, const int32_t* pj, const int32_t* qord,
                              const double* tt, int m_series, void* partial, int query_set,
                              hipStream_t st);

@@ -838,26 +838,26 @@ hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* 
 #undef CCM_CALL
 }
 
-hipError_t launch_walk_moments(int E, const Realization* rzs, const int64_t* out_off,
+hipError_t launch_walk_moments(int E, const Realization* rzs, const WalkOut* where,
                                const Item* items, int n_items, const double* out,
                                const int32_t* pj, const int32_t* qord, const double* tgt,
                                Moments* partial, int query_set, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
 #define CCM_CALL(e)                                                                       \
-  launch_walk_moments_e<e>(rzs, out_off, items, n_items, out, pj, qord, tgt, partial,     \
+  launch_walk_moments_e<e>(rzs, where, items, n_items, out, pj, qord, tgt, partial,     \
                            query_set, st)
   CCM_BY_E(E, CCM_CALL)
 #undef CCM_CALL
 }
 
 hipError_t launch_multi_keys(int E, const Realization* rzs, const int32_t* self_of,
-                             const int64_t* key_off, const Item* items, int n_items,
+                             const WalkOut* where, const Item* items, int n_items,
                              const double* keys, const int32_t* pj, const int32_t* qord,
                              const double* tt, int m_series, void* partial, int query_set,
                              hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
 #define CCM_CALL(e)                                                                        \
-  launch_multi_keys_e<e>(rzs, self_of, key_off, items, n_items, keys, pj, qord, tt,        \
+  launch_multi_keys_e<e>(rzs, self_of, where, items, n_items, keys, pj, qord, tt,        \
                          m_series, partial, query_set, st)
   CCM_BY_E(E, CCM_CALL)
 #undef CCM_CALL

@@ -468,15 +468,14 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
       int64_t out = 0;
       size_t h = g;
       for (; h < g_end; ++h) {
-        const WalkGroup& wg = p.walk_groups[h];
-        const int64_t ne = p.row_jobs[wg.emb].n_e;
-        const int64_t need = (int64_t)wg.n_lib * ne * per_query;
+        WalkGroup& wg = p.walk_groups[h];
+        // whole cache lines per group
+        const int64_t need =
+            ((int64_t)wg.n_lib * p.row_jobs[wg.emb].n_e * per_query + 15) / 16 * 16;
         if (h > g && (out + need) * 8 > kWalkOutBytes) break;
-        for (int l = 0; l < wg.n_lib; ++l) {
-          WalkLib& wl = p.walk_libs[wg.lib_first + l];
-          wl.out_off = out + (int64_t)l * ne * per_query;
-          p.walk_out[wl.rz] = wl.out_off;
-        }
+        wg.out_off = out;
+        for (int l = 0; l < wg.n_lib; ++l)
+          p.walk_out[p.walk_libs[wg.lib_first + l].rz] = {out + l, wg.n_lib, 0};
         out += need;
       }
       for (size_t a = g; a < h;) {
@@ -486,11 +485,19 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
         const int32_t blocks = (ne + la.walk_per - 1) / la.walk_per;
         for (int32_t q = 0; q < blocks; ++q)
           for (size_t x = a; x < b; ++x) p.walk_items.push_back({(int32_t)x, q});
-        for (size_t x = a; x < b; ++x)
-          for (int l = 0; l < p.walk_groups[x].n_lib; ++l) {
-            const int32_t r = p.walk_libs[p.walk_groups[x].lib_first + l].rz;
-            for (int32_t t = 0; t < p.rz[r].n_tiles; ++t) p.mom_items.push_back({r, t});
-          }
+        // a tile of every library of a group together: they read the same
+        // cache lines of the walk's output (and the same target rows)
+        for (size_t x = a; x < b; ++x) {
+          const WalkGroup& wg = p.walk_groups[x];
+          int32_t tiles = 0;
+          for (int l = 0; l < wg.n_lib; ++l)
+            tiles = std::max(tiles, p.rz[p.walk_libs[wg.lib_first + l].rz].n_tiles);
+          for (int32_t t = 0; t < tiles; ++t)
+            for (int l = 0; l < wg.n_lib; ++l) {
+              const int32_t r = p.walk_libs[wg.lib_first + l].rz;
+              if (t < p.rz[r].n_tiles) p.mom_items.push_back({r, t});
+            }
+        }
         a = b;
       }
       ch.item_count = (int64_t)p.walk_items.size() - ch.item_first;
@@ -514,7 +521,7 @@ static void order_items(Plan& p) {
   split_waves(p);
   p.walked.assign(p.rz.size(), 0);
   p.want_table.resize(p.rz.size(), 0);
-  if (p.spec.walk) p.walk_out.assign(p.rz.size(), 0);
+  if (p.spec.walk) p.walk_out.assign(p.rz.size(), WalkOut{});
   auto cost = [&](const Realization& R) {
     return R.table_off >= 0 ? (double)R.n_query * (R.E + 1) * R.n_e / R.l_eff / 8.0
                             : (double)R.n_query * R.l_eff;

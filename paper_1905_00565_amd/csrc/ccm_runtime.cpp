@@ -107,7 +107,7 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
     upload(ex->d_walk_groups, p.walk_groups);
     upload(ex->d_walk_items, p.walk_items);
     upload(ex->d_mom_items, p.mom_items);
-    upload(ex->d_walk_off, p.walk_out);
+    upload(ex->d_walk_where, p.walk_out);
     ex->d_rows.ensure(p.n_rows * 8);
     ex->d_bits.ensure(p.n_bits * 8);
     ex->d_masks.ensure(p.n_mask * 8);
@@ -177,7 +177,7 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   b.walk_groups = ex->d_walk_groups.as<WalkGroup>();
   b.walk_items = ex->d_walk_items.as<Item>();
   b.mom_items = ex->d_mom_items.as<Item>();
-  b.walk_out_off = ex->d_walk_off.as<int64_t>();
+  b.walk_where = ex->d_walk_where.as<WalkOut>();
   b.rows = ex->d_rows.as<uint64_t>();
   b.bits = ex->d_bits.as<uint64_t>();
   b.masks = ex->d_masks.as<uint64_t>();
@@ -216,11 +216,11 @@ void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStrea
                          b.rows, b.qord, b.emb, b.s64, b.walk_out, excl,
                          p.spec.query_set, st));
       if (p.spec.M > 0)
-        HIPCHK(launch_multi_keys(L.E, b.rz, b.self, b.walk_out_off, b.mom_items + ch.mom_first,
+        HIPCHK(launch_multi_keys(L.E, b.rz, b.self, b.walk_where, b.mom_items + ch.mom_first,
                                  (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.tt, p.spec.M,
                                  b.partial, p.spec.query_set, st));
       else
-        HIPCHK(launch_walk_moments(L.E, b.rz, b.walk_out_off, b.mom_items + ch.mom_first,
+        HIPCHK(launch_walk_moments(L.E, b.rz, b.walk_where, b.mom_items + ch.mom_first,
                                    (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.s64,
                                    static_cast<Moments*>(b.partial), p.spec.query_set, st));
     }

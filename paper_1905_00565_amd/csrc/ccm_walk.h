@@ -475,33 +475,48 @@ __global__ __launch_bounds__(kBlock) void k_walk(
   const int32_t* __restrict__ qord = qord_pool + J.qord_off;
   const double* __restrict__ tgt = tgt_pool + G.tgt_off;
   const bool mine = lane < G.n_lib;
-  const int64_t out_off = libs[G.lib_first + (mine ? lane : 0)].out_off;
   const BitTranspose transpose(lane);
   const int sub = (per + kWaves - 1) / kWaves;
   const int pa = I.tile * per + wave * sub;
   const int pb = min(min(pa + sub, I.tile * per + per), J.n_e);
+  if (pa >= pb) return;                            // no barrier below
 
+  // Software pipeline over the queries: the first chunk of the next query's
+  // row is requested while this query's is taken apart, and its membership
+  // words and targets before this query's prediction.
+  int i = qord[pa];
+  const uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)pa * J.w;
+  uint64_t key = row[lane];
+  uint64_t m = 0;
+  double tv = 0.0;
+  // membership word and target of a row entry (0 for excluded points)
+  const auto entry = [&](uint64_t k, int self, uint64_t& mm, double& tt) {
+    const int j = (int)(uint32_t)k;
+    mm = 0;
+    if (j >= 0) {
+      const int gap = j > self ? j - self : self - j;
+      if (gap > excl) mm = masks[j];
+      if (!KEYS) tt = tgt[j];
+    }
+  };
+  entry(key, i, m, tv);
   for (int p = pa; p < pb; ++p) {
-    const int i = qord[p];
-    const uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)p * J.w;
+    const int p1 = min(p + 1, pb - 1);
+    const int i_next = qord[p1];
+    const uint64_t* __restrict__ row_next = row_pool + J.out_off + (int64_t)p1 * J.w;
+    const uint64_t key_next = row_next[lane];
     bool active = mine;
     if (query_set) active = active && ((masks[i] >> lane) & 1ull);
     int cnt = active ? 0 : K;
-    for (int c = 0; c < G.chunks; ++c) {
-      if (!__builtin_amdgcn_ballot_w64(cnt < K)) break;
-      const uint64_t key = row[c * 64 + lane];
-      const int j = (int)(uint32_t)key;
-      uint64_t m = 0;
+    for (int c = 0;;) {
+      const bool more = c + 1 < G.chunks;
+      const uint64_t key_c = row[(more ? c + 1 : c) * 64 + lane];
       wave_sync();
-      if (j >= 0) {
-        const int gap = j > i ? j - i : i - j;
-        if (gap > excl) m = masks[j];
-        if (KEYS) {
-          lds.chunk[0][lane] = __longlong_as_double((long long)key);
-        } else {
-          lds.chunk[0][lane] = sqrt((double)__uint_as_float((uint32_t)(key >> 32)));
-          lds.chunk[KEYS ? 0 : 1][lane] = tgt[j];
-        }
+      if (KEYS) {
+        lds.chunk[0][lane] = __longlong_as_double((long long)key);
+      } else {
+        lds.chunk[0][lane] = sqrt((double)__uint_as_float((uint32_t)(key >> 32)));
+        lds.chunk[KEYS ? 0 : 1][lane] = tv;
       }
       uint64_t bits = transpose(m);
       if (cnt >= K) bits = 0;
@@ -515,7 +530,13 @@ __global__ __launch_bounds__(kBlock) void k_walk(
           if (++cnt == K) bits = 0;
         }
       }
+      if (!more || !__builtin_amdgcn_ballot_w64(cnt < K)) break;
+      ++c;
+      key = key_c;
+      entry(key, i, m, tv);
     }
+    key = key_next;
+    entry(key, i_next, m, tv);
     // libraries whose row ran short: the wavefront looks through the whole
     // library, each lane keeping the K smallest keys of its share, and takes
     // the K smallest of all of them one by one
@@ -569,9 +590,10 @@ __global__ __launch_bounds__(kBlock) void k_walk(
     }
     if (active) {
       if constexpr (KEYS) {
+        double* __restrict__ o =
+            out + G.out_off + (int64_t)(query_set ? i : p) * (K * G.n_lib) + lane;
 #pragma unroll
-        for (int t = 0; t < K; ++t)
-          out[out_off + (int64_t)t * J.n_e + (query_set ? i : p)] = lds.slot[0][t][lane];
+        for (int t = 0; t < K; ++t) o[t * G.n_lib] = lds.slot[0][t][lane];
       } else {
         // the operations of simplex_weights and of the weighted sum
         double u[K];
@@ -592,9 +614,11 @@ __global__ __launch_bounds__(kBlock) void k_walk(
 #pragma unroll
         for (int t = 0; t < K; ++t)
           pred += quotient(u[t], su, rs) * lds.slot[KEYS ? 0 : 1][t][lane];
-        out[out_off + (query_set ? i : p)] = pred;
+        out[G.out_off + (int64_t)(query_set ? i : p) * G.n_lib + lane] = pred;
       }
     }
+    i = i_next;
+    row = row_next;
   }
 }
 
@@ -602,7 +626,7 @@ __global__ __launch_bounds__(kBlock) void k_walk(
 // the same queries per lane, operations and merge order as crossmap_item.
 template <int E, int Q>
 __global__ __launch_bounds__(kBlock) void k_walk_moments(
-    const Realization* __restrict__ rzs, const int64_t* __restrict__ out_off,
+    const Realization* __restrict__ rzs, const WalkOut* __restrict__ where,
     const Item* __restrict__ items, int n_items, const double* __restrict__ pred,
     const int32_t* __restrict__ pj_pool, const int32_t* __restrict__ qord_pool,
     const double* __restrict__ tgt_pool, Moments* __restrict__ partial, int query_set) {
@@ -614,14 +638,15 @@ __global__ __launch_bounds__(kBlock) void k_walk_moments(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const double* __restrict__ tgt = tgt_pool + R.tgt_off + (int64_t)(E - 1) * R.tau;
   const int32_t* __restrict__ q = query_set ? pj_pool + R.pj_off : qord_pool + R.qord_off;
-  const double* __restrict__ pr = pred + out_off[I.rz];
+  const WalkOut W = where[I.rz];
+  const double* __restrict__ pr = pred + W.off;
   Moments mo = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int m = 0; m < Q; ++m) {
     const int qq = I.tile * (kBlock * Q) + wave * (64 * Q) + m * 64 + lane;
     if (qq < R.n_query) {
       const int i = q[qq];
-      mom_add(mo, tgt[i], pr[query_set ? i : qq]);
+      mom_add(mo, tgt[i], pr[(int64_t)(query_set ? i : qq) * W.stride]);
     }
   }
   red[tid] = mo;
@@ -635,12 +660,12 @@ __global__ __launch_bounds__(kBlock) void k_walk_moments(
 }
 
 // Causal matrix: one query tile of a walked realization, its neighbours read
-// from the walk's keys ([t][n_e] per library) instead of searched; then the
+// from the walk's keys instead of searched; then the
 // per-target stage of crossmap_multi_item.
 template <int E, int Q>
 __global__ __launch_bounds__(kBlock) void k_multi_keys(
     const Realization* __restrict__ rzs, const int32_t* __restrict__ self_of,
-    const int64_t* __restrict__ key_off, const Item* __restrict__ items,
+    const WalkOut* __restrict__ where, const Item* __restrict__ items,
     const double* __restrict__ keys, const int32_t* __restrict__ pj_pool,
     const int32_t* __restrict__ qord_pool, const double* __restrict__ tt, int m_series,
     Sums* __restrict__ partial, int query_set) {
@@ -650,7 +675,8 @@ __global__ __launch_bounds__(kBlock) void k_multi_keys(
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t* __restrict__ q = query_set ? pj_pool + R.pj_off : qord_pool + R.qord_off;
-  const double* __restrict__ k = keys + key_off[I.rz];
+  const WalkOut W = where[I.rz];
+  const double* __restrict__ k = keys + W.off;
   ScanState<E, Q, kKeepSelf> S;
 #pragma unroll
   for (int m = 0; m < Q; ++m) {
@@ -660,7 +686,7 @@ __global__ __launch_bounds__(kBlock) void k_multi_keys(
     const int at = query_set ? i : (valid ? qq : 0);
     S.qi[m] = valid ? i : -1;
 #pragma unroll
-    for (int t = 0; t < E + 1; ++t) S.key[m][t] = k[(int64_t)t * R.n_e + at];
+    for (int t = 0; t < E + 1; ++t) S.key[m][t] = k[((int64_t)at * (E + 1) + t) * W.stride];
   }
   multi_targets<E, Q, kKeepSelf>(S, R, I.tile, tt, m_series, self_of[I.rz], partial, lds);
 }
