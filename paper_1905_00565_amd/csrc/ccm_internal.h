@@ -180,7 +180,8 @@ struct RowJob {
   int64_t emb_off;   // floats: AoS embedding
   int64_t qord_off;  // int32: its points in visiting order
   int64_t pts_off;   // floats: its points in visiting order, [E][n_e]
-  int64_t box_off;   // floats: bounding boxes of runs of 64 of them, [runs][2][E]
+  int64_t box_off;   // floats: bounding boxes of runs of 64 of them, [2][E] each (a
+                     // multiple of 256 places)
   int64_t out_off;   // uint64: rows [n_e][w]
   int32_t n_e;
   int32_t w;

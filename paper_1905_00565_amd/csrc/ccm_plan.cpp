@@ -445,7 +445,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
       rj.box_off = box;
       rows += need;
       opts += (int64_t)rj.n_e * E;
-      box += (int64_t)((rj.n_e + 63) / 64) * 2 * E;
+      box += (int64_t)((rj.n_e + 64 * 256 - 1) / (64 * 256)) * 256 * 2 * E;
       n_row += rj.n_e;
       wb.max_ne = std::max(wb.max_ne, rj.n_e);
       wb.max_w = std::max(wb.max_w, rj.w);

@@ -23,7 +23,14 @@ namespace ccmk {
 
 // The points of one embedding in visiting order, one array per coordinate
 // (float [E][n_e]), and the bounding box of every run of 64 of them (float
-// [E] lowest, then [E] highest, per run).  One wavefront per run.
+// [E] lowest, then [E] highest, at box_slot(run)).  One wavefront per run.
+// Run 4 l + v of every 256 is looked at by lane l of wavefront v of the row
+// kernel: its box lies where the wavefront reads consecutive ones.  (One
+// array per coordinate instead: 3.5 against 2.1 ms for 2 x 10^5 rows at E = 3.)
+__device__ __forceinline__ int box_slot(int run) {
+  return (run & ~255) + ((run & 3) << 6) + ((run & 255) >> 2);
+}
+
 template <int E>
 __global__ __launch_bounds__(kBlock) void k_order_points(const RowJob* __restrict__ jobs,
                                                          const float* __restrict__ emb_pool,
@@ -38,7 +45,7 @@ __global__ __launch_bounds__(kBlock) void k_order_points(const RowJob* __restric
   const int i = qord_pool[J.qord_off + p];
   const float* __restrict__ v = emb_pool + J.emb_off + (int64_t)i * E;
   float* __restrict__ o = pts_pool + J.pts_off;
-  float* __restrict__ box = box_pool + J.box_off + (int64_t)b * (2 * E);
+  float* __restrict__ box = box_pool + J.box_off + (int64_t)box_slot(b) * (2 * E);
 #pragma unroll
   for (int k = 0; k < E; ++k) {
     const float x = v[k];
@@ -57,11 +64,15 @@ __global__ __launch_bounds__(kBlock) void k_order_points(const RowJob* __restric
 }
 
 // LDS of the row kernel (dynamic): four candidate segments of seg keys, one
-// per wavefront; the same candidates grouped by bucket; bucket counters.
+// per wavefront, in which the keys are later grouped by bucket; bucket
+// counters.  Room for 2 w + 768 keys, at most eleven per thread.
 constexpr int kRowBuckets = 1024;
+constexpr float kRowTarget = 1.5f;               // candidates aimed at, times w
+constexpr int kRowPerThread = 11;
 constexpr int row_segment(int w) { return w / 2 + 192; }
+static_assert(kWaves * row_segment(kRowMaxW) <= kRowPerThread * kBlock, "keys held in registers");
 inline size_t row_lds_bytes(int w) {
-  return (size_t)kWaves * row_segment(w) * 16 + kRowBuckets * 4;
+  return (size_t)kWaves * row_segment(w) * 8 + kRowBuckets * 4;
 }
 
 // Distances of the lanes' points of run b to the query.
@@ -101,27 +112,48 @@ __device__ __forceinline__ int row_bucket(uint64_t key, float scale) {
 }
 
 // Calls f(c, d2, valid) for the 64 points c of every run whose bound does
-// not exceed t, runs dealt to the workgroup's wavefronts in turn.
+// not exceed t, runs dealt to the workgroup's wavefronts in turn.  Four runs
+// are loaded together: one at a time, the wavefronts waited on their loads
+// for most of the pass (2 x 5 x 10^4 rows of 10^4 points at E = 10: 4.5
+// against 3.2 ms).
 template <int E, class F>
 __device__ __forceinline__ void visit_runs(const float* __restrict__ pts,
                                            const float* __restrict__ boxes, int n_e,
                                            const float (&q)[E], float t, F&& f) {
+  constexpr int kTogether = 4;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nb = (n_e + 63) >> 6;
+  int run[kTogether];                              // found and not yet visited
+#pragma unroll
+  for (int u = 0; u < kTogether; ++u) run[u] = 0;
+  int found = 0;
+  const auto visit = [&] {
+    float d2[kTogether];
+#pragma unroll
+    for (int u = 0; u < kTogether; ++u)
+      d2[u] = run_d2<E>(pts, n_e, min(run[u] * 64 + lane, n_e - 1), q);
+#pragma unroll
+    for (int u = 0; u < kTogether; ++u)
+      if (u < found) f(run[u] * 64 + lane, d2[u], run[u] * 64 + lane < n_e);
+    found = 0;
+  };
   for (int g = 0; g < nb; g += kBlock) {
     const int b = g + lane * kWaves + wave;
-    const bool near = b < nb && run_bound<E>(boxes + (int64_t)b * (2 * E), q) <= t;
+    // (slots past the last run are read and ignored)
+    const bool near =
+        run_bound<E>(boxes + (int64_t)(g + wave * 64 + lane) * (2 * E), q) <= t && b < nb;
     uint64_t open = __builtin_amdgcn_ballot_w64(near);
     while (open) {
-      const int l = __builtin_ctzll(open);
+      const int r = g + __builtin_ctzll(open) * kWaves + wave;
       open &= open - 1ull;
-      const int c = (g + l * kWaves + wave) * 64 + lane;
-      const bool valid = c < n_e;
-      const float d2 = run_d2<E>(pts, n_e, valid ? c : n_e - 1, q);
-      f(c, d2, valid);
+#pragma unroll
+      for (int u = 0; u < kTogether; ++u)
+        if (u == found) run[u] = r;
+      if (++found == kTogether) visit();
     }
   }
+  if (found) visit();
 }
 
 // Neighbour rows: row p of a job = the first w embedded points of its
@@ -130,16 +162,25 @@ __device__ __forceinline__ void visit_runs(const float* __restrict__ pts,
 //
 // One workgroup per run of consecutive positions.  The w-th distance changes
 // little from one position to the next, so each row starts from a threshold
-// just above the previous row's w-th distance: one pass over the runs of 64
-// points whose box reaches within it collects the candidates (bound by that
-// pass: 2E operations and one load per coordinate for each point visited),
-// and only a row whose threshold caught too few or too many repeats it with
-// another.  The candidates, about 1.2 w, are then ordered by bucket of d2
+// above the previous row's w-th distance, aimed at 1.5 w points by the
+// measured growth of their number: one pass over the runs of 64 points whose
+// box reaches within it collects the candidates (bound by that pass: 2E
+// operations and one load per coordinate for each point visited), and only a
+// row whose threshold caught fewer than w or more than fit repeats it with
+// another (1.04 passes per row at E = 2, 1.1 at E = 3 and 4, 1.3 to 1.7 at
+// E = 10).  The candidates are then ordered by bucket of d2
 // and by comparison within a bucket, a tenth of the work of a sorting
-// network at w = 1024.  A row whose w-th distance is shared by more points
+// network at w = 1024.  The keys are regrouped in place through registers:
+// a second array left a third of the wavefronts (10^5 rows of 10^4 points,
+// E = 1: 0.98 against 0.66 ms).  Building two or four rows per pass, to load
+// the points once for them, was 15-25% slower: their thresholds are missed
+// more often together, and their candidates take LDS from other workgroups.  A row whose w-th distance is shared by more points
 // than fit (repeated values) is selected by radix passes instead.
+// Minimum wavefronts per SIMD: 6 spills nothing in the pass at small E, and 5
+// was 2-7% faster from E = 6 on (4: 4-10% slower).
 template <int E>
-__global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs, int per_block,
+__global__ __launch_bounds__(kBlock)
+__attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(const RowJob* __restrict__ jobs, int per_block,
                                                  const float* __restrict__ pts_pool,
                                                  const float* __restrict__ box_pool,
                                                  const int32_t* __restrict__ qord_pool,
@@ -155,8 +196,8 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
   const int w = min(J.w, n);
   const int seg = row_segment(J.w);
   uint64_t* __restrict__ cand = row_lds;
-  uint64_t* __restrict__ grouped = row_lds + kWaves * seg;
-  uint32_t* __restrict__ hist = reinterpret_cast<uint32_t*>(grouped + kWaves * seg);
+  uint64_t* __restrict__ grouped = row_lds;       // over the segments
+  uint32_t* __restrict__ hist = reinterpret_cast<uint32_t*>(row_lds + kWaves * seg);
   const float* __restrict__ pts = pts_pool + J.pts_off;
   const float* __restrict__ boxes = box_pool + J.box_off;
   const int32_t* __restrict__ qord = qord_pool + J.qord_off;
@@ -164,7 +205,8 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  float slack = 1.25f;
+  // the number of points within t grows about like t^growth; from the last rows
+  float growth = 0.5f * E;
   float t_next = -1.f;
 
   for (int p = p0; p < min(p0 + per_block, n); ++p) {
@@ -172,34 +214,42 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
 #pragma unroll
     for (int k = 0; k < E; ++k) q[k] = pts[(int64_t)k * n + p];
     uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)p * J.w;
-    float t = t_next;
-    if (t < 0.f) {
-      // the first row: the farthest of the w points around it in visiting
-      // order bounds the w-th distance
+    // the farthest of the w points around p in visiting order: a bound of the
+    // w-th distance (the whole workgroup; two barriers)
+    const auto order_bound = [&] {
       const int a = max(0, min(p - w / 2, n - w));
       float m = 0.f;
       for (int c = a + tid; c < a + w; c += kBlock) m = fmaxf(m, run_d2<E>(pts, n, c, q));
 #pragma unroll
       for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
+      __syncthreads();
       if (lane == 0) s_n[wave] = __float_as_int(m);
       __syncthreads();
-      t = 0.f;
+      m = 0.f;
 #pragma unroll
-      for (int v = 0; v < kWaves; ++v) t = fmaxf(t, __int_as_float(s_n[v]));
-      __syncthreads();
-    }
+      for (int v = 0; v < kWaves; ++v) m = fmaxf(m, __int_as_float(s_n[v]));
+      return m;
+    };
+    float t = t_next < 0.f ? order_bound() : t_next;
     // thresholds known to catch too few / too many
     float t_few = -1.f, t_many = __builtin_inff();
     int total = 0;
     bool done = false;
     for (int attempt = 0; attempt < 16 && !done; ++attempt) {
+      const float scale = t > 0.f ? (float)kRowBuckets / t : 0.f;
+      for (int b = tid; b < kRowBuckets; b += kBlock) hist[b] = 0u;
+      __syncthreads();
       int mine = 0;
       visit_runs<E>(pts, boxes, n, q, t, [&](int c, float d2, bool valid) {
         const bool keep = valid && d2 <= t;
         const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
         if (m) {
           const int at = mine + __popcll(m & below);
-          if (keep && at < seg) cand[wave * seg + at] = row_key(d2, qord[c]);
+          if (keep && at < seg) {
+            const uint64_t key = row_key(d2, qord[c]);
+            cand[wave * seg + at] = key;
+            atomicAdd(&hist[row_bucket(key, scale)], 1u);
+          }
           mine += __popcll(m);
         }
       });
@@ -212,16 +262,17 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
         over |= s_n[v] > seg;
         total += s_n[v];
       }
-      __syncthreads();
-      if (total < w) {
-        t_few = t;
-        slack = fminf(2.f, 1.f + (slack - 1.f) * 1.5f);
-        t = t_many < __builtin_inff() ? 0.5f * (t_few + t_many)
-                                      : fmaxf(t * (attempt < 3 ? 1.5f : 4.f), 1e-37f);
-        if (!(t > t_few && t < t_many)) break;
-      } else if (over) {
-        t_many = t;
-        t = t_few >= 0.f ? 0.5f * (t_few + t_many) : 0.6f * t;
+      if (total < w || over) {
+        (over ? t_many : t_few) = t;
+        // by the power law, else into the bracket
+        float to = t * exp2f(log2f(kRowTarget * (float)w / (float)max(total, 1)) / growth);
+        if (attempt >= 2 || !(to > t_few && to < t_many)) {
+          if (!(t_many < __builtin_inff()))
+            to = order_bound();
+          else
+            to = t_few > 0.f ? sqrtf(t_few) * sqrtf(t_many) : 0.5f * t_many;
+        }
+        t = to;
         if (!(t > t_few && t < t_many)) break;
       } else {
         done = true;
@@ -229,12 +280,22 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
     }
     if (done) {
       const float scale = t > 0.f ? (float)kRowBuckets / t : 0.f;
-      for (int b = tid; b < kRowBuckets; b += kBlock) hist[b] = 0u;
-      __syncthreads();
-      const int mine = s_n[wave];
-      for (int x = lane; x < mine; x += 64)
-        atomicAdd(&hist[row_bucket(cand[wave * seg + x], scale)], 1u);
-      __syncthreads();
+      // the keys into registers, spread over the threads
+      int before[kWaves + 1];
+      before[0] = 0;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) before[v + 1] = before[v] + s_n[v];
+      uint64_t mine[kRowPerThread];
+#pragma unroll
+      for (int u = 0; u < kRowPerThread; ++u) {
+        const int x = u * kBlock + tid;
+        if (u * kBlock >= total) break;
+        int at = x;
+#pragma unroll
+        for (int v = 1; v < kWaves; ++v)
+          if (x >= before[v]) at = v * seg + x - before[v];
+        mine[u] = x < total ? cand[at] : 0ull;
+      }
       // exclusive prefix over the buckets: four per thread
       constexpr int per = kRowBuckets / kBlock;
       uint32_t h[per], sum = 0;
@@ -260,9 +321,11 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
       }
       __syncthreads();
       // grouped by bucket; afterwards hist[b] is the end of bucket b
-      for (int x = lane; x < mine; x += 64) {
-        const uint64_t key = cand[wave * seg + x];
-        grouped[atomicAdd(&hist[row_bucket(key, scale)], 1u)] = key;
+#pragma unroll
+      for (int u = 0; u < kRowPerThread; ++u) {
+        if (u * kBlock >= total) break;
+        if (u * kBlock + tid < total)
+          grouped[atomicAdd(&hist[row_bucket(mine[u], scale)], 1u)] = mine[u];
       }
       __syncthreads();
       for (int x = tid; x < total; x += kBlock) {
@@ -276,7 +339,10 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
         if (r == w - 1) s_t = __uint_as_float((uint32_t)(key >> 32));
       }
       __syncthreads();
-      if (total > w + w / 2) slack = 1.f + (slack - 1.f) * 0.7f;
+      const float s = s_t;
+      if (total > w && t > 1.0001f * s && s > 0.f)
+        growth += 0.3f * (fminf(2.f * E, fmaxf(0.5f, log2f((float)total / (float)w) /
+                                                         log2f(t / s))) - growth);
     } else {
       // more points share the w-th distance than the segments hold: radix
       // select of that distance (four 8-bit passes over the runs that can
@@ -362,8 +428,7 @@ __global__ __launch_bounds__(kBlock) void k_rows(const RowJob* __restrict__ jobs
       __syncthreads();
     }
     for (int x = w + tid; x < J.w; x += kBlock) row[x] = ~0ull;
-    t_next = s_t * slack;
-    __syncthreads();
+    t_next = s_t * exp2f(log2f(kRowTarget) / growth);
   }
 }
 
