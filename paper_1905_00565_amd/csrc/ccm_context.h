@@ -60,6 +60,8 @@ struct PlanBuffers {
   uint64_t* masks = nullptr;
   float* opts = nullptr;
   float* boxes = nullptr;
+  RowTodo* todo = nullptr;
+  int* todo_n = nullptr;
   double* walk_out = nullptr;
 };
 
@@ -73,7 +75,7 @@ struct Exec {
   DevBuf d_tables, d_table;   // distance indexing table jobs and rows
   DevBuf d_nested, d_scratch, d_segs, d_rz_fin;   // nested libraries
   DevBuf d_row_jobs, d_mask_jobs, d_walk_libs, d_walk_groups, d_walk_items, d_mom_items,
-      d_walk_where, d_rows, d_bits, d_masks, d_opts, d_boxes, d_walk_out;   // neighbour rows
+      d_walk_where, d_rows, d_bits, d_masks, d_opts, d_boxes, d_todo, d_walk_out;   // neighbour rows
   std::vector<int64_t> plain_first;   // per realization: first plain item
   PlanBuffers buf;
   hipGraphExec_t graph = nullptr;

@@ -215,11 +215,12 @@ struct Plan {
   std::vector<WalkBatch> walk_batches;
   std::vector<WalkChunk> walk_chunks;
   int64_t n_rows = 0, n_opts = 0, n_box = 0, n_bits = 0, n_mask = 0, n_walk_out = 0;
+  int64_t n_todo = 0;                 // rows of the largest batch
   uint64_t walk_bytes() const {
     return (uint64_t)(n_rows + n_bits + n_mask + n_walk_out) * 8 + (uint64_t)(n_opts + n_box) * 4 +
            row_jobs.size() * sizeof(RowJob) + mask_jobs.size() * sizeof(MaskJob) +
            walk_libs.size() * sizeof(WalkLib) + walk_groups.size() * sizeof(WalkGroup) +
-           (walk_items.size() + mom_items.size()) * sizeof(Item) + walk_out.size() * sizeof(WalkOut);
+           (walk_items.size() + mom_items.size()) * sizeof(Item) + walk_out.size() * sizeof(WalkOut) + n_todo * sizeof(RowTodo);
   }
   // nested libraries (CCM_FLAG_NESTED): rz holds chains, rz_fin one record
   // per rho (slot range of its segment, output index)

@@ -42,12 +42,13 @@ hipError_t launch_table_build_e(const TableJob* jobs, int n_jobs, int max_n_e, c
 
 template <int E>
 hipError_t launch_order_points_e(const RowJob* jobs, int n_jobs, int max_ne, const float* emb,
-                                 const int32_t* qord, float* pts, float* box, hipStream_t st);
+                                 const int32_t* qord, float* pts, float* box, int* todo_n,
+                                 hipStream_t st);
 
 template <int E>
 hipError_t launch_rows_e(const RowJob* jobs, int n_jobs, int max_ne, int max_w, int per_block,
                          const float* pts, const float* box, const int32_t* qord,
-                         uint64_t* rows, hipStream_t st);
+                         uint64_t* rows, RowTodo* todo, int* todo_n, hipStream_t st);
 
 template <int E>
 hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,

@@ -1,5 +1,7 @@
 // ccm_inst_walk.hip -- the neighbour-row kernels of one embedding dimension
 // (ccm_walk.h), compiled once per E = 1..10 with -DCCM_INST_E=E.
+#include <algorithm>
+
 #include "ccm_walk.h"
 #include "ccm_inst.h"
 
@@ -11,19 +13,25 @@ namespace ccmk {
 
 template <int E>
 hipError_t launch_order_points_e(const RowJob* jobs, int n_jobs, int max_ne, const float* emb,
-                                 const int32_t* qord, float* pts, float* box, hipStream_t st) {
+                                 const int32_t* qord, float* pts, float* box, int* todo_n,
+                                 hipStream_t st) {
   const unsigned runs = (unsigned)((max_ne + 63) / 64);
   k_order_points<E><<<dim3((runs + kWaves - 1) / kWaves, (unsigned)n_jobs), kBlock, 0, st>>>(
-      jobs, emb, qord, pts, box);
+      jobs, emb, qord, pts, box, todo_n);
   return hipGetLastError();
 }
 
 template <int E>
 hipError_t launch_rows_e(const RowJob* jobs, int n_jobs, int max_ne, int max_w, int per_block,
                          const float* pts, const float* box, const int32_t* qord,
-                         uint64_t* rows, hipStream_t st) {
+                         uint64_t* rows, RowTodo* todo, int* todo_n, hipStream_t st) {
   const dim3 grid((unsigned)((max_ne + per_block - 1) / per_block), (unsigned)n_jobs);
-  k_rows<E><<<grid, kBlock, row_lds_bytes(max_w), st>>>(jobs, per_block, pts, box, qord, rows);
+  k_rows<E><<<grid, kBlock, row_lds_bytes(max_w), st>>>(jobs, per_block, pts, box, qord, rows,
+                                                        todo, todo_n);
+  // a resident grid over the rows it has left, usually none
+  const unsigned rows_all = (unsigned)std::min<int64_t>(2048, (int64_t)max_ne * n_jobs);
+  k_rows_repeats<E><<<rows_all, kBlock, row_lds_bytes(max_w), st>>>(jobs, todo, todo_n, pts, box,
+                                                                    qord, rows);
   return hipGetLastError();
 }
 
@@ -55,11 +63,11 @@ hipError_t launch_walk_moments_e(const Realization* rzs, const WalkOut* where,
 }
 
 template hipError_t launch_order_points_e<CCM_INST_E>(const RowJob*, int, int, const float*,
-                                                      const int32_t*, float*, float*,
+                                                      const int32_t*, float*, float*, int*,
                                                       hipStream_t);
 template hipError_t launch_rows_e<CCM_INST_E>(const RowJob*, int, int, int, int, const float*,
-                                              const float*, const int32_t*, uint64_t*,
-                                              hipStream_t);
+                                              const float*, const int32_t*, uint64_t*, RowTodo*,
+                                              int*, hipStream_t);
 template hipError_t launch_walk_e<CCM_INST_E>(int, const WalkGroup*, const WalkLib*,
                                               const RowJob*, const Item*, int, int,
                                               const uint64_t*, const uint64_t*, const int32_t*,

@@ -187,6 +187,15 @@ struct RowJob {
   int32_t w;
 };
 
+// A row left to the second row kernel (repeated values): position p of a
+// job, whose w-th distance is at most reach.
+struct RowTodo {
+  int32_t job;
+  int32_t p;
+  float reach;
+  int32_t pad;
+};
+
 // A library of a walk group.
 struct WalkLib {
   int64_t bit_off;   // uint64: its bitmap over 0..n_e-1
@@ -328,13 +337,14 @@ hipError_t refine_orders_kd(const OrderJob* orders, int32_t n_sets, int levels,
 
 // Neighbour-row path.  Rows of jobs [0, n_jobs) (max_ne, max_w: the largest
 // of them), the points' visiting-order copies and boxes first; per_block
-// consecutive rows per workgroup.
+// consecutive rows per workgroup.  todo (one place per row) and its counter
+// are scratch.
 hipError_t launch_order_points(int E, const RowJob* jobs, int n_jobs, int max_ne,
                                const float* emb, const int32_t* qord, float* pts, float* box,
-                               hipStream_t st);
+                               int* todo_n, hipStream_t st);
 hipError_t launch_rows(int E, const RowJob* jobs, int n_jobs, int max_ne, int max_w,
                        int per_block, const float* pts, const float* box, const int32_t* qord,
-                       uint64_t* rows, hipStream_t st);
+                       uint64_t* rows, RowTodo* todo, int* todo_n, hipStream_t st);
 hipError_t launch_masks(const MaskJob* jobs, int n_jobs, int max_ne, const WalkLib* libs,
                         const uint64_t* bits, uint64_t* masks, hipStream_t st);
 // The walk of `per` queries per item ({group, block of queries}): keys == 0

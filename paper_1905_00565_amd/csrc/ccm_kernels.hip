@@ -806,21 +806,22 @@ hipError_t launch_masks(const MaskJob* jobs, int n_jobs, int max_ne, const WalkL
 
 hipError_t launch_order_points(int E, const RowJob* jobs, int n_jobs, int max_ne,
                                const float* emb, const int32_t* qord, float* pts, float* box,
-                               hipStream_t st) {
+                               int* todo_n, hipStream_t st) {
   if (n_jobs <= 0 || max_ne <= 0) return hipSuccess;
-#define CCM_CALL(e) launch_order_points_e<e>(jobs, n_jobs, max_ne, emb, qord, pts, box, st)
+#define CCM_CALL(e) launch_order_points_e<e>(jobs, n_jobs, max_ne, emb, qord, pts, box, todo_n, st)
   CCM_BY_E(E, CCM_CALL)
 #undef CCM_CALL
 }
 
 hipError_t launch_rows(int E, const RowJob* jobs, int n_jobs, int max_ne, int max_w,
                        int per_block, const float* pts, const float* box, const int32_t* qord,
-                       uint64_t* rows, hipStream_t st) {
+                       uint64_t* rows, RowTodo* todo, int* todo_n, hipStream_t st) {
   if (n_jobs <= 0 || max_ne <= 0) return hipSuccess;
   if (max_w < 64 || max_w > kRowMaxW || max_w % 64 != 0 || per_block < 1)
     return hipErrorInvalidValue;
 #define CCM_CALL(e) \
-  launch_rows_e<e>(jobs, n_jobs, max_ne, max_w, per_block, pts, box, qord, rows, st)
+  launch_rows_e<e>(jobs, n_jobs, max_ne, max_w, per_block, pts, box, qord, rows, todo, \
+                   todo_n, st)
   CCM_BY_E(E, CCM_CALL)
 #undef CCM_CALL
 }

@@ -296,8 +296,9 @@ static double walk_cost(int E, int64_t chunks) {
 static double row_cost(int E, int64_t ne, int64_t w) {
   return (2.0 * E + 20.0) * (double)ne / 64.0 + 8.0 * (double)w + 1500.0;
 }
-// Slots below which the walk's extra launches cost more than it saves.
-constexpr double kWalkMinGain = 2.0e7;
+// Slots below which the walk's seven launches cost more than it saves (at
+// 2 x 10^7 a pair of N = 1331 at E = 1 went from 153 to 183 us).
+constexpr double kWalkMinGain = 5.0e7;
 
 // The realizations of one launch (rzs: one E of one wave) that walk
 // neighbour rows: per embedding its largest libraries, in groups of 64, as
@@ -455,6 +456,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
     p.n_rows = std::max(p.n_rows, rows);
     p.n_opts = std::max(p.n_opts, opts);
     p.n_box = std::max(p.n_box, box);
+    p.n_todo = std::max(p.n_todo, n_row);
     wb.chunk_first = (int32_t)p.walk_chunks.size();
     // chunks: consecutive groups whose output fits; within a chunk the
     // groups of one embedding take the same block of queries together, so

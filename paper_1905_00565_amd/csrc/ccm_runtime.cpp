@@ -113,6 +113,7 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
     ex->d_masks.ensure(p.n_mask * 8);
     ex->d_opts.ensure(p.n_opts * 4);
     ex->d_boxes.ensure(p.n_box * 4);
+    ex->d_todo.ensure(256 + p.n_todo * sizeof(RowTodo));
     ex->d_walk_out.ensure(p.n_walk_out * 8);
   }
   ex->d_s64.ensure(p.n64 * 8);
@@ -183,6 +184,8 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   b.masks = ex->d_masks.as<uint64_t>();
   b.opts = ex->d_opts.as<float>();
   b.boxes = ex->d_boxes.as<float>();
+  b.todo_n = ex->d_todo.as<int>();
+  b.todo = reinterpret_cast<RowTodo*>(ex->d_todo.as<char>() + 256);
   b.walk_out = ex->d_walk_out.as<double>();
   c->exec = std::move(ex);
   return c->exec.get();
@@ -206,9 +209,9 @@ void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStrea
     const WalkBatch& wb = p.walk_batches[bi];
     const RowJob* jobs = b.row_jobs + wb.emb_first;
     HIPCHK(launch_order_points(L.E, jobs, wb.emb_count, wb.max_ne, b.emb, b.qord, b.opts,
-                               b.boxes, st));
+                               b.boxes, b.todo_n, st));
     HIPCHK(launch_rows(L.E, jobs, wb.emb_count, wb.max_ne, wb.max_w, wb.rows_per_block, b.opts,
-                       b.boxes, b.qord, b.rows, st));
+                       b.boxes, b.qord, b.rows, b.todo, b.todo_n, st));
     for (int ci = wb.chunk_first; ci < wb.chunk_first + wb.chunk_count; ++ci) {
       const WalkChunk& ch = p.walk_chunks[ci];
       HIPCHK(launch_walk(L.E, p.spec.M > 0, b.walk_groups, b.walk_libs, b.row_jobs,

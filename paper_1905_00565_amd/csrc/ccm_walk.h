@@ -36,8 +36,10 @@ __global__ __launch_bounds__(kBlock) void k_order_points(const RowJob* __restric
                                                          const float* __restrict__ emb_pool,
                                                          const int32_t* __restrict__ qord_pool,
                                                          float* __restrict__ pts_pool,
-                                                         float* __restrict__ box_pool) {
+                                                         float* __restrict__ box_pool,
+                                                         int* __restrict__ todo_n) {
   const RowJob J = jobs[blockIdx.y];
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *todo_n = 0;   // for k_rows
   const int lane = threadIdx.x & 63;
   const int b = blockIdx.x * kWaves + (threadIdx.x >> 6);
   if (b * 64 >= J.n_e) return;
@@ -67,6 +69,8 @@ __global__ __launch_bounds__(kBlock) void k_order_points(const RowJob* __restric
 // per wavefront, in which the keys are later grouped by bucket; bucket
 // counters.  Room for 2 w + 768 keys, at most eleven per thread.
 constexpr int kRowBuckets = 1024;
+constexpr uint32_t kRowCrowd = 96;               // larger buckets: by octave instead
+constexpr uint32_t kRowMost = 384;               // largest bucket ordered by comparison
 constexpr float kRowTarget = 1.5f;               // candidates aimed at, times w
 constexpr int kRowPerThread = 11;
 constexpr int row_segment(int w) { return w / 2 + 192; }
@@ -106,8 +110,12 @@ __device__ __forceinline__ float run_bound(const float* __restrict__ box, const 
 __device__ __forceinline__ uint64_t row_key(float d2, int j) {
   return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
 }
-__device__ __forceinline__ int row_bucket(uint64_t key, float scale) {
-  const float x = __uint_as_float((uint32_t)(key >> 32)) * scale;
+// Bucket of a key: by d2 scaled to the threshold, or (scale < 0) by its binary
+// exponent and leading mantissa bits, 32 to the octave below the threshold.
+__device__ __forceinline__ int row_bucket(uint64_t key, float scale, uint32_t base) {
+  const uint32_t u = (uint32_t)(key >> 32);
+  if (scale < 0.f) return u <= base ? 0 : min(kRowBuckets - 1, (int)((u - base) >> 18));
+  const float x = __uint_as_float(u) * scale;
   return x < (float)(kRowBuckets - 1) ? (int)x : (x >= 0.f ? kRowBuckets - 1 : 0);
 }
 
@@ -156,6 +164,200 @@ __device__ __forceinline__ void visit_runs(const float* __restrict__ pts,
   if (found) visit();
 }
 
+// The farthest of the w points around position p in visiting order: a bound of
+// its w-th distance (the whole workgroup; two barriers, s_n is used).
+template <int E>
+__device__ __forceinline__ float order_reach(const float* __restrict__ pts, int n, int w, int p,
+                                             const float (&q)[E], int* s_n) {
+  const int tid = threadIdx.x;
+  const int a = max(0, min(p - w / 2, n - w));
+  float m = 0.f;
+  for (int c = a + tid; c < a + w; c += kBlock) m = fmaxf(m, run_d2<E>(pts, n, c, q));
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
+  __syncthreads();
+  if ((tid & 63) == 0) s_n[tid >> 6] = __float_as_int(m);
+  __syncthreads();
+  m = 0.f;
+#pragma unroll
+  for (int v = 0; v < kWaves; ++v) m = fmaxf(m, __int_as_float(s_n[v]));
+  return m;
+}
+
+// Rows among repeated values, where many points share a distance: the
+// distances in ascending order from 0 (the query's own), one pass over the
+// runs within reach (at least the w-th distance) for each, which marks the
+// points at this distance in a bitmap over their indices and finds the next
+// one; the marked indices are the row's next entries, in order.  Given up
+// (false) when the distances bring fewer than w / 16 points each.  The bitmap
+// takes `words` 32-bit words of LDS; longer series take more passes per
+// distance.  The whole workgroup.
+template <int E>
+__device__ bool row_by_level(const float* __restrict__ pts, const float* __restrict__ boxes,
+                             const int32_t* __restrict__ qord, int n, int w, const float (&q)[E],
+                             float reach, uint32_t* bits, int words,
+                             uint64_t* __restrict__ row) {
+  __shared__ uint32_t s_min;
+  __shared__ int s_cnt[kWaves];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t far = __float_as_uint(__builtin_inff());
+  int filled = 0;
+  uint32_t T = 0u;                                 // bits of this distance
+  for (int level = 0;; ++level) {
+    if (tid == 0) s_min = far;
+    uint32_t next = far;
+    for (int j0 = 0; j0 < n; j0 += words * 32) {
+      const int nw = min(words, (n - j0 + 31) >> 5);
+      for (int x = tid; x < nw; x += kBlock) bits[x] = 0u;
+      __syncthreads();
+      visit_runs<E>(pts, boxes, n, q, reach, [&](int c, float d2, bool valid) {
+        if (!valid) return;
+        const uint32_t u = __float_as_uint(d2);
+        if (u > T) {
+          next = min(next, u);
+        } else if (u == T) {
+          const int j = qord[c] - j0;
+          if (j >= 0 && j < nw * 32) atomicOr(&bits[j >> 5], 1u << (j & 31));
+        }
+      });
+      __syncthreads();
+      // the marked indices, consecutive words per thread
+      const int per = (nw + kBlock - 1) / kBlock;
+      int sum = 0;
+      for (int x = tid * per; x < min((tid + 1) * per, nw); ++x) sum += __popc(bits[x]);
+      int inc = sum;
+#pragma unroll
+      for (int s = 1; s < 64; s <<= 1) {
+        const int y = __shfl_up(inc, s, 64);
+        if (lane >= s) inc += y;
+      }
+      if (lane == 63) s_cnt[wave] = inc;
+      __syncthreads();
+      int at = filled + inc - sum, all = 0;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) {
+        if (v < wave) at += s_cnt[v];
+        all += s_cnt[v];
+      }
+      for (int x = tid * per; x < min((tid + 1) * per, nw) && at < w; ++x) {
+        uint32_t b = bits[x];
+        while (b && at < w) {
+          row[at++] = ((uint64_t)T << 32) | (uint32_t)(j0 + x * 32 + __builtin_ctz(b));
+          b &= b - 1u;
+        }
+      }
+      filled += all;
+      __syncthreads();
+      if (filled >= w) return true;
+    }
+    if (filled * 16 < (level + 1) * w) return false;
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) next = min(next, (uint32_t)__shfl_xor((int)next, s, 64));
+    if (lane == 0) atomicMin(&s_min, next);
+    __syncthreads();
+    T = s_min;
+    __syncthreads();
+    if (T == far) return false;                    // (reach below the w-th distance)
+  }
+}
+
+// Rows with no end to their distances among the repeated ones: radix select of
+// the w-th distance (four 8-bit passes over the runs that can hold it), then
+// the nearer points and the lowest-index ones at it, sorted in `grouped`
+// (room for the power of two >= w).  hist: 256 counters.  The whole
+// workgroup.
+template <int E>
+__device__ void row_by_select(const float* __restrict__ pts, const float* __restrict__ boxes,
+                               const int32_t* __restrict__ qord, int n, int w,
+                               const float (&q)[E], float reach, uint64_t* grouped,
+                               uint32_t* hist, uint64_t* __restrict__ row) {
+  __shared__ uint32_t s_pick[3];
+  __shared__ int s_at;
+  const int tid = threadIdx.x;
+  uint32_t prefix = 0u, mask = 0u, need = (uint32_t)w, at_T = 0u;
+  // the counter that holds the need-th entry, and its own count
+  const auto pick = [&](int shift) {
+    __syncthreads();
+    if (tid == 0) {
+      uint32_t cum = 0u, b = 0u;
+      for (; b < 255u && cum + hist[b] < need; ++b) cum += hist[b];
+      s_pick[0] = b;
+      s_pick[1] = need - cum;
+      s_pick[2] = hist[b];
+    }
+    __syncthreads();
+    need = s_pick[1];
+    at_T = s_pick[2];
+    const uint32_t byte = s_pick[0] << shift;
+    __syncthreads();
+    return byte;
+  };
+  for (int shift = 24; shift >= 0; shift -= 8) {
+    hist[tid] = 0u;
+    __syncthreads();
+    visit_runs<E>(pts, boxes, n, q, reach, [&](int, float d2, bool valid) {
+      const uint32_t u = __float_as_uint(d2);
+      if (valid && (u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 255u], 1u);
+    });
+    prefix |= pick(shift);
+    mask |= 255u << shift;
+    // no entry needed lies beyond the counter's range
+    reach = fminf(reach, __uint_as_float(min(prefix | ~mask, 0x7f800000u)));
+  }
+  // rank of the last index taken at distance T, when not all are: radix
+  // select on j
+  const uint32_t T = prefix;
+  uint32_t jpre = 0u, jmask = 0u;
+  if (need == at_T) {
+    jpre = ~0u;
+  } else {
+    for (int shift = 24; shift >= 0; shift -= 8) {
+      hist[tid] = 0u;
+      __syncthreads();
+      visit_runs<E>(pts, boxes, n, q, reach, [&](int c, float d2, bool valid) {
+        if (valid && __float_as_uint(d2) == T) {
+          const uint32_t j = (uint32_t)qord[c];
+          if ((j & jmask) == jpre) atomicAdd(&hist[(j >> shift) & 255u], 1u);
+        }
+      });
+      jpre |= pick(shift);
+      jmask |= 255u << shift;
+    }
+  }
+  // exactly w keys are at most (T, jpre): collect and sort them
+  const uint64_t last = ((uint64_t)T << 32) | jpre;
+  if (tid == 0) s_at = 0;
+  __syncthreads();
+  visit_runs<E>(pts, boxes, n, q, reach, [&](int c, float d2, bool valid) {
+    const uint64_t key = row_key(d2, valid ? qord[c] : -1);
+    if (valid && key <= last) {
+      const int at = atomicAdd(&s_at, 1);
+      if (at < w) grouped[at] = key;
+    }
+  });
+  int P = 1;
+  while (P < w) P <<= 1;
+  for (int x = w + tid; x < P; x += kBlock) grouped[x] = ~0ull;
+  __syncthreads();
+  for (int size = 2; size <= P; size <<= 1)
+    for (int stride = size >> 1; stride > 0; stride >>= 1) {
+      for (int x = tid; x < P / 2; x += kBlock) {
+        const int lo = 2 * x - (x & (stride - 1));
+        const int hi = lo + stride;
+        const bool up = (lo & size) == 0;
+        const uint64_t a = grouped[lo], b = grouped[hi];
+        if ((a > b) == up) {
+          grouped[lo] = b;
+          grouped[hi] = a;
+        }
+      }
+      __syncthreads();
+    }
+  for (int x = tid; x < w; x += kBlock) row[x] = grouped[x];
+}
+
 // Neighbour rows: row p of a job = the first w embedded points of its
 // embedding in ascending (d2, j) order from the point at visiting position
 // p, as keys (d2 bits, j); entries past n_e are ~0.
@@ -174,21 +376,21 @@ __device__ __forceinline__ void visit_runs(const float* __restrict__ pts,
 // a second array left a third of the wavefronts (10^5 rows of 10^4 points,
 // E = 1: 0.98 against 0.66 ms).  Building two or four rows per pass, to load
 // the points once for them, was 15-25% slower: their thresholds are missed
-// more often together, and their candidates take LDS from other workgroups.  A row whose w-th distance is shared by more points
-// than fit (repeated values) is selected by radix passes instead.
-// Minimum wavefronts per SIMD: 6 spills nothing in the pass at small E, and 5
-// was 2-7% faster from E = 6 on (4: 4-10% slower).
+// more often together, and their candidates take LDS from other workgroups.
+// Rows among repeated values (more points at one distance than fit, or than
+// are worth comparing) are left to k_rows_repeats.
+//
+// Minimum wavefronts per SIMD: 6 at small E and 5 from E = 6 on, each within
+// 3% of the other and 4-13% faster than 4 or 7.
 template <int E>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(const RowJob* __restrict__ jobs, int per_block,
-                                                 const float* __restrict__ pts_pool,
-                                                 const float* __restrict__ box_pool,
-                                                 const int32_t* __restrict__ qord_pool,
-                                                 uint64_t* __restrict__ row_pool) {
+__attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(
+    const RowJob* __restrict__ jobs, int per_block, const float* __restrict__ pts_pool,
+    const float* __restrict__ box_pool, const int32_t* __restrict__ qord_pool,
+    uint64_t* __restrict__ row_pool, RowTodo* __restrict__ todo, int* __restrict__ todo_n) {
   extern __shared__ uint64_t row_lds[];
-  __shared__ int s_n[kWaves], s_wave[kWaves];
+  __shared__ int s_n[kWaves], s_wave[kWaves], s_full[kWaves];
   __shared__ float s_t;
-  __shared__ uint32_t s_pick[2];
   const RowJob J = jobs[blockIdx.y];
   const int n = J.n_e;
   const int p0 = (int)blockIdx.x * per_block;
@@ -208,34 +410,20 @@ __attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(const RowJob*
   // the number of points within t grows about like t^growth; from the last rows
   float growth = 0.5f * E;
   float t_next = -1.f;
+  bool repeats = false;                            // the last row was left
 
   for (int p = p0; p < min(p0 + per_block, n); ++p) {
     float q[E];
 #pragma unroll
     for (int k = 0; k < E; ++k) q[k] = pts[(int64_t)k * n + p];
     uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)p * J.w;
-    // the farthest of the w points around p in visiting order: a bound of the
-    // w-th distance (the whole workgroup; two barriers)
-    const auto order_bound = [&] {
-      const int a = max(0, min(p - w / 2, n - w));
-      float m = 0.f;
-      for (int c = a + tid; c < a + w; c += kBlock) m = fmaxf(m, run_d2<E>(pts, n, c, q));
-#pragma unroll
-      for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
-      __syncthreads();
-      if (lane == 0) s_n[wave] = __float_as_int(m);
-      __syncthreads();
-      m = 0.f;
-#pragma unroll
-      for (int v = 0; v < kWaves; ++v) m = fmaxf(m, __int_as_float(s_n[v]));
-      return m;
-    };
-    float t = t_next < 0.f ? order_bound() : t_next;
+    const auto order_bound = [&] { return order_reach<E>(pts, n, w, p, q, s_n); };
+    float t = repeats && (p & 7) ? 0.f : t_next < 0.f ? order_bound() : t_next;
     // thresholds known to catch too few / too many
     float t_few = -1.f, t_many = __builtin_inff();
     int total = 0;
     bool done = false;
-    for (int attempt = 0; attempt < 16 && !done; ++attempt) {
+    for (int attempt = 0; attempt < (repeats && (p & 7) ? 0 : 16) && !done; ++attempt) {
       const float scale = t > 0.f ? (float)kRowBuckets / t : 0.f;
       for (int b = tid; b < kRowBuckets; b += kBlock) hist[b] = 0u;
       __syncthreads();
@@ -248,7 +436,7 @@ __attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(const RowJob*
           if (keep && at < seg) {
             const uint64_t key = row_key(d2, qord[c]);
             cand[wave * seg + at] = key;
-            atomicAdd(&hist[row_bucket(key, scale)], 1u);
+            atomicAdd(&hist[row_bucket(key, scale, 0u)], 1u);
           }
           mine += __popcll(m);
         }
@@ -278,8 +466,11 @@ __attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(const RowJob*
         done = true;
       }
     }
+    int crowded = 0;
     if (done) {
-      const float scale = t > 0.f ? (float)kRowBuckets / t : 0.f;
+      float scale = t > 0.f ? (float)kRowBuckets / t : 0.f;
+      const uint32_t t_bits = __float_as_uint(t);
+      const uint32_t base = t_bits > (32u << 23) ? t_bits - (32u << 23) : 0u;
       // the keys into registers, spread over the threads
       int before[kWaves + 1];
       before[0] = 0;
@@ -296,139 +487,125 @@ __attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(const RowJob*
           if (x >= before[v]) at = v * seg + x - before[v];
         mine[u] = x < total ? cand[at] : 0ull;
       }
-      // exclusive prefix over the buckets: four per thread
-      constexpr int per = kRowBuckets / kBlock;
-      uint32_t h[per], sum = 0;
+      for (;;) {
+        // exclusive prefix over the buckets: four per thread
+        constexpr int per = kRowBuckets / kBlock;
+        uint32_t h[per], sum = 0;
 #pragma unroll
-      for (int u = 0; u < per; ++u) {
-        h[u] = hist[tid * per + u];
-        sum += h[u];
-      }
-      uint32_t inc = sum;
+        for (int u = 0; u < per; ++u) {
+          h[u] = hist[tid * per + u];
+          sum += h[u];
+        }
+        uint32_t inc = sum;
 #pragma unroll
-      for (int s = 1; s < 64; s <<= 1) {
-        const uint32_t y = __shfl_up(inc, s, 64);
-        if (lane >= s) inc += y;
-      }
-      if (lane == 63) s_wave[wave] = (int)inc;
-      __syncthreads();
-      uint32_t at = inc - sum;
-      for (int v = 0; v < wave; ++v) at += (uint32_t)s_wave[v];
+        for (int s = 1; s < 64; s <<= 1) {
+          const uint32_t y = __shfl_up(inc, s, 64);
+          if (lane >= s) inc += y;
+        }
+        if (lane == 63) s_wave[wave] = (int)inc;
+        __syncthreads();
+        uint32_t at = inc - sum;
+        for (int v = 0; v < wave; ++v) at += (uint32_t)s_wave[v];
+        // a bucket of the row too full to be ordered by comparison
+        const uint32_t most = scale < 0.f ? kRowMost : kRowCrowd;
+        int full = 0;
 #pragma unroll
-      for (int u = 0; u < per; ++u) {
-        hist[tid * per + u] = at;
-        at += h[u];
+        for (int u = 0; u < per; ++u) {
+          if (h[u] > most && (int)at < w) full = 1;
+          hist[tid * per + u] = at;
+          at += h[u];
+        }
+        const bool any_full = __builtin_amdgcn_ballot_w64(full) != 0;
+        if (lane == 0) s_full[wave] = any_full ? 1 : 0;
+        __syncthreads();
+        crowded = s_full[0] | s_full[1] | s_full[2] | s_full[3];
+        if (!crowded || scale < 0.f) break;
+        // (distances of very different sizes: by octave)
+        scale = -1.f;
+        for (int b = tid; b < kRowBuckets; b += kBlock) hist[b] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kRowPerThread; ++u) {
+          if (u * kBlock >= total) break;
+          if (u * kBlock + tid < total) atomicAdd(&hist[row_bucket(mine[u], scale, base)], 1u);
+        }
+        __syncthreads();
       }
-      __syncthreads();
       // grouped by bucket; afterwards hist[b] is the end of bucket b
 #pragma unroll
       for (int u = 0; u < kRowPerThread; ++u) {
         if (u * kBlock >= total) break;
         if (u * kBlock + tid < total)
-          grouped[atomicAdd(&hist[row_bucket(mine[u], scale)], 1u)] = mine[u];
+          grouped[atomicAdd(&hist[row_bucket(mine[u], scale, base)], 1u)] = mine[u];
       }
       __syncthreads();
-      for (int x = tid; x < total; x += kBlock) {
-        const uint64_t key = grouped[x];
-        const int b = row_bucket(key, scale);
-        const int lo = b ? (int)hist[b - 1] : 0, hi = (int)hist[b];
-        if (lo >= w) continue;
-        int r = lo;
-        for (int y = lo; y < hi; ++y) r += grouped[y] < key ? 1 : 0;
-        if (r < w) row[r] = key;
-        if (r == w - 1) s_t = __uint_as_float((uint32_t)(key >> 32));
+      if (!crowded) {
+        for (int x = tid; x < total; x += kBlock) {
+          const uint64_t key = grouped[x];
+          const int b = row_bucket(key, scale, base);
+          const int lo = b ? (int)hist[b - 1] : 0, hi = (int)hist[b];
+          if (lo >= w) continue;
+          int r = lo;
+          for (int y = lo; y < hi; ++y) r += grouped[y] < key ? 1 : 0;
+          if (r < w) row[r] = key;
+          if (r == w - 1) s_t = __uint_as_float((uint32_t)(key >> 32));
+        }
+        __syncthreads();
+        const float s = s_t;
+        if (total > w && t > 1.0001f * s && s > 0.f)
+          growth += 0.3f * (fminf(2.f * E, fmaxf(0.5f, log2f((float)total / (float)w) /
+                                                           log2f(t / s))) - growth);
       }
-      __syncthreads();
-      const float s = s_t;
-      if (total > w && t > 1.0001f * s && s > 0.f)
-        growth += 0.3f * (fminf(2.f * E, fmaxf(0.5f, log2f((float)total / (float)w) /
-                                                         log2f(t / s))) - growth);
-    } else {
-      // more points share the w-th distance than the segments hold: radix
-      // select of that distance (four 8-bit passes over the runs that can
-      // hold it), then the nearer points and the lowest-index ones at it
-      const float reach = t_many;
-      uint32_t prefix = 0u, mask = 0u, need = (uint32_t)w;
-      for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0u;
-        __syncthreads();
-        visit_runs<E>(pts, boxes, n, q, reach, [&](int, float d2, bool valid) {
-          const uint32_t u = __float_as_uint(d2);
-          if (valid && (u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 255u], 1u);
-        });
-        __syncthreads();
-        if (tid == 0) {
-          uint32_t cum = 0u, b = 0u;
-          for (; b < 255u && cum + hist[b] < need; ++b) cum += hist[b];
-          s_pick[0] = b;
-          s_pick[1] = need - cum;
-        }
-        __syncthreads();
-        prefix |= s_pick[0] << shift;
-        mask |= 255u << shift;
-        need = s_pick[1];
-        __syncthreads();
-      }
-      // rank of the last index taken at distance T: radix select on j
-      const uint32_t T = prefix;
-      uint32_t jpre = 0u, jmask = 0u, jneed = need;
-      for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0u;
-        __syncthreads();
-        visit_runs<E>(pts, boxes, n, q, reach, [&](int c, float d2, bool valid) {
-          if (valid && __float_as_uint(d2) == T) {
-            const uint32_t j = (uint32_t)qord[c];
-            if ((j & jmask) == jpre) atomicAdd(&hist[(j >> shift) & 255u], 1u);
-          }
-        });
-        __syncthreads();
-        if (tid == 0) {
-          uint32_t cum = 0u, b = 0u;
-          for (; b < 255u && cum + hist[b] < jneed; ++b) cum += hist[b];
-          s_pick[0] = b;
-          s_pick[1] = jneed - cum;
-        }
-        __syncthreads();
-        jpre |= s_pick[0] << shift;
-        jmask |= 255u << shift;
-        jneed = s_pick[1];
-        __syncthreads();
-      }
-      // exactly w keys are at most (T, jpre): collect and sort them
-      const uint64_t last = ((uint64_t)T << 32) | jpre;
-      if (tid == 0) s_wave[0] = 0;
-      __syncthreads();
-      visit_runs<E>(pts, boxes, n, q, reach, [&](int c, float d2, bool valid) {
-        const uint64_t key = row_key(d2, valid ? qord[c] : -1);
-        if (valid && key <= last) {
-          const int at = atomicAdd(&s_wave[0], 1);
-          if (at < w) grouped[at] = key;
-        }
-      });
-      int P = 1;
-      while (P < w) P <<= 1;
-      for (int x = w + tid; x < P; x += kBlock) grouped[x] = ~0ull;
-      __syncthreads();
-      for (int size = 2; size <= P; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-          for (int x = tid; x < P / 2; x += kBlock) {
-            const int lo = 2 * x - (x & (stride - 1));
-            const int hi = lo + stride;
-            const bool up = (lo & size) == 0;
-            const uint64_t a = grouped[lo], b = grouped[hi];
-            if ((a > b) == up) {
-              grouped[lo] = b;
-              grouped[hi] = a;
-            }
-          }
-          __syncthreads();
-        }
-      for (int x = tid; x < w; x += kBlock) row[x] = grouped[x];
-      if (tid == 0) s_t = __uint_as_float(T);
-      __syncthreads();
     }
-    for (int x = w + tid; x < J.w; x += kBlock) row[x] = ~0ull;
-    t_next = s_t * exp2f(log2f(kRowTarget) / growth);
+    if (!done || crowded) {
+      // left to k_rows_repeats; the rows after it go there unseen, but for
+      // every eighth
+      if (tid == 0) {
+        const int at = atomicAdd(todo_n, 1);
+        todo[at] = {(int)blockIdx.y, p, done ? t : t_many, 0};
+      }
+      repeats = true;
+      t_next = -1.f;
+    } else {
+      for (int x = w + tid; x < J.w; x += kBlock) row[x] = ~0ull;
+      repeats = false;
+      t_next = s_t * exp2f(log2f(kRowTarget) / growth);
+    }
+  }
+}
+
+// The rows k_rows has left (todo_n of them), by distance or by selection.
+template <int E>
+__global__ __launch_bounds__(kBlock) void k_rows_repeats(
+    const RowJob* __restrict__ jobs, const RowTodo* __restrict__ todo,
+    const int* __restrict__ todo_n, const float* __restrict__ pts_pool,
+    const float* __restrict__ box_pool, const int32_t* __restrict__ qord_pool,
+    uint64_t* __restrict__ row_pool) {
+  extern __shared__ uint64_t row_lds[];
+  __shared__ int s_n[kWaves];
+  const int count = *todo_n;
+  for (int x = blockIdx.x; x < count; x += gridDim.x) {
+    const RowTodo D = todo[x];
+    const RowJob J = jobs[D.job];
+    const int n = J.n_e, w = min(J.w, n);
+    const int words = kWaves * row_segment(J.w) * 2;
+    const float* __restrict__ pts = pts_pool + J.pts_off;
+    const float* __restrict__ boxes = box_pool + J.box_off;
+    const int32_t* __restrict__ qord = qord_pool + J.qord_off;
+    uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)D.p * J.w;
+    float q[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) q[k] = pts[(int64_t)k * n + D.p];
+    const float reach =
+        D.reach < __builtin_inff() ? D.reach : order_reach<E>(pts, n, w, D.p, q, s_n);
+    if (!row_by_level<E>(pts, boxes, qord, n, w, q, reach, reinterpret_cast<uint32_t*>(row_lds),
+                         words, row)) {
+      __syncthreads();
+      row_by_select<E>(pts, boxes, qord, n, w, q, reach, row_lds,
+                       reinterpret_cast<uint32_t*>(row_lds + kWaves * row_segment(J.w)), row);
+    }
+    for (int y = w + (int)threadIdx.x; y < J.w; y += kBlock) row[y] = ~0ull;
+    __syncthreads();
   }
 }
 

@@ -28,6 +28,11 @@ def series(kind, n):
     rng = np.random.default_rng([n, len(kind)])
     if kind == "quantised":
         return synth.quantised_series(n, 6, rng), synth.quantised_series(n, 9, rng)
+    if kind == "coarse":
+        return np.floor(rng.random(n) * 12), np.floor(rng.random(n) * 5)
+    if kind == "bursts":
+        quiet = np.where(np.arange(n) % 97 < 90, 1e-7, 1.0)
+        return rng.standard_normal(n) * quiet, rng.standard_normal(n) * quiet
     if kind == "constant":
         return np.ones(n), synth.coupled_logistic(n)[1]
     if kind == "gauss":
@@ -50,6 +55,8 @@ CASES = [
     (4000, 1, 1, [1500, 4000], 10, 0, 0, "quantised"),  # w-th distance shared by many
     (4000, 2, 1, [1500, 4000], 10, 0, 0, "quantised"),
     (5000, 3, 1, [2500], 4, 0, 0, "constant"),          # every distance equal
+    (70000, 1, 1, [30000, 70000], 2, 0, 0, "coarse"),   # thousands at each distance
+    (3000, 3, 1, [900, 2998], 9, 0, 0, "bursts"),       # distances of very different sizes
     (2000, 3, 1, [800, 1998], 20, 0, 1, "logistic"),    # library-point queries
     (2000, 6, 1, [800, 1995], 20, 5, 1, "gauss"),
     (90000, 1, 1, [1060], 2, 0, 0, "logistic"),         # some rows run short
