@@ -153,7 +153,7 @@ const char *ccm_last_error(const ccm_ctx *ctx);
  * when it alone does not fit (at least one realization per wave).  The
  * results do not depend on the bound; other buffers of a call (series,
  * embeddings, visiting orders, per-tile moments, neighbour rows and the
- * walks' output: at most 2.5 GiB) are not counted.  bytes = 0
+ * walks' output: at most 3.5 GiB) are not counted.  bytes = 0
  * restores the default, min(8 GiB, device memory / 8) and at least 1 GiB.
  * The bound applies to calls made after it is set.
  */

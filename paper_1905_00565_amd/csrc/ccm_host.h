@@ -118,6 +118,7 @@ inline int64_t min_library(int32_t E, int32_t excl) {
 struct WalkChunk {
   int64_t item_first = 0, item_count = 0;   // into Plan::walk_items
   int64_t mom_first = 0, mom_count = 0;     // into Plan::mom_items
+  bool grouped = false;   // causal matrix: moment items are {4 * group + part, tile}
 };
 
 // Embeddings whose neighbour rows are held at once, and the chunks that walk

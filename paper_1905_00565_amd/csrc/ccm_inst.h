@@ -70,4 +70,10 @@ hipError_t launch_multi_keys_e(const Realization* rzs, const int32_t* self_of,
                                const double* tt, int m_series, void* partial, int query_set,
                                hipStream_t st);
 
+template <int E>
+hipError_t launch_multi_group_e(const Realization* rzs, const int32_t* self_of,
+                                const WalkGroup* groups, const WalkLib* libs, const Item* items,
+                                int n_items, const double* keys, const int32_t* qord,
+                                const double* tt, int m_series, void* partial, hipStream_t st);
+
 }  // namespace ccmk

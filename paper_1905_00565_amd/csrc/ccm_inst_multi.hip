@@ -61,6 +61,22 @@ hipError_t launch_multi_keys_e(const Realization* rzs, const int32_t* self_of,
   return hipGetLastError();
 }
 
+template <int E>
+hipError_t launch_multi_group_e(const Realization* rzs, const int32_t* self_of,
+                                const WalkGroup* groups, const WalkLib* libs, const Item* items,
+                                int n_items, const double* keys, const int32_t* qord,
+                                const double* tt, int m_series, void* partial, hipStream_t st) {
+  k_multi_group<E, DefaultQ<E>::Q><<<(unsigned)n_items, kBlock, 0, st>>>(
+      rzs, self_of, groups, libs, items, keys, qord, tt, m_series,
+      static_cast<Sums*>(partial));
+  return hipGetLastError();
+}
+
+template hipError_t launch_multi_group_e<CCM_INST_E>(const Realization*, const int32_t*,
+                                                     const WalkGroup*, const WalkLib*,
+                                                     const Item*, int, const double*,
+                                                     const int32_t*, const double*, int, void*,
+                                                     hipStream_t);
 template hipError_t launch_multi_keys_e<CCM_INST_E>(const Realization*, const int32_t*,
                                                     const WalkOut*, const Item*, int,
                                                     const double*, const int32_t*,

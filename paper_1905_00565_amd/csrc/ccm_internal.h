@@ -367,6 +367,13 @@ hipError_t launch_multi_keys(int E, const Realization* rzs, const int32_t* self_
                              const double* keys, const int32_t* pj, const int32_t* qord,
                              const double* tt, int m_series, void* partial, int query_set,
                              hipStream_t st);
+// The same of up to kMultiLibs libraries of a group together, every embedded
+// point a query: items {4 * group + part, tile}.
+hipError_t launch_multi_group(int E, const Realization* rzs, const int32_t* self_of,
+                              const WalkGroup* groups, const WalkLib* libs, const Item* items,
+                              int n_items, const double* keys, const int32_t* qord,
+                              const double* tt, int m_series, void* partial, hipStream_t st);
+constexpr int kMultiLibs = 16;              // libraries of one per-target item
 constexpr int kRowMaxW = 1024;              // longest neighbour row
 constexpr int kWalkLibs = 64;               // libraries per walk group
 

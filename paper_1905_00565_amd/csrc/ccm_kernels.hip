@@ -864,6 +864,18 @@ hipError_t launch_multi_keys(int E, const Realization* rzs, const int32_t* self_
 #undef CCM_CALL
 }
 
+hipError_t launch_multi_group(int E, const Realization* rzs, const int32_t* self_of,
+                              const WalkGroup* groups, const WalkLib* libs, const Item* items,
+                              int n_items, const double* keys, const int32_t* qord,
+                              const double* tt, int m_series, void* partial, hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+#define CCM_CALL(e)                                                                       \
+  launch_multi_group_e<e>(rzs, self_of, groups, libs, items, n_items, keys, qord, tt,     \
+                          m_series, partial, st)
+  CCM_BY_E(E, CCM_CALL)
+#undef CCM_CALL
+}
+
 hipError_t launch_zero_int(int* p, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   k_zero_int<<<(n + 255) / 256, 256, 0, st>>>(p, n);

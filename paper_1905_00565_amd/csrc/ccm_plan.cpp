@@ -267,10 +267,14 @@ static void split_waves(Plan& p) {
 
 // Device bytes of neighbour rows held at once (a batch holds at least one
 // embedding's; a single embedding past the cap scans instead), and of walk
-// output held at once.  Larger pools measured no faster.
+// output held at once: predictions (256 MiB was 1% slower, 1 GiB the same), or
+// a causal matrix's neighbour keys (its per-target stage has few, long items:
+// 512 MiB 21.9 against 18.4 ms for 64 series, N = 20000, r = 10).
 constexpr int64_t kRowPoolBytes = 1ll << 30;
 constexpr int64_t kRowPoolCap = 2ll << 30;
-constexpr int64_t kWalkOutBytes = 256ll << 20;
+constexpr int64_t kWalkOutBytes = 512ll << 20;
+constexpr int64_t kWalkKeyBytes = 1ll << 30;
+constexpr int64_t kMultiMinItems = 1024;
 
 // Row entries that hold, all but about once in 10^7, the first E+1 acceptable
 // members of a library of le of ne points: a member turns up every ne / le
@@ -375,6 +379,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
   const size_t group0 = p.walk_groups.size();
   std::vector<size_t> emb_group;      // first group of each row job
   const int32_t job0 = (int32_t)p.row_jobs.size();
+  if (p.walk_groups.size() > (size_t)INT32_MAX / 8) return;   // (item numbers)
   for (Pick& pk : picks) {
     const Realization& R0 = p.rz[pk.groups[0][0]];
     RowJob rj{};
@@ -474,12 +479,20 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
         // whole cache lines per group
         const int64_t need =
             ((int64_t)wg.n_lib * p.row_jobs[wg.emb].n_e * per_query + 15) / 16 * 16;
-        if (h > g && (out + need) * 8 > kWalkOutBytes) break;
+        if (h > g && (out + need) * 8 > (keys ? kWalkKeyBytes : kWalkOutBytes)) break;
         wg.out_off = out;
         for (int l = 0; l < wg.n_lib; ++l)
           p.walk_out[p.walk_libs[wg.lib_first + l].rz] = {out + l, wg.n_lib, 0};
         out += need;
       }
+      // causal matrix over every point: kMultiLibs libraries to an item when
+      // that leaves enough items (3 series, N = 5809: 54 items took 1.9 ms, one
+      // per library 1.3 ms)
+      int64_t parts = 0;
+      for (size_t x = g; x < h; ++x)
+        parts += (int64_t)((p.walk_groups[x].n_lib + kMultiLibs - 1) / kMultiLibs) *
+                 p.rz[p.walk_libs[p.walk_groups[x].lib_first].rz].n_tiles;
+      ch.grouped = keys && p.spec.query_set == 0 && parts >= kMultiMinItems;
       for (size_t a = g; a < h;) {
         size_t b = a;
         while (b < h && p.walk_groups[b].emb == p.walk_groups[a].emb) ++b;
@@ -494,6 +507,12 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
           int32_t tiles = 0;
           for (int l = 0; l < wg.n_lib; ++l)
             tiles = std::max(tiles, p.rz[p.walk_libs[wg.lib_first + l].rz].n_tiles);
+          if (ch.grouped) {
+            for (int32_t t = 0; t < tiles; ++t)
+              for (int l = 0; l < wg.n_lib; l += kMultiLibs)
+                p.mom_items.push_back({(int32_t)(4 * x) + l / kMultiLibs, t});
+            continue;
+          }
           for (int32_t t = 0; t < tiles; ++t)
             for (int l = 0; l < wg.n_lib; ++l) {
               const int32_t r = p.walk_libs[wg.lib_first + l].rz;

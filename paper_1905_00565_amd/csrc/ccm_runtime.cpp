@@ -218,7 +218,11 @@ void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStrea
                          b.walk_items + ch.item_first, (int)ch.item_count, L.walk_per, b.masks,
                          b.rows, b.qord, b.emb, b.s64, b.walk_out, excl,
                          p.spec.query_set, st));
-      if (p.spec.M > 0)
+      if (ch.grouped)
+        HIPCHK(launch_multi_group(L.E, b.rz, b.self, b.walk_groups, b.walk_libs,
+                                  b.mom_items + ch.mom_first, (int)ch.mom_count, b.walk_out,
+                                  b.qord, b.tt, p.spec.M, b.partial, st));
+      else if (p.spec.M > 0)
         HIPCHK(launch_multi_keys(L.E, b.rz, b.self, b.walk_where, b.mom_items + ch.mom_first,
                                  (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.tt, p.spec.M,
                                  b.partial, p.spec.query_set, st));

@@ -901,8 +901,221 @@ __global__ __launch_bounds__(kBlock) void k_walk_moments(
   if (tid == 0) partial[R.slot_base + I.tile] = red[0];
 }
 
-// Causal matrix: one query tile of a walked realization, its neighbours read
-// from the walk's keys instead of searched; then the
+// Causal matrix: one query tile of up to 16 libraries of a walk group, whose
+// neighbours the walk has left as keys.  Wavefront v takes the libraries
+// 4 v .. 4 v + 3 of the sixteen, two at a time: lanes 0..31 one of them, lanes
+// 32..63 the other, each lane two neighbouring targets, and goes through the
+// tile's queries in order.
+//
+// Bound by the vector memory path: a load of one 8-byte value per lane takes
+// 16 of its cycles like one of 16 bytes, so two targets per lane halve them
+// (64 series, N = 20000, E = 4, r = 10: 27.8 ms with one target per lane and
+// one library at a time, 18.4 now).  The neighbours of one query in different
+// libraries are mostly the same few points, so two thirds of the loads hit in
+// L1 (a workgroup per library read 360 GB from L2; 23 ms); a fourth wavefront
+// per SIMD, with the earlier runs' sums in memory, gained nothing for the L1
+// it took.  The observed side of the sums is formed once for the four
+// libraries.
+//
+// Sums as in multi_target_block, in its order: over the run of 64 Q queries
+// of each of its four wavefronts, then the four runs' sums in order.
+template <int E>
+struct GroupLds {
+  static constexpr int K = E + 1;
+  static constexpr int kLibs = kMultiLibs / kWaves;  // libraries of one wavefront
+  static constexpr int kSet = 128 / kLibs;           // queries staged together
+  double w[kLibs][K][kSet];
+  uint32_t row[kLibs][K][kSet];                      // byte offsets of the neighbours' rows
+  uint32_t qrow[kSet];
+};
+
+template <int E, int Q>
+__global__ __launch_bounds__(kBlock) void k_multi_group(
+    const Realization* __restrict__ rzs, const int32_t* __restrict__ self_of,
+    const WalkGroup* __restrict__ groups, const WalkLib* __restrict__ libs,
+    const Item* __restrict__ items, const double* __restrict__ keys,
+    const int32_t* __restrict__ qord_pool, const double* __restrict__ tt, int m_series,
+    Sums* __restrict__ partial) {
+  constexpr int K = E + 1;
+  constexpr int kLibs = GroupLds<E>::kLibs;
+  constexpr int kSet = GroupLds<E>::kSet;
+  __shared__ GroupLds<E> s_lds[kWaves];
+  const Item I = items[xcd_item(blockIdx.x, gridDim.x)];
+  const WalkGroup G = groups[I.rz >> 2];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l0 = (I.rz & 3) * kMultiLibs + wave * kLibs;   // first library of the wavefront
+  if (l0 >= G.n_lib) return;                       // no barrier below
+  const int nl = min(kLibs, G.n_lib - l0);
+  const Realization R = rzs[libs[G.lib_first + l0].rz];   // shape shared by the group
+  const int self = self_of[libs[G.lib_first + l0].rz];
+  GroupLds<E>& lds = s_lds[wave];
+  const int mp = target_stride(m_series);
+  const double* __restrict__ T = tt + (int64_t)(E - 1) * R.tau * mp;
+  const char* __restrict__ Tc = reinterpret_cast<const char*>(T);
+  const int32_t* __restrict__ qord = qord_pool + R.qord_off;
+  const double* __restrict__ kp = keys + G.out_off + l0;
+  const int half = lane >> 5;                      // library of the pair
+  constexpr int kPairs = kLibs / 2;
+  constexpr int kT = 2;                            // targets per lane
+
+  for (int b0 = 0; b0 < m_series; b0 += 64) {
+    const int b = b0 + kT * (lane & 31);                   // (mp is even: both columns exist)
+    const uint32_t lb = b < m_series ? (uint32_t)b * 8u : 0u;
+    const auto at = [&](uint32_t row_bytes) {
+      return *reinterpret_cast<const double2*>(Tc + (row_bytes + lb));
+    };
+    const double2 sh = at(0u);
+    const double shift[kT] = {sh.x, sh.y};
+    // the sums of the runs before this one: n and the observed side, then
+    // each library's predicted side
+    double n_all = 0.0, so_all[kT], soo_all[kT];
+    double sp_all[kPairs][kT], spp_all[kPairs][kT], sop_all[kPairs][kT];
+    double mno[kT], mxo[kT], mnp[kPairs][kT], mxp[kPairs][kT];
+#pragma unroll
+    for (int x = 0; x < kT; ++x) {
+      mno[x] = __builtin_inf();
+      mxo[x] = -__builtin_inf();
+#pragma unroll
+      for (int h = 0; h < kPairs; ++h) {
+        mnp[h][x] = __builtin_inf();
+        mxp[h][x] = -__builtin_inf();
+      }
+    }
+    for (int run = 0; run < kWaves; ++run) {
+      double n_run = 0.0, so[kT] = {0.0, 0.0}, soo[kT] = {0.0, 0.0};
+      double sp[kPairs][kT], spp[kPairs][kT], sop[kPairs][kT];
+#pragma unroll
+      for (int h = 0; h < kPairs; ++h)
+#pragma unroll
+        for (int x = 0; x < kT; ++x) sp[h][x] = spp[h][x] = sop[h][x] = 0.0;
+      const int q_run = I.tile * (kBlock * Q) + run * (64 * Q);
+      for (int s0 = 0; s0 < 64 * Q; s0 += kSet) {
+        const int nq = min(kSet, R.n_query - (q_run + s0));
+        if (nq <= 0) break;
+        // stage, lane by (library, query); past the last library, the last one
+        // again
+        const int sub = lane & (kSet - 1);
+        const int p = q_run + s0 + min(sub, nq - 1);
+        wave_sync();
+        if (lane < kSet) lds.qrow[sub] = (uint32_t)(qord[p] * mp) * 8u;
+#pragma unroll
+        for (int h = 0; h < kLibs * kSet / 64; ++h) {
+          const int u = h * (64 / kSet) + lane / kSet;
+          // the operations of stage_weights
+          double v[K], su = 0.0;
+          int32_t j[K];
+#pragma unroll
+          for (int t = 0; t < K; ++t) {
+            const double key = kp[((int64_t)p * K + t) * G.n_lib + min(u, nl - 1)];
+            v[t] = sqrt((double)key_d2(key));
+            j[t] = key_j(key);
+          }
+          const double d0 = v[0];
+          if (d0 > 0.0) {
+            const double r = 1.0 / d0;
+#pragma unroll
+            for (int t = 0; t < K; ++t) {
+              v[t] = exp(-quotient(v[t], d0, r));
+              su += v[t];
+            }
+          } else {
+#pragma unroll
+            for (int t = 0; t < K; ++t) {
+              v[t] = v[t] == 0.0 ? 1.0 : 0.0;
+              su += v[t];
+            }
+          }
+          const double rs = 1.0 / su;
+#pragma unroll
+          for (int t = 0; t < K; ++t) {
+            lds.w[u][t][sub] = quotient(v[t], su, rs);
+            lds.row[u][t][sub] = (uint32_t)(j[t] * mp) * 8u;
+          }
+        }
+        wave_sync();
+        n_run += (double)nq;
+        for (int q = 0; q < nq; ++q) {
+          const double2 ov = at(lds.qrow[q]);
+          const double o[kT] = {ov.x, ov.y};
+          double a[kT];
+#pragma unroll
+          for (int x = 0; x < kT; ++x) {
+            a[x] = o[x] - shift[x];
+            so[x] += a[x];
+            soo[x] = fma(a[x], a[x], soo[x]);
+            mno[x] = kmin(mno[x], o[x]);
+            mxo[x] = kmax(mxo[x], o[x]);
+          }
+#pragma unroll
+          for (int h = 0; h < kPairs; ++h) {
+            if (2 * h >= nl) break;
+            const int u = 2 * h + half;
+            double2 v[K];
+#pragma unroll
+            for (int t = 0; t < K; ++t) v[t] = at(lds.row[u][t][q]);
+            double wt = lds.w[u][0][q];
+            double pred[kT] = {wt * v[0].x, wt * v[0].y};
+#pragma unroll
+            for (int t = 1; t < K; ++t) {
+              wt = lds.w[u][t][q];
+              pred[0] = fma(wt, v[t].x, pred[0]);
+              pred[1] = fma(wt, v[t].y, pred[1]);
+            }
+#pragma unroll
+            for (int x = 0; x < kT; ++x) {
+              const double d = pred[x] - shift[x];
+              sp[h][x] += d;
+              spp[h][x] = fma(d, d, spp[h][x]);
+              sop[h][x] = fma(a[x], d, sop[h][x]);
+              mnp[h][x] = kmin(mnp[h][x], pred[x]);
+              mxp[h][x] = kmax(mxp[h][x], pred[x]);
+            }
+          }
+        }
+      }
+      // the first run's sums are taken as they are, the others' added
+      n_all = run == 0 ? n_run : n_all + n_run;
+#pragma unroll
+      for (int x = 0; x < kT; ++x) {
+        so_all[x] = run == 0 ? so[x] : so_all[x] + so[x];
+        soo_all[x] = run == 0 ? soo[x] : soo_all[x] + soo[x];
+#pragma unroll
+        for (int h = 0; h < kPairs; ++h) {
+          sp_all[h][x] = run == 0 ? sp[h][x] : sp_all[h][x] + sp[h][x];
+          spp_all[h][x] = run == 0 ? spp[h][x] : spp_all[h][x] + spp[h][x];
+          sop_all[h][x] = run == 0 ? sop[h][x] : sop_all[h][x] + sop[h][x];
+        }
+      }
+    }
+#pragma unroll
+    for (int h = 0; h < kPairs; ++h) {
+      const int u = 2 * h + half;
+      if (u >= nl) continue;
+      const int64_t slot = rzs[libs[G.lib_first + l0 + u].rz].slot_base;
+#pragma unroll
+      for (int x = 0; x < kT; ++x) {
+        if (b + x >= m_series || b + x == self) continue;
+        Sums s;
+        s.v[0] = n_all;
+        s.v[1] = so_all[x];
+        s.v[2] = sp_all[h][x];
+        s.v[3] = soo_all[x];
+        s.v[4] = spp_all[h][x];
+        s.v[5] = sop_all[h][x];
+        s.v[6] = mno[x];
+        s.v[7] = mxo[x];
+        s.v[8] = mnp[h][x];
+        s.v[9] = mxp[h][x];
+        partial[(slot + I.tile) * m_series + b + x] = s;
+      }
+    }
+  }
+}
+
+// Causal matrix, few items or library-point queries (each library has its
+// own): one query tile of a walked realization, its neighbours read from the
+// walk's keys instead of searched; then the
 // per-target stage of crossmap_multi_item.
 template <int E, int Q>
 __global__ __launch_bounds__(kBlock) void k_multi_keys(
