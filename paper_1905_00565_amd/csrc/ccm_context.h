@@ -23,14 +23,10 @@ struct PlanBuffers {
   Item* items = nullptr;
   Item* plain_items = nullptr;       // CCM_FLAG_PLAIN: each realization's items
   OrderJob* orders = nullptr;
-  int32_t* segoff = nullptr;
   double* s64 = nullptr;
   float* s32 = nullptr;
-  int32_t* iota = nullptr;
-  uint32_t* keys = nullptr;
-  uint32_t* keys_out = nullptr;
-  int32_t* order = nullptr;
-  void* sort_temp = nullptr;
+  void* order_mem = nullptr;
+  int32_t* order = nullptr;          // inside order_mem
   int32_t* qord = nullptr;
   int32_t* start = nullptr;
   float* emb = nullptr;
@@ -69,7 +65,7 @@ struct Exec {
   Plan plan;
   DevBuf d_ingest, d_embed, d_sample, d_gather, d_rz, d_items, d_plain_items;
   DevBuf d_s64, d_s32, d_emb, d_lib, d_pts, d_pj, d_partial, d_out, d_counter;
-  DevBuf d_iota, d_keys, d_keys_out, d_order, d_segoff, d_sort_temp, d_qord, d_start, d_self;
+  DevBuf d_order, d_qord, d_start, d_self;
   DevBuf d_orders;
   DevBuf d_tt;       // causal matrix: targets time-major [N][target_stride(M)]
   DevBuf d_tables, d_table;   // distance indexing table jobs and rows

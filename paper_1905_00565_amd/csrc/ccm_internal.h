@@ -45,7 +45,7 @@ struct IngestJob {
 // points close in all E coordinates are close in the order.
 struct OrderJob {
   int64_t src_off;   // floats into the FP32 series pool
-  int64_t key_off;   // uint32 keys (and the sorted order) of this set
+  int64_t key_off;   // entries of this set in the order pool
   int64_t n;         // series length
   int32_t dims;
   int32_t lag[4];
@@ -68,6 +68,8 @@ struct EmbedJob {
   int64_t n_series;
   int32_t E;
   int32_t tau;
+  int32_t whole;     // 1: the set's first n_e entries are the embedded points
+  int32_t pad;
 };
 
 // One library draw (selection sampling keyed by (seed, E, tau, L_eff, r)).
@@ -246,11 +248,7 @@ hipError_t launch_ingest(const IngestJob* jobs, int n_jobs, int64_t max_n,
                          const double* src, float* dst, hipStream_t st);
 hipError_t launch_embed(const EmbedJob* jobs, int n_jobs, int64_t max_n,
                         const float* s32, float* emb, hipStream_t st);
-hipError_t launch_iota_segments(int32_t* out, int64_t n_series, int32_t segs,
-                                hipStream_t st);
-hipError_t launch_order_keys(const OrderJob* jobs, int n_jobs, const float* s32,
-                             uint32_t* keys, hipStream_t st);
-hipError_t launch_query_order(const EmbedJob* jobs, int n_jobs,
+hipError_t launch_query_order(const EmbedJob* jobs, int n_jobs, int64_t n_series,
                               const int32_t* order, int32_t* qord, hipStream_t st);
 hipError_t launch_sample(const SampleJob* jobs, int64_t n_jobs, int32_t* out, uint64_t* bits,
                          hipStream_t st);
@@ -319,21 +317,17 @@ hipError_t launch_finalize_multi(const Realization* rzs, const int32_t* self_of,
                                  int64_t out_stride_b, double* out, hipStream_t st);
 size_t multi_sums_bytes();
 
-// Order sets (ccm_sort.hip): per segment of n_series keys, the time indices
-// sorted by key (stable).  temp_bytes is queried with temp == nullptr.
-hipError_t sort_series(void* temp, size_t& temp_bytes, const uint32_t* keys_in,
-                       uint32_t* keys_out, const int32_t* idx_in, int32_t* idx_out,
-                       int64_t n_series, int32_t segs, const int32_t* seg_offsets,
-                       hipStream_t st);
-
-// k-d refinement of the order sets with kd_E > 0 (see OrderJob), on the
-// order pool of n_sets segments of n_series entries: `order` holds the
-// sorted sets on entry and the refined ones on return; alt and keys (the
-// size of the pool) are scratch.  Only kernels of this library run (no
-// library sort: the sequence is captured in graphs and replayed).
-hipError_t refine_orders_kd(const OrderJob* orders, int32_t n_sets, int levels,
-                            int64_t n_series, const float* emb, int32_t* order, int32_t* alt,
-                            uint32_t* keys, hipStream_t st);
+// The order sets: per set of n_series points the time indices sorted by the
+// set's key (stable), then `levels` levels of k-d refinement of the sets with
+// kd_E > 0 (see OrderJob).  mem: 16 bytes per entry of n_sets * n_series; the
+// orders are at order_of(mem, n_sets * n_series).  Only kernels of this
+// library run (the sequence is captured in graphs and replayed).
+constexpr int kOrderBytes = 16;
+inline int32_t* order_of(void* mem, int64_t entries) {
+  return reinterpret_cast<int32_t*>(static_cast<char*>(mem) + 8 * entries);
+}
+hipError_t build_orders(const OrderJob* orders, int32_t n_sets, int levels, int64_t n_series,
+                        const float* s32, const float* emb, void* mem, hipStream_t st);
 
 // Neighbour-row path.  Rows of jobs [0, n_jobs) (max_ne, max_w: the largest
 // of them), the points' visiting-order copies and boxes first; per_block

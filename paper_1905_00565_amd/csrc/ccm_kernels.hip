@@ -10,9 +10,10 @@
 // Kernels, in pipeline order:
 //   k_ingest       double series -> float series (round to nearest even)
 //   k_embed        lagged-coordinate embedding, AoS float[n_e][E]
-//   k_order_keys   visiting-order keys of each order set (value, or Hilbert
-//                  position over a few lag coordinates)
-//   (sort_series)  each order set's embedded indices sorted by key
+//   k_sort_chunks  visiting-order keys of each order set (value, or Hilbert
+//                  position over a few lag coordinates), sorted in chunks
+//   k_merge_runs   the chunks merged
+//   k_kd_level     one level of the k-d refinement of the orders
 //   k_query_order  each embedding's points in its set's visiting order
 //   k_sample       library subsamples: selection sampling driven by SplitMix64
 //   k_gather       each library laid out in visiting order, plus the
@@ -76,13 +77,6 @@ __global__ void k_embed(const EmbedJob* __restrict__ jobs,
   }
 }
 
-// Time indices 0..n-1 for every series segment (input of the value sort).
-__global__ void k_iota_segments(int32_t* __restrict__ out, int64_t n, int64_t total) {
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < total;
-       x += (int64_t)gridDim.x * blockDim.x)
-    out[x] = (int32_t)(x % n);
-}
-
 // Position of (x, y) on the Hilbert curve filling [0, 2^16)^2 (the classic
 // quadrant-by-quadrant construction: at each scale the quadrant contributes
 // s*s*((3*rx) ^ ry) and the remaining coordinates are reflected/swapped into
@@ -110,6 +104,10 @@ __device__ __forceinline__ uint32_t hilbert16(uint32_t x, uint32_t y) {
 __device__ __forceinline__ uint32_t ordered_bits(float v) {
   const uint32_t b = __float_as_uint(v);
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+
+__device__ __forceinline__ float from_ordered_bits(uint32_t u) {
+  return __uint_as_float((u & 0x80000000u) ? u ^ 0x80000000u : ~u);
 }
 
 // Index on the n-dimensional Hilbert curve of b bits per axis (n <= 4,
@@ -142,73 +140,197 @@ __device__ __forceinline__ uint32_t hilbert_nd(uint32_t (&x)[4], int n, int b) {
   return h;
 }
 
-// Keys of one order set (see OrderJob).  One workgroup per set: the series'
-// range first (for the scaling), then one key per time point.
-__global__ __launch_bounds__(256) void k_order_keys(const OrderJob* __restrict__ jobs,
-                                                    const float* __restrict__ s32,
-                                                    uint32_t* __restrict__ keys) {
-  __shared__ float s_lo[256], s_hi[256];
-  const OrderJob J = jobs[blockIdx.x];
-  const float* __restrict__ s = s32 + J.src_off;
-  uint32_t* __restrict__ k = keys + J.key_off;
-  const int tid = threadIdx.x;
-  const int dims = J.dims;
-  int64_t lag_max = 0;
-  for (int d = 0; d < dims; ++d) lag_max = max(lag_max, (int64_t)J.lag[d]);
-  if (dims == 1) {
-    for (int64_t t = tid; t < J.n; t += 256)
-      k[t] = t + lag_max < J.n ? ordered_bits(s[t + J.lag[0]]) : 0xffffffffu;
-    return;
+// Sum of v over the threads below this one of a workgroup of BLOCK, and the
+// sum over all of them.  One barrier: calls in a row take turns at two sets
+// of s_sum (turn 0 and 1).
+template <int BLOCK>
+__device__ __forceinline__ int block_scan(int v, int (*s_sum)[BLOCK / 64], int turn, int& total) {
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  int inc = v;
+#pragma unroll
+  for (int s = 1; s < 64; s <<= 1) {
+    const int y = __shfl_up(inc, s, 64);
+    if (lane >= s) inc += y;
   }
-  float lo = __builtin_inff(), hi = -__builtin_inff();
-  for (int64_t t = tid; t < J.n; t += 256) {
-    lo = fminf(lo, s[t]);
-    hi = fmaxf(hi, s[t]);
-  }
-  s_lo[tid] = lo;
-  s_hi[tid] = hi;
+  if (lane == 63) s_sum[turn][wave] = inc;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) {
-      s_lo[tid] = fminf(s_lo[tid], s_lo[tid + w]);
-      s_hi[tid] = fmaxf(s_hi[tid], s_hi[tid + w]);
-    }
-    __syncthreads();
+  int before = inc - v;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < BLOCK / 64; ++w) {
+    if (w < wave) before += s_sum[turn][w];
+    total += s_sum[turn][w];
   }
-  lo = s_lo[0];
-  const int bits = dims == 2 ? 16 : 32 / dims;
-  const float top = (float)((1u << bits) - 1u);
-  const float span = s_hi[0] - lo;
-  const float scale = span > 0.f ? top / span : 0.f;
-  for (int64_t i = tid; i < J.n; i += 256) {
-    if (i + lag_max >= J.n) {
-      k[i] = 0xffffffffu;
-      continue;
-    }
-    uint32_t x[4] = {0u, 0u, 0u, 0u};
-    for (int d = 0; d < dims; ++d)
-      x[d] = (uint32_t)fminf(top, fmaxf(0.f, (s[i + J.lag[d]] - lo) * scale));
-    k[i] = dims == 2 ? hilbert16(x[0], x[1]) : hilbert_nd(x, dims, bits);
+  return before;
+}
+
+// Smallest and largest value of the series by a workgroup (every thread gets
+// both; s_lo, s_hi: one entry per wavefront).
+__device__ __forceinline__ void series_range(const float* __restrict__ s, int64_t n, float* s_lo,
+                                             float* s_hi, float& a, float& b) {
+  a = __builtin_inff();
+  b = -__builtin_inff();
+#pragma unroll 4
+  for (int64_t t = threadIdx.x; t < n; t += blockDim.x) {
+    a = fminf(a, s[t]);
+    b = fmaxf(b, s[t]);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    a = fminf(a, __shfl_xor(a, o, 64));
+    b = fmaxf(b, __shfl_xor(b, o, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_lo[threadIdx.x >> 6] = a;
+    s_hi[threadIdx.x >> 6] = b;
+  }
+  __syncthreads();
+  for (int w = 0; w < (int)blockDim.x / 64; ++w) {
+    a = fminf(a, s_lo[w]);
+    b = fmaxf(b, s_hi[w]);
   }
 }
 
-// Smallest and largest value over the 256 threads of a workgroup (every
-// thread gets both).
-__device__ __forceinline__ void block_minmax(float& lo, float& hi, float* s_lo, float* s_hi) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    lo = fminf(lo, __shfl_xor(lo, o, 64));
-    hi = fmaxf(hi, __shfl_xor(hi, o, 64));
+// The ranges of the sets' series, once for sets of several chunks (one
+// workgroup per set).
+__global__ __launch_bounds__(1024) void k_series_range(const OrderJob* __restrict__ jobs,
+                                                       const float* __restrict__ s32,
+                                                       float2* __restrict__ range) {
+  __shared__ float s_lo[16], s_hi[16];
+  const OrderJob J = jobs[blockIdx.x];
+  if (J.dims == 1) return;                         // not used
+  float a, b;
+  series_range(s32 + J.src_off, J.n, s_lo, s_hi, a, b);
+  if (threadIdx.x == 0) range[blockIdx.x] = make_float2(a, b);
+}
+
+// Keys of the order sets (see OrderJob), sorted in chunks of `chunk` positions
+// (a power of two from 64 to kSortChunk): a workgroup forms its chunk's keys in LDS and ranks 64 of them
+// against all (by key, then time index: the ranks are all different, the sort
+// stable), each wavefront over its share of the chunk.  The (key, time index)
+// go to out64 by rank (merged by k_merge_runs), or with one chunk per set the
+// indices to out32.  range: the sets' ranges (k_series_range), or null: taken
+// here.  Grid ((n / 64) rounded up, sets).
+//
+// Latency-bound at every size: the 4096^2 comparisons (two instructions each)
+// take 1 us over a chip's worth of wavefronts, while a bitonic network in one
+// workgroup's LDS has 78 dependent steps (two chunks per set: 42 us, here 18)
+// and a radix sort with one workgroup per set took 132 us there, and 2.0 ms
+// for two sets of 10^5 (here 0.09 with the merges).
+constexpr int kSortChunk = 4096;
+
+__global__ __launch_bounds__(1024) void k_sort_chunks(const OrderJob* __restrict__ jobs,
+                                                      const float* __restrict__ s32,
+                                                      const float2* __restrict__ range,
+                                                      int chunk, uint64_t* __restrict__ out64,
+                                                      int32_t* __restrict__ out32) {
+  __shared__ __align__(16) uint32_t key[kSortChunk];
+  __shared__ float s_lo[16], s_hi[16];
+  __shared__ int s_less[16][64];
+  const OrderJob J = jobs[blockIdx.y];
+  const float* __restrict__ s = s32 + J.src_off;
+  const int tid = threadIdx.x;
+  const int nt = blockDim.x;
+  const int dims = J.dims;
+  const int64_t first = (int64_t)blockIdx.x * 64;
+  if (first >= J.n) return;                        // the whole workgroup
+  const int64_t c0 = first & ~(int64_t)(chunk - 1);
+  const int own = (int)(first - c0);
+  const int m = (int)min((int64_t)chunk, J.n - c0);
+  const int nw = nt / 64;
+  const int share = (m + 4 * nw - 1) / (4 * nw) * 4;   // keys per wavefront
+  int64_t lag_max = 0;
+  for (int d = 0; d < dims; ++d) lag_max = max(lag_max, (int64_t)J.lag[d]);
+  float lo = 0.f, scale = 0.f, top = 0.f;
+  int bits = 32;
+  if (dims > 1) {
+    float hi;
+    if (range) {
+      lo = range[blockIdx.y].x;
+      hi = range[blockIdx.y].y;
+    } else {
+      series_range(s, J.n, s_lo, s_hi, lo, hi);
+    }
+    bits = dims == 2 ? 16 : 32 / dims;
+    top = (float)((1u << bits) - 1u);
+    const float span = hi - lo;
+    scale = span > 0.f ? top / span : 0.f;
   }
-  const int wave = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-    s_lo[wave] = lo;
-    s_hi[wave] = hi;
+  for (int x = tid; x < share * nw && x < kSortChunk; x += nt) {
+    const int64_t i = c0 + x;
+    uint32_t u = 0xffffffffu;                      // past the end: counts nowhere
+    if (x < m && i + lag_max < J.n) {
+      if (dims == 1) {
+        u = ordered_bits(s[i + J.lag[0]]);
+      } else {
+        uint32_t g[4] = {0u, 0u, 0u, 0u};
+        for (int d = 0; d < dims; ++d)
+          g[d] = (uint32_t)fminf(top, fmaxf(0.f, (s[i + J.lag[d]] - lo) * scale));
+        u = dims == 2 ? hilbert16(g[0], g[1]) : hilbert_nd(g, dims, bits);
+      }
+    }
+    key[x] = u;
   }
   __syncthreads();
-  lo = fminf(fminf(s_lo[0], s_lo[1]), fminf(s_lo[2], s_lo[3]));
-  hi = fmaxf(fmaxf(s_hi[0], s_hi[1]), fmaxf(s_hi[2], s_hi[3]));
+  const int lane = tid & 63;
+  const int wave = tid >> 6;
+  const bool mine = own + lane < m;
+  const uint32_t u = mine ? key[own + lane] : 0u;
+  int less = 0;
+  const int a = min(wave * share, kSortChunk), b = min(a + share, kSortChunk);
+  // before the 64 keys equal ones count, after them not
+  const uint4* __restrict__ k4 = reinterpret_cast<const uint4*>(key);
+#pragma unroll 4
+  for (int q = a / 4; q < min(b, own) / 4; ++q) {
+    const uint4 v = k4[q];
+    less += (v.x <= u ? 1 : 0) + (v.y <= u ? 1 : 0) + (v.z <= u ? 1 : 0) + (v.w <= u ? 1 : 0);
+  }
+  for (int x = max(a, own); x < min(b, own + 64); ++x)
+    less += key[x] < u || (key[x] == u && x < own + lane) ? 1 : 0;
+#pragma unroll 4
+  for (int q = max(a, own + 64) / 4; q < b / 4; ++q) {
+    const uint4 v = k4[q];
+    less += (v.x < u ? 1 : 0) + (v.y < u ? 1 : 0) + (v.z < u ? 1 : 0) + (v.w < u ? 1 : 0);
+  }
+  s_less[wave][lane] = less;
+  __syncthreads();
+  if (wave == 0 && mine) {
+    int r = 0;
+    for (int w = 0; w < nw; ++w) r += s_less[w][lane];
+    const int64_t i = first + lane;
+    if (out64)
+      out64[J.key_off + c0 + r] = ((uint64_t)u << 32) | (uint32_t)i;
+    else
+      out32[J.key_off + c0 + r] = (int32_t)i;
+  }
+}
+
+// One merge of sorted runs of `run` keys into runs twice as long, every set
+// (n keys each) at once: a key's place is its place in its own run plus the
+// number of smaller keys in the other one (found by bisection; the keys are
+// all different).  The last merge writes the indices only (out32).
+__global__ __launch_bounds__(256) void k_merge_runs(const uint64_t* __restrict__ src, int64_t run,
+                                                    int64_t n, uint64_t* __restrict__ out64,
+                                                    int32_t* __restrict__ out32) {
+  const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (x >= n) return;
+  const uint64_t* __restrict__ k = src + (int64_t)blockIdx.y * n;
+  const uint64_t key = k[x];
+  const int64_t r = x / run;
+  const int64_t o = (r ^ 1) * run;                 // the other run
+  int64_t lo = min(o, n), hi = min(o + run, n);
+  const int64_t first = lo;
+  while (lo < hi) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (k[mid] < key) lo = mid + 1;
+    else hi = mid;
+  }
+  const int64_t at = (int64_t)blockIdx.y * n + (r & ~1ll) * run + (x - r * run) + (lo - first);
+  if (out64)
+    out64[at] = key;
+  else
+    out32[at] = (int32_t)(uint32_t)key;
 }
 
 // One level of the k-d refinement (see OrderJob): workgroup (x, y) splits
@@ -218,36 +340,56 @@ __device__ __forceinline__ void block_minmax(float& lo, float& hi, float* s_lo, 
 // mid - lo smallest (coordinate, position) entries go to [lo, mid), the rest
 // to [mid, hi), each side in its input order, where mid = (2x+1) n_e /
 // 2^(level+1) is the next level's boundary between the node's halves.  The
-// h-th smallest coordinate T is found by a radix select on its ordered bits
-// (four 8-bit passes, histograms in LDS); the entries below T and the first
-// ones equal to T make up the lower half (the node's keys are formed once
-// into `keys`, scratch of the pool's size).  Sets set0 + blockIdx.y.  Input
-// `order`, output `out` (the
-// caller has copied every entry to out first, so nodes that do not split
-// keep their entries).
-__global__ __launch_bounds__(kBlock) void k_kd_split(const OrderJob* __restrict__ orders,
-                                                     int set0, int level,
-                                                     const float* __restrict__ emb,
-                                                     const int32_t* __restrict__ order,
-                                                     uint32_t* __restrict__ keys,
-                                                     int32_t* __restrict__ out) {
-  __shared__ float s_lo[kBlock / 64][kMaxE], s_hi[kBlock / 64][kMaxE];
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t s_pick[2];
-  __shared__ int s_wave[2][kBlock / 64];
+// h-th smallest coordinate T is found by counting the entries in equal bins
+// of the range and ranking those of the bin that holds it, or, with many in
+// that bin, by a radix select on the ordered bits (11, 11 and 10 bits); the
+// entries below T and the first ones equal to T make up the lower half (the
+// node's keys are formed once into `keys`, scratch of the pool's size).  Sets set0 + blockIdx.y.  Input
+// `order`, output `out`; nodes that do not split and entries outside the
+// nodes are copied.
+//
+// Latency-bound (a node is one workgroup): every step is parallel over the
+// workgroup, and the top levels' nodes get 1024 threads.  With four 8-bit
+// passes, each ended by one thread's walk over the counters, and a copy of
+// the pool per level, two sets of 777 points took 46 us a level and two of
+// 10^5 2.3 ms in all; now 9 us and 0.95 ms.
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_kd_level(const OrderJob* __restrict__ orders, int set0,
+                                                    int level, const float* __restrict__ emb,
+                                                    const int32_t* __restrict__ order,
+                                                    uint32_t* __restrict__ keys,
+                                                    int32_t* __restrict__ out) {
+  constexpr int kNW = BLOCK / 64;
+  constexpr int kBins = 2048;
+  constexpr int kPer = kBins / BLOCK;              // counters per thread
+  __shared__ float s_lo[kNW][kMaxE], s_hi[kNW][kMaxE];
+  __shared__ uint32_t hist[kBins];
+  __shared__ uint32_t s_key[BLOCK];
+  __shared__ uint32_t s_pick[3];
+  __shared__ int s_sum[2][kNW];
+  __shared__ int s_n;
   const OrderJob J = orders[set0 + (int)blockIdx.y];
-  if (J.kd_E <= 0 || level >= J.kd_levels) return;
-  const int E = J.kd_E;
+  const int tid = threadIdx.x;
   const int64_t x = blockIdx.x;
+  const int32_t* __restrict__ o = order + J.key_off;
+  int32_t* __restrict__ w = out + J.key_off;
+  if (J.kd_E <= 0 || level >= J.kd_levels) {       // no (further) refinement: its share
+    const int64_t b = ((x + 1) * J.n) >> level;
+    for (int64_t p = ((x * J.n) >> level) + tid; p < b; p += BLOCK) w[p] = o[p];
+    return;
+  }
+  const int E = J.kd_E;
   const int64_t lo = (x * J.kd_n_e) >> level;
   const int64_t hi = ((x + 1) * J.kd_n_e) >> level;
   const int64_t mid = ((2 * x + 1) * J.kd_n_e) >> (level + 1);
   const int64_t h = mid - lo;                       // entries of the lower half
-  if (h <= 0 || h >= hi - lo) return;               // nothing moves
+  if (x == 0)                                       // past the embedded points
+    for (int64_t p = J.kd_n_e + tid; p < J.n; p += BLOCK) w[p] = o[p];
+  if (h <= 0 || h >= hi - lo) {                     // nothing moves
+    for (int64_t p = lo + tid; p < hi; p += BLOCK) w[p] = o[p];
+    return;
+  }
   const float* __restrict__ e = emb + J.kd_emb_off;
-  const int32_t* __restrict__ o = order + J.key_off;
-  int32_t* __restrict__ w = out + J.key_off;
-  const int tid = threadIdx.x;
 
   // the widest coordinate: every coordinate's range in one pass
   float mn[kMaxE], mx[kMaxE];
@@ -256,7 +398,7 @@ __global__ __launch_bounds__(kBlock) void k_kd_split(const OrderJob* __restrict_
     mn[k] = __builtin_inff();
     mx[k] = -__builtin_inff();
   }
-  for (int64_t p = lo + tid; p < hi; p += kBlock) {
+  for (int64_t p = lo + tid; p < hi; p += BLOCK) {
     const float* __restrict__ v = e + (int64_t)o[p] * E;
 #pragma unroll
     for (int k = 0; k < kMaxE; ++k)
@@ -268,6 +410,7 @@ __global__ __launch_bounds__(kBlock) void k_kd_split(const OrderJob* __restrict_
   const int wave = tid >> 6;
 #pragma unroll
   for (int k = 0; k < kMaxE; ++k) {
+    if (k >= E) break;
 #pragma unroll
     for (int sh = 32; sh > 0; sh >>= 1) {
       mn[k] = fminf(mn[k], __shfl_xor(mn[k], sh, 64));
@@ -280,92 +423,194 @@ __global__ __launch_bounds__(kBlock) void k_kd_split(const OrderJob* __restrict_
   }
   __syncthreads();
   int d = 0;
-  float width = -1.f;
+  float width = -1.f, least = 0.f;
   for (int k = 0; k < E; ++k) {
     float a = s_lo[0][k], b = s_hi[0][k];
 #pragma unroll
-    for (int wv = 1; wv < kBlock / 64; ++wv) {
+    for (int wv = 1; wv < kNW; ++wv) {
       a = fminf(a, s_lo[wv][k]);
       b = fmaxf(b, s_hi[wv][k]);
     }
     if (b - a > width) {
       width = b - a;
+      least = a;
       d = k;
     }
   }
-  // the node's keys, formed once (scratch of the order pool's size)
+
+  // the keys, counted in 2048 equal bins of the node's range (values map to
+  // bins monotonically; without a finite scale all are in bin 0)
   uint32_t* __restrict__ kc = keys + J.key_off;
-  for (int64_t p = lo + tid; p < hi; p += kBlock) kc[p] = ordered_bits(e[(int64_t)o[p] * E + d]);
-
-  // radix select of the key of rank h - 1 (0-based); each thread reads the
-  // keys it wrote
-  uint32_t prefix = 0u, mask = 0u;
-  uint32_t rank = (uint32_t)(h - 1);
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    hist[tid] = 0u;
+  const float scale = (float)(kBins - 1) / width;
+  const bool binned = width > 0.f && width < __builtin_inff() && scale < __builtin_inff();
+  auto bin_of = [&](float v) {
+    return binned ? min(kBins - 1, (int)((v - least) * scale)) : 0;
+  };
+  for (int b = tid; b < kBins; b += BLOCK) hist[b] = 0u;
+  if (tid == 0) s_n = 0;
+  __syncthreads();
+  for (int64_t p = lo + tid; p < hi; p += BLOCK) {
+    const float v = e[(int64_t)o[p] * E + d];
+    kc[p] = ordered_bits(v);
+    atomicAdd(&hist[bin_of(v)], 1u);
+  }
+  __syncthreads();
+  // the counter that holds the entry of rank `rank`, and its rank in there
+  auto pick = [&](uint32_t rank, int turn) {
+    uint32_t c[kPer], sum = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      c[u] = hist[tid * kPer + u];
+      sum += c[u];
+    }
+    int all;
+    uint32_t cum = (uint32_t)block_scan<BLOCK>((int)sum, s_sum, turn, all);
+    if (cum <= rank && rank < cum + sum) {          // one thread
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        if (rank >= cum && rank < cum + c[u]) {
+          s_pick[0] = (uint32_t)(tid * kPer + u);
+          s_pick[1] = rank - cum;
+          s_pick[2] = c[u];
+        }
+        cum += c[u];
+      }
+    }
     __syncthreads();
-    for (int64_t p = lo + tid; p < hi; p += kBlock) {
+  };
+  // the key T of rank h - 1 (0-based), and how many entries equal to it are
+  // in the lower half
+  uint32_t T;
+  int eq_left;
+  pick((uint32_t)(h - 1), 0);
+  if (binned && s_pick[2] <= (uint32_t)BLOCK) {
+    // the bin's few entries, each ranked against the others
+    const int bin = (int)s_pick[0];
+    const int rank = (int)s_pick[1];
+    for (int64_t p = lo + tid; p < hi; p += BLOCK) {
       const uint32_t key = kc[p];
-      if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
+      if (bin_of(from_ordered_bits(key)) == bin) s_key[atomicAdd(&s_n, 1)] = key;
     }
     __syncthreads();
-    if (tid == 0) {
-      uint32_t cum = 0u, b = 0u;
-      for (; b < 255u && cum + hist[b] <= rank; ++b) cum += hist[b];
-      s_pick[0] = b;
-      s_pick[1] = rank - cum;
+    const int n = s_n;
+    if (tid < n) {
+      const uint32_t key = s_key[tid];
+      int less = 0, same = 0;
+      for (int x = 0; x < n; ++x) {
+        less += s_key[x] < key ? 1 : 0;
+        same += s_key[x] == key ? 1 : 0;
+      }
+      if (less <= rank && rank < less + same) {     // equal keys write the same
+        s_pick[0] = key;
+        s_pick[1] = (uint32_t)(rank - less);
+      }
     }
     __syncthreads();
-    prefix |= s_pick[0] << shift;
-    mask |= 255u << shift;
-    rank = s_pick[1];
-    __syncthreads();
+    T = s_pick[0];
+    eq_left = (int)s_pick[1] + 1;
+  } else {
+    // many in one bin: radix select over the keys
+    uint32_t prefix = 0u, mask = 0u;
+    uint32_t rank = (uint32_t)(h - 1);
+#pragma unroll 1
+    for (int pass = 0; pass < 3; ++pass) {
+      const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
+      const uint32_t digit = pass == 2 ? 1023u : 2047u;
+      for (int b = tid; b < kBins; b += BLOCK) hist[b] = 0u;
+      __syncthreads();
+      for (int64_t p = lo + tid; p < hi; p += BLOCK) {
+        const uint32_t key = kc[p];
+        if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & digit], 1u);
+      }
+      __syncthreads();
+      pick(rank, (pass & 1) ^ 1);
+      prefix |= s_pick[0] << shift;
+      mask |= digit << shift;
+      rank = s_pick[1];
+      __syncthreads();
+    }
+    T = prefix;
+    eq_left = (int)rank + 1;
   }
-  const uint32_t T = prefix;
-  const int64_t eq_left = (int64_t)rank + 1;      // entries equal to T in the lower half
 
-  // stable partition, 256 entries at a time
-  int64_t at_lo = lo, at_hi = mid, eq_seen = 0;
-  for (int64_t base = lo; base < hi; base += kBlock) {
-    const int64_t p = base + tid;
-    const bool valid = p < hi;
-    const int32_t idx = valid ? o[p] : 0;
-    const uint32_t key = valid ? kc[p] : 0u;
-    const bool is_eq = valid && key == T;
-    int n_eq;
-    const int r_eq = block_rank(is_eq, s_wave[0], n_eq);
-    const bool left = valid && (key < T || (is_eq && eq_seen + r_eq < eq_left));
-    int n_left;
-    const int r_left = block_rank(left, s_wave[1], n_left);
-    if (left) w[at_lo + r_left] = idx;
-    else if (valid) w[at_hi + (tid - r_left)] = idx;
-    const int64_t n_valid = hi - base < kBlock ? hi - base : kBlock;
-    at_lo += n_left;
-    at_hi += n_valid - n_left;
-    eq_seen += n_eq;
+  // stable partition, four consecutive entries per thread at a time
+  constexpr int kRun = 4;
+  int64_t at_lo = lo, at_hi = mid;
+  int eq_seen = 0;
+  for (int64_t base = lo; base < hi; base += BLOCK * kRun) {
+    const int64_t p0 = base + (int64_t)tid * kRun;
+    uint32_t key[kRun];
+    int32_t idx[kRun];
+    int n_eq = 0, n_in = 0;
+#pragma unroll
+    for (int u = 0; u < kRun; ++u) {
+      const bool in = p0 + u < hi;
+      key[u] = in ? kc[p0 + u] : 0u;
+      idx[u] = in ? o[p0 + u] : 0;
+      n_in += in ? 1 : 0;
+      n_eq += in && key[u] == T ? 1 : 0;
+    }
+    int all_eq, all_left;
+    int eq = eq_seen + block_scan<BLOCK>(n_eq, s_sum, 0, all_eq);
+    bool left[kRun];
+    int n_left = 0;
+#pragma unroll
+    for (int u = 0; u < kRun; ++u) {
+      const bool in = u < n_in;
+      left[u] = in && (key[u] < T || (key[u] == T && eq < eq_left));
+      if (in && key[u] == T) ++eq;
+      n_left += left[u] ? 1 : 0;
+    }
+    const int before = block_scan<BLOCK>(n_left, s_sum, 1, all_left);
+    int64_t to_lo = at_lo + before;
+    int64_t to_hi = at_hi + ((int64_t)tid * kRun - before);
+#pragma unroll
+    for (int u = 0; u < kRun; ++u) {
+      if (u >= n_in) break;
+      if (left[u]) w[to_lo++] = idx[u];
+      else w[to_hi++] = idx[u];
+    }
+    const int64_t n_tile = hi - base < BLOCK * kRun ? hi - base : BLOCK * kRun;
+    at_lo += all_left;
+    at_hi += n_tile - all_left;
+    eq_seen += all_eq;
   }
-}
-
-__global__ void k_copy_int(const int32_t* __restrict__ src, int32_t* __restrict__ dst,
-                           int64_t n) {
-  for (int64_t x = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; x < n;
-       x += (int64_t)gridDim.x * blockDim.x)
-    dst[x] = src[x];
 }
 
 // Embedded points in visiting order: the order set restricted to indices
-// below n_e.  One workgroup per embedding.
+// below n_e.  Workgroup (x, y) places the entries at positions
+// [x kOrderSpan, (x+1) kOrderSpan) of embedding y's set, after counting the
+// ones kept before them; a k-d set holds exactly the embedded points first.
+constexpr int kOrderSpan = 2048;
+
 __global__ __launch_bounds__(kBlock) void k_query_order(
     const EmbedJob* __restrict__ jobs, const int32_t* __restrict__ order_pool,
     int32_t* __restrict__ qord_pool) {
   __shared__ int s_wave[kBlock / 64];
-  const EmbedJob J = jobs[blockIdx.x];
+  const EmbedJob J = jobs[blockIdx.y];
   const int32_t* __restrict__ ord = order_pool + J.order_off;
   int32_t* __restrict__ q = qord_pool + J.qord_off;
+  const int64_t a = (int64_t)blockIdx.x * kOrderSpan;
+  if (a >= J.n_series) return;                     // the whole workgroup
+  const int64_t b = min(a + kOrderSpan, J.n_series);
+  if (J.whole || J.n_e == J.n_series) {
+    for (int64_t k = a + threadIdx.x; k < min(b, J.n_e); k += kBlock) q[k] = ord[k];
+    return;
+  }
+  int mine = 0;
+#pragma unroll 8
+  for (int64_t k = threadIdx.x; k < a; k += kBlock) mine += ord[k] < J.n_e ? 1 : 0;
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) mine += __shfl_xor(mine, s, 64);
+  if ((threadIdx.x & 63) == 0) s_wave[threadIdx.x >> 6] = mine;
+  __syncthreads();
   int64_t out = 0;
-  for (int64_t base = 0; base < J.n_series; base += kBlock) {
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) out += s_wave[w];
+  __syncthreads();
+  for (int64_t base = a; base < b; base += kBlock) {
     const int64_t k = base + threadIdx.x;
-    const int64_t i = k < J.n_series ? ord[k] : J.n_e;
+    const int64_t i = k < b ? ord[k] : J.n_e;
     const bool f = i < J.n_e;
     int total;
     const int r = block_rank(f, s_wave, total);
@@ -708,51 +953,70 @@ hipError_t launch_embed(const EmbedJob* jobs, int n_jobs, int64_t max_n,
   return hipGetLastError();
 }
 
-hipError_t launch_iota_segments(int32_t* out, int64_t n_series, int32_t segs,
-                                hipStream_t st) {
-  const int64_t total = n_series * segs;
-  if (total <= 0) return hipSuccess;
-  k_iota_segments<<<blocks_for(total, 256), 256, 0, st>>>(out, n_series, total);
-  return hipGetLastError();
-}
-
-hipError_t launch_order_keys(const OrderJob* jobs, int n_jobs, const float* s32,
-                             uint32_t* keys, hipStream_t st) {
-  if (n_jobs <= 0) return hipSuccess;
-  k_order_keys<<<n_jobs, 256, 0, st>>>(jobs, s32, keys);
-  return hipGetLastError();
-}
-
-hipError_t launch_query_order(const EmbedJob* jobs, int n_jobs,
-                              const int32_t* order, int32_t* qord, hipStream_t st) {
-  if (n_jobs <= 0) return hipSuccess;
-  k_query_order<<<n_jobs, kBlock, 0, st>>>(jobs, order, qord);
-  return hipGetLastError();
-}
-
-hipError_t refine_orders_kd(const OrderJob* orders, int32_t n_sets, int levels,
-                            int64_t n_series, const float* emb, int32_t* order, int32_t* alt,
-                            uint32_t* keys, hipStream_t st) {
-  if (n_sets <= 0 || levels <= 0) return hipSuccess;
+hipError_t build_orders(const OrderJob* orders, int32_t n_sets, int levels, int64_t n_series,
+                        const float* s32, const float* emb, void* mem, hipStream_t st) {
+  if (n_sets <= 0) return hipSuccess;
   const int64_t n = n_series * n_sets;
-  int32_t* cur = order;
-  int32_t* nxt = alt;
-  for (int lv = 0; lv < levels; ++lv) {
-    k_copy_int<<<blocks_for(n, 256), 256, 0, st>>>(cur, nxt, n);
+  uint64_t* half[2] = {static_cast<uint64_t*>(mem), static_cast<uint64_t*>(mem) + n};
+  int32_t* order = order_of(mem, n);
+  int32_t* alt = order + n;
+  uint32_t* keys = static_cast<uint32_t*>(mem);    // the first half, free after the sort
+  // each level moves the entries to the other array; the last one leaves them
+  // in `order`
+  int32_t* cur = levels & 1 ? alt : order;
+  // a chunk's comparisons grow with its size for every 64 keys: two sets of
+  // 10^5 points take 105 us in chunks of 4096 and 37 in 5 merges, 35 in chunks
+  // of 1024 and 50 in 7 merges
+  const int chunk = n_series > 4 * kSortChunk ? 1024 : kSortChunk;
+  const unsigned chunks = (unsigned)((n_series + chunk - 1) / chunk);
+  int merges = 0;
+  while ((1u << merges) < chunks) ++merges;
+  const unsigned threads = std::min<int64_t>(n_series, chunk) > 1024 ? 1024 : 256;
+  const unsigned blocks = (unsigned)((n_series + 63) / 64);
+  // the last merge reads the first half and writes into the second
+  int at = merges > 0 ? (merges - 1) & 1 : 0;
+  for (int32_t s0 = 0; s0 < n_sets; s0 += 65535) {
+    const unsigned ny = (unsigned)std::min<int32_t>(65535, n_sets - s0);
+    float2* const range = merges > 0 ? reinterpret_cast<float2*>(half[at ^ 1]) + s0 : nullptr;
+    if (range) k_series_range<<<ny, 1024, 0, st>>>(orders + s0, s32, range);
+    k_sort_chunks<<<dim3(blocks, ny), threads, 0, st>>>(
+        orders + s0, s32, range, chunk, merges > 0 ? half[at] : nullptr, cur);
+  }
+  for (int m = 0; m < merges; ++m) {
+    const bool last = m + 1 == merges;
     for (int32_t s0 = 0; s0 < n_sets; s0 += 65535) {
       const unsigned ny = (unsigned)std::min<int32_t>(65535, n_sets - s0);
-      k_kd_split<<<dim3(1u << lv, ny), kBlock, 0, st>>>(orders, s0, lv, emb, cur, keys, nxt);
+      const int64_t off = (int64_t)s0 * n_series;
+      k_merge_runs<<<dim3((unsigned)((n_series + 255) / 256), ny), 256, 0, st>>>(
+          half[at] + off, (int64_t)chunk << m, n_series,
+          last ? nullptr : half[at ^ 1] + off, cur + off);
     }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    int32_t* t = cur;
-    cur = nxt;
-    nxt = t;
+    at ^= 1;
   }
-  if (cur != order) k_copy_int<<<blocks_for(n, 256), 256, 0, st>>>(cur, order, n);
+  for (int lv = 0; lv < levels; ++lv) {
+    int32_t* nxt = cur == order ? alt : order;
+    for (int32_t s0 = 0; s0 < n_sets; s0 += 65535) {
+      const unsigned ny = (unsigned)std::min<int32_t>(65535, n_sets - s0);
+      const dim3 grid(1u << lv, ny);
+      if ((n_series >> lv) > 2048)
+        k_kd_level<1024><<<grid, 1024, 0, st>>>(orders, s0, lv, emb, cur, keys, nxt);
+      else
+        k_kd_level<256><<<grid, 256, 0, st>>>(orders, s0, lv, emb, cur, keys, nxt);
+    }
+    cur = nxt;
+  }
   return hipGetLastError();
 }
 
+hipError_t launch_query_order(const EmbedJob* jobs, int n_jobs, int64_t n_series,
+                              const int32_t* order, int32_t* qord, hipStream_t st) {
+  if (n_jobs <= 0) return hipSuccess;
+  const unsigned spans = (unsigned)((n_series + kOrderSpan - 1) / kOrderSpan);
+  for (int j0 = 0; j0 < n_jobs; j0 += 65535)
+    k_query_order<<<dim3(spans, (unsigned)std::min(65535, n_jobs - j0)), kBlock, 0, st>>>(
+        jobs + j0, order, qord);
+  return hipGetLastError();
+}
 
 hipError_t launch_sample(const SampleJob* jobs, int64_t n_jobs, int32_t* out, uint64_t* bits,
                          hipStream_t st) {

@@ -82,14 +82,10 @@ extern "C" ccm_status ccm_dev_noalloc(ccm_ctx* c, const double* X, const double*
     b.rz = reinterpret_cast<Realization*>(take(p.rz.size() * sizeof(Realization)));
     b.items = reinterpret_cast<Item*>(take(p.items.size() * sizeof(Item)));
     b.orders = reinterpret_cast<OrderJob*>(take(p.orders.size() * sizeof(OrderJob)));
-    b.segoff = reinterpret_cast<int32_t*>(take(p.seg_off.size() * 4));
     b.s64 = reinterpret_cast<double*>(take(p.n64 * 8));
     b.s32 = reinterpret_cast<float*>(take(p.n32 * 4));
-    b.iota = reinterpret_cast<int32_t*>(take(p.n_ord * 4));
-    b.keys = reinterpret_cast<uint32_t*>(take(p.n_ord * 4));
-    b.keys_out = reinterpret_cast<uint32_t*>(take(p.n_ord * 4));
-    b.order = reinterpret_cast<int32_t*>(take(p.n_ord * 4));
-    b.sort_temp = take(p.sort_temp);
+    b.order_mem = take((uint64_t)p.n_ord * kOrderBytes);
+    b.order = order_of(b.order_mem, p.n_ord);
     b.qord = reinterpret_cast<int32_t*>(take(p.n_qord * 4));
     b.start = reinterpret_cast<int32_t*>(take((uint64_t)p.n_slots * 4 * kWaves));
     b.emb = reinterpret_cast<float*>(take(p.n_emb * 4));
@@ -115,7 +111,6 @@ extern "C" ccm_status ccm_dev_noalloc(ccm_ctx* c, const double* X, const double*
     put(b.rz, p.rz.data(), p.rz.size() * sizeof(Realization));
     put(b.items, p.items.data(), p.items.size() * sizeof(Item));
     put(b.orders, p.orders.data(), p.orders.size() * sizeof(OrderJob));
-    put(b.segoff, p.seg_off.data(), p.seg_off.size() * 4);
     HIPCHK(hipMemcpyAsync(b.s64, X, N * 8, hipMemcpyDeviceToDevice, st));
     HIPCHK(hipMemcpyAsync(b.s64 + N, Y, N * 8, hipMemcpyDeviceToDevice, st));
     enqueue_plan(c, p, b, {}, st, nullptr);

@@ -35,12 +35,8 @@ void attach_kd(Plan& p, int64_t key_off, int32_t E, int64_t emb_off, int64_t ne)
   while (lv < kKdMaxLevels && (ne >> lv) > kKdLeaf) ++lv;
   o.kd_levels = lv;
   p.kd_levels = std::max(p.kd_levels, lv);
+  if (!p.embed.empty()) p.embed.back().whole = 1;
   (void)E;
-}
-
-void size_order_sort(Plan& p) {
-  HIPCHK(sort_series(nullptr, p.sort_temp, nullptr, nullptr, nullptr, nullptr, p.spec.N,
-                     p.n_sets, nullptr, nullptr));
 }
 
 OrderKey shared_order(int32_t Emax, int32_t tau) {
@@ -69,8 +65,6 @@ int64_t order_set(Plan& p, int series, const OrderKey& key) {
   p.n_sets = (int32_t)p.orders.size();
   p.n_ord = p.n_sets * N;
   if (p.n_ord > (int64_t)INT32_MAX) fail(CCM_E_INVAL, "too many time points to order");
-  p.seg_off.clear();
-  for (int k = 0; k <= p.n_sets; ++k) p.seg_off.push_back((int32_t)(k * N));
   return off;
 }
 
@@ -648,7 +642,7 @@ static Plan make_plan_nested(const Spec& s) {
         emb_off[sr] = p.n_emb;
         qord_off[sr] = p.n_qord;
         ord_off[sr] = order_set(p, sr, embedding_order(E, tau));
-        p.embed.push_back({sr * N, p.n_emb, ord_off[sr], p.n_qord, ne, N, E, tau});
+        p.embed.push_back({sr * N, p.n_emb, ord_off[sr], p.n_qord, ne, N, E, tau, 0, 0});
         attach_kd(p, ord_off[sr], E, emb_off[sr], ne);
         p.n_emb += ne * E;
         p.n_qord += ne;
@@ -735,9 +729,8 @@ static Plan make_plan_nested(const Spec& s) {
   p.n_rho = (int64_t)p.rz_fin.size();
   if (p.rz.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many realizations");
   order_items(p);
-  size_order_sort(p);
   p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 +
-                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves + p.sort_temp +
+                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    (size_t)p.n_ord * 16 + p.n_scratch * 4 + p.segs.size() * 4 +
                    p.n_slots * sizeof(Moments) + p.n_out * 8 +
                    (p.rz.size() + p.rz_fin.size()) * sizeof(Realization) +
@@ -778,7 +771,7 @@ static Plan make_plan_shared(const Spec& s) {
       emb_off[sr] = p.n_emb;
       qord_off[sr] = p.n_qord;
       ord_off[sr] = order_set(p, sr, shared_order(Emax, tau));
-      p.embed.push_back({sr * N, p.n_emb, ord_off[sr], p.n_qord, nc, N, Emax, tau});
+      p.embed.push_back({sr * N, p.n_emb, ord_off[sr], p.n_qord, nc, N, Emax, tau, 0, 0});
       p.n_emb += nc * Emax;
       p.n_qord += nc;
       p.max_embed = std::max(p.max_embed, nc * Emax);
@@ -852,9 +845,8 @@ static Plan make_plan_shared(const Spec& s) {
   p.n_rho = (int64_t)p.rz_fin.size();
   if (p.rz.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many realizations");
   order_items(p);
-  size_order_sort(p);
   p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 +
-                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves + p.sort_temp +
+                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    (size_t)p.n_ord * 16 + p.n_slots * sizeof(Moments) + p.n_out * 8 +
                    (p.rz.size() + p.rz_fin.size()) * sizeof(Realization) +
                    p.items.size() * sizeof(Item) + p.sample.size() * sizeof(SampleJob) +
@@ -911,7 +903,7 @@ Plan make_plan(const Spec& s) {
         emb_off[sr] = p.n_emb;
         qord_off[sr] = p.n_qord;
         ord_off[sr] = order_set(p, sr, embedding_order(E, tau));
-        p.embed.push_back({sr * N, p.n_emb, ord_off[sr], p.n_qord, ne, N, E, tau});
+        p.embed.push_back({sr * N, p.n_emb, ord_off[sr], p.n_qord, ne, N, E, tau, 0, 0});
         attach_kd(p, ord_off[sr], E, emb_off[sr], ne);
         p.n_emb += ne * E;
         p.n_qord += ne;
@@ -992,9 +984,8 @@ Plan make_plan(const Spec& s) {
 
   order_items(p);
 
-  size_order_sort(p);
   p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 +
-                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves + p.sort_temp +
+                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    (size_t)p.n_ord * 16 + p.n_table * 4 + p.tables.size() * sizeof(TableJob) +
                    p.n_slots * sizeof(Moments) + p.n_out * 8 +
                    p.rz.size() * sizeof(Realization) + p.items.size() * sizeof(Item) +
@@ -1047,7 +1038,7 @@ Plan make_plan_matrix(const Spec& s) {
     emb_off[a] = p.n_emb;
     qord_off[a] = p.n_qord;
     ord_off[a] = order_set(p, a, embedding_order(E, tau));
-    p.embed.push_back({a * N, p.n_emb, ord_off[a], p.n_qord, ne, N, E, tau});
+    p.embed.push_back({a * N, p.n_emb, ord_off[a], p.n_qord, ne, N, E, tau, 0, 0});
     attach_kd(p, ord_off[a], E, emb_off[a], ne);
     p.n_emb += ne * E;
     p.n_qord += ne;
@@ -1122,10 +1113,9 @@ Plan make_plan_matrix(const Spec& s) {
       }
   p.n_rho = (int64_t)p.rz.size() * (M - 1);
   order_items(p);
-  size_order_sort(p);
   p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_ord * 16 + p.n_emb * 4 + p.n_lib * 4 +
                    p.n_pts * 4 +
-                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves + p.sort_temp +
+                   p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    p.n_slots * M * multi_sums_bytes() + p.n_out * 8 +
                    N * target_stride(M) * 8 + p.n_table * 4 +
                    p.tables.size() * sizeof(TableJob) +

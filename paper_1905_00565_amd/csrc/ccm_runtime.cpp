@@ -88,7 +88,6 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
     }
     upload(ex->d_plain_items, pi);
   }
-  upload(ex->d_segoff, p.seg_off);
   upload(ex->d_orders, p.orders);
   if (!p.tables.empty()) {
     upload(ex->d_tables, p.tables);
@@ -118,11 +117,7 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   }
   ex->d_s64.ensure(p.n64 * 8);
   ex->d_s32.ensure(p.n32 * 4);
-  ex->d_iota.ensure(p.n_ord * 4);
-  ex->d_keys.ensure(p.n_ord * 4);
-  ex->d_keys_out.ensure(p.n_ord * 4);
-  ex->d_order.ensure(p.n_ord * 4);
-  ex->d_sort_temp.ensure(p.sort_temp);
+  ex->d_order.ensure(p.n_ord * kOrderBytes);
   ex->d_qord.ensure(p.n_qord * 4);
   ex->d_start.ensure(p.n_slots * 4 * kWaves);
   ex->d_emb.ensure(p.n_emb * 4);
@@ -147,14 +142,10 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   b.items = ex->d_items.as<Item>();
   b.plain_items = ex->d_plain_items.as<Item>();
   b.orders = ex->d_orders.as<OrderJob>();
-  b.segoff = ex->d_segoff.as<int32_t>();
   b.s64 = ex->d_s64.as<double>();
   b.s32 = ex->d_s32.as<float>();
-  b.iota = ex->d_iota.as<int32_t>();
-  b.keys = ex->d_keys.as<uint32_t>();
-  b.keys_out = ex->d_keys_out.as<uint32_t>();
-  b.order = ex->d_order.as<int32_t>();
-  b.sort_temp = ex->d_sort_temp.p;
+  b.order_mem = ex->d_order.p;
+  b.order = order_of(b.order_mem, p.n_ord);
   b.qord = ex->d_qord.as<int32_t>();
   b.start = ex->d_start.as<int32_t>();
   b.emb = ex->d_emb.as<float>();
@@ -279,17 +270,8 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
   HIPCHK(launch_ingest(b.ingest, (int)p.ingest.size(), p.n64, b.s64, b.s32, st));
   HIPCHK(launch_embed(b.embed, (int)p.embed.size(), p.max_embed, b.s32, b.emb, st));
   if (p.spec.M > 0) HIPCHK(launch_transpose_targets(b.s64, p.spec.M, p.spec.N, b.tt, st));
-  HIPCHK(launch_order_keys(b.orders, p.n_sets, b.s32, b.keys, st));
-  HIPCHK(launch_iota_segments(b.iota, p.spec.N, p.n_sets, st));
-  {
-    size_t tb = p.sort_temp;
-    HIPCHK(sort_series(b.sort_temp, tb, b.keys, b.keys_out, b.iota, b.order, p.spec.N,
-                       p.n_sets, b.segoff, st));
-    if (p.kd_levels > 0)
-      HIPCHK(refine_orders_kd(b.orders, p.n_sets, p.kd_levels, p.spec.N, b.emb, b.order, b.iota,
-                              b.keys, st));
-  }
-  HIPCHK(launch_query_order(b.embed, (int)p.embed.size(), b.order, b.qord, st));
+  HIPCHK(build_orders(b.orders, p.n_sets, p.kd_levels, p.spec.N, b.s32, b.emb, b.order_mem, st));
+  HIPCHK(launch_query_order(b.embed, (int)p.embed.size(), p.spec.N, b.order, b.qord, st));
   for (int E = 1; E <= kMaxE; ++E)
     HIPCHK(launch_table_build(E, b.tables + p.te_first[E], p.te_count[E], p.te_max_ne[E], b.emb,
                               b.table, st));
@@ -698,21 +680,17 @@ ccm_status ccm_neighbors(ccm_ctx* c, const double* lib_series, const double* tar
     const int32_t sorted = ne <= gather_max_sorted_n_e() ? 1 : 0;
 
     DevBuf d_s64, d_s32, d_emb, d_lib, d_pts, d_pj, d_rz, d_items, d_ingest, d_embed,
-        d_gather, d_partial, d_out, d_nbr, d_d2, d_pred, d_iota, d_keys, d_keys_out, d_order,
-        d_segoff, d_temp, d_qord, d_start, d_orders;
-    std::vector<int32_t> seg{0, (int32_t)N};
+        d_gather, d_partial, d_out, d_nbr, d_d2, d_pred, d_order, d_qord, d_start, d_orders;
     // the same visiting order as the batched plans
     Plan op;
     op.spec.N = N;
     {
       const int64_t ko = order_set(op, 0, embedding_order(E, tau));
       attach_kd(op, ko, E, 0, ne);
-      size_order_sort(op);
     }
     const std::vector<OrderJob>& oj = op.orders;
-    size_t temp_bytes = op.sort_temp;
     std::vector<IngestJob> ij{{0, 0, N}};
-    std::vector<EmbedJob> ej{{0, 0, 0, 0, ne, N, E, tau}};
+    std::vector<EmbedJob> ej{{0, 0, 0, 0, ne, N, E, tau, 0, 0}};
     GatherJob g{};
     g.l_eff = L_eff;
     g.n_e = ne;
@@ -740,7 +718,6 @@ ccm_status ccm_neighbors(ccm_ctx* c, const double* lib_series, const double* tar
     std::vector<Realization> rv{R};
     std::vector<Item> items;
     for (int t = 0; t < n_tiles; ++t) items.push_back({0, t});
-    upload(d_segoff, seg);
     upload(d_orders, oj);
     upload(d_ingest, ij);
     upload(d_embed, ej);
@@ -759,11 +736,8 @@ ccm_status ccm_neighbors(ccm_ctx* c, const double* lib_series, const double* tar
     }
     d_s64.ensure(2 * N * 8);
     d_s32.ensure(N * 4);
-    d_iota.ensure(N * 4);
-    d_keys.ensure(N * 4);
-    d_keys_out.ensure(N * 4);
-    d_order.ensure(N * 4);
-    d_temp.ensure(temp_bytes);
+    d_order.ensure(N * kOrderBytes);
+    int32_t* const order = order_of(d_order.p, N);
     d_qord.ensure(ne * 4);
     d_start.ensure(n_tiles * 4 * kWaves);
     d_emb.ensure(ne * E * 4);
@@ -784,20 +758,11 @@ ccm_status ccm_neighbors(ccm_ctx* c, const double* lib_series, const double* tar
                          d_s32.as<float>(), st));
     HIPCHK(launch_embed(d_embed.as<EmbedJob>(), 1, ne * E, d_s32.as<float>(),
                         d_emb.as<float>(), st));
-    HIPCHK(launch_order_keys(d_orders.as<OrderJob>(), 1, d_s32.as<float>(),
-                             d_keys.as<uint32_t>(), st));
-    HIPCHK(launch_iota_segments(d_iota.as<int32_t>(), N, 1, st));
-    HIPCHK(sort_series(d_temp.p, temp_bytes, d_keys.as<uint32_t>(), d_keys_out.as<uint32_t>(),
-                       d_iota.as<int32_t>(), d_order.as<int32_t>(), N, 1,
-                       d_segoff.as<int32_t>(), st));
-    if (op.kd_levels > 0)
-      HIPCHK(refine_orders_kd(d_orders.as<OrderJob>(), 1, op.kd_levels, N, d_emb.as<float>(),
-                              d_order.as<int32_t>(), d_iota.as<int32_t>(),
-                              d_keys.as<uint32_t>(), st));
-    HIPCHK(launch_query_order(d_embed.as<EmbedJob>(), 1, d_order.as<int32_t>(),
-                              d_qord.as<int32_t>(), st));
+    HIPCHK(build_orders(d_orders.as<OrderJob>(), 1, op.kd_levels, N, d_s32.as<float>(),
+                        d_emb.as<float>(), d_order.p, st));
+    HIPCHK(launch_query_order(d_embed.as<EmbedJob>(), 1, N, order, d_qord.as<int32_t>(), st));
     HIPCHK(launch_gather(d_gather.as<GatherJob>(), 1, sorted ? ne : 0, d_emb.as<float>(),
-                         d_lib.as<int32_t>(), d_order.as<int32_t>(), d_pts.as<float>(),
+                         d_lib.as<int32_t>(), order, d_pts.as<float>(),
                          d_pj.as<int32_t>(), d_start.as<int32_t>(), st));
     if (tab)
       HIPCHK(launch_table_build(E, d_tj.as<TableJob>(), 1, (int)ne, d_emb.as<float>(),

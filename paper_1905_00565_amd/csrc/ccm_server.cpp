@@ -79,8 +79,8 @@ enum JobState { kPending, kActive, kDone, kCancelled, kFailed };
 // staging block holds the same bytes at the same offsets, so one copy
 // uploads them.
 struct Layout {
-  uint64_t s64, s32, iota, keys, keys_out, order, temp, qord, emb, lib, pts, pj, out, table;
-  uint64_t d_ingest, d_embed, d_sample, d_gather, d_segoff, d_orders, d_tables;
+  uint64_t s64, s32, order, qord, emb, lib, pts, pj, out, table;
+  uint64_t d_ingest, d_embed, d_sample, d_gather, d_orders, d_tables;
   uint64_t upload;   // bytes of the series and descriptor block
   uint64_t bytes;
 };
@@ -100,16 +100,11 @@ Layout layout_of(const Plan& p) {
   l.d_embed = take(p.embed.size() * sizeof(EmbedJob));
   l.d_sample = take(p.sample.size() * sizeof(SampleJob));
   l.d_gather = take(p.gather.size() * sizeof(GatherJob));
-  l.d_segoff = take(p.seg_off.size() * 4);
   l.d_orders = take(p.orders.size() * sizeof(OrderJob));
   l.d_tables = take(p.tables.size() * sizeof(TableJob));
   l.upload = o;
   l.s32 = take(p.n32 * 4);
-  l.iota = take(p.n_ord * 4);
-  l.keys = take(p.n_ord * 4);
-  l.keys_out = take(p.n_ord * 4);
-  l.order = take(p.n_ord * 4);
-  l.temp = take(p.sort_temp);
+  l.order = take(p.n_ord * kOrderBytes);
   l.qord = take(p.n_qord * 4);
   l.emb = take(p.n_emb * 4);
   l.lib = take(p.n_lib * 4);
@@ -259,7 +254,6 @@ void stage_job(Job& j, const double* X, const double* Y) {
   put(L.d_embed, p.embed.data(), p.embed.size() * sizeof(EmbedJob));
   put(L.d_sample, p.sample.data(), p.sample.size() * sizeof(SampleJob));
   put(L.d_gather, p.gather.data(), p.gather.size() * sizeof(GatherJob));
-  put(L.d_segoff, p.seg_off.data(), p.seg_off.size() * 4);
   put(L.d_orders, p.orders.data(), p.orders.size() * sizeof(OrderJob));
   put(L.d_tables, p.tables.data(), p.tables.size() * sizeof(TableJob));
   put(j.staging_rz, p.rz.data(), p.rz.size() * sizeof(Realization));
@@ -309,25 +303,17 @@ void start_job(ccm_server* s, Job& j) {
     HIPCHK(launch_table_build(E, at<TableJob>(s, R0 + L.d_tables) + p.te_first[E],
                               p.te_count[E], p.te_max_ne[E], at<float>(s, 0),
                               at<int32_t>(s, 0), st));
-  HIPCHK(launch_order_keys(at<OrderJob>(s, R0 + L.d_orders), p.n_sets,
-                           at<float>(s, R0 + L.s32), at<uint32_t>(s, R0 + L.keys), st));
-  HIPCHK(launch_iota_segments(at<int32_t>(s, R0 + L.iota), N, p.n_sets, st));
-  size_t tb = p.sort_temp;
-  HIPCHK(sort_series(at<void>(s, R0 + L.temp), tb, at<uint32_t>(s, R0 + L.keys),
-                     at<uint32_t>(s, R0 + L.keys_out), at<int32_t>(s, R0 + L.iota),
-                     at<int32_t>(s, R0 + L.order), N, p.n_sets,
-                     at<int32_t>(s, R0 + L.d_segoff), st));
-  if (p.kd_levels > 0)
-    HIPCHK(refine_orders_kd(at<OrderJob>(s, R0 + L.d_orders), p.n_sets, p.kd_levels, N,
-                            at<float>(s, R0 + L.emb), at<int32_t>(s, R0 + L.order),
-                            at<int32_t>(s, R0 + L.iota), at<uint32_t>(s, R0 + L.keys), st));
-  HIPCHK(launch_query_order(at<EmbedJob>(s, R0 + L.d_embed), (int)p.embed.size(),
-                            at<int32_t>(s, R0 + L.order), at<int32_t>(s, R0 + L.qord), st));
+  void* const order_mem = at<void>(s, R0 + L.order);
+  int32_t* const order = order_of(order_mem, p.n_ord);
+  HIPCHK(build_orders(at<OrderJob>(s, R0 + L.d_orders), p.n_sets, p.kd_levels, N,
+                      at<float>(s, R0 + L.s32), at<float>(s, R0 + L.emb), order_mem, st));
+  HIPCHK(launch_query_order(at<EmbedJob>(s, R0 + L.d_embed), (int)p.embed.size(), N, order,
+                            at<int32_t>(s, R0 + L.qord), st));
   HIPCHK(launch_sample(at<SampleJob>(s, R0 + L.d_sample), (int64_t)p.sample.size(),
                        at<int32_t>(s, R0 + L.lib), nullptr, st));
   HIPCHK(launch_gather(at<GatherJob>(s, R0 + L.d_gather), (int64_t)p.gather.size(),
                        p.max_sorted_n_e, at<float>(s, R0 + L.emb), at<int32_t>(s, R0 + L.lib),
-                       at<int32_t>(s, R0 + L.order), at<float>(s, R0 + L.pts),
+                       order, at<float>(s, R0 + L.pts),
                        at<int32_t>(s, R0 + L.pj), s->slots_start.as<int32_t>(), st));
   HIPCHK(hipEventRecord(j.prep_ev, st));
 }
