@@ -115,7 +115,8 @@ typedef struct {
    Each query then scans the largest library once, in segments, taking its
    E+1 neighbours at every library size: the cross map costs
    N_e * max(L_eff) pairs per (E, tau, r, direction) instead of
-   N_e * sum(L_eff).  The rho values differ from the default draws (the
+   N_e * sum(L_eff).  Larger calls take the larger sizes' neighbours from
+   sorted neighbour rows of the embedding instead (the same rho bit for bit).  The rho values differ from the default draws (the
    libraries are correlated across L).  ccm and ccm_sweep (and their device
    forms) only, with query_set 0; not with CCM_FLAG_TABLE, CCM_FLAG_PLAIN or
    CCM_FLAG_SHARED_E (CCM_E_INVAL). */

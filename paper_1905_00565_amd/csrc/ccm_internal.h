@@ -128,14 +128,23 @@ struct Realization {
 };
 
 // One nested ordering: the first n_out points of a forward Fisher-Yates
-// shuffle of 0..n_e-1 (stream keyed by (seed, E, tau, r_index)), written to
-// out; scratch holds the n_e positions being shuffled.
+// shuffle of 0..n_e-1 (stream keyed by (seed, E, tau, r_index)), the first
+// n_list of them written to out; scratch holds the n_e positions being
+// shuffled.  bits > 0: also the bitmaps (n_e bits in uint64 words each) of
+// the libraries that end with segments seg0 .. n_seg-1, from bits - 1 on
+// (n_e <= kNestedLdsNe).
+constexpr int kNestedLdsNe = 65536;
 struct NestedJob {
   uint64_t seed;
   int64_t n_e;
   int64_t n_out;
   int64_t out_off;      // int32 into the library pool
   int64_t scratch_off;  // int32 into the shuffle scratch
+  int64_t n_list;
+  int64_t bits;         // 1 + uint64 offset, or 0
+  int64_t seg_off;      // int32: n_seg + 1 segment bounds
+  int32_t n_seg;
+  int32_t seg0;
   int32_t E;
   int32_t tau;
   int32_t r_index;
@@ -277,8 +286,9 @@ constexpr int table_row_stride(int w) { return (w + 3) & ~3; }
 // of chains (one realization per (E, tau, r, direction) holding every
 // library size as a segment; partial slot of segment k, tile t:
 // slot_base + k * n_tiles + t; scan starts likewise, kWaves per slot).
-hipError_t launch_sample_nested(const NestedJob* jobs, int64_t n_jobs, int32_t* scratch,
-                                int32_t* out_pool, hipStream_t st);
+hipError_t launch_sample_nested(const NestedJob* jobs, int64_t n_jobs, int64_t max_n_e,
+                                const int32_t* seg, int32_t* scratch, int32_t* out_pool,
+                                uint64_t* bits, hipStream_t st);
 hipError_t launch_crossmap_nested(int E, int mode, int grid, const Realization* rzs,
                                   const Item* items, int n_items, int* next,
                                   const float* emb, const float* pts, const int32_t* pj,

@@ -298,73 +298,183 @@ static double row_cost(int E, int64_t ne, int64_t w) {
 // 2 x 10^7 a pair of N = 1331 at E = 1 went from 153 to 183 us).
 constexpr double kWalkMinGain = 5.0e7;
 
+// Groups of one embedding's libraries that walk its rows together.
+struct WalkPick {
+  std::vector<std::vector<int32_t>> groups;
+  std::vector<int32_t> chunks;      // 64-entry chunks each group may need
+  int64_t w = 0;
+};
+
+// The libraries of one embedding (v: its realizations in one launch) worth
+// walking: the largest first, in groups of 64, as many groups as each save
+// more than they cost.  Returns the slots saved per query, the rows' cost
+// not counted; forced: CCM_FLAG_TABLE asks for some of them.
+static double pick_libraries(const Plan& p, int E, double excl, std::vector<int32_t>& v,
+                             WalkPick& pk, bool& forced) {
+  std::stable_sort(v.begin(), v.end(), [&](int32_t a, int32_t b) {
+    const bool fa = p.want_table[a] != 0, fb = p.want_table[b] != 0;
+    if (fa != fb) return fa;
+    return p.rz[a].l_eff > p.rz[b].l_eff;
+  });
+  const int64_t ne = p.rz[v[0]].n_e;
+  const int64_t full = (ne + 63) / 64 * 64;
+  double gain = 0;
+  for (size_t g0 = 0; g0 < v.size(); g0 += kWalkLibs) {
+    const size_t g1 = std::min(v.size(), g0 + kWalkLibs);
+    std::vector<int32_t> grp;
+    int64_t need = 64;
+    double scan = 0;
+    bool force = false;
+    for (size_t k = g0; k < g1; ++k) {
+      const Realization& R = p.rz[v[k]];
+      int64_t n = std::min(full, (row_need(E, excl, ne, R.l_eff) + 63) / 64 * 64);
+      const bool want = p.want_table[v[k]] != 0;
+      if (want) n = std::min<int64_t>(n, kRowMaxW);
+      if (n > kRowMaxW) continue;
+      force |= want;
+      need = std::max(need, n);
+      scan += scan_cost(E, R.l_eff) * (double)R.n_query / (double)ne;
+      grp.push_back(v[k]);
+    }
+    if (grp.empty()) continue;
+    const double save = scan - walk_cost(E, need / 64);
+    if (save <= 0 && !force) continue;
+    gain += save;
+    forced |= force;
+    pk.w = std::max(pk.w, need);
+    pk.groups.push_back(std::move(grp));
+    pk.chunks.push_back((int32_t)(need / 64));
+  }
+  return gain;
+}
+
+// The same for nested libraries (v: the embedding's chains): a chain's scan
+// reads each segment once for every size after it, so the sizes that walk are
+// the last ones of every chain, from the size `first` on which saves most.
+// Each becomes a realization of its own (appended to p.rz; slots as the
+// chain's), and the chains keep the segments before it.  Row widths as above.
+static double pick_sizes(const Plan& p, int E, double excl, const std::vector<int32_t>& v,
+                         int& first) {
+  const Realization& R = p.rz[v[0]];
+  const int64_t ne = R.n_e;
+  const int64_t full = (ne + 63) / 64 * 64;
+  const int32_t* seg = &p.segs[R.seg_off];
+  const double n = (double)v.size();
+  double best = 0, walk = 0;
+  first = R.n_seg;
+  for (int k = R.n_seg - 1; k >= 0; --k) {
+    const int64_t w = std::min(full, (row_need(E, excl, ne, seg[k + 1]) + 63) / 64 * 64);
+    if (w > kRowMaxW) break;
+    walk += walk_cost(E, w / 64) * n / kWalkLibs;
+    // what the chains' scans lose: the points past seg[k], one selection and
+    // prediction per size
+    const double scan = n * (scan_cost(E, R.l_eff) - scan_cost(E, seg[k]) +
+                             (double)(R.n_seg - 1 - k) * scan_cost(E, 0) +
+                             (k == 0 ? scan_cost(E, 0) : 0.0));
+    const double gain = scan - walk - row_cost(E, ne, w);
+    if (gain > best) {
+      best = gain;
+      first = k;
+    }
+  }
+  return best;
+}
+
+static void nested_libraries(Plan& p, int E, double excl, const std::vector<int32_t>& v, int first,
+                             WalkPick& pk) {
+  std::vector<int32_t> libs;
+  const int n_seg = p.rz[v[0]].n_seg;
+  for (int k = n_seg - 1; k >= first; --k)
+    for (int32_t chain : v) {
+      Realization R = p.rz[chain];
+      R.l_eff = p.segs[R.seg_off + k + 1];
+      R.slot_base += (int64_t)k * R.n_tiles;
+      R.n_seg = 0;
+      R.seg_off = k;                // (the size: for its bitmap)
+      libs.push_back((int32_t)p.rz.size());
+      p.rz.push_back(R);
+      p.rz_sample.push_back(p.rz_sample[chain]);
+      p.rz_gather.push_back(p.rz_gather[chain]);
+      p.want_table.push_back(0);
+      p.walked.push_back(0);
+      p.walk_out.push_back(WalkOut{});
+    }
+  if (p.rz.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many realizations");
+  for (int32_t chain : v) {
+    p.rz[chain].n_seg = first;
+    NestedJob& nj = p.nested[p.rz_sample[chain]];
+    nj.seg0 = std::min(nj.bits ? nj.seg0 : n_seg, first);
+    nj.bits = -1;                   // placed by the caller
+  }
+  const int64_t ne = p.rz[v[0]].n_e;
+  const int64_t full = (ne + 63) / 64 * 64;
+  for (size_t g0 = 0; g0 < libs.size(); g0 += kWalkLibs) {
+    const size_t g1 = std::min(libs.size(), g0 + kWalkLibs);
+    // sizes fall: the last library needs the longest row
+    const int64_t le = p.rz[libs[g1 - 1]].l_eff;
+    const int64_t w = std::min(full, (row_need(E, excl, ne, le) + 63) / 64 * 64);
+    pk.w = std::max(pk.w, w);
+    pk.groups.emplace_back(libs.begin() + g0, libs.begin() + g1);
+    pk.chunks.push_back((int32_t)(w / 64));
+  }
+}
+
 // The realizations of one launch (rzs: one E of one wave) that walk
-// neighbour rows: per embedding its largest libraries, in groups of 64, as
-// many groups as each save more than they cost, when all they save together
-// exceeds the cost of the rows.
+// neighbour rows: per embedding those picked above, when all they save
+// together exceeds the cost of the rows and launches.
 static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int64_t& bits) {
   if (!p.spec.walk || rzs.empty()) return;
   const int E = la.E;
   const bool keys = p.spec.M > 0;
+  const bool nested = !p.nested.empty();
+  // the shuffle's bitmaps come from positions in LDS
+  if (nested && p.spec.N > kNestedLdsNe) return;
   const double excl =
       p.mode == kExclSelf ? 1.0 : (p.mode == kWindow ? 2.0 * p.window + 1.0 : 0.0);
   std::map<int64_t, std::vector<int32_t>> by_emb;   // in embedding order
   for (int32_t r : rzs) by_emb[p.rz[r].emb_off].push_back(r);
 
-  struct Pick {
-    std::vector<std::vector<int32_t>> groups;
-    std::vector<int32_t> chunks;
-    int64_t w = 0;
-  };
-  std::vector<Pick> picks;
+  std::vector<WalkPick> picks;
   double gain_all = 0;
   bool forced_any = false;
-  for (auto& kv : by_emb) {
-    std::vector<int32_t>& v = kv.second;
-    std::stable_sort(v.begin(), v.end(), [&](int32_t a, int32_t b) {
-      const bool fa = p.want_table[a] != 0, fb = p.want_table[b] != 0;
-      if (fa != fb) return fa;
-      return p.rz[a].l_eff > p.rz[b].l_eff;
-    });
-    const int64_t ne = p.rz[v[0]].n_e;
-    const int64_t full = (ne + 63) / 64 * 64;
-    Pick pk;
-    double gain = 0;
-    bool forced = false;
-    for (size_t g0 = 0; g0 < v.size(); g0 += kWalkLibs) {
-      const size_t g1 = std::min(v.size(), g0 + kWalkLibs);
-      std::vector<int32_t> grp;
-      int64_t need = 64;
-      double scan = 0;
-      bool force = false;
-      for (size_t k = g0; k < g1; ++k) {
-        const Realization& R = p.rz[v[k]];
-        int64_t n = std::min(full, (row_need(E, excl, ne, R.l_eff) + 63) / 64 * 64);
-        const bool want = p.want_table[v[k]] != 0;
-        if (want) n = std::min<int64_t>(n, kRowMaxW);
-        if (n > kRowMaxW) continue;
-        force |= want;
-        need = std::max(need, n);
-        scan += scan_cost(E, R.l_eff) * (double)R.n_query / (double)ne;
-        grp.push_back(v[k]);
-      }
-      if (grp.empty()) continue;
-      const double save = scan - walk_cost(E, need / 64);
-      if (save <= 0 && !force) continue;
-      gain += save;
-      forced |= force;
-      pk.w = std::max(pk.w, need);
-      pk.groups.push_back(std::move(grp));
-      pk.chunks.push_back((int32_t)(need / 64));
+  if (nested) {
+    std::vector<std::pair<const std::vector<int32_t>*, int>> sizes;
+    for (auto& kv : by_emb) {
+      int first = 0;
+      const double gain = pick_sizes(p, E, excl, kv.second, first);
+      const Realization& R = p.rz[kv.second[0]];
+      if (gain <= 0 || (int64_t)R.n_e * kRowMaxW * 8 > kRowPoolCap) continue;
+      gain_all += gain * (double)R.n_e;
+      sizes.emplace_back(&kv.second, first);
     }
-    const bool fits = ne * pk.w * 8 <= kRowPoolCap;
-    gain = (gain - row_cost(E, ne, pk.w)) * (double)ne;
-    if (pk.groups.empty() || !fits || (gain <= 0 && !forced)) continue;
-    gain_all += gain;
-    forced_any |= forced;
-    picks.push_back(std::move(pk));
+    if (gain_all < kWalkMinGain) return;
+    for (auto& s : sizes) {
+      picks.emplace_back();
+      nested_libraries(p, E, excl, *s.first, s.second, picks.back());
+    }
+    for (auto& s : sizes)
+      for (int32_t chain : *s.first) {
+        NestedJob& nj = p.nested[p.rz_sample[chain]];
+        if (nj.bits >= 0) continue;               // placed already
+        nj.bits = 1 + bits;
+        bits += (int64_t)(nj.n_seg - nj.seg0) * ((nj.n_e + 63) / 64);
+      }
+  } else {
+    for (auto& kv : by_emb) {
+      WalkPick pk;
+      bool forced = false;
+      double gain = pick_libraries(p, E, excl, kv.second, pk, forced);
+      const int64_t ne = p.rz[kv.second[0]].n_e;
+      const bool fits = ne * pk.w * 8 <= kRowPoolCap;
+      gain = (gain - row_cost(E, ne, pk.w)) * (double)ne;
+      if (pk.groups.empty() || !fits || (gain <= 0 && !forced)) continue;
+      gain_all += gain;
+      forced_any |= forced;
+      picks.push_back(std::move(pk));
+    }
+    if (picks.empty() || (gain_all < kWalkMinGain && !forced_any)) return;
   }
-  if (picks.empty() || (gain_all < kWalkMinGain && !forced_any)) return;
+  if (picks.empty()) return;
 
   // groups of different embeddings that draw the same libraries share masks
   std::map<std::vector<int64_t>, int64_t> mask_of;
@@ -374,7 +484,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
   std::vector<size_t> emb_group;      // first group of each row job
   const int32_t job0 = (int32_t)p.row_jobs.size();
   if (p.walk_groups.size() > (size_t)INT32_MAX / 8) return;   // (item numbers)
-  for (Pick& pk : picks) {
+  for (WalkPick& pk : picks) {
     const Realization& R0 = p.rz[pk.groups[0][0]];
     RowJob rj{};
     rj.emb_off = R0.emb_off;
@@ -394,12 +504,17 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
       for (int32_t r : grp) {
         WalkLib wl{};
         // the draw's bitmap, one per draw of the wave
-        SampleJob& sj = p.sample[p.rz_sample[r]];
-        if (sj.bits == 0) {
-          sj.bits = 1 + bits;
-          bits += (rj.n_e + 63) / 64;
+        if (nested) {
+          const NestedJob& nj = p.nested[p.rz_sample[r]];
+          wl.bit_off = nj.bits - 1 + (p.rz[r].seg_off - nj.seg0) * ((nj.n_e + 63) / 64);
+        } else {
+          SampleJob& sj = p.sample[p.rz_sample[r]];
+          if (sj.bits == 0) {
+            sj.bits = 1 + bits;
+            bits += (sj.n_e + 63) / 64;
+          }
+          wl.bit_off = sj.bits - 1;
         }
-        wl.bit_off = sj.bits - 1;
         wl.l_eff = p.rz[r].l_eff;
         wl.rz = r;
         p.walk_libs.push_back(wl);
@@ -559,7 +674,7 @@ static void order_items(Plan& p) {
       plan_walks(p, std::vector<int32_t>(order.begin() + a, order.begin() + b), la,
                  bits);
       for (; a < b; ++a) {
-        if (p.walked[order[a]]) continue;
+        if (p.walked[order[a]] || (!p.nested.empty() && p.rz[order[a]].n_seg == 0)) continue;
         const Realization& R = p.rz[order[a]];
         for (int t = 0; t < R.n_tiles; ++t) p.items.push_back({order[a], t});
         la.count += R.n_tiles;
@@ -572,27 +687,40 @@ static void order_items(Plan& p) {
   }
   if (p.walk_groups.empty()) return;
   // a walked realization needs neither its draw as a list nor a gathered
-  // library, but for library-point queries, whose order is the gathered one
-  if (p.spec.query_set == 0) {
+  // library, but for library-point queries, whose order is the gathered one;
+  // a chain needs the segments it still scans
+  if (p.spec.query_set != 0) return;
+  std::vector<char> skip(p.gather.size(), 0);
+  if (!p.nested.empty()) {
+    for (NestedJob& nj : p.nested) {
+      if (nj.bits == 0) continue;
+      nj.n_list = 0;
+    }
+    for (int32_t r : p.wave_rz) {
+      const Realization& R = p.rz[r];
+      NestedJob& nj = p.nested[p.rz_sample[r]];
+      nj.n_list = std::max<int64_t>(nj.n_list, p.segs[R.seg_off + R.n_seg]);
+      for (int k = R.n_seg; k < nj.n_seg; ++k) skip[p.rz_gather[r] + k] = 1;
+    }
+  } else {
     for (size_t r = 0; r < p.rz.size(); ++r)
       if (p.walked[r]) p.sample[p.rz_sample[r]].no_list = 1;
     for (size_t r = 0; r < p.rz.size(); ++r)
       if (!p.walked[r]) p.sample[p.rz_sample[r]].no_list = 0;
-    std::vector<char> skip(p.gather.size(), 0);
     for (size_t r = 0; r < p.rz.size(); ++r)
       if (p.walked[r]) skip[p.rz_gather[r]] = 1;
-    for (Wave& w : p.waves) {
-      std::vector<GatherJob> keep;
-      int64_t max_ne = 0;
-      for (int64_t g = w.gather_first; g < w.gather_first + w.gather_count; ++g)
-        if (!skip[g]) {
-          keep.push_back(p.gather[g]);
-          if (p.gather[g].sorted) max_ne = std::max(max_ne, p.gather[g].n_e);
-        }
-      std::copy(keep.begin(), keep.end(), p.gather.begin() + w.gather_first);
-      w.gather_count = (int64_t)keep.size();
-      w.max_sorted_n_e = max_ne;
-    }
+  }
+  for (Wave& w : p.waves) {
+    std::vector<GatherJob> keep;
+    int64_t max_ne = 0;
+    for (int64_t g = w.gather_first; g < w.gather_first + w.gather_count; ++g)
+      if (!skip[g]) {
+        keep.push_back(p.gather[g]);
+        if (p.gather[g].sorted) max_ne = std::max(max_ne, p.gather[g].n_e);
+      }
+    std::copy(keep.begin(), keep.end(), p.gather.begin() + w.gather_first);
+    w.gather_count = (int64_t)keep.size();
+    w.max_sorted_n_e = max_ne;
   }
 }
 
@@ -655,6 +783,9 @@ static Plan make_plan_nested(const Spec& s) {
         nj.seed = s.seed;
         nj.n_e = ne;
         nj.n_out = lmax;
+        nj.n_list = lmax;
+        nj.seg_off = seg_off;
+        nj.n_seg = n_seg;
         nj.out_off = p.n_lib;
         nj.scratch_off = p.n_scratch;
         nj.E = E;
@@ -735,7 +866,7 @@ static Plan make_plan_nested(const Spec& s) {
                    p.n_slots * sizeof(Moments) + p.n_out * 8 +
                    (p.rz.size() + p.rz_fin.size()) * sizeof(Realization) +
                    p.items.size() * sizeof(Item) + p.nested.size() * sizeof(NestedJob) +
-                   p.gather.size() * sizeof(GatherJob);
+                   p.gather.size() * sizeof(GatherJob) + p.walk_bytes();
   return p;
 }
 

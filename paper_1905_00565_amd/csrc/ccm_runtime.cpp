@@ -44,10 +44,10 @@ void drain_events(ccm_ctx* c) {
   c->ev_pending.clear();
 }
 
-// The batched forms walk neighbour rows; the plain baseline and the forms
-// with draws of their own scan.
+// The batched forms walk neighbour rows; the plain baseline and the scan
+// that all E share do not.
 bool walks(const Spec& s) {
-  return !(s.flags & (CCM_FLAG_PLAIN | CCM_FLAG_NESTED | CCM_FLAG_SHARED_E));
+  return !(s.flags & (CCM_FLAG_PLAIN | CCM_FLAG_SHARED_E));
 }
 
 // Device buffers and descriptors for a plan (reused when the shape repeats).
@@ -284,8 +284,8 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
     const Wave& w = p.waves[wi];
     if (!plain) {
       if (nested)
-        HIPCHK(launch_sample_nested(b.nested + w.sample_first, w.sample_count, b.shuffle, b.lib,
-                                    st));
+        HIPCHK(launch_sample_nested(b.nested + w.sample_first, w.sample_count, p.spec.N, b.segs,
+                                    b.shuffle, b.lib, b.bits, st));
       else
         HIPCHK(launch_sample(b.sample + w.sample_first, w.sample_count, b.lib, b.bits, st));
       HIPCHK(launch_gather(b.gather + w.gather_first, w.gather_count, w.max_sorted_n_e, b.emb,
@@ -637,6 +637,7 @@ ccm_status ccm_nested_library(ccm_ctx* c, int64_t N_e, int32_t E, int32_t tau,
     nj.seed = seed;
     nj.n_e = N_e;
     nj.n_out = n_out;
+    nj.n_list = n_out;
     nj.E = E;
     nj.tau = tau;
     nj.r_index = r_index;
@@ -644,8 +645,8 @@ ccm_status ccm_nested_library(ccm_ctx* c, int64_t N_e, int32_t E, int32_t tau,
     upload(job, j);
     scratch.ensure(N_e * 4);
     out.ensure(n_out * 4);
-    HIPCHK(launch_sample_nested(job.as<NestedJob>(), 1, scratch.as<int32_t>(),
-                                out.as<int32_t>(), c->stream));
+    HIPCHK(launch_sample_nested(job.as<NestedJob>(), 1, N_e, nullptr, scratch.as<int32_t>(),
+                                out.as<int32_t>(), nullptr, c->stream));
     HIPCHK(hipMemcpyAsync(idx_out, out.p, n_out * 4, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
   });

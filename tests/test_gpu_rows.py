@@ -11,6 +11,7 @@ rows whatever the call's size, so the small cases reach them.
 import numpy as np
 import pytest
 
+import oracle
 from paper_1905_00565_amd import capi, synth
 
 pytestmark = pytest.mark.gpu
@@ -106,3 +107,32 @@ def test_rows_matrix_equal_scan(ctx, M, N, E, L, excl, qs):
     assert walked > 0
     b = ctx.ccm_matrix(S, E, 1, L, 5, 3, flags=PLAIN, **kw)
     assert np.array_equal(a.view(np.uint64), b.view(np.uint64))
+
+
+# Large calls walk neighbour rows for their larger sizes, small ones scan every
+# segment; the orderings do not depend on r, so the first columns must agree
+# bit for bit.  Sizes: every one walked, the first ones scanned (rows past 1024
+# entries), equal and whole-embedding sizes, ties, exclusions, and shuffles of
+# more than 16384 points.
+@pytest.mark.parametrize("N,E,tau,L,r,excl,kind", [
+    (3000, 3, 1, [1500, 2998], 70, 0, "logistic"),
+    (3001, 7, 2, [20, 21, 500, 1000, 2989], 65, 0, "logistic"),
+    (4000, 1, 1, [30, 2000, 4000, 9999], 90, -1, "quantised"),
+    (2500, 2, 3, [100, 1300, 2497], 150, 6, "quantised"),
+    (17000, 4, 1, [64, 9000, 16997], 6, 0, "logistic"),
+])
+def test_nested_rows_equal_scan(ctx, N, E, tau, L, r, excl, kind):
+    X, Y = series(kind, N)
+    kw = dict(exclusion_radius=excl, flags=capi.CCM_FLAG_NESTED)
+    few = ctx.ccm_sweep(X, Y, [E], [tau], L, 1, 5, **kw)
+    many = ctx.ccm_sweep(X, Y, [E], [tau], L, r, 5, **kw)
+    assert np.array_equal(few[..., 0].view(np.uint64),
+                          np.ascontiguousarray(many[..., 0]).view(np.uint64))
+
+
+@pytest.mark.parametrize("n,n_out", [(64, 64), (65, 65), (16384, 16384), (16385, 16385),
+                                     (65536, 65536), (65537, 9000), (70001, 70001), (5, 1)])
+def test_nested_ordering_sizes(ctx, n, n_out):
+    oracle.build(force=False)
+    got = ctx.ccm_nested_library(n, 3, 2, 1, 9, n_out)
+    assert np.array_equal(got, oracle.default().sample_nested(9, 3, 2, 1, n, n_out))
