@@ -129,7 +129,9 @@ typedef struct {
    stream keyed by (seed, 0, tau, L_eff, r).  Each E is then the default
    cross map of the series shifted by (E_max-E) tau, and one scan per
    (tau, L, r, direction) computes every E's neighbours: the binary32
-   distance after E coordinates is E's d2.  The rho values differ from the
+   distance after E coordinates is E's d2.  (The larger libraries of larger
+   calls take them from each E's sorted neighbour rows over the common points
+   instead, the same rho bit for bit.)  The rho values differ from the
    default draws (fewer points for E < E_max, other libraries).  ccm and
    ccm_sweep (and their device forms) only, with query_set 0; not with
    CCM_FLAG_TABLE, CCM_FLAG_NESTED or CCM_FLAG_PLAIN (CCM_E_INVAL). */

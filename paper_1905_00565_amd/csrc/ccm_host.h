@@ -139,6 +139,7 @@ struct Launch {
   int32_t mask_first = 0, mask_count = 0, mask_max_ne = 0;   // into Plan::mask_jobs
   int32_t batch_first = 0, batch_count = 0;                  // into Plan::walk_batches
   int32_t walk_per = 0;                                      // queries per walk item
+  int32_t sub_first = 0, sub_count = 0;   // into Plan::sub_launches
 };
 
 // A wave: realizations whose drawn libraries and gathered points are live at
@@ -183,6 +184,8 @@ struct Plan {
   // wave, then E, longest library first within a group
   std::vector<Wave> waves;
   std::vector<Launch> launches;
+  // E-sweep sharing: the walks of a launch, one (no items) per E
+  std::vector<Launch> sub_launches;
   std::vector<int32_t> wave_rz;       // realizations in wave order
   std::vector<int64_t> wave_rz_first; // per wave, into wave_rz (+1 sentinel)
   std::vector<Item> items;

@@ -58,7 +58,7 @@ hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,
                          int query_set, hipStream_t st);
 
 template <int E>
-hipError_t launch_walk_moments_e(const Realization* rzs, const WalkOut* where,
+hipError_t launch_walk_moments_e(int shared, const Realization* rzs, const WalkOut* where,
                                  const Item* items, int n_items, const double* out,
                                  const int32_t* pj, const int32_t* qord, const double* tgt,
                                  Moments* partial, int query_set, hipStream_t st);

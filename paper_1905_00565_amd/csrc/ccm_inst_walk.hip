@@ -53,12 +53,16 @@ hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,
 }
 
 template <int E>
-hipError_t launch_walk_moments_e(const Realization* rzs, const WalkOut* where,
+hipError_t launch_walk_moments_e(int shared, const Realization* rzs, const WalkOut* where,
                                  const Item* items, int n_items, const double* out,
                                  const int32_t* pj, const int32_t* qord, const double* tgt,
                                  Moments* partial, int query_set, hipStream_t st) {
-  k_walk_moments<E, DefaultQ<E>::Q><<<(unsigned)n_items, kBlock, 0, st>>>(
-      rzs, where, items, n_items, out, pj, qord, tgt, partial, query_set);
+  if (shared)
+    k_walk_moments<kSharedQ[E]><<<(unsigned)n_items, kBlock, 0, st>>>(
+        rzs, where, items, n_items, out, pj, qord, tgt, partial, query_set);
+  else
+    k_walk_moments<DefaultQ<E>::Q><<<(unsigned)n_items, kBlock, 0, st>>>(
+        rzs, where, items, n_items, out, pj, qord, tgt, partial, query_set);
   return hipGetLastError();
 }
 
@@ -73,7 +77,7 @@ template hipError_t launch_walk_e<CCM_INST_E>(int, const WalkGroup*, const WalkL
                                               const uint64_t*, const uint64_t*, const int32_t*,
                                               const float*, const double*, double*, int, int,
                                               hipStream_t);
-template hipError_t launch_walk_moments_e<CCM_INST_E>(const Realization*, const WalkOut*,
+template hipError_t launch_walk_moments_e<CCM_INST_E>(int, const Realization*, const WalkOut*,
                                                       const Item*, int, const double*,
                                                       const int32_t*, const int32_t*,
                                                       const double*, Moments*, int,

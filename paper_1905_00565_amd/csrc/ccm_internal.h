@@ -196,6 +196,8 @@ struct RowJob {
   int64_t out_off;   // uint64: rows [n_e][w]
   int32_t n_e;
   int32_t w;
+  int32_t stride;    // floats per point in the embedding (E, or a shared E_max)
+  int32_t pad;
 };
 
 // A row left to the second row kernel (repeated values): position p of a
@@ -360,7 +362,7 @@ hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* 
                        const float* emb, const double* tgt, double* out, int excl,
                        int query_set, hipStream_t st);
 // Moments of the items' tiles from the predictions at where[rz].
-hipError_t launch_walk_moments(int E, const Realization* rzs, const WalkOut* where,
+hipError_t launch_walk_moments(int E, int shared, const Realization* rzs, const WalkOut* where,
                                const Item* items, int n_items, const double* out,
                                const int32_t* pj, const int32_t* qord, const double* tgt,
                                Moments* partial, int query_set, hipStream_t st);

@@ -1170,13 +1170,13 @@ hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* 
 #undef CCM_CALL
 }
 
-hipError_t launch_walk_moments(int E, const Realization* rzs, const WalkOut* where,
+hipError_t launch_walk_moments(int E, int shared, const Realization* rzs, const WalkOut* where,
                                const Item* items, int n_items, const double* out,
                                const int32_t* pj, const int32_t* qord, const double* tgt,
                                Moments* partial, int query_set, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
 #define CCM_CALL(e)                                                                       \
-  launch_walk_moments_e<e>(rzs, where, items, n_items, out, pj, qord, tgt, partial,     \
+  launch_walk_moments_e<e>(shared, rzs, where, items, n_items, out, pj, qord, tgt, partial,     \
                            query_set, st)
   CCM_BY_E(E, CCM_CALL)
 #undef CCM_CALL

@@ -380,6 +380,19 @@ static double pick_sizes(const Plan& p, int E, double excl, const std::vector<in
   return best;
 }
 
+// A realization of its own for a library walked out of realization `of`
+// (same draw and gather jobs); returns its index.
+static int32_t add_walked(Plan& p, const Realization& R, int32_t of) {
+  if (p.rz.size() >= (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many realizations");
+  p.rz.push_back(R);
+  p.rz_sample.push_back((int64_t)p.rz_sample[of]);
+  p.rz_gather.push_back((int64_t)p.rz_gather[of]);
+  p.want_table.push_back(0);
+  p.walked.push_back(1);
+  p.walk_out.push_back(WalkOut{});
+  return (int32_t)p.rz.size() - 1;
+}
+
 static void nested_libraries(Plan& p, int E, double excl, const std::vector<int32_t>& v, int first,
                              WalkPick& pk) {
   std::vector<int32_t> libs;
@@ -391,15 +404,8 @@ static void nested_libraries(Plan& p, int E, double excl, const std::vector<int3
       R.slot_base += (int64_t)k * R.n_tiles;
       R.n_seg = 0;
       R.seg_off = k;                // (the size: for its bitmap)
-      libs.push_back((int32_t)p.rz.size());
-      p.rz.push_back(R);
-      p.rz_sample.push_back(p.rz_sample[chain]);
-      p.rz_gather.push_back(p.rz_gather[chain]);
-      p.want_table.push_back(0);
-      p.walked.push_back(0);
-      p.walk_out.push_back(WalkOut{});
+      libs.push_back(add_walked(p, R, chain));
     }
-  if (p.rz.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many realizations");
   for (int32_t chain : v) {
     p.rz[chain].n_seg = first;
     NestedJob& nj = p.nested[p.rz_sample[chain]];
@@ -419,63 +425,13 @@ static void nested_libraries(Plan& p, int E, double excl, const std::vector<int3
   }
 }
 
-// The realizations of one launch (rzs: one E of one wave) that walk
-// neighbour rows: per embedding those picked above, when all they save
-// together exceeds the cost of the rows and launches.
-static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int64_t& bits) {
-  if (!p.spec.walk || rzs.empty()) return;
+// Lay out the walks of one launch: per pick (an embedding's groups) a row
+// job, the groups' libraries, bitmaps and membership words, the batches of
+// embeddings whose rows fit together and the chunks whose output does.
+static void lay_out_walks(Plan& p, std::vector<WalkPick>& picks, Launch& la, int64_t& bits) {
   const int E = la.E;
   const bool keys = p.spec.M > 0;
   const bool nested = !p.nested.empty();
-  // the shuffle's bitmaps come from positions in LDS
-  if (nested && p.spec.N > kNestedLdsNe) return;
-  const double excl =
-      p.mode == kExclSelf ? 1.0 : (p.mode == kWindow ? 2.0 * p.window + 1.0 : 0.0);
-  std::map<int64_t, std::vector<int32_t>> by_emb;   // in embedding order
-  for (int32_t r : rzs) by_emb[p.rz[r].emb_off].push_back(r);
-
-  std::vector<WalkPick> picks;
-  double gain_all = 0;
-  bool forced_any = false;
-  if (nested) {
-    std::vector<std::pair<const std::vector<int32_t>*, int>> sizes;
-    for (auto& kv : by_emb) {
-      int first = 0;
-      const double gain = pick_sizes(p, E, excl, kv.second, first);
-      const Realization& R = p.rz[kv.second[0]];
-      if (gain <= 0 || (int64_t)R.n_e * kRowMaxW * 8 > kRowPoolCap) continue;
-      gain_all += gain * (double)R.n_e;
-      sizes.emplace_back(&kv.second, first);
-    }
-    if (gain_all < kWalkMinGain) return;
-    for (auto& s : sizes) {
-      picks.emplace_back();
-      nested_libraries(p, E, excl, *s.first, s.second, picks.back());
-    }
-    for (auto& s : sizes)
-      for (int32_t chain : *s.first) {
-        NestedJob& nj = p.nested[p.rz_sample[chain]];
-        if (nj.bits >= 0) continue;               // placed already
-        nj.bits = 1 + bits;
-        bits += (int64_t)(nj.n_seg - nj.seg0) * ((nj.n_e + 63) / 64);
-      }
-  } else {
-    for (auto& kv : by_emb) {
-      WalkPick pk;
-      bool forced = false;
-      double gain = pick_libraries(p, E, excl, kv.second, pk, forced);
-      const int64_t ne = p.rz[kv.second[0]].n_e;
-      const bool fits = ne * pk.w * 8 <= kRowPoolCap;
-      gain = (gain - row_cost(E, ne, pk.w)) * (double)ne;
-      if (pk.groups.empty() || !fits || (gain <= 0 && !forced)) continue;
-      gain_all += gain;
-      forced_any |= forced;
-      picks.push_back(std::move(pk));
-    }
-    if (picks.empty() || (gain_all < kWalkMinGain && !forced_any)) return;
-  }
-  if (picks.empty()) return;
-
   // groups of different embeddings that draw the same libraries share masks
   std::map<std::vector<int64_t>, int64_t> mask_of;
   int64_t masks = 0, total_q = 0;
@@ -491,6 +447,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
     rj.qord_off = R0.qord_off;
     rj.n_e = R0.n_e;
     rj.w = (int32_t)pk.w;
+    rj.stride = p.shared_emax > 0 ? p.shared_emax : E;
     emb_group.push_back(p.walk_groups.size());
     for (size_t g = 0; g < pk.groups.size(); ++g) {
       const std::vector<int32_t>& grp = pk.groups[g];
@@ -643,6 +600,154 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
   la.batch_count = (int32_t)p.walk_batches.size() - la.batch_first;
 }
 
+// The realizations of one launch (rzs: one E of one wave) that walk
+// neighbour rows: per embedding those picked above, when all they save
+// together exceeds the cost of the rows and launches.
+static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int64_t& bits) {
+  if (!p.spec.walk || rzs.empty()) return;
+  const int E = la.E;
+  const bool keys = p.spec.M > 0;
+  const bool nested = !p.nested.empty();
+  // the shuffle's bitmaps come from positions in LDS
+  if (nested && p.spec.N > kNestedLdsNe) return;
+  const double excl =
+      p.mode == kExclSelf ? 1.0 : (p.mode == kWindow ? 2.0 * p.window + 1.0 : 0.0);
+  std::map<int64_t, std::vector<int32_t>> by_emb;   // in embedding order
+  for (int32_t r : rzs) by_emb[p.rz[r].emb_off].push_back(r);
+
+  std::vector<WalkPick> picks;
+  double gain_all = 0;
+  bool forced_any = false;
+  if (nested) {
+    std::vector<std::pair<const std::vector<int32_t>*, int>> sizes;
+    for (auto& kv : by_emb) {
+      int first = 0;
+      const double gain = pick_sizes(p, E, excl, kv.second, first);
+      const Realization& R = p.rz[kv.second[0]];
+      if (gain <= 0 || (int64_t)R.n_e * kRowMaxW * 8 > kRowPoolCap) continue;
+      gain_all += gain * (double)R.n_e;
+      sizes.emplace_back(&kv.second, first);
+    }
+    if (gain_all < kWalkMinGain) return;
+    for (auto& s : sizes) {
+      picks.emplace_back();
+      nested_libraries(p, E, excl, *s.first, s.second, picks.back());
+    }
+    for (auto& s : sizes)
+      for (int32_t chain : *s.first) {
+        NestedJob& nj = p.nested[p.rz_sample[chain]];
+        if (nj.bits >= 0) continue;               // placed already
+        nj.bits = 1 + bits;
+        bits += (int64_t)(nj.n_seg - nj.seg0) * ((nj.n_e + 63) / 64);
+      }
+  } else {
+    for (auto& kv : by_emb) {
+      WalkPick pk;
+      bool forced = false;
+      double gain = pick_libraries(p, E, excl, kv.second, pk, forced);
+      const int64_t ne = p.rz[kv.second[0]].n_e;
+      const bool fits = ne * pk.w * 8 <= kRowPoolCap;
+      gain = (gain - row_cost(E, ne, pk.w)) * (double)ne;
+      if (pk.groups.empty() || !fits || (gain <= 0 && !forced)) continue;
+      gain_all += gain;
+      forced_any |= forced;
+      picks.push_back(std::move(pk));
+    }
+    if (picks.empty() || (gain_all < kWalkMinGain && !forced_any)) return;
+  }
+  if (!picks.empty()) lay_out_walks(p, picks, la, bits);
+}
+
+// E-sweep sharing: realizations (scans of every E at once) whose libraries
+// walk the rows of each requested E instead, over the first E coordinates of
+// the shared embedding: one walked realization per E, in the scan's slots.
+static void plan_shared_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la,
+                              int64_t& bits) {
+  if (!p.spec.walk || rzs.empty()) return;
+  const int Emax = p.shared_emax;
+  const double excl =
+      p.mode == kExclSelf ? 1.0 : (p.mode == kWindow ? 2.0 * p.window + 1.0 : 0.0);
+  std::vector<int32_t> Es = p.spec.E;
+  std::sort(Es.begin(), Es.end());
+  Es.erase(std::unique(Es.begin(), Es.end()), Es.end());
+  std::map<int64_t, std::vector<int32_t>> by_emb;
+  for (int32_t r : rzs) by_emb[p.rz[r].emb_off].push_back(r);
+
+  std::vector<std::vector<std::vector<int32_t>>> groups;   // per embedding
+  double gain_all = 0;
+  for (auto& kv : by_emb) {
+    std::vector<int32_t>& v = kv.second;
+    std::stable_sort(v.begin(), v.end(),
+                     [&](int32_t a, int32_t b) { return p.rz[a].l_eff > p.rz[b].l_eff; });
+    const int64_t ne = p.rz[v[0]].n_e;
+    if (ne * kRowMaxW * 8 > kRowPoolCap) continue;
+    const int64_t full = (ne + 63) / 64 * 64;
+    const auto width = [&](int E, int64_t le) {
+      return std::min(full, (row_need(E, excl, ne, le) + 63) / 64 * 64);
+    };
+    std::vector<std::vector<int32_t>> gs;
+    std::vector<int64_t> w(Es.size(), 64);
+    double gain = 0;
+    for (size_t g0 = 0; g0 < v.size(); g0 += kWalkLibs) {
+      std::vector<int32_t> grp;
+      double save = 0;
+      for (size_t k = g0; k < std::min(v.size(), g0 + kWalkLibs); ++k) {
+        const Realization& R = p.rz[v[k]];
+        if (width(Es.back(), R.l_eff) > kRowMaxW) continue;
+        save += scan_cost(Emax, R.l_eff);
+        for (int E : Es) save += scan_cost(E, 0);
+        grp.push_back(v[k]);
+      }
+      if (grp.empty()) break;
+      const int64_t le = p.rz[grp.back()].l_eff;
+      for (int E : Es) save -= walk_cost(E, width(E, le) / 64);
+      if (save <= 0) break;
+      for (size_t e = 0; e < Es.size(); ++e) w[e] = std::max(w[e], width(Es[e], le));
+      gain += save;
+      gs.push_back(std::move(grp));
+    }
+    for (size_t e = 0; e < Es.size(); ++e) gain -= row_cost(Es[e], ne, w[e]);
+    if (gs.empty() || gain <= 0) continue;
+    gain_all += gain * (double)ne;
+    groups.push_back(std::move(gs));
+  }
+  if (gain_all < kWalkMinGain) return;
+
+  for (auto& gs : groups)
+    for (auto& grp : gs)
+      for (int32_t r : grp) p.walked[r] = 1;
+  la.sub_first = (int32_t)p.sub_launches.size();
+  for (int E : Es) {
+    std::vector<WalkPick> picks;
+    for (auto& gs : groups) {
+      WalkPick pk;
+      for (auto& grp : gs) {
+        const Realization& last = p.rz[grp.back()];
+        const int64_t full = ((int64_t)last.n_e + 63) / 64 * 64;
+        const int64_t w =
+            std::min(full, (row_need(E, excl, last.n_e, last.l_eff) + 63) / 64 * 64);
+        std::vector<int32_t> libs;
+        for (int32_t r : grp) {
+          Realization R = p.rz[r];
+          R.E = E;
+          R.tgt_off += (int64_t)(Emax - E) * R.tau;     // target at common point 0
+          R.slot_base += (int64_t)(E - 1) * R.n_tiles;
+          libs.push_back(add_walked(p, R, r));
+        }
+        pk.w = std::max(pk.w, w);
+        pk.groups.push_back(std::move(libs));
+        pk.chunks.push_back((int32_t)(w / 64));
+      }
+      picks.push_back(std::move(pk));
+    }
+    Launch sub{};
+    sub.E = E;
+    lay_out_walks(p, picks, sub, bits);
+    p.sub_launches.push_back(sub);
+  }
+  la.sub_count = (int32_t)p.sub_launches.size() - la.sub_first;
+}
+
 // Waves, then the work items of each wave grouped by E (one launch each):
 // the realizations that walk neighbour rows, and the scanned ones, the
 // costliest first within a group: a scan costs n_query * l_eff pairs, a
@@ -671,8 +776,11 @@ static void order_items(Plan& p) {
       Launch la{};
       la.E = p.rz[order[a]].E;
       la.first = (int32_t)p.items.size();
-      plan_walks(p, std::vector<int32_t>(order.begin() + a, order.begin() + b), la,
-                 bits);
+      const std::vector<int32_t> group(order.begin() + a, order.begin() + b);
+      if (p.shared_emax > 0)
+        plan_shared_walks(p, group, la, bits);
+      else
+        plan_walks(p, group, la, bits);
       for (; a < b; ++a) {
         if (p.walked[order[a]] || (!p.nested.empty() && p.rz[order[a]].n_seg == 0)) continue;
         const Realization& R = p.rz[order[a]];
@@ -981,7 +1089,7 @@ static Plan make_plan_shared(const Spec& s) {
                    (size_t)p.n_ord * 16 + p.n_slots * sizeof(Moments) + p.n_out * 8 +
                    (p.rz.size() + p.rz_fin.size()) * sizeof(Realization) +
                    p.items.size() * sizeof(Item) + p.sample.size() * sizeof(SampleJob) +
-                   p.gather.size() * sizeof(GatherJob);
+                   p.gather.size() * sizeof(GatherJob) + p.walk_bytes();
   return p;
 }
 

@@ -44,10 +44,9 @@ void drain_events(ccm_ctx* c) {
   c->ev_pending.clear();
 }
 
-// The batched forms walk neighbour rows; the plain baseline and the scan
-// that all E share do not.
+// The batched forms walk neighbour rows; the plain baseline does not.
 bool walks(const Spec& s) {
-  return !(s.flags & (CCM_FLAG_PLAIN | CCM_FLAG_SHARED_E));
+  return !(s.flags & CCM_FLAG_PLAIN);
 }
 
 // Device buffers and descriptors for a plan (reused when the shape repeats).
@@ -218,7 +217,8 @@ void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStrea
                                  (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.tt, p.spec.M,
                                  b.partial, p.spec.query_set, st));
       else
-        HIPCHK(launch_walk_moments(L.E, b.rz, b.walk_where, b.mom_items + ch.mom_first,
+        HIPCHK(launch_walk_moments(p.shared_emax > 0 ? p.shared_emax : L.E, p.shared_emax > 0,
+                                   b.rz, b.walk_where, b.mom_items + ch.mom_first,
                                    (int)ch.mom_count, b.walk_out, b.pj, b.qord, b.s64,
                                    static_cast<Moments*>(b.partial), p.spec.query_set, st));
     }
@@ -236,7 +236,11 @@ void launch_items(ccm_ctx* c, const Plan& p, const PlanBuffers& b, const Item* i
     ev = take_events(c);
     HIPCHK(hipEventRecord(ev.a, st));
   }
-  if (walks) launch_walks(p, b, *walks, st);
+  if (walks) {
+    launch_walks(p, b, *walks, st);
+    for (int k = 0; k < walks->sub_count; ++k)
+      launch_walks(p, b, p.sub_launches[walks->sub_first + k], st);
+  }
   const Dump nodump{nullptr, nullptr, nullptr};
   if (p.shared_emax > 0)
     HIPCHK(launch_crossmap_shared(E, p.mode, grid, b.rz, items, n, next, b.emb, b.pts, b.pj,

@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kBlock) void k_order_points(const RowJob* __restric
   if (b * 64 >= J.n_e) return;
   const int p = min(b * 64 + lane, J.n_e - 1);     // the tail repeats the last point
   const int i = qord_pool[J.qord_off + p];
-  const float* __restrict__ v = emb_pool + J.emb_off + (int64_t)i * E;
+  const float* __restrict__ v = emb_pool + J.emb_off + (int64_t)i * J.stride;
   float* __restrict__ o = pts_pool + J.pts_off;
   float* __restrict__ box = box_pool + J.box_off + (int64_t)box_slot(b) * (2 * E);
 #pragma unroll
@@ -789,7 +789,7 @@ __global__ __launch_bounds__(kBlock) void k_walk(
       const float* __restrict__ emb = emb_pool + J.emb_off;
       float q[E];
 #pragma unroll
-      for (int k = 0; k < E; ++k) q[k] = emb[(int64_t)i * E + k];
+      for (int k = 0; k < E; ++k) q[k] = emb[(int64_t)i * J.stride + k];
       double best[K];
 #pragma unroll
       for (int t = 0; t < K; ++t) best[t] = empty_key();
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kBlock) void k_walk(
           const int j = j0 + u * 64 + lane;
           const int gap = j > i ? j - i : i - j;
           if (j < J.n_e && gap > excl && ((m[u] >> l) & 1ull))
-            insert_key<K>(best, make_key(sqdist<E>(q, emb + (int64_t)j * E), j));
+            insert_key<K>(best, make_key(sqdist<E>(q, emb + (int64_t)j * J.stride), j));
         }
       }
 #pragma unroll 1
@@ -866,7 +866,7 @@ __global__ __launch_bounds__(kBlock) void k_walk(
 
 // Moments of one query tile of a walked realization from its predictions:
 // the same queries per lane, operations and merge order as crossmap_item.
-template <int E, int Q>
+template <int Q>
 __global__ __launch_bounds__(kBlock) void k_walk_moments(
     const Realization* __restrict__ rzs, const WalkOut* __restrict__ where,
     const Item* __restrict__ items, int n_items, const double* __restrict__ pred,
@@ -878,7 +878,7 @@ __global__ __launch_bounds__(kBlock) void k_walk_moments(
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const double* __restrict__ tgt = tgt_pool + R.tgt_off + (int64_t)(E - 1) * R.tau;
+  const double* __restrict__ tgt = tgt_pool + R.tgt_off + (int64_t)(R.E - 1) * R.tau;
   const int32_t* __restrict__ q = query_set ? pj_pool + R.pj_off : qord_pool + R.qord_off;
   const WalkOut W = where[I.rz];
   const double* __restrict__ pr = pred + W.off;

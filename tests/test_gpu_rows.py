@@ -136,3 +136,22 @@ def test_nested_ordering_sizes(ctx, n, n_out):
     oracle.build(force=False)
     got = ctx.ccm_nested_library(n, 3, 2, 1, 9, n_out)
     assert np.array_equal(got, oracle.default().sample_nested(9, 3, 2, 1, n, n_out))
+
+
+# E-sweep sharing likewise: a large call's libraries walk every E's rows over
+# the shared embedding, a small call's are scanned.  Every E of 1..10, single
+# and repeated E, rows past 1024 entries, ties, exclusions.
+@pytest.mark.parametrize("N,Es,tau,L,r,excl,kind", [
+    (3000, [1, 2, 3, 4, 5, 6], 1, [40, 1500, 2995], 70, 0, "logistic"),
+    (3000, list(range(1, 11)), 2, [1000, 2982], 65, 0, "logistic"),
+    (2600, [7, 2, 7], 3, [900, 2582], 90, 5, "quantised"),
+    (4000, [1], 1, [1500, 4000], 100, -1, "quantised"),
+    (12000, [8, 3], 1, [100, 4000, 11993], 20, 0, "gauss"),
+])
+def test_shared_rows_equal_scan(ctx, N, Es, tau, L, r, excl, kind):
+    X, Y = series(kind, N)
+    kw = dict(exclusion_radius=excl, flags=capi.CCM_FLAG_SHARED_E)
+    few = ctx.ccm_sweep(X, Y, Es, [tau], L, 1, 5, **kw)
+    many = ctx.ccm_sweep(X, Y, Es, [tau], L, r, 5, **kw)
+    assert np.array_equal(few[..., 0].view(np.uint64),
+                          np.ascontiguousarray(many[..., 0]).view(np.uint64))
