@@ -61,6 +61,27 @@ struct PlanBuffers {
   double* walk_out = nullptr;
 };
 
+// The side branch of a captured plan.
+struct Fork {
+  hipStream_t side = nullptr;
+  hipEvent_t ev = nullptr;
+  void create() {
+    if (!side) HIPCHK(hipStreamCreateWithFlags(&side, hipStreamNonBlocking));
+    if (!ev) HIPCHK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+  }
+  void destroy() {
+    if (ev) (void)hipEventDestroy(ev);
+    if (side) (void)hipStreamDestroy(side);
+    ev = nullptr;
+    side = nullptr;
+  }
+  // What `to` is given from here on waits for what `from` has been given.
+  void after(hipStream_t to, hipStream_t from) {
+    HIPCHK(hipEventRecord(ev, from));
+    HIPCHK(hipStreamWaitEvent(to, ev, 0));
+  }
+};
+
 struct Exec {
   Plan plan;
   DevBuf d_ingest, d_embed, d_sample, d_gather, d_rz, d_items, d_plain_items;
@@ -93,6 +114,7 @@ struct ccm_ctx {
   std::vector<ccmh::EvPair> ev_pending, ev_free;
   ccm_profile prof{};
   std::unique_ptr<ccmh::Exec> exec;   // the most recent plan
+  ccmh::Fork fork;                    // used while capturing only
   // pinned staging of the host-array forms' series and results (one
   // buffer, grown as needed; calls on a context are serialised)
   void* pinned = nullptr;
@@ -107,7 +129,7 @@ namespace ccmh {
 // (taken from the context's pool), appended to *evs.
 void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
                   const std::vector<int64_t>& plain_first, hipStream_t st,
-                  std::vector<EvPair>* evs);
+                  std::vector<EvPair>* evs, Fork* fork = nullptr);
 
 // The static workspace of the no-allocation entry point on the current
 // device: set up once per device (at context creation); false, with a

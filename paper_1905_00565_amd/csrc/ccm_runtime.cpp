@@ -190,6 +190,8 @@ int persistent_grid(ccm_ctx* c, int n_items) {
 // The walks of one launch: membership words, then per batch of embeddings
 // their neighbour rows, and per chunk the walk and the moments it leaves.
 void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStream_t st) {
+  for (int k = 0; k < L.sub_count; ++k)
+    launch_walks(p, b, p.sub_launches[L.sub_first + k], st);
   if (L.batch_count == 0) return;
   const int excl = p.mode == kKeepSelf ? -1 : p.window;
   for (int m0 = 0; m0 < L.mask_count; m0 += 65535)
@@ -236,11 +238,7 @@ void launch_items(ccm_ctx* c, const Plan& p, const PlanBuffers& b, const Item* i
     ev = take_events(c);
     HIPCHK(hipEventRecord(ev.a, st));
   }
-  if (walks) {
-    launch_walks(p, b, *walks, st);
-    for (int k = 0; k < walks->sub_count; ++k)
-      launch_walks(p, b, p.sub_launches[walks->sub_first + k], st);
-  }
+  if (walks) launch_walks(p, b, *walks, st);
   const Dump nodump{nullptr, nullptr, nullptr};
   if (p.shared_emax > 0)
     HIPCHK(launch_crossmap_shared(E, p.mode, grid, b.rz, items, n, next, b.emb, b.pts, b.pj,
@@ -270,7 +268,21 @@ namespace ccmh {
 
 void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
                   const std::vector<int64_t>& plain_first, hipStream_t st,
-                  std::vector<EvPair>* evs) {
+                  std::vector<EvPair>* evs, Fork* fork) {
+  const bool plain = (p.spec.flags & CCM_FLAG_PLAIN) != 0;
+  const bool persistent = (p.spec.flags & CCM_FLAG_PERSISTENT) != 0;
+  const bool nested = !p.nested.empty();
+  const auto draw = [&](const Wave& w, hipStream_t s) {
+    if (nested)
+      HIPCHK(launch_sample_nested(b.nested + w.sample_first, w.sample_count, p.spec.N, b.segs,
+                                  b.shuffle, b.lib, b.bits, s));
+    else
+      HIPCHK(launch_sample(b.sample + w.sample_first, w.sample_count, b.lib, b.bits, s));
+  };
+  if (fork) {
+    fork->after(fork->side, st);
+    draw(p.waves[0], fork->side);
+  }
   HIPCHK(launch_ingest(b.ingest, (int)p.ingest.size(), p.n64, b.s64, b.s32, st));
   HIPCHK(launch_embed(b.embed, (int)p.embed.size(), p.max_embed, b.s32, b.emb, st));
   if (p.spec.M > 0) HIPCHK(launch_transpose_targets(b.s64, p.spec.M, p.spec.N, b.tt, st));
@@ -279,21 +291,22 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
   for (int E = 1; E <= kMaxE; ++E)
     HIPCHK(launch_table_build(E, b.tables + p.te_first[E], p.te_count[E], p.te_max_ne[E], b.emb,
                               b.table, st));
-  const bool plain = (p.spec.flags & CCM_FLAG_PLAIN) != 0;
-  const bool persistent = (p.spec.flags & CCM_FLAG_PERSISTENT) != 0;
-  const bool nested = !p.nested.empty();
   // each wave draws and gathers its libraries into the shared pools, then
   // runs its cross-map launches (one per E)
   for (size_t wi = 0; wi < p.waves.size(); ++wi) {
     const Wave& w = p.waves[wi];
     if (!plain) {
-      if (nested)
-        HIPCHK(launch_sample_nested(b.nested + w.sample_first, w.sample_count, p.spec.N, b.segs,
-                                    b.shuffle, b.lib, b.bits, st));
-      else
-        HIPCHK(launch_sample(b.sample + w.sample_first, w.sample_count, b.lib, b.bits, st));
+      // forked: the gather and the scans in the side branch, the walks here
+      const hipStream_t side = fork ? fork->side : st;
+      if (!fork || wi > 0) draw(w, st);
+      if (fork) {
+        if (wi == 0) fork->after(st, side);
+        fork->after(side, st);
+      }
       HIPCHK(launch_gather(b.gather + w.gather_first, w.gather_count, w.max_sorted_n_e, b.emb,
-                           b.lib, b.order, b.pts, b.pj, b.start, st));
+                           b.lib, b.order, b.pts, b.pj, b.start, side));
+      // (the walks of library-point queries read the gathered order)
+      if (fork && p.spec.query_set != 0) fork->after(st, side);
       for (int li = w.launch_first; li < w.launch_first + w.launch_count; ++li) {
         const Launch& L = p.launches[li];
         int grid = L.count;
@@ -301,11 +314,13 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
         if (persistent && L.count > 0) {
           grid = persistent_grid(c, L.count);
           next = b.counter + li;
-          HIPCHK(launch_zero_int(next, 1, st));
+          HIPCHK(launch_zero_int(next, 1, side));
         }
+        if (fork) launch_walks(p, b, L, st);
         launch_items(c, p, b, b.items + L.first, L.count, L.E, grid, next, p.e_table_ne[L.E],
-                     &L, st, evs);
+                     fork ? nullptr : &L, side, evs);
       }
+      if (fork) fork->after(st, side);
     } else {
       // the unbatched baseline: sampler, gather and cross-map launched per
       // realization
@@ -341,13 +356,24 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
 
 namespace {
 
-// Capture the plan's launches into an executable graph.
+// Capture the plan's launches into an executable graph.  With walks, a side
+// branch holds what does not depend on the rows (the draws beside the series'
+// preparation, then the gather and the scans beside rows and walks): a pair
+// of 5003 points at E = 7 takes 538 us, one after the other 714, a sweep of
+// 50 cells of 10^4 points 42.3 and 44.5 ms.  A graph's branches cost about
+// 30 us to part and join (a pair of 120 points: 119 against 90 us), so a plan
+// of scans alone, mostly a small one, stays one chain.
 hipGraphExec_t capture(ccm_ctx* c, Exec* ex) {
   hipStream_t cap = c->stream;
+  Fork* fork = nullptr;
+  if (!ex->plan.walk_groups.empty()) {
+    c->fork.create();
+    fork = &c->fork;
+  }
   HIPCHK(hipStreamSynchronize(cap));
   HIPCHK(hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal));
   try {
-    enqueue_plan(c, ex->plan, ex->buf, ex->plain_first, cap, nullptr);
+    enqueue_plan(c, ex->plan, ex->buf, ex->plain_first, cap, nullptr, fork);
   } catch (...) {
     hipGraph_t g = nullptr;
     (void)hipStreamEndCapture(cap, &g);
@@ -444,6 +470,7 @@ void ccm_destroy(ccm_ctx* c) {
       (void)hipEventDestroy(e.a);
       (void)hipEventDestroy(e.b);
     }
+    c->fork.destroy();
     if (c->stream) (void)hipStreamDestroy(c->stream);
     if (c->pinned) (void)hipHostFree(c->pinned);
   }

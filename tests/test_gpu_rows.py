@@ -155,3 +155,17 @@ def test_shared_rows_equal_scan(ctx, N, Es, tau, L, r, excl, kind):
     many = ctx.ccm_sweep(X, Y, Es, [tau], L, r, 5, **kw)
     assert np.array_equal(few[..., 0].view(np.uint64),
                           np.ascontiguousarray(many[..., 0]).view(np.uint64))
+
+
+def test_replays_agree(ctx):
+    """A captured call has two branches; every replay gives the first,
+    uncaptured result, with other work of the device in between."""
+    torch = pytest.importorskip("torch")
+    X, Y = series("logistic", 4000)
+    args = (X, Y, [2, 5], [1], [40, 1500, 3000], 60, 7)
+    want = ctx.ccm_sweep(*args, flags=capi.CCM_FLAG_NO_GRAPH)
+    for k in range(4):
+        got = ctx.ccm_sweep(*args)
+        assert np.array_equal(got.view(np.uint64), want.view(np.uint64)), k
+        torch.randn(1 << 22, device="cuda").sort()
+        torch.cuda.synchronize()
