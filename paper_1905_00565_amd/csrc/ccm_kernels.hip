@@ -1031,15 +1031,15 @@ hipError_t build_orders(const OrderJob* orders, int32_t n_sets, int levels, int6
   // each level moves the entries to the other array; the last one leaves them
   // in `order`
   int32_t* cur = levels & 1 ? alt : order;
-  // a chunk's comparisons grow with its size for every 64 keys: two sets of
-  // 10^5 points take 105 us in chunks of 4096 and 37 in 5 merges, 35 in chunks
-  // of 1024 and 50 in 7 merges
-  const int chunk = n_series > 4 * kSortChunk ? 1024 : kSortChunk;
+  // every 64 keys form and compare a chunk's: long series in short chunks
+  const int chunk = n_series > kSortChunk ? 1024 : kSortChunk;
   const unsigned chunks = (unsigned)((n_series + chunk - 1) / chunk);
   int merges = 0;
   while ((1u << merges) < chunks) ++merges;
-  const unsigned threads = std::min<int64_t>(n_series, chunk) > 1024 ? 1024 : 256;
   const unsigned blocks = (unsigned)((n_series + 63) / 64);
+  // sixteen wavefronts share the chunk's 4096 keys while the chip has room
+  const bool few = (int64_t)blocks * n_sets <= 512;
+  const unsigned threads = few && std::min<int64_t>(n_series, chunk) > 1024 ? 1024 : 256;
   // the last merge reads the first half and writes into the second
   int at = merges > 0 ? (merges - 1) & 1 : 0;
   for (int32_t s0 = 0; s0 < n_sets; s0 += 65535) {
