@@ -338,8 +338,16 @@ constexpr int kOrderBytes = 16;
 inline int32_t* order_of(void* mem, int64_t entries) {
   return reinterpret_cast<int32_t*>(static_cast<char*>(mem) + 8 * entries);
 }
+// draws: library draws made in the same launch as the keys (n == 0: none).
+struct Draws {
+  const SampleJob* jobs = nullptr;
+  int64_t n = 0;
+  int32_t* out = nullptr;
+  uint64_t* bits = nullptr;
+};
 hipError_t build_orders(const OrderJob* orders, int32_t n_sets, int levels, int64_t n_series,
-                        const float* s32, const float* emb, void* mem, hipStream_t st);
+                        const float* s32, const float* emb, void* mem, hipStream_t st,
+                        const Draws& draws = Draws{});
 
 // Neighbour-row path.  Rows of jobs [0, n_jobs) (max_ne, max_w: the largest
 // of them), the points' visiting-order copies and boxes first; per_block

@@ -140,6 +140,130 @@ __device__ __forceinline__ uint32_t hilbert_nd(uint32_t (&x)[4], int n, int b) {
   return h;
 }
 
+// ---------------------------------------------------------------------------
+// library subsamples
+// ---------------------------------------------------------------------------
+
+// SplitMix64 output mix (Steele, Lea & Flood, OOPSLA 2014).
+__device__ __forceinline__ uint64_t sm_mix(uint64_t z) {
+  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+  return z ^ (z >> 31);
+}
+
+// Selection sampling (Knuth, TAOCP Vol. 2, Sec. 3.4.2, Algorithm S): visit
+// candidates 0..n_e-1 in order and take candidate j with probability
+// (needed / remaining); the uniform integer below (n_e - j) is the high word of
+// the 64x64-bit product of one SplitMix64 draw with (n_e - j).  The stream of
+// a library is keyed by (seed, E, tau, L_eff, r) folded through the mix.
+// Once every remaining candidate is needed the rest are taken without draws:
+// the test would accept each of them whatever the draw.
+//
+// One wavefront per library.  The stream's state advances by the same
+// constant for every candidate visited, so candidate j's draw is the output
+// mix of (keyed state + (j+1) gamma): the 64 lanes form the draws and their
+// integers u_j below (n_e - j) of 64 consecutive candidates at once.  The
+// decisions depend on how many were taken before (t_j = needed before j;
+// take j when u_j < t_j), but within 64 candidates t_j is at most 63 below
+// the step's t_0: u_j < t_0 - 63 is taken and u_j >= t_0 is not whatever
+// came before, and only the lanes in between are decided one after another,
+// in candidate order, with the count of takes below them.  Then t_j is known
+// for every lane, and the first j with t_j = n_e - j (every remaining one
+// needed) takes the rest.  Each u_j is below n_e < 2^31.
+constexpr uint64_t kGamma = 0x9e3779b97f4a7c15ull;
+
+// The candidates at or below n_e - 1 among the 64 from j0 on.
+__device__ __forceinline__ uint64_t tail_word(int64_t ne, int64_t j0) {
+  return ne - j0 >= 64 ? ~0ull : ~(~0ull << (ne - j0));
+}
+
+__device__ __forceinline__ void sample_library(const SampleJob& J,
+                                               int32_t* __restrict__ out_pool,
+                                               uint64_t* __restrict__ bit_pool) {
+  const int lane = threadIdx.x & 63;
+  uint64_t st = 0;
+  st = sm_mix(st ^ J.seed);
+  st = sm_mix(st ^ (uint64_t)(int64_t)J.E);
+  st = sm_mix(st ^ (uint64_t)(int64_t)J.tau);
+  st = sm_mix(st ^ (uint64_t)J.l_eff);
+  st = sm_mix(st ^ (uint64_t)(int64_t)J.r_index);
+  int32_t* __restrict__ out = out_pool + J.out_off;
+  const int64_t ne = J.n_e, le = J.l_eff;
+  const bool list = J.no_list == 0;
+  uint64_t* __restrict__ bits = J.bits > 0 ? bit_pool + (J.bits - 1) : nullptr;
+  const int64_t nw = (ne + 63) / 64;
+  uint64_t word = 0;                              // word 64 * (j0 / 4096) + lane
+  const uint64_t below_lane = lane == 0 ? 0ull : (~0ull >> (64 - lane));
+  int64_t s = 0;                                  // taken so far
+  int64_t j0 = 0;
+  for (; s < le && j0 < ne; j0 += 64) {
+    const int64_t j = j0 + lane;
+    const bool valid = j < ne;
+    int64_t u = 0;
+    if (valid)
+      u = (int64_t)__umul64hi(sm_mix(st + (uint64_t)(j + 1) * kGamma), (uint64_t)(ne - j));
+    const int64_t t0 = le - s;
+    uint64_t take = __builtin_amdgcn_ballot_w64(valid && u + 63 < t0);
+    uint64_t open = __builtin_amdgcn_ballot_w64(valid && u + 63 >= t0 && u < t0);
+    while (open) {                                // in candidate order
+      const int l = __builtin_ctzll(open);
+      open &= open - 1ull;
+      const int64_t tl = t0 - __popcll(take & ((1ull << l) - 1ull));
+      const int64_t ul = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)u, l);
+      if (ul < tl) take |= 1ull << l;
+    }
+    // the first candidate from which every remaining one is needed
+    const int64_t tj = t0 - __popcll(take & below_lane);
+    const uint64_t full = __builtin_amdgcn_ballot_w64(valid && tj == ne - j);
+    int64_t rest = -1;
+    if (full) {
+      const int l = __builtin_ctzll(full);
+      rest = j0 + l;
+      take &= (1ull << l) - 1ull;
+    }
+    if (list && ((take >> lane) & 1ull)) out[s + __popcll(take & below_lane)] = (int32_t)j;
+    s += __popcll(take);
+    if (rest >= 0) {
+      if (list)
+        for (int64_t k = lane; k < le - s; k += 64) out[s + k] = (int32_t)(rest + k);
+      s = le;
+      // candidates rest .. n_e - 1, all of them: to the end of the bitmap
+      take |= (~0ull << (rest - j0)) & tail_word(ne, j0);
+    }
+    if (bits) {
+      const int64_t x = j0 >> 6;
+      if (lane == (int)(x & 63)) word = take;
+      if ((x & 63) == 63) {
+        bits[x - 63 + lane] = word;
+        word = 0;
+      }
+      if (rest >= 0) {
+        // the words not yet stored of this 64, then the remaining ones
+        const int64_t y0 = (x & ~63ll) + ((x & 63) == 63 ? 64 : 0);
+        for (int64_t y = y0 + lane; y < nw; y += 64)
+          bits[y] = y <= x ? word : tail_word(ne, y * 64);
+        return;
+      }
+    }
+  }
+  if (bits) {
+    // every candidate is taken already: the pending words, then zeros
+    const int64_t x = j0 >> 6;                    // words formed
+    for (int64_t y = (x & ~63ll) + lane; y < nw; y += 64) bits[y] = y < x ? word : 0ull;
+  }
+}
+
+__global__ __launch_bounds__(256) void k_sample(const SampleJob* __restrict__ jobs,
+                                                int64_t n_jobs, int32_t* __restrict__ out_pool,
+                                                uint64_t* __restrict__ bit_pool) {
+  const int64_t id = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (id < n_jobs) sample_library(jobs[id], out_pool, bit_pool);
+}
+
+// ---------------------------------------------------------------------------
+// visiting orders
+// ---------------------------------------------------------------------------
+
 // Sum of v over the threads below this one of a workgroup of BLOCK, and the
 // sum over all of them.  One barrier: calls in a row take turns at two sets
 // of s_sum (turn 0 and 1).
@@ -211,7 +335,9 @@ __global__ __launch_bounds__(1024) void k_series_range(const OrderJob* __restric
 // stable), each wavefront over its share of the chunk.  The (key, time index)
 // go to out64 by rank (merged by k_merge_runs), or with one chunk per set the
 // indices to out32.  range: the sets' ranges (k_series_range), or null: taken
-// here.  Grid ((n / 64) rounded up, sets).
+// here.  Grid ((n / 64) rounded up, sets and slices of draws): the library
+// draws of a short call ride along, since neither needs the other (a launch of
+// its own: 7 us of a pair of 120 points, 16 of one of 777).
 //
 // Latency-bound at every size: the 4096^2 comparisons (two instructions each)
 // take 1 us over a chip's worth of wavefronts, while a bitonic network in one
@@ -224,10 +350,18 @@ __global__ __launch_bounds__(1024) void k_sort_chunks(const OrderJob* __restrict
                                                       const float* __restrict__ s32,
                                                       const float2* __restrict__ range,
                                                       int chunk, uint64_t* __restrict__ out64,
-                                                      int32_t* __restrict__ out32) {
+                                                      int32_t* __restrict__ out32, int n_sets,
+                                                      Draws draws) {
   __shared__ __align__(16) uint32_t key[kSortChunk];
   __shared__ float s_lo[16], s_hi[16];
   __shared__ int s_less[16][64];
+  if ((int)blockIdx.y >= n_sets) {                 // a wavefront per draw
+    const int64_t id = ((int64_t)(blockIdx.y - n_sets) * gridDim.x + blockIdx.x) *
+                           (blockDim.x / 64) +
+                       __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (id < draws.n) sample_library(draws.jobs[id], draws.out, draws.bits);
+    return;
+  }
   const OrderJob J = jobs[blockIdx.y];
   const float* __restrict__ s = s32 + J.src_off;
   const int tid = threadIdx.x;
@@ -619,122 +753,6 @@ __global__ __launch_bounds__(kBlock) void k_query_order(
   }
 }
 
-// ---------------------------------------------------------------------------
-// library subsamples
-// ---------------------------------------------------------------------------
-
-// SplitMix64 output mix (Steele, Lea & Flood, OOPSLA 2014).
-__device__ __forceinline__ uint64_t sm_mix(uint64_t z) {
-  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-  return z ^ (z >> 31);
-}
-
-// Selection sampling (Knuth, TAOCP Vol. 2, Sec. 3.4.2, Algorithm S): visit
-// candidates 0..n_e-1 in order and take candidate j with probability
-// (needed / remaining); the uniform integer below (n_e - j) is the high word of
-// the 64x64-bit product of one SplitMix64 draw with (n_e - j).  The stream of
-// a library is keyed by (seed, E, tau, L_eff, r) folded through the mix.
-// Once every remaining candidate is needed the rest are taken without draws:
-// the test would accept each of them whatever the draw.
-//
-// One wavefront per library.  The stream's state advances by the same
-// constant for every candidate visited, so candidate j's draw is the output
-// mix of (keyed state + (j+1) gamma): the 64 lanes form the draws and their
-// integers u_j below (n_e - j) of 64 consecutive candidates at once.  The
-// decisions depend on how many were taken before (t_j = needed before j;
-// take j when u_j < t_j), but within 64 candidates t_j is at most 63 below
-// the step's t_0: u_j < t_0 - 63 is taken and u_j >= t_0 is not whatever
-// came before, and only the lanes in between are decided one after another,
-// in candidate order, with the count of takes below them.  Then t_j is known
-// for every lane, and the first j with t_j = n_e - j (every remaining one
-// needed) takes the rest.  Each u_j is below n_e < 2^31.
-constexpr uint64_t kGamma = 0x9e3779b97f4a7c15ull;
-
-// The candidates at or below n_e - 1 among the 64 from j0 on.
-__device__ __forceinline__ uint64_t tail_word(int64_t ne, int64_t j0) {
-  return ne - j0 >= 64 ? ~0ull : ~(~0ull << (ne - j0));
-}
-
-__global__ __launch_bounds__(256) void k_sample(const SampleJob* __restrict__ jobs,
-                                                int64_t n_jobs, int32_t* __restrict__ out_pool,
-                                                uint64_t* __restrict__ bit_pool) {
-  const int lane = threadIdx.x & 63;
-  const int64_t id = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (id >= n_jobs) return;                       // the whole wavefront
-  const SampleJob J = jobs[id];
-  uint64_t st = 0;
-  st = sm_mix(st ^ J.seed);
-  st = sm_mix(st ^ (uint64_t)(int64_t)J.E);
-  st = sm_mix(st ^ (uint64_t)(int64_t)J.tau);
-  st = sm_mix(st ^ (uint64_t)J.l_eff);
-  st = sm_mix(st ^ (uint64_t)(int64_t)J.r_index);
-  int32_t* __restrict__ out = out_pool + J.out_off;
-  const int64_t ne = J.n_e, le = J.l_eff;
-  const bool list = J.no_list == 0;
-  uint64_t* __restrict__ bits = J.bits > 0 ? bit_pool + (J.bits - 1) : nullptr;
-  const int64_t nw = (ne + 63) / 64;
-  uint64_t word = 0;                              // word 64 * (j0 / 4096) + lane
-  const uint64_t below_lane = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-  int64_t s = 0;                                  // taken so far
-  int64_t j0 = 0;
-  for (; s < le && j0 < ne; j0 += 64) {
-    const int64_t j = j0 + lane;
-    const bool valid = j < ne;
-    int64_t u = 0;
-    if (valid)
-      u = (int64_t)__umul64hi(sm_mix(st + (uint64_t)(j + 1) * kGamma), (uint64_t)(ne - j));
-    const int64_t t0 = le - s;
-    uint64_t take = __builtin_amdgcn_ballot_w64(valid && u + 63 < t0);
-    uint64_t open = __builtin_amdgcn_ballot_w64(valid && u + 63 >= t0 && u < t0);
-    while (open) {                                // in candidate order
-      const int l = __builtin_ctzll(open);
-      open &= open - 1ull;
-      const int64_t tl = t0 - __popcll(take & ((1ull << l) - 1ull));
-      const int64_t ul = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)u, l);
-      if (ul < tl) take |= 1ull << l;
-    }
-    // the first candidate from which every remaining one is needed
-    const int64_t tj = t0 - __popcll(take & below_lane);
-    const uint64_t full = __builtin_amdgcn_ballot_w64(valid && tj == ne - j);
-    int64_t rest = -1;
-    if (full) {
-      const int l = __builtin_ctzll(full);
-      rest = j0 + l;
-      take &= (1ull << l) - 1ull;
-    }
-    if (list && ((take >> lane) & 1ull)) out[s + __popcll(take & below_lane)] = (int32_t)j;
-    s += __popcll(take);
-    if (rest >= 0) {
-      if (list)
-        for (int64_t k = lane; k < le - s; k += 64) out[s + k] = (int32_t)(rest + k);
-      s = le;
-      // candidates rest .. n_e - 1, all of them: to the end of the bitmap
-      take |= (~0ull << (rest - j0)) & tail_word(ne, j0);
-    }
-    if (bits) {
-      const int64_t x = j0 >> 6;
-      if (lane == (int)(x & 63)) word = take;
-      if ((x & 63) == 63) {
-        bits[x - 63 + lane] = word;
-        word = 0;
-      }
-      if (rest >= 0) {
-        // the words not yet stored of this 64, then the remaining ones
-        const int64_t y0 = (x & ~63ll) + ((x & 63) == 63 ? 64 : 0);
-        for (int64_t y = y0 + lane; y < nw; y += 64)
-          bits[y] = y <= x ? word : tail_word(ne, y * 64);
-        return;
-      }
-    }
-  }
-  if (bits) {
-    // every candidate is taken already: the pending words, then zeros
-    const int64_t x = j0 >> 6;                    // words formed
-    for (int64_t y = (x & ~63ll) + lane; y < nw; y += 64) bits[y] = y < x ? word : 0ull;
-  }
-}
-
 // Membership words of the libraries of walk groups: bit l of word j is set
 // when library l of the group holds embedded point j -- the transpose of the
 // libraries' bitmaps, 64 x 64 bits at a time, one library per lane.  Each
@@ -1021,8 +1039,9 @@ hipError_t launch_embed(const EmbedJob* jobs, int n_jobs, int64_t max_n,
 }
 
 hipError_t build_orders(const OrderJob* orders, int32_t n_sets, int levels, int64_t n_series,
-                        const float* s32, const float* emb, void* mem, hipStream_t st) {
-  if (n_sets <= 0) return hipSuccess;
+                        const float* s32, const float* emb, void* mem, hipStream_t st,
+                        const Draws& draws) {
+  if (n_sets <= 0) return draws.n > 0 ? hipErrorInvalidValue : hipSuccess;
   const int64_t n = n_series * n_sets;
   uint64_t* half[2] = {static_cast<uint64_t*>(mem), static_cast<uint64_t*>(mem) + n};
   int32_t* order = order_of(mem, n);
@@ -1046,8 +1065,17 @@ hipError_t build_orders(const OrderJob* orders, int32_t n_sets, int levels, int6
     const unsigned ny = (unsigned)std::min<int32_t>(65535, n_sets - s0);
     float2* const range = merges > 0 ? reinterpret_cast<float2*>(half[at ^ 1]) + s0 : nullptr;
     if (range) k_series_range<<<ny, 1024, 0, st>>>(orders + s0, s32, range);
-    k_sort_chunks<<<dim3(blocks, ny), threads, 0, st>>>(
-        orders + s0, s32, range, chunk, merges > 0 ? half[at] : nullptr, cur);
+    Draws d = s0 == 0 ? draws : Draws{};
+    const int64_t per = (int64_t)blocks * (threads / 64);
+    const int64_t slices = (d.n + per - 1) / per;
+    const bool ride = slices > 0 && ny + slices <= 65535;
+    if (slices > 0 && !ride) {
+      const hipError_t e = launch_sample(d.jobs, d.n, d.out, d.bits, st);
+      if (e != hipSuccess) return e;
+    }
+    if (!ride) d = Draws{};
+    k_sort_chunks<<<dim3(blocks, ny + (ride ? (unsigned)slices : 0u)), threads, 0, st>>>(
+        orders + s0, s32, range, chunk, merges > 0 ? half[at] : nullptr, cur, (int)ny, d);
   }
   for (int m = 0; m < merges; ++m) {
     const bool last = m + 1 == merges;

@@ -286,7 +286,13 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
   HIPCHK(launch_ingest(b.ingest, (int)p.ingest.size(), p.n64, b.s64, b.s32, st));
   HIPCHK(launch_embed(b.embed, (int)p.embed.size(), p.max_embed, b.s32, b.emb, st));
   if (p.spec.M > 0) HIPCHK(launch_transpose_targets(b.s64, p.spec.M, p.spec.N, b.tt, st));
-  HIPCHK(build_orders(b.orders, p.n_sets, p.kd_levels, p.spec.N, b.s32, b.emb, b.order_mem, st));
+  // the first wave's draws: in the side branch, with the orders' keys of a
+  // call of one short chain, or on their own
+  Draws draws;
+  if (!fork && !plain && !nested && p.spec.N <= 4096)
+    draws = {b.sample + p.waves[0].sample_first, p.waves[0].sample_count, b.lib, b.bits};
+  HIPCHK(build_orders(b.orders, p.n_sets, p.kd_levels, p.spec.N, b.s32, b.emb, b.order_mem, st,
+                      draws));
   HIPCHK(launch_query_order(b.embed, (int)p.embed.size(), p.spec.N, b.order, b.qord, st));
   for (int E = 1; E <= kMaxE; ++E)
     HIPCHK(launch_table_build(E, b.tables + p.te_first[E], p.te_count[E], p.te_max_ne[E], b.emb,
@@ -298,7 +304,7 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
     if (!plain) {
       // forked: the gather and the scans in the side branch, the walks here
       const hipStream_t side = fork ? fork->side : st;
-      if (!fork || wi > 0) draw(w, st);
+      if (wi > 0 || (!fork && draws.n == 0)) draw(w, st);
       if (fork) {
         if (wi == 0) fork->after(st, side);
         fork->after(side, st);
