@@ -61,8 +61,10 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "crossmap_sweep_coupled_logistic_N
 KERNEL_SOURCES = ["paper_1905_00565_amd/csrc/ccm_device.h",
                   "paper_1905_00565_amd/csrc/ccm_inst.hip",
                   "paper_1905_00565_amd/csrc/ccm_inst_multi.hip",
+                  "paper_1905_00565_amd/csrc/ccm_inst_walk.hip",
                   "paper_1905_00565_amd/csrc/ccm_internal.h",
-                  "paper_1905_00565_amd/csrc/ccm_tune.h"]
+                  "paper_1905_00565_amd/csrc/ccm_tune.h",
+                  "paper_1905_00565_amd/csrc/ccm_walk.h"]
 
 
 def kernel_sources_sha256() -> str:
@@ -662,7 +664,14 @@ def main():
                    "predictions_per_step": preds / a.steps},
         "roofline": {
             "bound": "alu",
-            "kernel": "k_crossmap (fused distance/top-(E+1)/predict/moments)",
+            "kernel": "cross map (k_crossmap scans small libraries; k_rows, k_walk and "
+                      "k_walk_moments serve the others)",
+            # 3E-1 per (query, library point) pair of the method's definition.  A
+            # walked library's pairs are not evaluated one by one (a query's row is
+            # built once for every library), so achieved counts the work
+            # answered, not executed, and frac may exceed 1.
+            "flops_counted": "3E-1 per (query, library point) pair of the definition, "
+                             "whether evaluated or answered from a neighbour row",
             "achieved": achieved_tflops,
             "peak": FP32_VECTOR_PEAK_TFLOPS,
             "unit": "TFLOP/s",
