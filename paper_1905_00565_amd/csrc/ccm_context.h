@@ -91,8 +91,7 @@ struct Exec {
   DevBuf d_tt;       // causal matrix: targets time-major [N][target_stride(M)]
   DevBuf d_tables, d_table;   // distance indexing table jobs and rows
   DevBuf d_nested, d_scratch, d_segs, d_rz_fin;   // nested libraries
-  DevBuf d_row_jobs, d_mask_jobs, d_walk_libs, d_walk_groups, d_walk_items, d_mom_items,
-      d_walk_where, d_rows, d_bits, d_masks, d_opts, d_boxes, d_todo, d_walk_out;   // neighbour rows
+  DevBuf d_walk;     // neighbour rows: descriptors and pools
   std::vector<int64_t> plain_first;   // per realization: first plain item
   PlanBuffers buf;
   hipGraphExec_t graph = nullptr;

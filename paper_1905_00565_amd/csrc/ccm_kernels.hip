@@ -341,9 +341,9 @@ __global__ __launch_bounds__(1024) void k_series_range(const OrderJob* __restric
 //
 // Latency-bound at every size: the 4096^2 comparisons (two instructions each)
 // take 1 us over a chip's worth of wavefronts, while a bitonic network in one
-// workgroup's LDS has 78 dependent steps (two chunks per set: 42 us, here 18)
-// and a radix sort with one workgroup per set took 132 us there, and 2.0 ms
-// for two sets of 10^5 (here 0.09 with the merges).
+// workgroup's LDS has 78 dependent steps.  Two sets of 5003 points: a radix
+// sort with one workgroup per set 132 us, bitonic chunks of 4096 and a merge
+// 47, here 12 and three merges of 5; two of 10^5: 2.0 ms and 0.09.
 constexpr int kSortChunk = 4096;
 
 __global__ __launch_bounds__(1024) void k_sort_chunks(const OrderJob* __restrict__ jobs,
@@ -797,7 +797,7 @@ __global__ __launch_bounds__(kBlock) void k_masks(const MaskJob* __restrict__ jo
 // steps in a mask, and runs of steps free of each other swap at once.  With
 // the positions in LDS (CAP of them) a run costs a few hundred cycles and
 // 64 steps of 10^4 points take one or two; one lane in global memory took
-// 0.29 us a step (2.9 ms for 10^4 points, here 0.2).
+// 0.29 us a step (2.9 ms for 10^4 points, here 0.33).
 template <int CAP>
 __global__ __launch_bounds__(kBlock) void k_sample_nested(const NestedJob* __restrict__ jobs,
                                                           const int32_t* __restrict__ seg_pool,

@@ -98,21 +98,52 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
     upload(ex->d_segs, p.segs);
   }
   if (!p.rz_fin.empty()) upload(ex->d_rz_fin, p.rz_fin);
+  PlanBuffers& b = ex->buf;
   if (!p.walk_groups.empty()) {
-    upload(ex->d_row_jobs, p.row_jobs);
-    upload(ex->d_mask_jobs, p.mask_jobs);
-    upload(ex->d_walk_libs, p.walk_libs);
-    upload(ex->d_walk_groups, p.walk_groups);
-    upload(ex->d_walk_items, p.walk_items);
-    upload(ex->d_mom_items, p.mom_items);
-    upload(ex->d_walk_where, p.walk_out);
-    ex->d_rows.ensure(p.n_rows * 8);
-    ex->d_bits.ensure(p.n_bits * 8);
-    ex->d_masks.ensure(p.n_mask * 8);
-    ex->d_opts.ensure(p.n_opts * 4);
-    ex->d_boxes.ensure(p.n_box * 4);
-    ex->d_todo.ensure(256 + p.n_todo * sizeof(RowTodo));
-    ex->d_walk_out.ensure(p.n_walk_out * 8);
+    // the descriptors and pools of the walks in one allocation, the
+    // descriptors in one copy (a small plan's first call is mostly these)
+    uint64_t o = 0;
+    const auto take = [&](uint64_t bytes) {
+      const uint64_t at = o;
+      o = (o + bytes + 255) / 256 * 256;
+      return at;
+    };
+    std::vector<std::pair<uint64_t, std::pair<const void*, size_t>>> desc;
+    const auto put = [&](const auto& v) {
+      const size_t bytes = v.size() * sizeof(v[0]);
+      const uint64_t at = take(bytes);
+      desc.push_back({at, {v.data(), bytes}});
+      return at;
+    };
+    const uint64_t row_jobs = put(p.row_jobs), mask_jobs = put(p.mask_jobs),
+                   walk_libs = put(p.walk_libs), walk_groups = put(p.walk_groups),
+                   walk_items = put(p.walk_items), mom_items = put(p.mom_items),
+                   walk_where = put(p.walk_out);
+    std::vector<char> host(o);
+    for (const auto& d : desc)
+      if (d.second.second) std::memcpy(host.data() + d.first, d.second.first, d.second.second);
+    const uint64_t rows = take(p.n_rows * 8), bits = take(p.n_bits * 8),
+                   masks = take(p.n_mask * 8), opts = take(p.n_opts * 4),
+                   boxes = take(p.n_box * 4), todo = take(256 + p.n_todo * sizeof(RowTodo)),
+                   walk_out = take(p.n_walk_out * 8);
+    ex->d_walk.ensure(o);
+    char* const base = ex->d_walk.as<char>();
+    HIPCHK(hipMemcpy(base, host.data(), host.size(), hipMemcpyHostToDevice));
+    b.row_jobs = reinterpret_cast<RowJob*>(base + row_jobs);
+    b.mask_jobs = reinterpret_cast<MaskJob*>(base + mask_jobs);
+    b.walk_libs = reinterpret_cast<WalkLib*>(base + walk_libs);
+    b.walk_groups = reinterpret_cast<WalkGroup*>(base + walk_groups);
+    b.walk_items = reinterpret_cast<Item*>(base + walk_items);
+    b.mom_items = reinterpret_cast<Item*>(base + mom_items);
+    b.walk_where = reinterpret_cast<WalkOut*>(base + walk_where);
+    b.rows = reinterpret_cast<uint64_t*>(base + rows);
+    b.bits = reinterpret_cast<uint64_t*>(base + bits);
+    b.masks = reinterpret_cast<uint64_t*>(base + masks);
+    b.opts = reinterpret_cast<float*>(base + opts);
+    b.boxes = reinterpret_cast<float*>(base + boxes);
+    b.todo_n = reinterpret_cast<int*>(base + todo);
+    b.todo = reinterpret_cast<RowTodo*>(base + todo + 256);
+    b.walk_out = reinterpret_cast<double*>(base + walk_out);
   }
   ex->d_s64.ensure(p.n64 * 8);
   ex->d_s32.ensure(p.n32 * 4);
@@ -132,7 +163,6 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   }
   ex->d_out.ensure(p.n_out * 8);
   ex->d_counter.ensure(std::max<size_t>(64, p.launches.size()) * sizeof(int));
-  PlanBuffers& b = ex->buf;
   b.ingest = ex->d_ingest.as<IngestJob>();
   b.embed = ex->d_embed.as<EmbedJob>();
   b.sample = ex->d_sample.as<SampleJob>();
@@ -162,21 +192,6 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   b.shuffle = ex->d_scratch.as<int32_t>();
   b.segs = ex->d_segs.as<int32_t>();
   b.rz_fin = ex->d_rz_fin.as<Realization>();
-  b.row_jobs = ex->d_row_jobs.as<RowJob>();
-  b.mask_jobs = ex->d_mask_jobs.as<MaskJob>();
-  b.walk_libs = ex->d_walk_libs.as<WalkLib>();
-  b.walk_groups = ex->d_walk_groups.as<WalkGroup>();
-  b.walk_items = ex->d_walk_items.as<Item>();
-  b.mom_items = ex->d_mom_items.as<Item>();
-  b.walk_where = ex->d_walk_where.as<WalkOut>();
-  b.rows = ex->d_rows.as<uint64_t>();
-  b.bits = ex->d_bits.as<uint64_t>();
-  b.masks = ex->d_masks.as<uint64_t>();
-  b.opts = ex->d_opts.as<float>();
-  b.boxes = ex->d_boxes.as<float>();
-  b.todo_n = ex->d_todo.as<int>();
-  b.todo = reinterpret_cast<RowTodo*>(ex->d_todo.as<char>() + 256);
-  b.walk_out = ex->d_walk_out.as<double>();
   c->exec = std::move(ex);
   return c->exec.get();
 }
