@@ -59,6 +59,7 @@ struct PlanBuffers {
   RowTodo* todo = nullptr;
   int* todo_n = nullptr;
   double* walk_out = nullptr;
+  double* pred = nullptr;            // predictions of spread launches
 };
 
 // The side branch of a captured plan.
@@ -85,7 +86,7 @@ struct Fork {
 struct Exec {
   Plan plan;
   DevBuf d_ingest, d_embed, d_sample, d_gather, d_rz, d_items, d_plain_items;
-  DevBuf d_s64, d_s32, d_emb, d_lib, d_pts, d_pj, d_partial, d_out, d_counter;
+  DevBuf d_s64, d_s32, d_emb, d_lib, d_pts, d_pred, d_pj, d_partial, d_out, d_counter;
   DevBuf d_order, d_qord, d_start, d_self;
   DevBuf d_orders;
   DevBuf d_tt;       // causal matrix: targets time-major [N][target_stride(M)]

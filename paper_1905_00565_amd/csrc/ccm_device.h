@@ -1326,6 +1326,88 @@ __attribute__((amdgpu_waves_per_eu(kTuneW[E] > 0 ? kTuneW[E] : 1, 8))) void k_cr
   }
 }
 
+// A launch with few items leaves most of the chip idle while each wavefront
+// takes Q queries per lane through the whole library.  Here wavefront m of
+// workgroup 4 item + v takes the m-th 64 queries of the item's run v, one per
+// lane, and leaves the predictions at pred[item * 256 Q + place in the tile];
+// k_item_moments then forms the tile's moments as crossmap_item does.  Bound by
+// the serial pass over the library: 198 libraries of a pair of 777 points at E =
+// 3 take 40 us and the moments 7, a tile per workgroup 122.
+template <int E, int Q, int MODE>
+__global__ __launch_bounds__(64 * Q) void k_scan_spread(
+    const Realization* __restrict__ rzs, const Item* __restrict__ items,
+    const float* __restrict__ emb_pool, const float* __restrict__ pts_pool,
+    const int32_t* __restrict__ pj_pool, const int32_t* __restrict__ qord_pool,
+    const int32_t* __restrict__ start_pool, const double* __restrict__ tgt_pool,
+    double* __restrict__ pred_pool, int query_set, int window) {
+  constexpr int K = E + 1;
+  constexpr int QT = kBlock * Q;
+  constexpr int QW = 64 * Q;
+  const int item = (int)blockIdx.x / kWaves;
+  const int run = (int)blockIdx.x % kWaves;
+  const Item I = items[item];
+  const Realization R = rzs[I.rz];
+  const int lane = threadIdx.x & 63;
+  const int m = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int at = run * QW + m * 64;                // place of the 64 in the tile
+  if (I.tile * QT + at >= R.n_query) return;       // no barrier below
+  const float* __restrict__ emb = emb_pool + R.emb_off;
+  const int32_t* __restrict__ pj = pj_pool + R.pj_off;
+  const double* __restrict__ tgt = tgt_pool + R.tgt_off + (int64_t)(E - 1) * R.tau;
+  const int qq = I.tile * QT + at + lane;
+  const bool valid = qq < R.n_query;
+  ScanState<E, 1, MODE> S;
+  const int i = valid ? (query_set ? pj[qq] : qord_pool[R.qord_off + qq]) : 0;
+  S.qi[0] = valid ? i : -1;
+#pragma unroll
+  for (int k = 0; k < E; ++k) S.qc[0][k] = emb[(int64_t)i * E + k];
+#pragma unroll
+  for (int s = 0; s < Slots<E, MODE>::KS; ++s) S.key[0][s] = empty_key();
+  const int s0 = query_set ? min(I.tile * QT + run * QW + QW / 2, R.l_eff - 1)
+                           : start_pool[(R.slot_base + I.tile) * kWaves + run];
+  scan_range<E, 1, MODE>(pts_pool + R.pts_off, pj, R.l_eff, s0, window, S);
+  if (!valid) return;
+  float nd[K];
+  int32_t nj[K];
+  select_neighbors<E, 1, MODE>(S, 0, nd, nj);
+  double w[K];
+  simplex_weights<K>(nd, w);
+  double pred = 0.0;
+#pragma unroll
+  for (int t = 0; t < K; ++t) pred += w[t] * tgt[nj[t]];
+  pred_pool[(int64_t)item * QT + at + lane] = pred;
+}
+
+template <int Q>
+__global__ __launch_bounds__(kBlock) void k_item_moments(
+    const Realization* __restrict__ rzs, const Item* __restrict__ items,
+    const double* __restrict__ pred_pool, const int32_t* __restrict__ pj_pool,
+    const int32_t* __restrict__ qord_pool, const double* __restrict__ tgt_pool,
+    Moments* __restrict__ partial, int query_set) {
+  __shared__ Moments red[kBlock];
+  const Item I = items[blockIdx.x];
+  const Realization R = rzs[I.rz];
+  const int tid = threadIdx.x;
+  const double* __restrict__ tgt = tgt_pool + R.tgt_off + (int64_t)(R.E - 1) * R.tau;
+  const int32_t* __restrict__ q = query_set ? pj_pool + R.pj_off : qord_pool + R.qord_off;
+  const double* __restrict__ pr = pred_pool + (int64_t)blockIdx.x * (kBlock * Q);
+  Moments mo = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int m = 0; m < Q; ++m) {
+    const int at = (tid >> 6) * (64 * Q) + m * 64 + (tid & 63);
+    const int qq = I.tile * (kBlock * Q) + at;
+    if (qq < R.n_query) mom_add(mo, tgt[q[qq]], pr[at]);
+  }
+  red[tid] = mo;
+  __syncthreads();
+#pragma unroll
+  for (int s = kBlock / 2; s > 0; s >>= 1) {
+    if (tid < s) red[tid] = mom_merge(red[tid], red[tid + s]);
+    __syncthreads();
+  }
+  if (tid == 0) partial[R.slot_base + I.tile] = red[0];
+}
+
 // Causal-matrix form: realization rz searches the manifold of series
 // R.emb_off's owner (index self_of[rz]) and predicts all m_series series.
 template <int E, int Q, int MODE, bool TBL>

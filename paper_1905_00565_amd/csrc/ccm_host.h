@@ -93,12 +93,15 @@ struct Spec {
   // Whether realizations may walk neighbour rows where that is cheaper than
   // the scan (the batched calls; not the served and no-allocation forms).
   bool walk = false;
+  // Whether launches of few items spread their queries (the same and the
+  // no-allocation form).
+  bool spread = false;
 
   bool operator==(const Spec& o) const {
     return M == o.M && N == o.N && E == o.E && tau == o.tau && L == o.L && r == o.r &&
            seed == o.seed && excl == o.excl && query_set == o.query_set &&
            (flags & ~CCM_FLAG_NO_GRAPH) == (o.flags & ~CCM_FLAG_NO_GRAPH) &&
-           wave_limit == o.wave_limit && walk == o.walk;
+           wave_limit == o.wave_limit && walk == o.walk && spread == o.spread;
   }
 };
 
@@ -140,6 +143,7 @@ struct Launch {
   int32_t batch_first = 0, batch_count = 0;                  // into Plan::walk_batches
   int32_t walk_per = 0;                                      // queries per walk item
   int32_t sub_first = 0, sub_count = 0;   // into Plan::sub_launches
+  bool spread = false;                    // few items: 64 queries per wavefront
 };
 
 // A wave: realizations whose drawn libraries and gathered points are live at
@@ -190,6 +194,7 @@ struct Plan {
   std::vector<int64_t> wave_rz_first; // per wave, into wave_rz (+1 sentinel)
   std::vector<Item> items;
   int64_t n_slots = 0;
+  int64_t n_pred = 0;                 // predictions of the largest spread launch
   int64_t n_out = 0;
   std::vector<int64_t> L_eff;   // per (iE, itau, iL)
   double pairs = 0, flops = 0, preds = 0;

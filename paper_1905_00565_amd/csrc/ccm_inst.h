@@ -16,6 +16,13 @@ hipError_t launch_crossmap_e(int mode, int grid, const Realization* rzs, const I
                              Dump d, const int32_t* table, int table_n_e, hipStream_t st);
 
 template <int E>
+hipError_t launch_spread_e(int mode, const Realization* rzs, const Item* items, int n_items,
+                           const float* emb, const float* pts, const int32_t* pj,
+                           const int32_t* qord, const int32_t* start, const double* tgt,
+                           double* pred, Moments* partial, int query_set, int window,
+                           hipStream_t st);
+
+template <int E>
 hipError_t launch_multi_e(int mode, int grid, const Realization* rzs, const int32_t* self_of,
                           const Item* items, int n_items, int* next, const float* emb,
                           const float* pts, const int32_t* pj, const int32_t* qord,

@@ -48,6 +48,28 @@ hipError_t launch_crossmap_e(int mode, int grid, const Realization* rzs, const I
 }
 
 template <int E>
+hipError_t launch_spread_e(int mode, const Realization* rzs, const Item* items, int n_items,
+                           const float* emb, const float* pts, const int32_t* pj,
+                           const int32_t* qord, const int32_t* start, const double* tgt,
+                           double* pred, Moments* partial, int query_set, int window,
+                           hipStream_t st) {
+  constexpr int Q = DefaultQ<E>::Q;
+  const auto f = mode == kExclSelf   ? k_scan_spread<E, Q, kExclSelf>
+                 : mode == kKeepSelf ? k_scan_spread<E, Q, kKeepSelf>
+                                     : k_scan_spread<E, Q, kWindow>;
+  f<<<(unsigned)n_items * kWaves, 64 * Q, 0, st>>>(rzs, items, emb, pts, pj, qord, start, tgt,
+                                                   pred, query_set, window);
+  k_item_moments<Q><<<(unsigned)n_items, kBlock, 0, st>>>(rzs, items, pred, pj, qord, tgt,
+                                                          partial, query_set);
+  return hipGetLastError();
+}
+
+template hipError_t launch_spread_e<CCM_INST_E>(int, const Realization*, const Item*, int,
+                                                const float*, const float*, const int32_t*,
+                                                const int32_t*, const int32_t*, const double*,
+                                                double*, Moments*, int, int, hipStream_t);
+
+template <int E>
 hipError_t launch_nested_e(int mode, int grid, const Realization* rzs, const Item* items,
                            int n_items, int* next, const float* emb, const float* pts,
                            const int32_t* pj, const int32_t* qord, const int32_t* start,

@@ -277,6 +277,14 @@ hipError_t launch_crossmap(int E, int mode, int grid,
                            const double* tgt, Moments* partial, int query_set,
                            int window, Dump d, const int32_t* table, int table_n_e,
                            hipStream_t st);
+// The same for a launch of few items (pairs, no tables, no export): 64 queries
+// per wavefront, then the tiles' moments; pred: 256 * queries per lane doubles
+// per item.
+hipError_t launch_spread(int E, int mode, const Realization* rzs, const Item* items, int n_items,
+                           const float* emb, const float* pts, const int32_t* pj,
+                           const int32_t* qord, const int32_t* start, const double* tgt,
+                           double* pred, Moments* partial, int query_set, int window,
+                           hipStream_t st);
 // Distance indexing tables (Section 3.2), one launch per E: grid
 // (max_n_e, n_jobs); rows of job k at table + jobs[k].out_off.
 hipError_t launch_table_build(int E, const TableJob* jobs, int n_jobs, int max_n_e,

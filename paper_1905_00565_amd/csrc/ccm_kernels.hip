@@ -1198,6 +1198,19 @@ hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* 
 #undef CCM_CALL
 }
 
+hipError_t launch_spread(int E, int mode, const Realization* rzs, const Item* items, int n_items,
+                           const float* emb, const float* pts, const int32_t* pj,
+                           const int32_t* qord, const int32_t* start, const double* tgt,
+                           double* pred, Moments* partial, int query_set, int window,
+                           hipStream_t st) {
+  if (n_items <= 0) return hipSuccess;
+#define CCM_CALL(e)                                                                       \
+  launch_spread_e<e>(mode, rzs, items, n_items, emb, pts, pj, qord, start, tgt, pred, partial, \
+                     query_set, window, st)
+  CCM_BY_E(E, CCM_CALL)
+#undef CCM_CALL
+}
+
 hipError_t launch_walk_moments(int E, int shared, const Realization* rzs, const WalkOut* where,
                                const Item* items, int n_items, const double* out,
                                const int32_t* pj, const int32_t* qord, const double* tgt,

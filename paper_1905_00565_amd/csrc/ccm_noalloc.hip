@@ -62,8 +62,9 @@ extern "C" ccm_status ccm_dev_noalloc(ccm_ctx* c, const double* X, const double*
     if (s.flags & ~CCM_FLAG_NO_GRAPH)
       fail(CCM_E_INVAL, "the no-allocation form runs the default batched launches only");
     s.flags = 0;
+    s.spread = true;
     s.wave_limit = 0;   // one wave: the workspace bound is checked below
-    const Plan p = make_plan(s);
+    Plan p = make_plan(s);
     char* base = workspace(c->device);
     if (!base) fail(CCM_E_DEVICE, "no workspace on this device");
 
@@ -96,6 +97,11 @@ extern "C" ccm_status ccm_dev_noalloc(ccm_ctx* c, const double* X, const double*
     b.partial = take((uint64_t)p.n_slots * sizeof(Moments));
     b.out = reinterpret_cast<double*>(take(p.n_out * 8));
     b.counter = reinterpret_cast<int*>(take(std::max<size_t>(64, p.launches.size()) * 4));
+    const uint64_t pred_bytes = (uint64_t)p.n_pred * 8;
+    if (pred_bytes > 0 && up256(o + pred_bytes) <= kWorkspaceBytes)
+      b.pred = reinterpret_cast<double*>(take(pred_bytes));
+    else
+      for (Launch& la : p.launches) la.spread = false;
     if (o > kWorkspaceBytes)
       fail(CCM_E_NOMEM, "the call needs " + std::to_string(o) +
                             " bytes of workspace; the static workspace holds " +

@@ -269,6 +269,14 @@ constexpr int64_t kRowPoolCap = 2ll << 30;
 constexpr int64_t kWalkOutBytes = 512ll << 20;
 constexpr int64_t kWalkKeyBytes = 1ll << 30;
 constexpr int64_t kMultiMinItems = 1024;
+// Launches of scans that spread their queries over more wavefronts: at most
+// two wavefronts per SIMD otherwise, and a serial scan that outweighs the
+// second launch's 6 us, in instructions per lane (198 libraries of a pair of 777
+// points, up to 770 at E = 3: scan 122 us, spread 40 + 7; 119 points at E = 2:
+// 27 and 10 + 6; 46 to 87 points: calls 5 to 10 us longer).  Beside walks the
+// scan is not what the call waits for (5003 points at E = 7: 543 and 556 us).
+constexpr int32_t kSpreadItems = 512;
+constexpr double kSpreadMinWork = 2500.0;
 
 // Row entries that hold, all but about once in 10^7, the first E+1 acceptable
 // members of a library of le of ne points: a member turns up every ne / le
@@ -788,6 +796,18 @@ static void order_items(Plan& p) {
         la.count += R.n_tiles;
         if (p.items.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many work items");
       }
+      // few items: each lane's queries spread over more wavefronts
+      int64_t l_max = 0;
+      for (int32_t x = la.first; x < la.first + la.count; ++x)
+        l_max = std::max<int64_t>(l_max, p.rz[p.items[x].rz].l_eff);
+      const int q = crossmap_queries_per_lane(la.E);
+      la.spread = p.spec.spread && p.spec.M == 0 && p.nested.empty() && p.shared_emax == 0 &&
+                  p.tables.empty() && la.batch_count == 0 && la.count > 0 &&
+                  la.count <= kSpreadItems &&
+                  (double)l_max * (2 * la.E + 4) * (q - 1) >= kSpreadMinWork;
+      if (la.spread)
+        p.n_pred = std::max(p.n_pred,
+                            (int64_t)la.count * kBlock * q);
       p.launches.push_back(la);
     }
     p.waves[w].launch_count = (int32_t)p.launches.size() - p.waves[w].launch_first;
@@ -968,7 +988,7 @@ static Plan make_plan_nested(const Spec& s) {
   p.n_rho = (int64_t)p.rz_fin.size();
   if (p.rz.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many realizations");
   order_items(p);
-  p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 +
+  p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 + p.n_pred * 8 +
                    p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    (size_t)p.n_ord * 16 + p.n_scratch * 4 + p.segs.size() * 4 +
                    p.n_slots * sizeof(Moments) + p.n_out * 8 +
@@ -1084,7 +1104,7 @@ static Plan make_plan_shared(const Spec& s) {
   p.n_rho = (int64_t)p.rz_fin.size();
   if (p.rz.size() > (size_t)INT32_MAX) fail(CCM_E_INVAL, "too many realizations");
   order_items(p);
-  p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 +
+  p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 + p.n_pred * 8 +
                    p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    (size_t)p.n_ord * 16 + p.n_slots * sizeof(Moments) + p.n_out * 8 +
                    (p.rz.size() + p.rz_fin.size()) * sizeof(Realization) +
@@ -1223,7 +1243,7 @@ Plan make_plan(const Spec& s) {
 
   order_items(p);
 
-  p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 +
+  p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_emb * 4 + p.n_lib * 4 + p.n_pts * 4 + p.n_pred * 8 +
                    p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    (size_t)p.n_ord * 16 + p.n_table * 4 + p.tables.size() * sizeof(TableJob) +
                    p.n_slots * sizeof(Moments) + p.n_out * 8 +
@@ -1353,7 +1373,7 @@ Plan make_plan_matrix(const Spec& s) {
   p.n_rho = (int64_t)p.rz.size() * (M - 1);
   order_items(p);
   p.device_bytes = p.n64 * 8 + p.n32 * 4 + p.n_ord * 16 + p.n_emb * 4 + p.n_lib * 4 +
-                   p.n_pts * 4 +
+                   p.n_pts * 4 + p.n_pred * 8 +
                    p.n_pj * 4 + p.n_qord * 4 + p.n_slots * 4 * kWaves +
                    p.n_slots * M * multi_sums_bytes() + p.n_out * 8 +
                    N * target_stride(M) * 8 + p.n_table * 4 +

@@ -153,6 +153,7 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   ex->d_emb.ensure(p.n_emb * 4);
   ex->d_lib.ensure(p.n_lib * 4);
   ex->d_pts.ensure(p.n_pts * 4);
+  if (p.n_pred) ex->d_pred.ensure(p.n_pred * 8);
   ex->d_pj.ensure(p.n_pj * 4);
   if (s.M > 0) {
     upload(ex->d_self, p.self_of);
@@ -180,6 +181,7 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   b.emb = ex->d_emb.as<float>();
   b.lib = ex->d_lib.as<int32_t>();
   b.pts = ex->d_pts.as<float>();
+  b.pred = ex->d_pred.as<double>();
   b.pj = ex->d_pj.as<int32_t>();
   b.partial = ex->d_partial.p;
   b.out = ex->d_out.as<double>();
@@ -246,7 +248,8 @@ void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStrea
 // b.plain_items), E's kernel variant for the plan's form, after the walks of
 // `walks` (null: none).
 void launch_items(ccm_ctx* c, const Plan& p, const PlanBuffers& b, const Item* items, int n,
-                  int E, int grid, int* next, int table_ne, const Launch* walks, hipStream_t st,
+                  int E, int grid, int* next, int table_ne, bool spread, const Launch* walks,
+                  hipStream_t st,
                   std::vector<EvPair>* evs) {
   EvPair ev;
   if (evs) {
@@ -267,6 +270,10 @@ void launch_items(ccm_ctx* c, const Plan& p, const PlanBuffers& b, const Item* i
     HIPCHK(launch_crossmap_multi(E, p.mode, grid, b.rz, b.self, items, n, next, b.emb, b.pts,
                                  b.pj, b.qord, b.start, b.tt, p.spec.M, b.partial,
                                  p.spec.query_set, p.window, b.table, table_ne, st));
+  else if (spread)
+    HIPCHK(launch_spread(E, p.mode, b.rz, items, n, b.emb, b.pts, b.pj, b.qord, b.start, b.s64,
+                         b.pred, static_cast<Moments*>(b.partial), p.spec.query_set, p.window,
+                         st));
   else
     HIPCHK(launch_crossmap(E, p.mode, grid, b.rz, items, n, next, b.emb, b.pts, b.pj, b.qord,
                            b.start, b.s64, static_cast<Moments*>(b.partial), p.spec.query_set,
@@ -339,7 +346,7 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
         }
         if (fork) launch_walks(p, b, L, st);
         launch_items(c, p, b, b.items + L.first, L.count, L.E, grid, next, p.e_table_ne[L.E],
-                     fork ? nullptr : &L, side, evs);
+                     L.spread && !persistent, fork ? nullptr : &L, side, evs);
       }
       if (fork) fork->after(st, side);
     } else {
@@ -358,7 +365,7 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
         HIPCHK(launch_gather(b.gather + p.rz_gather[r], 1, G.sorted ? G.n_e : 0, b.emb, b.lib,
                              b.order, b.pts, b.pj, b.start, st));
         launch_items(c, p, b, b.plain_items + plain_first[r], R.n_tiles, R.E, R.n_tiles,
-                     nullptr, R.table_off >= 0 ? R.n_e : 0, nullptr, st, evs);
+                     nullptr, R.table_off >= 0 ? R.n_e : 0, false, nullptr, st, evs);
       }
     }
   }
@@ -548,7 +555,7 @@ ccm_status ccm_sweep(ccm_ctx* c, const double* X, const double* Y, int64_t N,
     if (!rho) fail(CCM_E_INVAL, "rho is NULL");
     Spec s = make_spec(N, E, nE, tau, ntau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
-    s.walk = walks(s);
+    s.walk = s.spread = walks(s);
     check_host_series(X, N, "X");
     check_host_series(Y, N, "Y");
     Exec* ex = prepare(c, s);
@@ -569,7 +576,7 @@ ccm_status ccm(ccm_ctx* c, const double* X, const double* Y, int64_t N, int32_t 
     if (!rho_xy || !rho_yx) fail(CCM_E_INVAL, "rho output is NULL");
     Spec s = make_spec(N, &E, 1, &tau, 1, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
-    s.walk = walks(s);
+    s.walk = s.spread = walks(s);
     check_host_series(X, N, "X");
     check_host_series(Y, N, "Y");
     Exec* ex = prepare(c, s);
@@ -594,7 +601,7 @@ ccm_status ccm_sweep_dev(ccm_ctx* c, const double* X, const double* Y, int64_t N
     if (!X || !Y || !rho) fail(CCM_E_INVAL, "NULL device pointer");
     Spec s = make_spec(N, E, nE, tau, ntau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
-    s.walk = walks(s);
+    s.walk = s.spread = walks(s);
     hipStream_t st = static_cast<hipStream_t>(stream);
     Exec* ex = prepare(c, s);
     HIPCHK(launch_copy_pair(X, Y, N, ex->d_s64.as<double>(), st));
@@ -611,7 +618,7 @@ ccm_status ccm_dev(ccm_ctx* c, const double* X, const double* Y, int64_t N, int3
     if (!X || !Y || !rho_xy || !rho_yx) fail(CCM_E_INVAL, "NULL device pointer");
     Spec s = make_spec(N, &E, 1, &tau, 1, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
-    s.walk = walks(s);
+    s.walk = s.spread = walks(s);
     hipStream_t st = static_cast<hipStream_t>(stream);
     Exec* ex = prepare(c, s);
     HIPCHK(launch_copy_pair(X, Y, N, ex->d_s64.as<double>(), st));
@@ -630,7 +637,7 @@ ccm_status ccm_matrix(ccm_ctx* c, const double* S, int32_t M, int64_t N, int32_t
     if (!rho) fail(CCM_E_INVAL, "rho is NULL");
     Spec s = make_matrix_spec(M, N, E, tau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
-    s.walk = walks(s);
+    s.walk = s.spread = walks(s);
     check_host_series(S, (int64_t)M * N, "S");
     Exec* ex = prepare(c, s);
     const int64_t n_out = ex->plan.n_out;
@@ -650,7 +657,7 @@ ccm_status ccm_matrix_dev(ccm_ctx* c, const double* S, int32_t M, int64_t N, int
     if (!S || !rho) fail(CCM_E_INVAL, "NULL device pointer");
     Spec s = make_matrix_spec(M, N, E, tau, L, nL, r, seed, opts);
     s.wave_limit = c->wave_limit;
-    s.walk = walks(s);
+    s.walk = s.spread = walks(s);
     hipStream_t st = static_cast<hipStream_t>(stream);
     Exec* ex = prepare(c, s);
     HIPCHK(hipMemcpyAsync(ex->d_s64.p, S, (size_t)M * N * 8, hipMemcpyDeviceToDevice, st));
