@@ -339,7 +339,8 @@ __device__ void row_by_select(const float* __restrict__ pts, const float* __rest
   });
   int P = 1;
   while (P < w) P <<= 1;
-  for (int x = w + tid; x < P; x += kBlock) grouped[x] = ~0ull;
+  __syncthreads();
+  for (int x = min(s_at, w) + tid; x < P; x += kBlock) grouped[x] = ~0ull;
   __syncthreads();
   for (int size = 2; size <= P; size <<= 1)
     for (int stride = size >> 1; stride > 0; stride >>= 1) {
@@ -378,7 +379,8 @@ __device__ void row_by_select(const float* __restrict__ pts, const float* __rest
 // the points once for them, was 15-25% slower: their thresholds are missed
 // more often together, and their candidates take LDS from other workgroups.
 // Rows among repeated values (more points at one distance than fit, or than
-// are worth comparing) are left to k_rows_repeats.
+// are worth comparing) are left to k_rows_repeats, and so are rows whose nearest
+// points lie in the runs of one wavefront, more than its segment holds.
 //
 // Minimum wavefronts per SIMD: 6 at small E and 5 from E = 6 on, each within
 // 3% of the other and 4-13% faster than 4 or 7.
@@ -419,7 +421,7 @@ __attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(
     uint64_t* __restrict__ row = row_pool + J.out_off + (int64_t)p * J.w;
     const auto order_bound = [&] { return order_reach<E>(pts, n, w, p, q, s_n); };
     float t = repeats && (p & 7) ? 0.f : t_next < 0.f ? order_bound() : t_next;
-    // thresholds known to catch too few / too many
+    // thresholds known to catch too few / enough, but more than fit
     float t_few = -1.f, t_many = __builtin_inff();
     int total = 0;
     bool done = false;
@@ -450,6 +452,9 @@ __attribute__((amdgpu_waves_per_eu(E < 6 ? 6 : 5, 8))) void k_rows(
         over |= s_n[v] > seg;
         total += s_n[v];
       }
+      // one wavefront's share is full before there are w: so it is for every
+      // larger threshold, and this one bounds nothing
+      if (over && total < w) break;
       if (total < w || over) {
         (over ? t_many : t_few) = t;
         // by the power law, else into the bracket
