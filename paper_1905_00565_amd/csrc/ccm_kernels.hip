@@ -501,7 +501,7 @@ __global__ __launch_bounds__(BLOCK) void k_kd_level(const OrderJob* __restrict__
   __shared__ uint32_t s_key[BLOCK];
   __shared__ uint32_t s_pick[3];
   __shared__ int s_sum[2][kNW];
-  __shared__ int s_n;
+  __shared__ int s_n, s_nan;
   const OrderJob J = orders[set0 + (int)blockIdx.y];
   const int tid = threadIdx.x;
   const int64_t x = blockIdx.x;
@@ -581,10 +581,11 @@ __global__ __launch_bounds__(BLOCK) void k_kd_level(const OrderJob* __restrict__
     return binned ? min(kBins - 1, (int)((v - least) * scale)) : 0;
   };
   for (int b = tid; b < kBins; b += BLOCK) hist[b] = 0u;
-  if (tid == 0) s_n = 0;
+  if (tid == 0) s_n = s_nan = 0;
   __syncthreads();
   for (int64_t p = lo + tid; p < hi; p += BLOCK) {
     const float v = e[(int64_t)o[p] * E + d];
+    if (v != v) s_nan = 1;
     kc[p] = ordered_bits(v);
     atomicAdd(&hist[bin_of(v)], 1u);
   }
@@ -617,7 +618,7 @@ __global__ __launch_bounds__(BLOCK) void k_kd_level(const OrderJob* __restrict__
   uint32_t T;
   int eq_left;
   pick((uint32_t)(h - 1), 0);
-  if (binned && s_pick[2] <= (uint32_t)BLOCK) {
+  if (binned && !s_nan && s_pick[2] <= (uint32_t)BLOCK) {
     // the bin's few entries, each ranked against the others
     const int bin = (int)s_pick[0];
     const int rank = (int)s_pick[1];

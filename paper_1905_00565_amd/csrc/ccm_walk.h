@@ -165,14 +165,18 @@ __device__ __forceinline__ void visit_runs(const float* __restrict__ pts,
 }
 
 // The farthest of the w points around position p in visiting order: a bound of
-// its w-th distance (the whole workgroup; two barriers, s_n is used).
+// its w-th distance, infinite with a NaN among them (the whole workgroup; two
+// barriers, s_n is used).
 template <int E>
 __device__ __forceinline__ float order_reach(const float* __restrict__ pts, int n, int w, int p,
                                              const float (&q)[E], int* s_n) {
   const int tid = threadIdx.x;
   const int a = max(0, min(p - w / 2, n - w));
   float m = 0.f;
-  for (int c = a + tid; c < a + w; c += kBlock) m = fmaxf(m, run_d2<E>(pts, n, c, q));
+  for (int c = a + tid; c < a + w; c += kBlock) {
+    const float d2 = run_d2<E>(pts, n, c, q);
+    m = d2 == d2 ? fmaxf(m, d2) : __builtin_inff();
+  }
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
   __syncthreads();
@@ -826,11 +830,13 @@ __global__ __launch_bounds__(kBlock) void k_walk(
           best[K - 1] = empty_key();
         }
         if (lane == l) {
+          // (an empty place, left where the distances are NaN: point 0)
+          const int j = max(key_j(lo), 0);
           if (KEYS) {
-            lds.slot[0][t][lane] = lo;
+            lds.slot[0][t][lane] = make_key(key_d2(lo), j);
           } else {
             lds.slot[0][t][lane] = sqrt((double)key_d2(lo));
-            lds.slot[KEYS ? 0 : 1][t][lane] = tgt[key_j(lo)];
+            lds.slot[KEYS ? 0 : 1][t][lane] = tgt[j];
           }
         }
       }
