@@ -73,17 +73,20 @@ struct EmbedJob {
 };
 
 // One library draw (selection sampling keyed by (seed, E, tau, L_eff, r)).
+// One per draw in the no-allocation form's workspace, which calls fill to the
+// last bytes: it must not grow.
 struct SampleJob {
   uint64_t seed;
-  int64_t n_e;
-  int64_t l_eff;
   int64_t out_off;   // int32 indices into the library pool
+  int64_t bits;      // 1 + uint64 offset of the bitmap over 0..n_e-1 (0: none)
+  int32_t n_e;
+  int32_t l_eff;
   int32_t E;
   int32_t tau;
   int32_t r_index;
   int32_t no_list;   // 1: the indices are not written (only the bitmap)
-  int64_t bits;      // 1 + uint64 offset of the bitmap over 0..n_e-1 (0: none)
 };
+static_assert(sizeof(SampleJob) == 48, "the workspace holds as many as it did");
 
 // One library gather: the library of one realization laid out in visiting
 // order (pts AoS [l_eff][E], pj the embedded index

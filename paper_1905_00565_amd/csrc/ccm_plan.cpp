@@ -1042,7 +1042,7 @@ static Plan make_plan_shared(const Spec& s) {
       for (int ie = 0; ie < nE; ++ie) p.L_eff[((size_t)ie * nT + it) * nL + il] = le;
       for (int ri = 0; ri < s.r; ++ri) {
         const int64_t lib_off = p.n_lib;
-        p.sample.push_back({s.seed, nc, le, lib_off, 0, tau, ri, 0, 0});
+        p.sample.push_back({s.seed, lib_off, 0, (int32_t)nc, (int32_t)le, 0, tau, ri, 0});
         p.n_lib += le;
         for (int dir = 0; dir < 2; ++dir) {
           const int lib_s = dir == 0 ? 1 : 0;
@@ -1175,7 +1175,7 @@ Plan make_plan(const Spec& s) {
         p.L_eff[((size_t)ie * nT + it) * nL + il] = le;
         for (int ri = 0; ri < s.r; ++ri) {
           const int64_t lib_off = p.n_lib;
-          p.sample.push_back({s.seed, ne, le, lib_off, E, tau, ri, 0, 0});
+          p.sample.push_back({s.seed, lib_off, 0, (int32_t)ne, (int32_t)le, E, tau, ri, 0});
           p.n_lib += le;
           for (int dir = 0; dir < 2; ++dir) {
             // dir 0: library Y (series 1) predicts X (series 0); dir 1: reverse
@@ -1309,7 +1309,7 @@ Plan make_plan_matrix(const Spec& s) {
     p.L_eff[il] = le;
     for (int ri = 0; ri < s.r; ++ri) {
       lib_off[(size_t)il * s.r + ri] = p.n_lib;
-      p.sample.push_back({s.seed, ne, le, p.n_lib, E, tau, ri, 0, 0});
+      p.sample.push_back({s.seed, p.n_lib, 0, (int32_t)ne, (int32_t)le, E, tau, ri, 0});
       p.n_lib += le;
     }
   }

@@ -674,7 +674,7 @@ ccm_status ccm_library(ccm_ctx* c, int64_t N_e, int32_t E, int32_t tau, int64_t 
       fail(CCM_E_INVAL, "need 1 <= L_eff <= N_e < 2^31");
     if (E < 1 || E > kMaxE || tau < 1) fail(CCM_E_INVAL, "E in [1, 10] and tau >= 1");
     DevBuf job, out;
-    std::vector<SampleJob> j{{seed, N_e, L_eff, 0, E, tau, r_index, 0, 0}};
+    std::vector<SampleJob> j{{seed, 0, 0, (int32_t)N_e, (int32_t)L_eff, E, tau, r_index, 0}};
     upload(job, j);
     out.ensure(L_eff * 4);
     HIPCHK(launch_sample(job.as<SampleJob>(), 1, out.as<int32_t>(), nullptr, c->stream));
