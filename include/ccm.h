@@ -154,9 +154,11 @@ const char *ccm_last_error(const ccm_ctx *ctx);
  * together fit `bytes`: all realizations of one E in one wave when they
  * fit, consecutive E merged while they fit, one E split over several waves
  * when it alone does not fit (at least one realization per wave).  The
- * results do not depend on the bound; other buffers of a call (series,
- * embeddings, visiting orders, per-tile moments, neighbour rows and the
- * walks' output: at most 3.5 GiB) are not counted.  bytes = 0
+ * results do not depend on the bound; other buffers of a call are not
+ * counted: series, embeddings, visiting orders, per-tile moments, neighbour
+ * rows and the walks' output (at most 3.5 GiB), and the membership bits of the
+ * libraries that walk (N_e / 8 bytes per library of a wave and N_e * 8 per
+ * group of up to 64 that walk together).  bytes = 0
  * restores the default, min(8 GiB, device memory / 8) and at least 1 GiB.
  * The bound applies to calls made after it is set.
  */

@@ -263,7 +263,9 @@ static void split_waves(Plan& p) {
 // embedding's; a single embedding past the cap scans instead), and of walk
 // output held at once: predictions (256 MiB was 1% slower, 1 GiB the same), or
 // a causal matrix's neighbour keys (its per-target stage has few, long items:
-// 512 MiB 21.9 against 18.4 ms for 64 series, N = 20000, r = 10).
+// 512 MiB 21.9 against 18.4 ms for 64 series, N = 20000, r = 10).  A group of
+// 64 libraries whose output is larger by itself (pairs beyond 2^20 points, a
+// matrix beyond 2^21 / (E+1)) is made of fewer.
 constexpr int64_t kRowPoolBytes = 1ll << 30;
 constexpr int64_t kRowPoolCap = 2ll << 30;
 constexpr int64_t kWalkOutBytes = 512ll << 20;
@@ -290,6 +292,14 @@ static int64_t row_need(int E, double excl, int64_t ne, int64_t le) {
   return n < 1e9 ? (int64_t)n + 1 : (int64_t)1e9;
 }
 
+// Libraries of an embedding of ne points that walk together.  (Nested and
+// shared-E calls walk up to 2^18 points at most, where 64 always fit.)
+static size_t group_libs(const Plan& p, int E, int64_t ne) {
+  const int64_t each = p.spec.M > 0 ? ne * (E + 1) * 8 : ne * 8;
+  const int64_t bytes = p.spec.M > 0 ? kWalkKeyBytes : kWalkOutBytes;
+  return (size_t)std::max<int64_t>(1, std::min<int64_t>(kWalkLibs, bytes / each));
+}
+
 // Costs in instruction slots of a wavefront, per query of an embedding: one
 // scanned library (64 queries share a wavefront), one walk of a group of
 // libraries, and building a row of w entries.
@@ -314,7 +324,7 @@ struct WalkPick {
 };
 
 // The libraries of one embedding (v: its realizations in one launch) worth
-// walking: the largest first, in groups of 64, as many groups as each save
+// walking: the largest first, in groups, as many groups as each save
 // more than they cost.  Returns the slots saved per query, the rows' cost
 // not counted; forced: CCM_FLAG_TABLE asks for some of them.
 static double pick_libraries(const Plan& p, int E, double excl, std::vector<int32_t>& v,
@@ -326,9 +336,10 @@ static double pick_libraries(const Plan& p, int E, double excl, std::vector<int3
   });
   const int64_t ne = p.rz[v[0]].n_e;
   const int64_t full = (ne + 63) / 64 * 64;
+  const size_t libs = group_libs(p, E, ne);
   double gain = 0;
-  for (size_t g0 = 0; g0 < v.size(); g0 += kWalkLibs) {
-    const size_t g1 = std::min(v.size(), g0 + kWalkLibs);
+  for (size_t g0 = 0; g0 < v.size(); g0 += libs) {
+    const size_t g1 = std::min(v.size(), g0 + libs);
     std::vector<int32_t> grp;
     int64_t need = 64;
     double scan = 0;

@@ -1,0 +1,55 @@
+"""The planner (host code of libccm): which realizations of a call walk
+neighbour rows, and what memory that takes.  Runs without a GPU: a small
+program (tests/native/plan_report.cpp) linked with the library prints the plan.
+"""
+import json
+import os
+import subprocess
+
+import pytest
+
+from paper_1905_00565_amd import build, capi
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+GIB = 1 << 30
+
+
+@pytest.fixture(scope="session")
+def plan(tmp_path_factory):
+    if not os.path.exists(capi.LIBRARY):
+        build.build_library()
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_report")
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(build.hipcc())))
+    subprocess.run(
+        ["g++", "-O1", "-std=c++17", "-D__HIP_PLATFORM_AMD__", f"-I{rocm}/include",
+         f"-I{build.INCLUDE}", f"-I{build.CSRC}", os.path.join(HERE, "native", "plan_report.cpp"),
+         "-o", exe, capi.LIBRARY, f"-L{rocm}/lib", "-lamdhip64",
+         f"-Wl,-rpath,{os.path.dirname(capi.LIBRARY)}", f"-Wl,-rpath,{rocm}/lib"], check=True)
+
+    def report(N, E, tau, L, r, M=0, excl=0, query_set=0, flags=0, wave_limit=None, walk=1,
+               spread=1):
+        text = [",".join(str(x) for x in v) for v in (E, tau, L)]
+        args = [M, N, *text, r, excl, query_set, flags]
+        args += [8 * GIB if wave_limit is None else wave_limit, walk, spread]
+        out = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True)
+        return json.loads(out.stdout)
+
+    return report
+
+
+@pytest.mark.parametrize("kw", [
+    dict(N=4_000_000, E=[1], tau=[1], L=[2_000_000, 4_000_000], r=64),
+    dict(N=1_048_577, E=[1], tau=[1], L=[1_000_000], r=64),       # one past 64 libraries' output
+    dict(N=1_000_000, E=[4], tau=[1], L=[500_000, 1_000_000], r=33, M=2),
+    dict(N=4_000_000, E=[10], tau=[1], L=[4_000_000], r=6, M=2),
+    dict(N=250_000, E=[1, 3], tau=[2], L=[100_000], r=64, flags=capi.CCM_FLAG_SHARED_E),
+    dict(N=65_536, E=[2], tau=[1], L=[30_000, 65_000], r=64, flags=capi.CCM_FLAG_NESTED),
+    dict(N=20_000, E=[4], tau=[1], L=[500, 5000, 20_000], r=40, M=64),
+], ids=str)
+def test_walk_memory_bound(plan, kw):
+    """Neighbour rows and the walks' output stay within the stated 3.5 GiB, the
+    output within its own bound."""
+    p = plan(**kw)
+    assert p["walked"] > 0
+    assert p["out_bytes"] <= (GIB if kw.get("M") else GIB // 2)
+    assert p["out_bytes"] + p["row_bytes"] <= 3.5 * GIB
