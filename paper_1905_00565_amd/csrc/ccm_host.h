@@ -93,6 +93,9 @@ struct Spec {
   // Whether realizations may walk neighbour rows where that is cheaper than
   // the scan (the batched calls; not the served and no-allocation forms).
   bool walk = false;
+  // Walk groups a plan can number (four 32-bit item numbers to a group); the
+  // launches past them scan.
+  int64_t max_walk_groups = INT32_MAX / 8;
   // Whether launches of few items spread their queries (the same and the
   // no-allocation form).
   bool spread = false;

@@ -444,6 +444,11 @@ static void nested_libraries(Plan& p, int E, double excl, const std::vector<int3
   }
 }
 
+// Whether the plan can number `more` walk groups.
+static bool groups_fit(const Plan& p, size_t more) {
+  return (int64_t)(p.walk_groups.size() + more) <= p.spec.max_walk_groups;
+}
+
 // Lay out the walks of one launch: per pick (an embedding's groups) a row
 // job, the groups' libraries, bitmaps and membership words, the batches of
 // embeddings whose rows fit together and the chunks whose output does.
@@ -455,10 +460,8 @@ static void lay_out_walks(Plan& p, std::vector<WalkPick>& picks, Launch& la, int
   std::map<std::vector<int64_t>, int64_t> mask_of;
   int64_t masks = 0, total_q = 0;
   la.mask_first = (int32_t)p.mask_jobs.size();
-  const size_t group0 = p.walk_groups.size();
   std::vector<size_t> emb_group;      // first group of each row job
   const int32_t job0 = (int32_t)p.row_jobs.size();
-  if (p.walk_groups.size() > (size_t)INT32_MAX / 8) return;   // (item numbers)
   for (WalkPick& pk : picks) {
     const Realization& R0 = p.rz[pk.groups[0][0]];
     RowJob rj{};
@@ -513,7 +516,6 @@ static void lay_out_walks(Plan& p, std::vector<WalkPick>& picks, Launch& la, int
   emb_group.push_back(p.walk_groups.size());
   la.mask_count = (int32_t)p.mask_jobs.size() - la.mask_first;
   p.n_mask = std::max(p.n_mask, masks);
-  (void)group0;
 
   // enough items to fill the chip, at most 64 queries each
   la.walk_per = (int32_t)std::min<int64_t>(64, std::max<int64_t>(4, total_q / 8192 / 4 * 4));
@@ -639,15 +641,17 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
   bool forced_any = false;
   if (nested) {
     std::vector<std::pair<const std::vector<int32_t>*, int>> sizes;
+    size_t groups = 0;
     for (auto& kv : by_emb) {
       int first = 0;
       const double gain = pick_sizes(p, E, excl, kv.second, first);
       const Realization& R = p.rz[kv.second[0]];
       if (gain <= 0 || (int64_t)R.n_e * kRowMaxW * 8 > kRowPoolCap) continue;
       gain_all += gain * (double)R.n_e;
+      groups += kv.second.size() * (size_t)(R.n_seg - first) / kWalkLibs + 1;
       sizes.emplace_back(&kv.second, first);
     }
-    if (gain_all < kWalkMinGain) return;
+    if (gain_all < kWalkMinGain || !groups_fit(p, groups)) return;
     for (auto& s : sizes) {
       picks.emplace_back();
       nested_libraries(p, E, excl, *s.first, s.second, picks.back());
@@ -660,6 +664,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
         bits += (int64_t)(nj.n_seg - nj.seg0) * ((nj.n_e + 63) / 64);
       }
   } else {
+    size_t groups = 0;
     for (auto& kv : by_emb) {
       WalkPick pk;
       bool forced = false;
@@ -670,9 +675,10 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
       if (pk.groups.empty() || !fits || (gain <= 0 && !forced)) continue;
       gain_all += gain;
       forced_any |= forced;
+      groups += pk.groups.size();
       picks.push_back(std::move(pk));
     }
-    if (picks.empty() || (gain_all < kWalkMinGain && !forced_any)) return;
+    if (picks.empty() || (gain_all < kWalkMinGain && !forced_any) || !groups_fit(p, groups)) return;
   }
   if (!picks.empty()) lay_out_walks(p, picks, la, bits);
 }
@@ -693,6 +699,7 @@ static void plan_shared_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& 
   for (int32_t r : rzs) by_emb[p.rz[r].emb_off].push_back(r);
 
   std::vector<std::vector<std::vector<int32_t>>> groups;   // per embedding
+  size_t n_groups = 0;
   double gain_all = 0;
   for (auto& kv : by_emb) {
     std::vector<int32_t>& v = kv.second;
@@ -728,9 +735,10 @@ static void plan_shared_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& 
     for (size_t e = 0; e < Es.size(); ++e) gain -= row_cost(Es[e], ne, w[e]);
     if (gs.empty() || gain <= 0) continue;
     gain_all += gain * (double)ne;
+    n_groups += gs.size() * Es.size();
     groups.push_back(std::move(gs));
   }
-  if (gain_all < kWalkMinGain) return;
+  if (gain_all < kWalkMinGain || !groups_fit(p, n_groups)) return;
 
   for (auto& gs : groups)
     for (auto& grp : gs)

@@ -27,10 +27,10 @@ def plan(tmp_path_factory):
          f"-Wl,-rpath,{os.path.dirname(capi.LIBRARY)}", f"-Wl,-rpath,{rocm}/lib"], check=True)
 
     def report(N, E, tau, L, r, M=0, excl=0, query_set=0, flags=0, wave_limit=None, walk=1,
-               spread=1):
+               spread=1, groups=(1 << 31) // 8 - 1):
         text = [",".join(str(x) for x in v) for v in (E, tau, L)]
         args = [M, N, *text, r, excl, query_set, flags]
-        args += [8 * GIB if wave_limit is None else wave_limit, walk, spread]
+        args += [8 * GIB if wave_limit is None else wave_limit, walk, spread, groups]
         out = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True)
         return json.loads(out.stdout)
 
@@ -53,3 +53,25 @@ def test_walk_memory_bound(plan, kw):
     assert p["walked"] > 0
     assert p["out_bytes"] <= (GIB if kw.get("M") else GIB // 2)
     assert p["out_bytes"] + p["row_bytes"] <= 3.5 * GIB
+
+
+NESTED, SHARED, TABLE = (capi.CCM_FLAG_NESTED, capi.CCM_FLAG_SHARED_E, capi.CCM_FLAG_TABLE)
+
+
+@pytest.mark.parametrize("groups", [(1 << 31) // 8 - 1, 3, 0])
+@pytest.mark.parametrize("kw", [
+    dict(N=3000, E=[2, 5], tau=[1, 3], L=[100, 600, 3000], r=70),
+    dict(N=3000, E=[2, 5], tau=[1], L=[100, 600, 3000], r=70, query_set=1, excl=3),
+    dict(N=3000, E=[2, 5], tau=[1], L=[100, 600, 3000], r=70, wave_limit=4 << 20),
+    dict(N=3000, E=[2, 5], tau=[1], L=[100, 600, 3000], r=70, flags=NESTED),
+    dict(N=3000, E=[1, 3, 4], tau=[1, 2], L=[100, 600, 3000], r=70, flags=SHARED),
+    dict(N=3000, E=[3], tau=[1], L=[100, 600, 3000], r=40, M=33),
+    dict(N=900, E=[3], tau=[1], L=[100, 600], r=2, flags=TABLE),
+    dict(N=900, E=[3], tau=[1], L=[100, 600], r=2),
+], ids=str)
+def test_every_tile_has_one_writer(plan, kw, groups):
+    """Whatever part of a call walks, every tile of every result is formed once;
+    also where the plan runs out of numbers for walk groups."""
+    p = plan(**kw, groups=groups)
+    assert p["missing"] == 0 and p["twice"] == 0
+    assert p["groups"] <= groups
