@@ -49,25 +49,12 @@ bool walks(const Spec& s) {
   return !(s.flags & CCM_FLAG_PLAIN);
 }
 
-// Device buffers and descriptors for a plan (reused when the shape repeats).
-Exec* prepare(ccm_ctx* c, const Spec& s) {
-  if (c->exec && c->exec->plan.spec == s) return c->exec.get();
-  if (c->exec) {
-    // work queued earlier on any stream may still read the old buffers
-    HIPCHK(hipDeviceSynchronize());
-    c->exec.reset();   // free the previous plan's memory first
-  }
+// A plan with its device buffers and descriptors.
+std::unique_ptr<Exec> make_exec(const Spec& s) {
   auto ex = std::make_unique<Exec>();
   ex->plan = s.M > 0 ? make_plan_matrix(s) : make_plan(s);
   size_t free_b = 0, total_b = 0;
   HIPCHK(hipMemGetInfo(&free_b, &total_b));
-  if (ex->plan.device_bytes > free_b && !ex->plan.walk_groups.empty()) {
-    // the neighbour rows are what does not fit: scan instead
-    Spec scan = s;
-    scan.walk = false;
-    ex->plan = s.M > 0 ? make_plan_matrix(scan) : make_plan(scan);
-    ex->plan.spec.walk = s.walk;
-  }
   Plan& p = ex->plan;
   if (p.device_bytes > free_b)
     fail(CCM_E_NOMEM, "plan needs " + std::to_string(p.device_bytes) + " device bytes, " +
@@ -194,7 +181,29 @@ Exec* prepare(ccm_ctx* c, const Spec& s) {
   b.shuffle = ex->d_scratch.as<int32_t>();
   b.segs = ex->d_segs.as<int32_t>();
   b.rz_fin = ex->d_rz_fin.as<Realization>();
-  c->exec = std::move(ex);
+  return ex;
+}
+
+// The Exec of a call (reused when the shape repeats).
+Exec* prepare(ccm_ctx* c, const Spec& s) {
+  if (c->exec && c->exec->plan.spec == s) return c->exec.get();
+  if (c->exec) {
+    // work queued earlier on any stream may still read the old buffers
+    HIPCHK(hipDeviceSynchronize());
+    c->exec.reset();   // free the previous plan's memory first
+  }
+  try {
+    c->exec = make_exec(s);
+  } catch (const Fail& f) {
+    if (f.status != CCM_E_NOMEM || !s.walk) throw;
+    // by the plan's own count or by an allocation, the neighbour rows may be
+    // what does not fit: scan instead
+    (void)hipGetLastError();
+    Spec scan = s;
+    scan.walk = false;
+    c->exec = make_exec(scan);
+    c->exec->plan.spec.walk = true;
+  }
   return c->exec.get();
 }
 
