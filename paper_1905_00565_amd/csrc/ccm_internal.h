@@ -262,6 +262,10 @@ hipError_t launch_ingest(const IngestJob* jobs, int n_jobs, int64_t max_n,
                          const double* src, float* dst, hipStream_t st);
 hipError_t launch_embed(const EmbedJob* jobs, int n_jobs, int64_t max_n,
                         const float* s32, float* emb, hipStream_t st);
+// Entries of an order set that one workgroup places: at most 512 workgroups.
+constexpr int64_t query_order_span(int64_t n_series) {
+  return n_series <= 2048 * 512 ? 2048 : (n_series + 512 * 256 - 1) / (512 * 256) * 256;
+}
 hipError_t launch_query_order(const EmbedJob* jobs, int n_jobs, int64_t n_series,
                               const int32_t* order, int32_t* qord, hipStream_t st);
 hipError_t launch_sample(const SampleJob* jobs, int64_t n_jobs, int32_t* out, uint64_t* bits,

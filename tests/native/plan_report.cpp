@@ -68,6 +68,8 @@ int main(int argc, char** argv) {
     for (const RowJob& j : p.row_jobs) max_w = std::max<int64_t>(max_w, j.w);
     int libs = 0;
     for (const WalkGroup& g : p.walk_groups) libs = std::max(libs, g.n_lib);
+    // entries that placing one set's embedded points counts beforehand
+    const int64_t span = query_order_span(s.N), spans = (s.N + span - 1) / span;
     int64_t missing = 0, twice = 0;
     const std::vector<int> n = written(p);
     const std::vector<Realization>& fin = p.rz_fin.empty() ? p.rz : p.rz_fin;
@@ -79,14 +81,14 @@ int main(int argc, char** argv) {
     printf("{\"realizations\": %zu, \"walked\": %lld, \"scan_items\": %lld, \"spread_items\": %lld, "
            "\"grouped_items\": %lld, \"groups\": %zu, \"group_libs\": %d, \"row_width\": %lld, "
            "\"out_bytes\": %lld, \"row_bytes\": %lld, \"bit_bytes\": %lld, \"mask_bytes\": %lld, "
-           "\"device_bytes\": %llu, \"waves\": %zu, \"missing\": %lld, \"twice\": %lld}\n",
+           "\"device_bytes\": %llu, \"waves\": %zu, \"missing\": %lld, \"twice\": %lld, \"order_reads\": %lld}\n",
            p.rz.size(), (long long)walked, (long long)scanned, (long long)spread,
            (long long)grouped, p.walk_groups.size(), libs, (long long)max_w,
            (long long)p.n_walk_out * 8,
            (long long)(p.n_rows * 8 + (p.n_opts + p.n_box) * 4 +
                        p.n_todo * (int64_t)sizeof(RowTodo)),
            (long long)p.n_bits * 8, (long long)p.n_mask * 8, (unsigned long long)p.device_bytes,
-           p.waves.size(), (long long)missing, (long long)twice);
+           p.waves.size(), (long long)missing, (long long)twice, (long long)(spans * (spans - 1) / 2 * span));
   } catch (const Fail& e) {
     printf("{\"status\": %d}\n", (int)e.status);
     return 0;

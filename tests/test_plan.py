@@ -75,3 +75,9 @@ def test_every_tile_has_one_writer(plan, kw, groups):
     p = plan(**kw, groups=groups)
     assert p["missing"] == 0 and p["twice"] == 0
     assert p["groups"] <= groups
+
+
+@pytest.mark.parametrize("N", [2048, 1_048_576, 1_048_577, 20_000_000])
+def test_query_order_work(plan, N):
+    """Placing an embedding's points in visiting order stays linear in the series."""
+    assert plan(N=N, E=[2], tau=[3], L=[40], r=1)["order_reads"] <= 256 * N
