@@ -177,7 +177,8 @@ __device__ __forceinline__ uint64_t tail_word(int64_t ne, int64_t j0) {
   return ne - j0 >= 64 ? ~0ull : ~(~0ull << (ne - j0));
 }
 
-__device__ __forceinline__ void sample_library(const SampleJob& J,
+template <bool BITS>
+__device__ __forceinline__ void sample_members(const SampleJob& J,
                                                int32_t* __restrict__ out_pool,
                                                uint64_t* __restrict__ bit_pool) {
   const int lane = threadIdx.x & 63;
@@ -189,8 +190,8 @@ __device__ __forceinline__ void sample_library(const SampleJob& J,
   st = sm_mix(st ^ (uint64_t)(int64_t)J.r_index);
   int32_t* __restrict__ out = out_pool + J.out_off;
   const int64_t ne = J.n_e, le = J.l_eff;
-  const bool list = J.no_list == 0;
-  uint64_t* __restrict__ bits = J.bits > 0 ? bit_pool + (J.bits - 1) : nullptr;
+  const bool list = !BITS || J.no_list == 0;
+  uint64_t* __restrict__ bits = BITS ? bit_pool + (J.bits - 1) : nullptr;
   const int64_t nw = (ne + 63) / 64;
   uint64_t word = 0;                              // word 64 * (j0 / 4096) + lane
   const uint64_t below_lane = lane == 0 ? 0ull : (~0ull >> (64 - lane));
@@ -230,7 +231,7 @@ __device__ __forceinline__ void sample_library(const SampleJob& J,
       // candidates rest .. n_e - 1, all of them: to the end of the bitmap
       take |= (~0ull << (rest - j0)) & tail_word(ne, j0);
     }
-    if (bits) {
+    if (BITS) {
       const int64_t x = j0 >> 6;
       if (lane == (int)(x & 63)) word = take;
       if ((x & 63) == 63) {
@@ -246,11 +247,23 @@ __device__ __forceinline__ void sample_library(const SampleJob& J,
       }
     }
   }
-  if (bits) {
+  if (BITS) {
     // every candidate is taken already: the pending words, then zeros
     const int64_t x = j0 >> 6;                    // words formed
     for (int64_t y = (x & ~63ll) + lane; y < nw; y += 64) bits[y] = y < x ? word : 0ull;
   }
+}
+
+// One draw: its list, its bitmap, or both.  The loop is one serial chain per
+// library, and a draw without a bitmap does not carry the bitmap's steps: with
+// them 19.5 ms for 4 x 10^6 candidates, without 16.7.
+__device__ __forceinline__ void sample_library(const SampleJob& J,
+                                               int32_t* __restrict__ out_pool,
+                                               uint64_t* __restrict__ bit_pool) {
+  if (J.bits > 0)
+    sample_members<true>(J, out_pool, bit_pool);
+  else
+    sample_members<false>(J, out_pool, bit_pool);
 }
 
 __global__ __launch_bounds__(256) void k_sample(const SampleJob* __restrict__ jobs,
