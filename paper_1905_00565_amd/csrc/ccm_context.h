@@ -96,6 +96,7 @@ struct Exec {
   std::vector<int64_t> plain_first;   // per realization: first plain item
   PlanBuffers buf;
   hipGraphExec_t graph = nullptr;
+  bool ran = false;                   // called before (with other series, maybe)
   ~Exec() {
     if (graph) (void)hipGraphExecDestroy(graph);
   }

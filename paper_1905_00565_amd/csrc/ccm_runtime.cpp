@@ -428,11 +428,17 @@ hipGraphExec_t capture(ccm_ctx* c, Exec* ex) {
 
 // Run a prepared plan on stream st: series already in ex->d_s64.  While
 // profiling, the launches are issued directly with an event pair around
-// each cross-map launch (events recorded by graph nodes cannot be timed).
+// each cross-map launch (events recorded by graph nodes cannot be timed).  So is
+// the first call of a plan with walks: a graph of two branches costs 170 us to
+// instantiate and 110 more to launch first and to free (one chain: 15 and 20),
+// which a call that never comes again would not earn back (a new seed for every
+// call, 1000 points, L to 1000, r = 100: 936 us through the graph, 785 directly).
 void run(ccm_ctx* c, Exec* ex, hipStream_t st) {
   const Plan& p = ex->plan;
+  const bool first = !ex->ran && !p.walk_groups.empty();
   const bool use_graph = !c->profiling && !(p.spec.flags & CCM_FLAG_NO_GRAPH) &&
-                         !(p.spec.flags & CCM_FLAG_PLAIN);
+                         !(p.spec.flags & CCM_FLAG_PLAIN) && !first;
+  ex->ran = true;
   if (use_graph) {
     if (!ex->graph) ex->graph = capture(c, ex);
     HIPCHK(hipGraphLaunch(ex->graph, st));
