@@ -8,6 +8,9 @@ import subprocess
 
 import pytest
 
+import test_gpu_paths as paths
+import test_gpu_rows as rows
+import test_gpu_rows_uneven as uneven
 from paper_1905_00565_amd import build, capi
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -81,3 +84,60 @@ def test_every_tile_has_one_writer(plan, kw, groups):
 def test_query_order_work(plan, N):
     """Placing an embedding's points in visiting order stays linear in the series."""
     assert plan(N=N, E=[2], tau=[3], L=[40], r=1)["order_reads"] <= 256 * N
+
+
+# ---------------------------------------------------------------------------
+# the GPU tests that compare two routes of a call take those two routes
+# ---------------------------------------------------------------------------
+
+def cases_of(test):
+    return next(m.args[1] for m in test.pytestmark if m.name == "parametrize")
+
+
+@pytest.mark.parametrize("case", paths.SPREAD, ids=str)
+def test_spread_cases_spread(plan, case):
+    E, tau, ne, L, excl, qs = case
+    kw = dict(N=ne + (E - 1) * tau, E=[E], tau=[tau], L=L, r=4, excl=excl, query_set=qs)
+    p = plan(**kw)
+    assert p["spread_items"] == p["scan_items"] > 0 and p["walked"] == 0
+    assert plan(**kw, flags=capi.CCM_FLAG_PLAIN, walk=0, spread=0)["spread_items"] == 0
+
+
+@pytest.mark.parametrize("case", paths.GROUPED, ids=str)
+def test_grouped_cases_group(plan, case):
+    M, N, E, tau, L, r, excl = case
+    p = plan(M=M, N=N, E=[E], tau=[tau], L=L, r=r, excl=excl)
+    assert p["grouped_items"] >= 1024 and p["scan_items"] == 0
+    assert p["missing"] == 0 and p["twice"] == 0
+
+
+@pytest.mark.parametrize("excl,L", cases_of(uneven.test_uneven_rows_equal_scan))
+def test_uneven_rows_are_long(plan, excl, L):
+    p = plan(N=6 * 8192, E=[6], tau=[8192], L=L, r=64, excl=excl)
+    assert p["row_width"] >= 768 and p["walked"] == 2 * 64 * len(L)
+
+
+@pytest.mark.parametrize("excl,qs", cases_of(rows.test_rows_by_rule_equal_scan))
+def test_rows_by_rule_cases_walk(plan, excl, qs):
+    p = plan(N=3001, E=[2, 5, 10], tau=[1, 3], L=[40, 150, 600, 2000, 3001], r=70, excl=excl,
+             query_set=qs)
+    assert p["walked"] > 0 and p["scan_items"] > 0
+
+
+@pytest.mark.parametrize("N,E,tau,L,r,excl,kind", cases_of(rows.test_nested_rows_equal_scan))
+def test_nested_cases_take_both(plan, N, E, tau, L, r, excl, kind):
+    kw = dict(N=N, E=[E], tau=[tau], L=L, excl=excl, flags=NESTED)
+    assert plan(**kw, r=1)["walked"] == 0
+    assert plan(**kw, r=r)["walked"] > 0
+
+
+@pytest.mark.parametrize("N,Es,tau,L,r,excl,kind", cases_of(rows.test_shared_rows_equal_scan))
+def test_shared_cases_take_both(plan, N, Es, tau, L, r, excl, kind):
+    kw = dict(N=N, E=Es, tau=[tau], L=L, excl=excl, flags=SHARED)
+    assert plan(**kw, r=1)["walked"] == 0
+    assert plan(**kw, r=r)["walked"] > 0
+
+
+def test_replayed_call_walks_and_scans(plan):
+    p = plan(N=4000, E=[2, 5], tau=[1], L=[40, 1500, 3000], r=60)
+    assert p["walked"] > 0 and p["scan_items"] > 0
