@@ -32,8 +32,8 @@ struct IngestJob {
 //   dims == 1: the value S[i + lag[0]];
 //   dims == 2: the position on a Hilbert curve over (S[i + lag[0]],
 //              S[i + lag[1]]), each scaled to 16 bits by the series' range;
-//   dims == 3, 4: the position on the dims-dimensional Hilbert curve over
-//              S[i + lag[d]], each scaled to 32 / dims bits.
+//   dims == 4: the position on the four-dimensional Hilbert curve over
+//              S[i + lag[d]], each scaled to 8 bits.
 // An index whose lags run past the series sorts last (it is never an
 // embedded point of an embedding that uses the set).
 //

@@ -110,15 +110,19 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u) {
   return __uint_as_float((u & 0x80000000u) ? u ^ 0x80000000u : ~u);
 }
 
-// Index on the n-dimensional Hilbert curve of b bits per axis (n <= 4,
-// n * b <= 32): Skilling's transpose form (J. Skilling, "Programming the
-// Hilbert curve", AIP Conf. Proc. 707, 2004) -- undo the excess work of the
-// recursive reflections and exchanges from the top bit down, Gray-encode
-// across axes, then read the index bits axis-interleaved, top bit first.
-__device__ __forceinline__ uint32_t hilbert_nd(uint32_t (&x)[4], int n, int b) {
+// Index on the n-dimensional Hilbert curve of 32 / n bits per axis (n known to
+// the compiler, so that x stays in registers): Skilling's transpose form
+// (J. Skilling, "Programming the Hilbert curve", AIP Conf. Proc. 707, 2004) --
+// undo the excess work of the recursive reflections and exchanges from the top
+// bit down, Gray-encode across axes, then read the index bits axis-interleaved,
+// top bit first.
+template <int n>
+__device__ __forceinline__ uint32_t hilbert_nd(uint32_t (&x)[n]) {
+  constexpr int b = 32 / n;
   const uint32_t top = 1u << (b - 1);
   for (uint32_t q = top; q > 1; q >>= 1) {
     const uint32_t low = q - 1;
+#pragma unroll
     for (int i = 0; i < n; ++i) {
       if (x[i] & q) {
         x[0] ^= low;
@@ -129,13 +133,16 @@ __device__ __forceinline__ uint32_t hilbert_nd(uint32_t (&x)[4], int n, int b) {
       }
     }
   }
+#pragma unroll
   for (int i = 1; i < n; ++i) x[i] ^= x[i - 1];
   uint32_t t = 0;
   for (uint32_t q = top; q > 1; q >>= 1)
     if (x[n - 1] & q) t ^= q - 1;
+#pragma unroll
   for (int i = 0; i < n; ++i) x[i] ^= t;
   uint32_t h = 0;
   for (int bit = b - 1; bit >= 0; --bit)
+#pragma unroll
     for (int i = 0; i < n; ++i) h = (h << 1) | ((x[i] >> bit) & 1u);
   return h;
 }
@@ -388,9 +395,10 @@ __global__ __launch_bounds__(1024) void k_sort_chunks(const OrderJob* __restrict
   const int nw = nt / 64;
   const int share = (m + 4 * nw - 1) / (4 * nw) * 4;   // keys per wavefront
   int64_t lag_max = 0;
-  for (int d = 0; d < dims; ++d) lag_max = max(lag_max, (int64_t)J.lag[d]);
+#pragma unroll
+  for (int d = 0; d < 4; ++d)
+    if (d < dims) lag_max = max(lag_max, (int64_t)J.lag[d]);
   float lo = 0.f, scale = 0.f, top = 0.f;
-  int bits = 32;
   if (dims > 1) {
     float hi;
     if (range) {
@@ -399,8 +407,7 @@ __global__ __launch_bounds__(1024) void k_sort_chunks(const OrderJob* __restrict
     } else {
       series_range(s, J.n, s_lo, s_hi, lo, hi);
     }
-    bits = dims == 2 ? 16 : 32 / dims;
-    top = (float)((1u << bits) - 1u);
+    top = (float)((1u << (dims == 2 ? 16 : 8)) - 1u);
     const float span = hi - lo;
     scale = span > 0.f ? top / span : 0.f;
   }
@@ -411,10 +418,14 @@ __global__ __launch_bounds__(1024) void k_sort_chunks(const OrderJob* __restrict
       if (dims == 1) {
         u = ordered_bits(s[i + J.lag[0]]);
       } else {
+        // (two coordinates or four: indexed at run time they lived in scratch
+        // memory, 80 bytes a lane, which a launch has to find on the device)
         uint32_t g[4] = {0u, 0u, 0u, 0u};
-        for (int d = 0; d < dims; ++d)
-          g[d] = (uint32_t)fminf(top, fmaxf(0.f, (s[i + J.lag[d]] - lo) * scale));
-        u = dims == 2 ? hilbert16(g[0], g[1]) : hilbert_nd(g, dims, bits);
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          if (d < dims)
+            g[d] = (uint32_t)fminf(top, fmaxf(0.f, (s[i + J.lag[d]] - lo) * scale));
+        u = dims == 2 ? hilbert16(g[0], g[1]) : hilbert_nd<4>(g);
       }
     }
     key[x] = u;
