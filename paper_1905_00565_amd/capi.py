@@ -381,7 +381,10 @@ def ccm_server_destroy(srv) -> None:
 class Server:
     """Owns one server; methods forward to the functions above."""
 
+    handle = None
+
     def __init__(self, ctx, **cfg):
+        self.context = ctx                # lives as long as its server
         self.ctx = ctx.handle if isinstance(ctx, Context) else ctx
         self.handle = ccm_server_create(self.ctx, **cfg)
 
@@ -407,6 +410,12 @@ class Server:
 
     def __exit__(self, *exc):
         self.close()
+
+    def __del__(self):
+        try:
+            self.close()
+        except Exception:
+            pass
 
 
 class Context:
