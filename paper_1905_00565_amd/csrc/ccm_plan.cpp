@@ -316,6 +316,34 @@ static double row_cost(int E, int64_t ne, int64_t w) {
 // 2 x 10^7 a pair of N = 1331 at E = 1 went from 153 to 183 us).
 constexpr double kWalkMinGain = 5.0e7;
 
+// Long series in many dimensions: a row's pass visits the runs of 64 points that
+// the ball of its nearest 1.5 w reaches, and the costs above hold for points on
+// an attractor of few dimensions.  Points that fill theirs (shuffled series)
+// take a multiple: about (0.7 (1.5 w)^(1/E) + 64^(1/E))^E / 64 runs, up to all.
+// `scan` and `walk`: nanoseconds of the whole chip per query, as below; a scan of
+// few items leaves part of its last round of workgroups (1536 resident) idle.
+// True where shuffled series would take over 1.45 times as long as scanned, and
+// so longer than before there were rows: 32768 points, E = 9, 40 libraries of
+// 2048, 10.1 ms walked, 3.5 scanned, 5.2 then (in the logistic map's order 3.4, 3.1
+// and 4.8); 10^5 points, 40 of 6250, 28.9, 20.2 and 24.4 (9.1, 19.1 and 23.4).
+// Below E = 7, and below 20000 points, shuffled series took less than then.
+static bool rows_too_dear(int E, int64_t ne, int64_t w, double scan, double walk, int64_t items) {
+  if (E < 7 || ne < 20000) return false;
+  const double side = 0.7 * std::pow(1.5 * (double)w, 1.0 / E) + std::pow(64.0, 1.0 / E);
+  const double runs = std::min((double)ne / 64.0, std::pow(side, E) / 64.0);
+  const double rows = 3.0 + 0.0024 * E * (double)w + 0.25 * runs + 6.8e-6 * E * (double)ne;
+  const double rounds = std::ceil((double)items / 1536.0) * 1536.0 / (double)items;
+  return 1.45 * rounds * scan < walk + rows;
+}
+// A scanned library, and a walk of a group (pairs of 10^4 to 10^5 points, E = 1 to
+// 10: within a factor 1.3).
+static double scan_ns(int E, int64_t le) {
+  return 0.042 + 3.2e-5 * E * (double)le + 0.0015 * E * std::log2((double)std::max<int64_t>(le, 1));
+}
+static double walk_ns(int E, int64_t chunks) {
+  return 0.74 + 0.12 * E + 0.27 * (double)chunks;
+}
+
 // Groups of one embedding's libraries that walk its rows together.
 struct WalkPick {
   std::vector<std::vector<int32_t>> groups;
@@ -328,7 +356,7 @@ struct WalkPick {
 // more than they cost.  Returns the slots saved per query, the rows' cost
 // not counted; forced: CCM_FLAG_TABLE asks for some of them.
 static double pick_libraries(const Plan& p, int E, double excl, std::vector<int32_t>& v,
-                             WalkPick& pk, bool& forced) {
+                             int64_t n_emb, WalkPick& pk, bool& forced) {
   std::stable_sort(v.begin(), v.end(), [&](int32_t a, int32_t b) {
     const bool fa = p.want_table[a] != 0, fb = p.want_table[b] != 0;
     if (fa != fb) return fa;
@@ -337,12 +365,13 @@ static double pick_libraries(const Plan& p, int E, double excl, std::vector<int3
   const int64_t ne = p.rz[v[0]].n_e;
   const int64_t full = (ne + 63) / 64 * 64;
   const size_t libs = group_libs(p, E, ne);
-  double gain = 0;
+  double gain = 0, all_scan = 0, all_walk = 0;
+  int64_t items = 0;                // of the scans, every embedding's
   for (size_t g0 = 0; g0 < v.size(); g0 += libs) {
     const size_t g1 = std::min(v.size(), g0 + libs);
     std::vector<int32_t> grp;
     int64_t need = 64;
-    double scan = 0;
+    double scan = 0, ns = 0;
     bool force = false;
     for (size_t k = g0; k < g1; ++k) {
       const Realization& R = p.rz[v[k]];
@@ -353,18 +382,22 @@ static double pick_libraries(const Plan& p, int E, double excl, std::vector<int3
       force |= want;
       need = std::max(need, n);
       scan += scan_cost(E, R.l_eff) * (double)R.n_query / (double)ne;
+      ns += scan_ns(E, R.l_eff) * (double)R.n_query / (double)ne;
+      items += R.n_tiles * n_emb;
       grp.push_back(v[k]);
     }
     if (grp.empty()) continue;
     const double save = scan - walk_cost(E, need / 64);
     if (save <= 0 && !force) continue;
     gain += save;
+    all_scan += ns;
+    all_walk += walk_ns(E, need / 64);
     forced |= force;
     pk.w = std::max(pk.w, need);
     pk.groups.push_back(std::move(grp));
     pk.chunks.push_back((int32_t)(need / 64));
   }
-  return gain;
+  return rows_too_dear(E, ne, pk.w, all_scan, all_walk, items) ? 0.0 : gain;
 }
 
 // The same for nested libraries (v: the embedding's chains): a chain's scan
@@ -373,18 +406,22 @@ static double pick_libraries(const Plan& p, int E, double excl, std::vector<int3
 // Each becomes a realization of its own (appended to p.rz; slots as the
 // chain's), and the chains keep the segments before it.  Row widths as above.
 static double pick_sizes(const Plan& p, int E, double excl, const std::vector<int32_t>& v,
-                         int& first) {
+                         int64_t n_emb, int& first) {
   const Realization& R = p.rz[v[0]];
   const int64_t ne = R.n_e;
   const int64_t full = (ne + 63) / 64 * 64;
   const int32_t* seg = &p.segs[R.seg_off];
   const double n = (double)v.size();
-  double best = 0, walk = 0;
+  double best = 0, walk = 0, ns = 0;
   first = R.n_seg;
   for (int k = R.n_seg - 1; k >= 0; --k) {
     const int64_t w = std::min(full, (row_need(E, excl, ne, seg[k + 1]) + 63) / 64 * 64);
     if (w > kRowMaxW) break;
     walk += walk_cost(E, w / 64) * n / kWalkLibs;
+    ns += walk_ns(E, w / 64) * n / kWalkLibs;
+    const double saved = n * (scan_ns(E, R.l_eff) - scan_ns(E, seg[k]) +
+                              (double)(R.n_seg - k) * scan_ns(E, 0));
+    if (rows_too_dear(E, ne, w, saved, ns, (int64_t)v.size() * n_emb * R.n_tiles)) continue;
     // what the chains' scans lose: the points past seg[k], one selection and
     // prediction per size
     const double scan = n * (scan_cost(E, R.l_eff) - scan_cost(E, seg[k]) +
@@ -627,7 +664,6 @@ static void lay_out_walks(Plan& p, std::vector<WalkPick>& picks, Launch& la, int
 static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int64_t& bits) {
   if (!p.spec.walk || rzs.empty()) return;
   const int E = la.E;
-  const bool keys = p.spec.M > 0;
   const bool nested = !p.nested.empty();
   // the shuffle's bitmaps come from positions in LDS
   if (nested && p.spec.N > kNestedLdsNe) return;
@@ -644,7 +680,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
     size_t groups = 0;
     for (auto& kv : by_emb) {
       int first = 0;
-      const double gain = pick_sizes(p, E, excl, kv.second, first);
+      const double gain = pick_sizes(p, E, excl, kv.second, (int64_t)by_emb.size(), first);
       const Realization& R = p.rz[kv.second[0]];
       if (gain <= 0 || (int64_t)R.n_e * kRowMaxW * 8 > kRowPoolCap) continue;
       gain_all += gain * (double)R.n_e;
@@ -668,7 +704,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
     for (auto& kv : by_emb) {
       WalkPick pk;
       bool forced = false;
-      double gain = pick_libraries(p, E, excl, kv.second, pk, forced);
+      double gain = pick_libraries(p, E, excl, kv.second, (int64_t)by_emb.size(), pk, forced);
       const int64_t ne = p.rz[kv.second[0]].n_e;
       const bool fits = ne * pk.w * 8 <= kRowPoolCap;
       gain = (gain - row_cost(E, ne, pk.w)) * (double)ne;

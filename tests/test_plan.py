@@ -141,3 +141,22 @@ def test_shared_cases_take_both(plan, N, Es, tau, L, r, excl, kind):
 def test_replayed_call_walks_and_scans(plan):
     p = plan(N=4000, E=[2, 5], tau=[1], L=[40, 1500, 3000], r=60)
     assert p["walked"] > 0 and p["scan_items"] > 0
+
+
+# Shuffled series fill their embedding, and a row then costs a multiple of what it
+# costs on an attractor.  Measured, ms walked / scanned / before there were rows.
+@pytest.mark.parametrize("N,E,L,r,flags,walks", [
+    (32768, 9, [200, 2048], 40, 0, False),       # 10.1 / 3.5 / 5.2
+    (32768, 10, [200, 2048, 32768], 4, 0, False),   # 10.9 / 6.5 / 8.0
+    (60000, 9, [200, 3750], 40, 0, False),       # 13.3 / 8.8 / 11.5
+    (100000, 10, [200, 6250], 40, 0, False),     # 44.7 / 22.0 / 26.4
+    (32768, 10, [200, 2048, 8192], 10, NESTED, False),   # 10.8 / 4.3 / 8.1
+    (16000, 10, [500, 4000], 10, 0, True),       # 2.2 / 1.5 / 2.4
+    (32768, 6, [500, 8192], 10, 0, True),        # 1.9 / 2.4 / 4.0
+    (60000, 9, [500, 15000], 10, 0, True),       # 8.7 / 9.2 / 11.8
+    (100000, 8, [200, 6250], 40, 0, True),       # 18.6 / 17.3 / 21.5
+    (100000, 9, [200, 6250, 100000], 4, 0, True),   # 27.4 / 38.0 / 41.7
+    (60000, 9, [200, 3750], 40, TABLE, True),    # asked for
+])
+def test_long_series_in_many_dimensions(plan, N, E, L, r, flags, walks):
+    assert (plan(N=N, E=[E], tau=[1], L=L, r=r, flags=flags)["walked"] > 0) == walks
