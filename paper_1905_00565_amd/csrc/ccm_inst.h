@@ -58,11 +58,11 @@ hipError_t launch_rows_e(const RowJob* jobs, int n_jobs, int max_ne, int max_w, 
                          uint64_t* rows, RowTodo* todo, int* todo_n, hipStream_t st);
 
 template <int E>
-hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,
-                         const RowJob* embs, const Item* items, int n_items, int per,
-                         const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
-                         const float* emb, const double* tgt, double* out, int excl,
-                         int query_set, hipStream_t st);
+hipError_t launch_walk_e(int keys, const WalkGroup* groups, const RowJob* embs,
+                         const Item* items, int n_items, int per, const uint64_t* masks,
+                         const uint64_t* rows, const int32_t* qord, const float* emb,
+                         const double* tgt, double* out, int excl, int query_set,
+                         hipStream_t st);
 
 template <int E>
 hipError_t launch_walk_moments_e(int shared, const Realization* rzs, const WalkOut* where,

@@ -36,19 +36,17 @@ hipError_t launch_rows_e(const RowJob* jobs, int n_jobs, int max_ne, int max_w, 
 }
 
 template <int E>
-hipError_t launch_walk_e(int keys, const WalkGroup* groups, const WalkLib* libs,
-                         const RowJob* embs, const Item* items, int n_items, int per,
-                         const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
-                         const float* emb, const double* tgt, double* out, int excl,
-                         int query_set, hipStream_t st) {
+hipError_t launch_walk_e(int keys, const WalkGroup* groups, const RowJob* embs,
+                         const Item* items, int n_items, int per, const uint64_t* masks,
+                         const uint64_t* rows, const int32_t* qord, const float* emb,
+                         const double* tgt, double* out, int excl, int query_set,
+                         hipStream_t st) {
   if (keys)
-    k_walk<E, true><<<(unsigned)n_items, kBlock, 0, st>>>(groups, libs, embs, items, per, masks,
-                                                          rows, qord, emb, tgt, out, excl,
-                                                          query_set);
+    k_walk<E, true><<<(unsigned)n_items, kBlock, 0, st>>>(groups, embs, items, per, masks, rows,
+                                                          qord, emb, tgt, out, excl, query_set);
   else
-    k_walk<E, false><<<(unsigned)n_items, kBlock, 0, st>>>(groups, libs, embs, items, per, masks,
-                                                           rows, qord, emb, tgt, out, excl,
-                                                           query_set);
+    k_walk<E, false><<<(unsigned)n_items, kBlock, 0, st>>>(groups, embs, items, per, masks, rows,
+                                                           qord, emb, tgt, out, excl, query_set);
   return hipGetLastError();
 }
 
@@ -59,10 +57,10 @@ hipError_t launch_walk_moments_e(int shared, const Realization* rzs, const WalkO
                                  Moments* partial, int query_set, hipStream_t st) {
   if (shared)
     k_walk_moments<kSharedQ[E]><<<(unsigned)n_items, kBlock, 0, st>>>(
-        rzs, where, items, n_items, out, pj, qord, tgt, partial, query_set);
+        rzs, where, items, out, pj, qord, tgt, partial, query_set);
   else
     k_walk_moments<DefaultQ<E>::Q><<<(unsigned)n_items, kBlock, 0, st>>>(
-        rzs, where, items, n_items, out, pj, qord, tgt, partial, query_set);
+        rzs, where, items, out, pj, qord, tgt, partial, query_set);
   return hipGetLastError();
 }
 
@@ -72,8 +70,8 @@ template hipError_t launch_order_points_e<CCM_INST_E>(const RowJob*, int, int, c
 template hipError_t launch_rows_e<CCM_INST_E>(const RowJob*, int, int, int, int, const float*,
                                               const float*, const int32_t*, uint64_t*, RowTodo*,
                                               int*, hipStream_t);
-template hipError_t launch_walk_e<CCM_INST_E>(int, const WalkGroup*, const WalkLib*,
-                                              const RowJob*, const Item*, int, int,
+template hipError_t launch_walk_e<CCM_INST_E>(int, const WalkGroup*, const RowJob*,
+                                              const Item*, int, int,
                                               const uint64_t*, const uint64_t*, const int32_t*,
                                               const float*, const double*, double*, int, int,
                                               hipStream_t);

@@ -215,8 +215,8 @@ struct RowTodo {
 // A library of a walk group.
 struct WalkLib {
   int64_t bit_off;   // uint64: its bitmap over 0..n_e-1
-  int32_t l_eff;
   int32_t rz;
+  int32_t pad;
 };
 
 // Up to 64 libraries of one embedding that walk its rows together.  The walk
@@ -379,7 +379,7 @@ hipError_t launch_masks(const MaskJob* jobs, int n_jobs, int max_ne, const WalkL
 // The walk of `per` queries per item ({group, block of queries}): keys == 0
 // leaves predictions, else the E+1 neighbour keys per query.  excl: candidates within it of the query in index are dropped
 // (-1: none).
-hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* libs,
+hipError_t launch_walk(int E, int keys, const WalkGroup* groups,
                        const RowJob* embs, const Item* items, int n_items, int per,
                        const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
                        const float* emb, const double* tgt, double* out, int excl,

@@ -1211,14 +1211,14 @@ hipError_t launch_rows(int E, const RowJob* jobs, int n_jobs, int max_ne, int ma
 #undef CCM_CALL
 }
 
-hipError_t launch_walk(int E, int keys, const WalkGroup* groups, const WalkLib* libs,
+hipError_t launch_walk(int E, int keys, const WalkGroup* groups,
                        const RowJob* embs, const Item* items, int n_items, int per,
                        const uint64_t* masks, const uint64_t* rows, const int32_t* qord,
                        const float* emb, const double* tgt, double* out, int excl,
                        int query_set, hipStream_t st) {
   if (n_items <= 0) return hipSuccess;
 #define CCM_CALL(e)                                                                        \
-  launch_walk_e<e>(keys, groups, libs, embs, items, n_items, per, masks, rows, qord, emb, \
+  launch_walk_e<e>(keys, groups, embs, items, n_items, per, masks, rows, qord, emb, \
                    tgt, out, excl, query_set, st)
   CCM_BY_E(E, CCM_CALL)
 #undef CCM_CALL

@@ -531,7 +531,6 @@ static void lay_out_walks(Plan& p, std::vector<WalkPick>& picks, Launch& la, int
           }
           wl.bit_off = sj.bits - 1;
         }
-        wl.l_eff = p.rz[r].l_eff;
         wl.rz = r;
         p.walk_libs.push_back(wl);
         p.walked[r] = 1;

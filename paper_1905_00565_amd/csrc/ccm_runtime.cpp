@@ -232,7 +232,7 @@ void launch_walks(const Plan& p, const PlanBuffers& b, const Launch& L, hipStrea
                        b.boxes, b.qord, b.rows, b.todo, b.todo_n, st));
     for (int ci = wb.chunk_first; ci < wb.chunk_first + wb.chunk_count; ++ci) {
       const WalkChunk& ch = p.walk_chunks[ci];
-      HIPCHK(launch_walk(L.E, p.spec.M > 0, b.walk_groups, b.walk_libs, b.row_jobs,
+      HIPCHK(launch_walk(L.E, p.spec.M > 0, b.walk_groups, b.row_jobs,
                          b.walk_items + ch.item_first, (int)ch.item_count, L.walk_per, b.masks,
                          b.rows, b.qord, b.emb, b.s64, b.walk_out, excl,
                          p.spec.query_set, st));

@@ -709,8 +709,8 @@ struct WalkLds {
 // transpose, and a member about 18 to take out.
 template <int E, bool KEYS>
 __global__ __launch_bounds__(kBlock) void k_walk(
-    const WalkGroup* __restrict__ groups, const WalkLib* __restrict__ libs,
-    const RowJob* __restrict__ embs, const Item* __restrict__ items, int per,
+    const WalkGroup* __restrict__ groups, const RowJob* __restrict__ embs,
+    const Item* __restrict__ items, int per,
     const uint64_t* __restrict__ mask_pool, const uint64_t* __restrict__ row_pool,
     const int32_t* __restrict__ qord_pool, const float* __restrict__ emb_pool,
     const double* __restrict__ tgt_pool, double* __restrict__ out, int excl, int query_set) {
@@ -880,7 +880,7 @@ __global__ __launch_bounds__(kBlock) void k_walk(
 template <int Q>
 __global__ __launch_bounds__(kBlock) void k_walk_moments(
     const Realization* __restrict__ rzs, const WalkOut* __restrict__ where,
-    const Item* __restrict__ items, int n_items, const double* __restrict__ pred,
+    const Item* __restrict__ items, const double* __restrict__ pred,
     const int32_t* __restrict__ pj_pool, const int32_t* __restrict__ qord_pool,
     const double* __restrict__ tgt_pool, Moments* __restrict__ partial, int query_set) {
   __shared__ Moments red[kBlock];
