@@ -247,6 +247,8 @@ ccm_status ccm_matrix_dev(ccm_ctx *ctx, const double *S, int32_t M, int64_t N,
  * context on that device until the process ends.  The descriptors are
  * copied from host memory of the call with hipMemcpyAsync (pageable: staged
  * before the call returns); the rest is queued on `stream` as in ccm_dev.
+ * A call made while `stream` is being captured keeps its descriptors, which
+ * every replay of the graph copies, until the context is destroyed.
  * CCM_E_NOMEM, with a message, when the call needs more than the workspace
  * holds (about 16 MB for N = 1000, E = 2, ten L to 1000, r = 100);
  * CCM_E_INVAL for flags other than CCM_FLAG_NO_GRAPH.  Every call on one

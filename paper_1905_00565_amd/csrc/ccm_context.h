@@ -120,6 +120,8 @@ struct ccm_ctx {
   // buffer, grown as needed; calls on a context are serialised)
   void* pinned = nullptr;
   size_t pinned_bytes = 0;
+  // descriptors of the no-allocation calls made under capture
+  std::vector<std::vector<char>> captured;
 };
 
 namespace ccmh {

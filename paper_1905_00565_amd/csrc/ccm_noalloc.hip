@@ -120,7 +120,15 @@ extern "C" ccm_status ccm_dev_noalloc(ccm_ctx* c, const double* X, const double*
     put(b.rz, p.rz.data(), p.rz.size() * sizeof(Realization));
     put(b.items, p.items.data(), p.items.size() * sizeof(Item));
     put(b.orders, p.orders.data(), p.orders.size() * sizeof(OrderJob));
-    HIPCHK(hipMemcpyAsync(base, desc.data(), described, hipMemcpyHostToDevice, st));
+    const char* src = desc.data();
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (st) HIPCHK(hipStreamIsCapturing(st, &cap));
+    if (cap != hipStreamCaptureStatusNone) {
+      // the graph's copy reads them at every replay
+      c->captured.push_back(std::move(desc));
+      src = c->captured.back().data();
+    }
+    HIPCHK(hipMemcpyAsync(base, src, described, hipMemcpyHostToDevice, st));
     HIPCHK(hipMemcpyAsync(b.s64, X, N * 8, hipMemcpyDeviceToDevice, st));
     HIPCHK(hipMemcpyAsync(b.s64 + N, Y, N * 8, hipMemcpyDeviceToDevice, st));
     enqueue_plan(c, p, b, {}, st, nullptr);
