@@ -160,3 +160,18 @@ def test_replayed_call_walks_and_scans(plan):
 ])
 def test_long_series_in_many_dimensions(plan, N, E, L, r, flags, walks):
     assert (plan(N=N, E=[E], tau=[1], L=L, r=r, flags=flags)["walked"] > 0) == walks
+
+
+@pytest.mark.parametrize("kw,walked,width", [
+    # 21.8 ms with rows of 1024 for the small libraries too, 10.7 with rows of 64
+    (dict(M=70, N=17687, E=[1], tau=[2], L=[83, 164, 337, 551, 556, 11036, 11415, 11591, 14815],
+          r=9), 70 * 4 * 9, 64),
+    # 1.87 and 1.23
+    (dict(N=5160, E=[8], tau=[1], L=[101, 185, 5160], r=11, excl=16), 2 * 11, 128),
+    (dict(N=5003, E=[7], tau=[3], L=[101, 999, 3001, 4985], r=25, excl=10), 128, 192),
+])
+def test_library_point_queries_leave_small_libraries(plan, kw, walked, width):
+    """A small library asks few of the rows that it would lengthen for all."""
+    p = plan(**kw, query_set=1)
+    assert (p["walked"], p["row_width"]) == (walked, width)
+    assert p["missing"] == 0 and p["twice"] == 0
