@@ -344,6 +344,14 @@ static double walk_ns(int E, int64_t chunks) {
   return 0.74 + 0.12 * E + 0.27 * (double)chunks;
 }
 
+// Causal matrices of more than 8 series: the same by query of an embedding.  A walk
+// leaves keys to a per-target stage of its own, which takes longer than the stage
+// within the scan (M = 17, N = 2050, E = 5, 64 libraries: 5.6 x 10^3 by this count,
+// 1.86 ms walked, 1.17 scanned, 1.44 before there were rows; M = 17, N = 9284, E = 7: 2
+// x 10^4, 5.1 and 6.1).  Of 23 calls below 8000, 20 were faster scanned, by 1.08 to
+// 1.75 times, the others slower by 1.05 to 1.24.
+constexpr double kMatrixMinGain = 8000.0;
+
 // Groups of one embedding's libraries that walk its rows together.
 struct WalkPick {
   std::vector<std::vector<int32_t>> groups;
@@ -722,6 +730,7 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
       }
   } else {
     size_t groups = 0;
+    double queries = 0;
     for (auto& kv : by_emb) {
       WalkPick pk;
       bool forced = false;
@@ -733,8 +742,10 @@ static void plan_walks(Plan& p, const std::vector<int32_t>& rzs, Launch& la, int
       gain_all += gain;
       forced_any |= forced;
       groups += pk.groups.size();
+      queries += (double)ne;
       picks.push_back(std::move(pk));
     }
+    if (p.spec.M > 8 && !forced_any && gain_all < kMatrixMinGain * queries) return;
     if (picks.empty() || (gain_all < kWalkMinGain && !forced_any) || !groups_fit(p, groups)) return;
   }
   if (!picks.empty()) lay_out_walks(p, picks, la, bits);

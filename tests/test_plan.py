@@ -175,3 +175,19 @@ def test_library_point_queries_leave_small_libraries(plan, kw, walked, width):
     p = plan(**kw, query_set=1)
     assert (p["walked"], p["row_width"]) == (walked, width)
     assert p["missing"] == 0 and p["twice"] == 0
+
+
+# ms walked / scanned / before there were rows
+@pytest.mark.parametrize("M,N,E,tau,L,r,flags,walks", [
+    (17, 2050, 5, 1, [30, 44, 48, 107, 374, 378, 397, 1377, 1730], 12, 0, False),  # 1.86 / 1.17 / 1.45
+    (70, 9815, 8, 2, [45, 46, 54, 67, 82, 151, 292, 390, 1677, 9815], 4, 0, False),  # 34.1 / 25.0 / 25.7
+    (33, 984, 1, 2, [23, 54, 92, 126, 205, 334, 595, 744, 984], 16, 0, False),   # 0.82 / 0.73 / 0.75
+    (17, 9290, 7, 1, [31, 50, 75, 177, 1196, 2871, 3668], 11, 0, True),          # 5.1 / 6.1
+    (64, 20000, 4, 1, [500, 2000, 20000], 10, 0, True),
+    (8, 13797, 4, 2, [13797], 6, 0, True),                                       # few series
+    (17, 2050, 5, 1, [30, 397, 1730], 12, TABLE, True),                          # asked for
+])
+def test_small_matrices_scan(plan, M, N, E, tau, L, r, flags, walks):
+    p = plan(M=M, N=N, E=[E], tau=[tau], L=L, r=r, flags=flags)
+    assert (p["walked"] > 0) == walks
+    assert p["missing"] == 0 and p["twice"] == 0
