@@ -62,7 +62,7 @@ struct PlanBuffers {
   double* pred = nullptr;            // predictions of spread launches
 };
 
-// The side branch of a captured plan.
+// The side branch of a plan with walks.
 struct Fork {
   hipStream_t side = nullptr;
   hipEvent_t ev = nullptr;
@@ -115,7 +115,7 @@ struct ccm_ctx {
   std::vector<ccmh::EvPair> ev_pending, ev_free;
   ccm_profile prof{};
   std::unique_ptr<ccmh::Exec> exec;   // the most recent plan
-  ccmh::Fork fork;                    // used while capturing only
+  ccmh::Fork fork;
   // pinned staging of the host-array forms' series and results (one
   // buffer, grown as needed; calls on a context are serialised)
   void* pinned = nullptr;

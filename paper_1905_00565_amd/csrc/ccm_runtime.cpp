@@ -44,6 +44,9 @@ void drain_events(ccm_ctx* c) {
   c->ev_pending.clear();
 }
 
+// Up to this length a call's draws ride in the launch that sorts the orders' keys.
+constexpr int64_t kDrawsRideN = 4096;
+
 // The batched forms walk neighbour rows; the plain baseline does not.
 bool walks(const Spec& s) {
   return !(s.flags & CCM_FLAG_PLAIN);
@@ -320,7 +323,7 @@ void enqueue_plan(ccm_ctx* c, const Plan& p, const PlanBuffers& b,
   // the first wave's draws: in the side branch, with the orders' keys of a
   // call of one short chain, or on their own
   Draws draws;
-  if (!fork && !plain && !nested && p.spec.N <= 4096)
+  if (!fork && !plain && !nested && p.spec.N <= kDrawsRideN)
     draws = {b.sample + p.waves[0].sample_first, p.waves[0].sample_count, b.lib, b.bits};
   HIPCHK(build_orders(b.orders, p.n_sets, p.kd_levels, p.spec.N, b.s32, b.emb, b.order_mem, st,
                       draws));
@@ -426,6 +429,18 @@ hipGraphExec_t capture(ccm_ctx* c, Exec* ex) {
   return gx;
 }
 
+// The side branch of a plan's first, uncaptured call: of series whose draws are
+// a launch of their own (10^5 points at E = 3: 5.0 ms with it, 5.8 without; parting
+// and joining the streams of a shorter one takes what it gains).
+Fork* direct_fork(ccm_ctx* c, const Plan& p, hipStream_t st) {
+  if (p.walk_groups.empty() || p.spec.N <= kDrawsRideN) return nullptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (st) HIPCHK(hipStreamIsCapturing(st, &cap));
+  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  c->fork.create();
+  return &c->fork;
+}
+
 // Run a prepared plan on stream st: series already in ex->d_s64.  While
 // profiling, the launches are issued directly with an event pair around
 // each cross-map launch (events recorded by graph nodes cannot be timed).  So is
@@ -435,16 +450,16 @@ hipGraphExec_t capture(ccm_ctx* c, Exec* ex) {
 // call, 1000 points, L to 1000, r = 100: 936 us through the graph, 785 directly).
 void run(ccm_ctx* c, Exec* ex, hipStream_t st) {
   const Plan& p = ex->plan;
+  const bool direct = c->profiling || (p.spec.flags & (CCM_FLAG_NO_GRAPH | CCM_FLAG_PLAIN));
   const bool first = !ex->ran && !p.walk_groups.empty();
-  const bool use_graph = !c->profiling && !(p.spec.flags & CCM_FLAG_NO_GRAPH) &&
-                         !(p.spec.flags & CCM_FLAG_PLAIN) && !first;
   ex->ran = true;
-  if (use_graph) {
+  if (!direct && !first) {
     if (!ex->graph) ex->graph = capture(c, ex);
     HIPCHK(hipGraphLaunch(ex->graph, st));
   } else {
     enqueue_plan(c, ex->plan, ex->buf, ex->plain_first, st,
-                 c->profiling ? &c->ev_pending : nullptr);
+                 c->profiling ? &c->ev_pending : nullptr,
+                 direct ? nullptr : direct_fork(c, p, st));
   }
   if (c->profiling) {
     c->prof.waves += (double)p.waves.size();
