@@ -172,11 +172,10 @@ __device__ __forceinline__ float order_reach(const float* __restrict__ pts, int 
                                              const float (&q)[E], int* s_n) {
   const int tid = threadIdx.x;
   const int a = max(0, min(p - w / 2, n - w));
-  float m = 0.f;
-  for (int c = a + tid; c < a + w; c += kBlock) {
-    const float d2 = run_d2<E>(pts, n, c, q);
-    m = d2 == d2 ? fmaxf(m, d2) : __builtin_inff();
-  }
+  uint32_t bits = 0u;                              // (a NaN's lie above infinity's)
+  for (int c = a + tid; c < a + w; c += kBlock)
+    bits = max(bits, __float_as_uint(run_d2<E>(pts, n, c, q)) & 0x7fffffffu);
+  float m = __uint_as_float(min(bits, 0x7f800000u));
 #pragma unroll
   for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
   __syncthreads();
