@@ -16,9 +16,10 @@ pass of the same steps right after (direct launches on the same stream); its
 wall time is reported beside the graph's.
 
 Prints one JSON line: value = cross-map predictions per second, plus
-rho-realizations per second, the roofline of the cross-map kernel (binary32
-flops per pair 3E-1, over the summed HIP-event duration of its launches; HBM
-traffic from the committed counter summary when it matches the kernel
+rho-realizations per second, the rate at which the cross map answers pairs
+(binary32 flops per pair 3E-1, over the summed HIP-event duration of its
+launches; a rate of work answered, since rows and walks do not evaluate every
+pair; HBM traffic from the committed counter summary when it matches the kernel
 sources), the other workloads of the method (`workloads`: small coupled map
 with plain vs batched launches, long noisy series, 64-series causal matrix),
 the sweep's launch forms (`forms`: persistent, no graph, plain vs batched on
@@ -668,14 +669,14 @@ def main():
                       "k_walk_moments serve the others)",
             # 3E-1 per (query, library point) pair of the method's definition.  A
             # walked library's pairs are not evaluated one by one (a query's row is
-            # built once for every library), so achieved counts the work
-            # answered, not executed, and frac may exceed 1.
+            # built once for every library), so this rate is of work answered, not
+            # executed, and no fraction of the peak.
             "flops_counted": "3E-1 per (query, library point) pair of the definition, "
                              "whether evaluated or answered from a neighbour row",
-            "achieved": achieved_tflops,
+            "answered": achieved_tflops,
             "peak": FP32_VECTOR_PEAK_TFLOPS,
             "unit": "TFLOP/s",
-            "frac": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
+            "frac": None,
             "traffic": measured_traffic(w.name),
             "launches_per_step": launches / a.steps,
             "avg_launch_ms": prof["kernel_ms"] / launches,
